@@ -65,16 +65,18 @@ void launch_mul_bcast(const DeviceTables& T, u64* out, const u64* a, const u64* 
 // acc += a * b (b broadcast with period b_limbs)
 void launch_mul_acc(const DeviceTables& T, u64* acc, const u64* a, const u64* b, int nlimbs, int b_limbs,
                     const LimbMap& m, hipStream_t s);
-// out (+)= sum_t a[t] * p[t] (p[t] broadcast with period b_limbs), nterms pairs
+// out (+)= sum_t a[t] * p[t] (p[t] broadcast with period b_limbs), nterms pairs;
+// the second half of the output limbs lies `skip` words further on (an
+// element of a batch whose two components stand apart)
 #define SUM_MAX_TERMS 64  // at most 64 signed products below q < 2^46: sums below 2^52
 void launch_mul_sum(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* p, int nterms,
-                    int nlimbs, int b_limbs, const LimbMap& m, bool accumulate, hipStream_t s);
+                    int nlimbs, int b_limbs, const LimbMap& m, bool accumulate, hipStream_t s, size_t skip = 0);
 // outs[g] = sum_t a[t] * p[g * nterms + t] for g < nouts (null p: term absent);
 // false (nothing launched) beyond SUM_MAX_OUTS outputs or SUM_MAX_TERMS terms
 #define SUM_MAX_OUTS 4
 bool launch_mul_sum_multi(const DeviceTables& T, u64* const* outs, int nouts, const u64* const* a,
                           const u64* const* p, int nterms, int nlimbs, int b_limbs, const LimbMap& m,
-                          hipStream_t s);
+                          hipStream_t s, const size_t* skips = nullptr);
 // out = a * c_k for a per-limb constant (host array, Shoup)
 void launch_mul_const(const DeviceTables& T, u64* out, const u64* a, int nlimbs, const u64* consts /*[map.n]*/,
                       const LimbMap& m, hipStream_t s);
@@ -155,6 +157,13 @@ void launch_moddown_final(const DeviceTables& T, u64* out, const u64* x, const u
 void launch_multsum(const DeviceTables& T, u64* out, const u64* digits, const u64* key, const u64* c0,
                     const u64* pmod /*device [nmods][2]*/, int level, int L, int alpha, int beta, u64 g,
                     int batch, hipStream_t s);
+// out[2][batch][nqp][N] (+)= the sum over ng giant steps t of the hoisted
+// rotation by gs[t] of element t: digits [ng][batch][beta][nqp][N], c0
+// [ng][batch][nq][N]
+#define GIANT_MAX 64
+void launch_multsum_giant(const DeviceTables& T, u64* out, const u64* const* keys, const u64* gs, int ng,
+                          const u64* digits, const u64* c0, const u64* pmod, int level, int L, int alpha, int beta,
+                          int batch, bool accumulate, hipStream_t s);
 // nrot hoisted rotations of the same digits (Galois elements gs[], keys[]) into
 // outs[r] (each [2][batch][nqp][N]); digits read from HBM once per launch.
 // With masks (plaintexts [nqp][N] in R_{Q_l P}, one per rotation) the outputs

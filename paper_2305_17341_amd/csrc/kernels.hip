@@ -1578,7 +1578,7 @@ struct SumTerms {
   const u64* p[SUM_MAX_TERMS];
 };
 __global__ void k_mul_sum(u64* out, SumTerms t, int nterms, int accumulate, int b_limbs, LimbMap map, int logN,
-                          const ModConst* __restrict__ mc, int il) {
+                          const ModConst* __restrict__ mc, int il, int half, size_t skip) {
   const u64 N = 1ull << logN;
   int blk, k;
   block_limb(il, b_limbs, (int)(N / TPB), blk, k);
@@ -1588,6 +1588,7 @@ __global__ void k_mul_sum(u64* out, SumTerms t, int nterms, int accumulate, int 
   if (m < 0) return;
   const ModConst mk = mc[m];
   const size_t o = (size_t)k * N + i, op = (size_t)(k % b_limbs) * N + i;
+  if (k >= half) out += skip;
   u64 an = t.a[0][o], pn = t.p[0][op];
   if (mk.bits <= F64_LAZY_BITS) {
     // up to 63 signed exact products and the old value, reduced once
@@ -1616,7 +1617,7 @@ __global__ void k_mul_sum(u64* out, SumTerms t, int nterms, int accumulate, int 
   out[o] = acc;
 }
 void launch_mul_sum(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* p, int nterms, int nl,
-                    int bl, const LimbMap& m, bool accumulate, hipStream_t s) {
+                    int bl, const LimbMap& m, bool accumulate, hipStream_t s, size_t skip) {
   // 63 terms a pass: with the old value, 64 summands below q < 2^46 each
   constexpr int TERMS = SUM_MAX_TERMS - 1;
   for (int t0 = 0; t0 < nterms; t0 += TERMS) {
@@ -1631,7 +1632,8 @@ void launch_mul_sum(const DeviceTables& T, u64* out, const u64* const* a, const 
                  mm_map(T, m, nl, (double)T.N * nt));
     int il;
     dim3 grid = sum_grid((int)cdiv(T.N, TPB), nl, bl, g_knobs.ew_interleave, il);
-    hipLaunchKernelGGL(k_mul_sum, grid, dim3(TPB), 0, s, out, t, nt, acc ? 1 : 0, bl, m, T.logN, T.mc, il);
+    hipLaunchKernelGGL(k_mul_sum, grid, dim3(TPB), 0, s, out, t, nt, acc ? 1 : 0, bl, m, T.logN, T.mc, il, nl / 2,
+                       skip);
   }
 }
 
@@ -1641,6 +1643,7 @@ struct SumMulti {
   const u64* a[SUM_MAX_TERMS];
   const u64* p[SUM_MAX_OUTS][SUM_MAX_TERMS];
   u64* out[SUM_MAX_OUTS];
+  size_t skip[SUM_MAX_OUTS];
 };
 // V = 2: two consecutive coefficients per thread, 16-byte loads and stores.
 // S: a thread sums S term streams that share their plaintexts (limbs k0 +
@@ -1648,7 +1651,7 @@ struct SumMulti {
 // for all of them.
 template <int G, int V, int S>
 __global__ void __launch_bounds__(TPB) k_mul_sum_multi(SumMulti t, int nterms, int b_limbs, LimbMap map, int logN,
-                                const ModConst* __restrict__ mc, int il) {
+                                const ModConst* __restrict__ mc, int il, int half) {
   const u64 N = 1ull << logN;
   int blk, k;
   block_limb(il, b_limbs, (int)(N / (TPB * V)), blk, k);
@@ -1758,25 +1761,27 @@ __global__ void __launch_bounds__(TPB) k_mul_sum_multi(SumMulti t, int nterms, i
   for (int g = 0; g < G; g++)
 #pragma unroll
     for (int s = 0; s < S; s++) {
+      u64* w = t.out[g] + o[s] + (k0 + s * b_limbs >= half ? t.skip[g] : 0);
       if (V == 2) {
         ulonglong2 y;
         y.x = res[g][s][0];
         y.y = res[g][s][V - 1];
-        *reinterpret_cast<ulonglong2*>(t.out[g] + o[s]) = y;
+        *reinterpret_cast<ulonglong2*>(w) = y;
       } else {
-        t.out[g][o[s]] = res[g][s][0];
+        *w = res[g][s][0];
       }
     }
 }
 bool launch_mul_sum_multi(const DeviceTables& T, u64* const* outs, int nouts, const u64* const* a,
                           const u64* const* p /* [nouts][nterms], null = absent */, int nterms, int nl, int bl,
-                          const LimbMap& m, hipStream_t s) {
+                          const LimbMap& m, hipStream_t s, const size_t* skips) {
   if (nterms > SUM_MAX_TERMS || nouts > SUM_MAX_OUTS || nouts < 1 || nterms < 1) return false;
   SumMulti t;
   int present = 0;
   for (int j = 0; j < nterms; j++) t.a[j] = a[j];
   for (int g = 0; g < SUM_MAX_OUTS; g++) {
     t.out[g] = g < nouts ? outs[g] : nullptr;
+    t.skip[g] = skips && g < nouts ? skips[g] : 0;
     for (int j = 0; j < SUM_MAX_TERMS; j++) {
       t.p[g][j] = (g < nouts && j < nterms) ? p[(size_t)g * nterms + j] : nullptr;
       present += t.p[g][j] != nullptr;
@@ -1794,7 +1799,7 @@ bool launch_mul_sum_multi(const DeviceTables& T, u64* const* outs, int nouts, co
   dim3 grid = sum_grid((int)cdiv(T.N, TPB * (v2 ? 2 : 1)), nl / S, bl, g_knobs.ew_interleave, il);
   auto go = [&](auto gc, auto vc, auto sc) {
     hipLaunchKernelGGL((k_mul_sum_multi<decltype(gc)::value, decltype(vc)::value, decltype(sc)::value>), grid,
-                       dim3(TPB), 0, s, t, nterms, bl, m, T.logN, T.mc, il);
+                       dim3(TPB), 0, s, t, nterms, bl, m, T.logN, T.mc, il, nl / 2);
   };
   auto by_s = [&](auto gc, auto vc) {
     if (S == 4) go(gc, vc, std::integral_constant<int, 4>{});
@@ -3315,6 +3320,18 @@ __device__ __forceinline__ u64 fold_pieces(const double* S, const ModConst& mk) 
   }
   return reduce128_est(lo, hi, mk);
 }
+// the nine piece products of d k added to the five sums by weight
+__device__ __forceinline__ void piece_mac(double* S, double d0, double d1, double d2, double k0, double k1, double k2) {
+  S[0] = fma(d0, k0, S[0]);
+  S[1] = fma(d0, k1, S[1]);
+  S[1] = fma(d1, k0, S[1]);
+  S[2] = fma(d0, k2, S[2]);
+  S[2] = fma(d1, k1, S[2]);
+  S[2] = fma(d2, k0, S[2]);
+  S[3] = fma(d1, k2, S[3]);
+  S[3] = fma(d2, k1, S[3]);
+  S[4] = fma(d2, k2, S[4]);
+}
 template <int MB>
 __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i, const u64* __restrict__ dig,
                                                  size_t dstride, size_t jstride, const u64* __restrict__ c0,
@@ -3349,24 +3366,8 @@ __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i
     for (int b = 0; b < MB; b++) {
       double d0, d1, d2;
       split20(dw[b], d0, d1, d2);
-      S0[b][0] = fma(d0, kb0, S0[b][0]);
-      S0[b][1] = fma(d0, kb1, S0[b][1]);
-      S0[b][1] = fma(d1, kb0, S0[b][1]);
-      S0[b][2] = fma(d0, kb2, S0[b][2]);
-      S0[b][2] = fma(d1, kb1, S0[b][2]);
-      S0[b][2] = fma(d2, kb0, S0[b][2]);
-      S0[b][3] = fma(d1, kb2, S0[b][3]);
-      S0[b][3] = fma(d2, kb1, S0[b][3]);
-      S0[b][4] = fma(d2, kb2, S0[b][4]);
-      S1[b][0] = fma(d0, ka0, S1[b][0]);
-      S1[b][1] = fma(d0, ka1, S1[b][1]);
-      S1[b][1] = fma(d1, ka0, S1[b][1]);
-      S1[b][2] = fma(d0, ka2, S1[b][2]);
-      S1[b][2] = fma(d1, ka1, S1[b][2]);
-      S1[b][2] = fma(d2, ka0, S1[b][2]);
-      S1[b][3] = fma(d1, ka2, S1[b][3]);
-      S1[b][3] = fma(d2, ka1, S1[b][3]);
-      S1[b][4] = fma(d2, ka2, S1[b][4]);
+      piece_mac(S0[b], d0, d1, d2, kb0, kb1, kb2);
+      piece_mac(S1[b], d0, d1, d2, ka0, ka1, ka2);
     }
   }
   const u64* mask = R.mask[r];
@@ -3929,6 +3930,250 @@ void launch_multsum(const DeviceTables& T, u64* out, const u64* digits, const u6
       MS_CASE(1) MS_CASE(2) MS_CASE(3) MS_CASE(4) MS_CASE(5) MS_CASE(6) MS_CASE(7) MS_CASE(8)
     }
 #undef MS_CASE
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The giant steps of a double-hoisted transform in one launch: the sum over
+// ng giant steps of the hoisted rotations by g[t] of the elements t (their
+// digits [ng][B][beta][nqp][N], their c0 [ng][B][nq][N]),
+//   out_b (+)= sum_t sum_j pi_t(d_(t,b,j)) key_(t,j) (+ P pi_t(c0_(t,b))),
+// out [2][B][nqp][N].  One launch per giant step wrote and re-read an
+// R_{Q_l P} element per step for the sum, and on the small rings each of
+// those launches lasted 4 to 12 us for its latency alone; here an output is
+// written once and the loads of U digits are in flight while U others are
+// multiplied.  SPLIT: the work-group's threads are cut into SPLIT groups that
+// take every SPLIT-th step of TPB / SPLIT coefficients and meet in LDS (a
+// small ring leaves most of the chip idle otherwise).
+// ---------------------------------------------------------------------------
+struct GiantKeys {
+  const u64* key[GIANT_MAX];
+  u64 g[GIANT_MAX];
+};
+template <int MB, int U>
+__device__ __forceinline__ void giant_f64(const GiantKeys& K, int t0, int dt, int ng, const u64* __restrict__ digits,
+                                          const u64* __restrict__ c0, u64 pm, u64 pmsh, int nq, int nqp, int beta,
+                                          int nmods, int B, int b0, int m, int pos, u32 i, int logN,
+                                          const ModConst& mk, double (&s0)[MB], double (&s1)[MB]) {
+  const u64 N = 1ull << logN;
+  const size_t dstride = (size_t)beta * nqp * N;
+  const double q = mk.qf, qi = mk.qinvf;
+  u64 kbn[U], kan[U], dn[U][MB];
+  u32 src = 0;
+  auto load = [&](int t, int j0) {
+    if (j0 == 0) src = automorph_src(i, K.g[t], logN);
+    const u64* key = K.key[t] + (size_t)m * N + i;
+    const u64* dg = digits + ((size_t)t * B + b0) * dstride + (size_t)pos * N + src;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int j = j0 + u;
+      if (U > 1 && j >= beta) break;
+      kbn[u] = ldnt(key + (size_t)(2 * j) * nmods * N);
+      kan[u] = ldnt(key + (size_t)(2 * j + 1) * nmods * N);
+#pragma unroll
+      for (int b = 0; b < MB; b++) dn[u][b] = dg[(size_t)b * dstride + (size_t)j * nqp * N];
+    }
+  };
+  if (t0 < ng) load(t0, 0);
+  for (int t = t0; t < ng; t += dt) {
+    u64 cw[MB];
+#pragma unroll
+    for (int b = 0; b < MB; b++) cw[b] = pos < nq ? c0[(((size_t)t * B + b0 + b) * nq + pos) * N + src] : 0;
+    for (int j0 = 0; j0 < beta; j0 += U) {
+      u64 kb[U], ka[U], d[U][MB];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        kb[u] = kbn[u];
+        ka[u] = kan[u];
+#pragma unroll
+        for (int b = 0; b < MB; b++) d[u][b] = dn[u][b];
+      }
+      if (j0 + U < beta) load(t, j0 + U);
+      else if (t + dt < ng) load(t + dt, 0);
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        if (U > 1 && j0 + u >= beta) break;
+        const double fb = __longlong_as_double((long long)kb[u]), fa = __longlong_as_double((long long)ka[u]);
+#pragma unroll
+        for (int b = 0; b < MB; b++) {
+          const double fd = __longlong_as_double((long long)d[u][b]);  // centred double digits
+          s0[b] += f64_mulmod_signed(fd, fb, q, qi);
+          s1[b] += f64_mulmod_signed(fd, fa, q, qi);
+        }
+      }
+    }
+    // beta <= 16 products below q, c0 P and the old centred sum: below 2^51
+#pragma unroll
+    for (int b = 0; b < MB; b++) {
+      if (pos < nq) s0[b] += u2d(mul_const_any(cw[b], pm, pmsh, mk));
+      s0[b] = f64_centre(s0[b], q, qi);
+      s1[b] = f64_centre(s1[b], q, qi);
+    }
+  }
+}
+// 60-bit limbs: the piece sums of multsum_int_pass, folded once per giant
+// step (their reduction takes at most 16 products)
+template <int MB>
+__device__ __forceinline__ void giant_int(const GiantKeys& K, int t0, int dt, int ng, const u64* __restrict__ digits,
+                                          const u64* __restrict__ c0, u64 pm, u64 pmsh, int nq, int nqp, int beta,
+                                          int nmods, int B, int b0, int m, int pos, u32 i, int logN,
+                                          const ModConst& mk, u64 (&r0)[MB], u64 (&r1)[MB]) {
+  const u64 N = 1ull << logN;
+  const size_t dstride = (size_t)beta * nqp * N;
+  u64 kbn = 0, kan = 0, dn[MB];
+  u32 src = 0;
+  auto load = [&](int t, int j) {
+    if (j == 0) src = automorph_src(i, K.g[t], logN);
+    const u64* key = K.key[t] + (size_t)m * N + i;
+    const u64* dg = digits + ((size_t)t * B + b0) * dstride + ((size_t)j * nqp + pos) * N + src;
+    kbn = ldnt(key + (size_t)(2 * j) * nmods * N);
+    kan = ldnt(key + (size_t)(2 * j + 1) * nmods * N);
+#pragma unroll
+    for (int b = 0; b < MB; b++) dn[b] = dg[(size_t)b * dstride];
+  };
+  if (t0 < ng) load(t0, 0);
+  for (int t = t0; t < ng; t += dt) {
+    u64 cw[MB];
+#pragma unroll
+    for (int b = 0; b < MB; b++) cw[b] = pos < nq ? c0[(((size_t)t * B + b0 + b) * nq + pos) * N + src] : 0;
+    double S0[MB][5], S1[MB][5];
+#pragma unroll
+    for (int b = 0; b < MB; b++)
+#pragma unroll
+      for (int w = 0; w < 5; w++) S0[b][w] = S1[b][w] = 0.0;
+    for (int j = 0; j < beta; j++) {
+      double kb0, kb1, kb2, ka0, ka1, ka2;
+      split20(kbn, kb0, kb1, kb2);
+      split20(kan, ka0, ka1, ka2);
+      u64 dw[MB];
+#pragma unroll
+      for (int b = 0; b < MB; b++) dw[b] = dn[b];
+      if (j + 1 < beta) load(t, j + 1);
+      else if (t + dt < ng) load(t + dt, 0);
+#pragma unroll
+      for (int b = 0; b < MB; b++) {
+        double d0, d1, d2;
+        split20(dw[b], d0, d1, d2);
+        piece_mac(S0[b], d0, d1, d2, kb0, kb1, kb2);
+        piece_mac(S1[b], d0, d1, d2, ka0, ka1, ka2);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < MB; b++) {
+      if (pos < nq) r0[b] = add_mod(r0[b], mul_const_any(cw[b], pm, pmsh, mk), mk.q);
+      r0[b] = add_mod(r0[b], fold_pieces(S0[b], mk), mk.q);
+      r1[b] = add_mod(r1[b], fold_pieces(S1[b], mk), mk.q);
+    }
+  }
+}
+template <int MB, int SPLIT>
+__global__ void __launch_bounds__(TPB) k_multsum_giant(u64* out, GiantKeys K, int ng, const u64* __restrict__ digits,
+                                                       const u64* __restrict__ c0, const u64* __restrict__ pmod,
+                                                       int nq, int nqp, int L, int beta, int nmods, int B, int b0,
+                                                       int accumulate, int logN, const ModConst* __restrict__ mc) {
+  constexpr int CO = TPB / SPLIT, U = MB <= 2 ? 4 : MB <= 4 ? 2 : 1, MI = MB > 4 ? 4 : MB;
+  __shared__ u64 sh[SPLIT > 1 ? (SPLIT - 1) * 2 * MB * CO : 1];
+  const u64 N = 1ull << logN;
+  const int part = SPLIT > 1 ? threadIdx.x / CO : 0, lane = threadIdx.x - part * CO;
+  const u32 i = blockIdx.x * CO + lane;
+  if (i >= N) return;  // CO divides N: never part of a work-group
+  const int pos = blockIdx.y, m = pos < nq ? pos : L + 1 + (pos - nq);
+  const ModConst mk = mc[m];
+  const u64 pm = pmod[2 * m], pmsh = pmod[2 * m + 1];
+  const bool f64 = mk.bits <= F64_LAZY_BITS;
+  u64 r0[MB], r1[MB];
+  if (f64) {
+    double s0[MB], s1[MB];
+#pragma unroll
+    for (int b = 0; b < MB; b++) s0[b] = s1[b] = 0.0;
+    giant_f64<MB, U>(K, part, SPLIT, ng, digits, c0, pm, pmsh, nq, nqp, beta, nmods, B, b0, m, pos, i, logN, mk, s0,
+                     s1);
+#pragma unroll
+    for (int b = 0; b < MB; b++) {
+      r0[b] = d2u(f64_canon(s0[b], mk.qf, mk.qinvf));
+      r1[b] = d2u(f64_canon(s1[b], mk.qf, mk.qinvf));
+    }
+  } else {
+#pragma unroll
+    for (int bb = 0; bb < MB; bb += MI) {
+      u64 t0[MI], t1[MI];
+#pragma unroll
+      for (int b = 0; b < MI; b++) t0[b] = t1[b] = 0;
+      // the last pass of an odd member count overlaps the one before it
+      const int bs = bb + MI <= MB ? bb : MB - MI;
+      giant_int<MI>(K, part, SPLIT, ng, digits, c0, pm, pmsh, nq, nqp, beta, nmods, B, b0 + bs, m, pos, i, logN, mk,
+                    t0, t1);
+#pragma unroll
+      for (int b = 0; b < MI; b++) {
+        r0[bs + b] = t0[b];
+        r1[bs + b] = t1[b];
+      }
+    }
+  }
+  if (SPLIT > 1) {
+    if (part > 0)
+#pragma unroll
+      for (int b = 0; b < MB; b++) {
+        sh[(((part - 1) * MB + b) * 2 + 0) * CO + lane] = r0[b];
+        sh[(((part - 1) * MB + b) * 2 + 1) * CO + lane] = r1[b];
+      }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int x = 0; x < SPLIT - 1; x++)
+#pragma unroll
+      for (int b = 0; b < MB; b++) {
+        r0[b] = add_mod(r0[b], sh[((x * MB + b) * 2 + 0) * CO + lane], mk.q);
+        r1[b] = add_mod(r1[b], sh[((x * MB + b) * 2 + 1) * CO + lane], mk.q);
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < MB; b++) {
+    u64* o0 = &out[((size_t)(b0 + b) * nqp + pos) * N + i];
+    u64* o1 = &out[((size_t)(B + b0 + b) * nqp + pos) * N + i];
+    if (accumulate) {
+      r0[b] = add_mod(r0[b], *o0, mk.q);
+      r1[b] = add_mod(r1[b], *o1, mk.q);
+    }
+    stnt(o0, r0[b]);
+    stnt(o1, r1[b]);
+  }
+}
+void launch_multsum_giant(const DeviceTables& T, u64* out, const u64* const* keys, const u64* gs, int ng,
+                          const u64* digits, const u64* c0, const u64* pmod, int level, int L, int alpha, int beta,
+                          int batch, bool accumulate, hipStream_t s) {
+  const int nq = level + 1, nqp = nq + alpha;
+  const int mstep = std::min(MS_MAXB, g_knobs.ms_members);
+  for (int t0 = 0; t0 < ng; t0 += GIANT_MAX) {
+    const int nt = std::min(ng - t0, GIANT_MAX);
+    GiantKeys K;
+    for (int t = 0; t < nt; t++) {
+      K.key[t] = keys[t0 + t];
+      K.g[t] = gs[t0 + t];
+    }
+    const u64* dg = digits + (size_t)t0 * batch * beta * nqp * T.N;
+    const u64* cz = c0 + (size_t)t0 * batch * nq * T.N;
+    const int acc = accumulate || t0 > 0 ? 1 : 0;
+    for (int b0 = 0; b0 < batch; b0 += mstep) {
+      const int mb = std::min(batch - b0, mstep);
+      ProfScope ps("multsum", s,
+                   8.0 * T.N * nt * (2.0 * beta * nqp + mb * (beta * nqp + nq)) + 16.0 * T.N * mb * nqp * (1 + acc),
+                   mm_qp(T, nq, nqp, L, (double)T.N * (2.0 * beta + 1), (double)T.N * 2.0 * beta, (double)mb * nt),
+                   8.0 * T.N * nt * (2.0 * beta * nqp + (double)mb * 4.0 * nq));
+      // fewer than 16 waves a CU without the split: share the steps out over
+      // four thread groups
+      const bool split = mb <= 2 && nt >= 4 && (size_t)(T.N / TPB) * nqp < 1024;
+#define MG_LAUNCH(K_, S_)                                                                                       \
+  hipLaunchKernelGGL((k_multsum_giant<K_, S_>), dim3(cdiv(T.N, TPB / S_), nqp), dim3(TPB), 0, s, out, K, nt, dg, \
+                     cz, pmod, nq, nqp, L, beta, T.nmods, batch, b0, acc, T.logN, T.mc)
+#define MG_CASE(K_) \
+  case K_: MG_LAUNCH(K_, 1); break;
+      if (split && mb == 1) MG_LAUNCH(1, 4);
+      else if (split) MG_LAUNCH(2, 4);
+      else switch (mb) { MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8) }
+#undef MG_CASE
+#undef MG_LAUNCH
+    }
   }
 }
 

@@ -95,6 +95,11 @@ struct CovState {
   std::vector<bool> set;
 };
 
+// temporaries of one batched stage (elements taken through ModDown, Decompose
+// and the key inner products together): 1 GiB holds every element of a
+// product up to N = 2^14 and the 3 to 20 that fill the chip above
+#define HE_STAGE_BYTES (1ull << 30)
+
 struct HeCtxImpl {
   int logN = 0;
   u64 N = 0;
@@ -152,6 +157,7 @@ struct HeCtxImpl {
   u64 galois(long step) const;
   u64* table_upload(const void* host, size_t bytes);
 
+  size_t stage_count(size_t per_element, size_t elements) const;
   HeCt ct_new(int level, bool qp, double scale, int B = 1);
   HeCt ct_copy(const HeCt& x);
   void copy_limbs(u64* dst, const u64* src, size_t nlimbs, const char* family = "copy_limbs");

@@ -549,6 +549,11 @@ void HeCtxImpl::init(const he_params* p, const he_device* dev, u64 seed_) {
 // ---------------------------------------------------------------------------
 // basic containers
 // ---------------------------------------------------------------------------
+// elements (of per_element temporary bytes each) a batched stage takes at
+// once: all of them where they fit HE_STAGE_BYTES, one at least
+size_t HeCtxImpl::stage_count(size_t per_element, size_t elements) const {
+  return std::max<size_t>(1, std::min(elements, (size_t)HE_STAGE_BYTES / per_element));
+}
 HeCt HeCtxImpl::ct_new(int level, bool qp, double scale, int B) {
   HeCt c;
   c.N = N;
@@ -1397,34 +1402,55 @@ HeCt HeCtxImpl::lintrans_perm(const HeCt& x, const std::vector<int>& perm, const
   xb = HeCt();
   LimbMap qpm = qpmap(level);
   HeCt acc = ct_new(level, true, x.scale * ql, x.B);
-  bool acc_set = false;
-  // giant steps with at least one diagonal: (j, index into pts) per step
+  // giant steps with at least one diagonal: (j, index into pts) per step; step
+  // 0 (no rotation) first, straight into the sum
   std::map<int, std::vector<std::pair<int, size_t>>> by_i;
   for (size_t e = 0; e < ij.size(); e++) by_i[ij[e].first].push_back({ij[e].second, e});
   std::vector<int> gi;
-  for (auto& kv : by_i) gi.push_back(kv.first);
-  const int nl = 2 * x.B * nqp;
-  for (size_t c0 = 0; c0 < gi.size(); c0 += SUM_MAX_OUTS) {
-    const int ng = (int)std::min<size_t>(SUM_MAX_OUTS, gi.size() - c0);
-    // inner_i = sum_j baby_j (.) diagonal_(i,j) for ng giant steps in one pass over the babies
-    std::vector<int> col(n1, -1), jl;
-    for (int g = 0; g < ng; g++)
-      for (auto& je : by_i[gi[c0 + g]])
-        if (col[je.first] < 0) {
-          col[je.first] = (int)jl.size();
-          jl.push_back(je.first);
-        }
-    const int nt = (int)jl.size();
-    std::vector<const u64*> ta(nt), tp((size_t)ng * nt, nullptr);
-    for (int t = 0; t < nt; t++) ta[t] = baby[jl[t]].d.p;
-    std::vector<HeCt> inner(ng);
-    std::vector<u64*> outs(ng);
-    for (int g = 0; g < ng; g++) {
-      for (auto& je : by_i[gi[c0 + g]]) tp[(size_t)g * nt + col[je.first]] = pts[je.second];
-      inner[g] = ct_new(level, true, x.scale * ql, x.B);
-      outs[g] = inner[g].d.p;
-    }
-    if (!launch_mul_sum_multi(T, outs.data(), ng, ta.data(), tp.data(), nt, nl, nqp, qpm, stream)) {
+  bool acc_set = by_i.count(0) > 0;
+  if (acc_set) gi.push_back(0);
+  for (auto& kv : by_i)
+    if (kv.first != 0) gi.push_back(kv.first);
+  // The other steps' inner sums go through ModDown and Decompose as one batch
+  // and into the sum by one launch (a step at a time, each of those kernels
+  // had a twelfth to a sixtieth of the chip's work-groups on the smaller
+  // rings).  A batch takes as many steps as its temporaries fit
+  // HE_STAGE_BYTES (on the largest ring a few steps fill the chip already), but
+  // the sums always run SUM_MAX_OUTS at a time: each pass reads every baby.
+  const int B = x.B, nq = nq_of(level), nl = 2 * B * nqp;
+  const size_t per_step = (size_t)B * (2 * nqp + 5 * nq + 2 * (alpha + 1) + (size_t)beta_at(level) * nqp) * N * 8;
+  const size_t gcap = stage_count(per_step, gi.size());
+  for (size_t c0 = 0; c0 < gi.size();) {
+    const int lone = gi[c0] == 0 ? 1 : 0;  // step 0 joins the first batch
+    const int nb = (int)std::min(std::max<size_t>(gcap, SUM_MAX_OUTS - lone), gi.size() - c0 - lone);
+    HeCt inner;
+    if (nb) inner = ct_new(level, true, x.scale * ql, nb * B);
+    for (int e0 = 0; e0 < lone + nb; e0 += SUM_MAX_OUTS) {
+      const int ng = std::min(SUM_MAX_OUTS, lone + nb - e0);
+      // inner_i = sum_j baby_j (.) diagonal_(i,j) for ng giant steps in one pass over the babies
+      std::vector<int> col(n1, -1), jl;
+      for (int g = 0; g < ng; g++)
+        for (auto& je : by_i[gi[c0 + e0 + g]])
+          if (col[je.first] < 0) {
+            col[je.first] = (int)jl.size();
+            jl.push_back(je.first);
+          }
+      const int nt = (int)jl.size();
+      std::vector<const u64*> ta(nt), tp((size_t)ng * nt, nullptr);
+      for (int t = 0; t < nt; t++) ta[t] = baby[jl[t]].d.p;
+      for (int g = 0; g < ng; g++)
+        for (auto& je : by_i[gi[c0 + e0 + g]]) tp[(size_t)g * nt + col[je.first]] = pts[je.second];
+      // step 0 writes the sum itself; the others members of the batch, whose
+      // components stand nb * B members apart
+      std::vector<u64*> outs(ng);
+      std::vector<size_t> skips(ng, 0);
+      for (int g = 0; g < ng; g++) {
+        const bool z = gi[c0 + e0 + g] == 0;
+        outs[g] = z ? acc.d.p : inner.member(0, (e0 + g - lone) * B);
+        if (!z) skips[g] = (size_t)(nb - 1) * B * nqp * N;
+      }
+      if (launch_mul_sum_multi(T, outs.data(), ng, ta.data(), tp.data(), nt, nl, nqp, qpm, stream, skips.data()))
+        continue;
       for (int g = 0; g < ng; g++) {
         std::vector<const u64*> a1, p1;
         for (int t = 0; t < nt; t++)
@@ -1432,27 +1458,28 @@ HeCt HeCtxImpl::lintrans_perm(const HeCt& x, const std::vector<int>& perm, const
             a1.push_back(ta[t]);
             p1.push_back(tp[(size_t)g * nt + t]);
           }
-        launch_mul_sum(T, outs[g], a1.data(), p1.data(), (int)a1.size(), nl, nqp, qpm, false, stream);
+        launch_mul_sum(T, outs[g], a1.data(), p1.data(), (int)a1.size(), nl, nqp, qpm, false, stream, skips[g]);
       }
     }
-    for (int g = 0; g < ng; g++) {
-      const int i = gi[c0 + g];
-      HeCt term;
-      if (i == 0) {
-        term = std::move(inner[g]);
-      } else {
-        HeCt t = moddown(inner[g], -1, true);
-        inner[g] = HeCt();
-        DevBuf d2 = decompose(t.poly(1), level, t.B);
-        term = hoisted(t, d2.p, galois((long)G.a * n1 * i));
-      }
-      if (!acc_set) {
-        acc = std::move(term);
+    if (nb) {
+      HeCt t = moddown(inner, -1, true);
+      inner = HeCt();
+      for (int d0 = 0; d0 < nb; d0 += (int)gcap) {
+        const int nd = std::min((int)gcap, nb - d0);
+        DevBuf d2 = decompose(t.member(1, d0 * B), level, nd * B);
+        std::vector<u64> gs;
+        std::vector<const u64*> ks;
+        for (int e = d0; e < d0 + nd; e++) {
+          gs.push_back(galois((long)G.a * n1 * gi[c0 + lone + e]));
+          ks.push_back(key(gs.back()).p);
+        }
+        launch_multsum_giant(T, acc.d.p, ks.data(), gs.data(), nd, d2.p, t.member(0, d0 * B), pmod.p, level, L, alpha,
+                             beta_at(level), B, acc_set, stream);
+        n_multsum += (long)B * nd;
         acc_set = true;
-      } else {
-        add_into(acc, term);
       }
     }
+    c0 += lone + nb;
   }
   HeCt md = moddown(acc, -1, true);
   HeCt r = rescale(md);
