@@ -185,6 +185,13 @@ struct DevBuf {
   size_t words = 0;
   DevBuf() {}
   DevBuf(DevPool* pl, size_t w) : pool(pl), words(w) { p = (u64*)pl->get(w * 8); }
+  // w words at at, owned elsewhere
+  static DevBuf part(u64* at, size_t w) {
+    DevBuf b;
+    b.p = at;
+    b.words = w;
+    return b;
+  }
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
   DevBuf(DevBuf&& o) noexcept : pool(o.pool), p(o.p), words(o.words) { o.p = nullptr; }
@@ -212,6 +219,8 @@ struct HeCt {
   int B = 1;
   double scale = 1.0;
   DevBuf d;
+  // set when d is a part of a larger block (d then owns nothing): keeps it
+  std::shared_ptr<DevBuf> whole;
   u64* poly(int p) const { return d.p + (size_t)p * B * nlimbs * N; }
   u64* limb(int p, int k) const { return d.p + ((size_t)p * B * nlimbs + k) * N; }
   // member b, component p

@@ -91,7 +91,9 @@ void launch_tensor_sum(const DeviceTables& T, u64* out3, const u64* const* a, co
                        const bool* b_packed = nullptr);
 void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, bool accumulate,
                    hipStream_t s);
-void launch_int_to_limbs(const DeviceTables& T, u64* out, const i64* in, int nlimbs, const LimbMap& m, hipStream_t s);
+// out [npoly][nlimbs][N] from in [npoly][N]
+void launch_int_to_limbs(const DeviceTables& T, u64* out, const i64* in, int nlimbs, const LimbMap& m, hipStream_t s,
+                         int npoly = 1);
 
 // key switching pieces
 struct FbcTable {
@@ -141,12 +143,14 @@ void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int
 // whether a fused ModDown into nq target limbs with this table takes digit
 // records (the int8 lift); only then may V arrive filled (v_ready)
 bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq);
+// skip: the second half of the polynomials' outputs lies skip words further on
 // pack_out: out's limbs of FP64 moduli (at most 46 bits) are stored packed in
 // their N-word slots: the low 32 bits of every residue, then one high byte
 // each (moduli of at most 40 bits) or two
 bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
                           const u64* x, int x_stride, const u64* pinv, u64* out, u64* y, u64* V, hipStream_t s,
-                          int src_stride = 0, int src_off = 0, bool v_ready = false, bool pack_out = false);
+                          int src_stride = 0, int src_off = 0, bool v_ready = false, bool pack_out = false,
+                          size_t skip = 0);
 // y[npoly][nq] = exact centred lift of the source limbs xp[npoly][ns] to each q_t
 void launch_fbc_to_q(const DeviceTables& T, u64* y, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
                      hipStream_t s);
@@ -169,6 +173,15 @@ void launch_multsum_giant(const DeviceTables& T, u64* out, const u64* const* key
 // With masks (plaintexts [nqp][N] in R_{Q_l P}, one per rotation) the outputs
 // are mask (.) rotation, added onto outs[r] when `accumulate`.
 #define MR_MAX 64
+#define MR_MEMBERS 8  // members a multi-rotation launch takes in one pass over the keys
+// Where the members of a multi-rotation launch lie, in words: member b's
+// digits from `digits`, its c0 from `c0`, its first component from an output,
+// the second component from the first, and (msk not empty) its mask from a
+// rotation's mask
+struct MrLayout {
+  std::vector<size_t> dig, c0, mem, msk;
+  size_t comp = 0;
+};
 // A second stream forked from and joined to the launching stream with
 // events (default priority).  With it, a multi-rotation launch runs the
 // kernel of its 60-bit limbs there, beside the kernel of its FP64 limbs: the
@@ -180,14 +193,14 @@ struct ForkStream {
 void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* const* keys, const u64* gs, int nrot,
                         const u64* digits, const u64* c0, const u64* pmod, int level, int L, int alpha, int beta,
                         int batch, hipStream_t s, const u64* const* masks = nullptr, bool accumulate = false,
-                        const ForkStream* fs = nullptr);
+                        const ForkStream* fs = nullptr, const MrLayout* lay = nullptr);
 // two bases under the same keys: outs[r] = masks[r] * rotation r of base 1
 // (digits, c0) + masks2[r] * rotation r of base 2 (digits2, c02), each key
 // word loaded once; false (nothing launched) where that does not apply
 bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64* const* keys, const u64* gs, int nrot,
                              const u64* digits, const u64* c0, const u64* const* masks, const u64* digits2,
                              const u64* c02, const u64* const* masks2, const u64* pmod, int level, int L, int alpha,
-                             int beta, int batch, hipStream_t s);
+                             int beta, int batch, hipStream_t s, const MrLayout* lay = nullptr);
 // Key inner products handed to a sink instead of being launched (merged
 // launches of several products): the arguments of one launch_multsum_rot or
 // launch_multsum call
@@ -205,6 +218,7 @@ struct KsWork {
 using KsSink = std::function<void(KsWork&&)>;
 // set the calling thread's sink (null: launch as usual); returns the previous one
 KsSink* ks_sink_exchange(KsSink* s);
+bool ks_sink_active();
 // one launch per member count over every item of `works` (any levels): the
 // same residues as their own launch_multsum_rot calls.  `table` is device
 // memory of multsum_list_table_bytes() bytes for the work table (uploaded
@@ -212,6 +226,11 @@ KsSink* ks_sink_exchange(KsSink* s);
 size_t multsum_list_table_bytes(const DeviceTables& T, const std::vector<KsWork>& works, int L, int alpha);
 void launch_multsum_list(const DeviceTables& T, const std::vector<KsWork>& works, void* table, size_t table_bytes,
                          int L, int alpha, hipStream_t s);
+// out[j][c][b] = P (mask1_j x[c][j][0][b] + mask2_j x[c][j][1][b]) for nblk
+// shift blocks' two bases, x [2][nblk][2][B][nq][N], out [nblk][2][B][nqp][N],
+// block j's masks j * mstride words after mask1 and mask2
+void launch_plift_masked(const DeviceTables& T, u64* out, const u64* x, const u64* mask1, const u64* mask2,
+                         size_t mstride, int nblk, int B, const u64* pmod, int level, int alpha, hipStream_t s);
 // P-lift: out[2][nqp][N] = (P c0, P c1) on Q limbs, 0 on P limbs
 void launch_plift(const DeviceTables& T, u64* out, const u64* c, const u64* pmod, int level, int alpha, int npoly,
                   hipStream_t s);

@@ -1074,7 +1074,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
                                                        const ModConst* __restrict__ mc, int nq,
                                                        const u64* __restrict__ x, int x_stride,
                                                        const u64* __restrict__ cpairs, u64* out, int il,
-                                                       int packed, int pack_out) {
+                                                       int packed, int pack_out, int half, size_t skip) {
   constexpr int S2 = GC + GD, T1 = 1 << S2, K = TILE / T1;
   __shared__ u64 sh[LDS_WORDS];
   const int limb = grid_limb(blockIdx.y, il);
@@ -1085,6 +1085,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
   const int blk0 = blockIdx.x * K;
   const size_t off = (size_t)blk0 * T1;
   u64* a = data + (size_t)limb * N + off;
+  if (p >= half) out += skip;
   const u64* xa = x + ((size_t)p * x_stride + t) * N + off;
   u64* oa = out + ((size_t)p * nq + t) * N + off;
   const ModConst mk = mc[m];
@@ -1282,7 +1283,7 @@ static void ntt2_modup(const DeviceTables& T, u64* digits, const ModupSrc& S, in
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void ntt2_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const LimbMap& map, const u64* x,
                          int x_stride, const u64* cpairs, u64* out, hipStream_t s, bool do_cols = true,
-                         bool packed = false, bool pack_out = false) {
+                         bool packed = false, bool pack_out = false, size_t skip = 0) {
   constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
   const int nlimbs = nq * npoly;
   dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
@@ -1294,7 +1295,7 @@ static void ntt2_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const
   ProfScope ps("ntt_fwd_rows_sub", s, 24.0 * nlimbs * T.N, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD) + T.N));
   hipLaunchKernelGGL((k_ntt_rows2_sub<LOGN, GC, GD>), gr, dim3(TPB), 0, s, y, map, T.psi, T.psi_sh, T.psi_f, T.mc,
                      nq, x, x_stride, cpairs, out, interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave),
-                     packed ? 1 : 0, pack_out ? 1 : 0);
+                     packed ? 1 : 0, pack_out ? 1 : 0, npoly / 2, skip);
 }
 
 template <int LOGN, int GA, int GB, int GC, int GD>
@@ -2074,7 +2075,8 @@ void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b,
   else hipLaunchKernelGGL(k_tensor<false>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
 }
 
-__global__ void k_int_to_limbs(u64* out, const i64* in, int nlimbs, LimbMap map, int logN,
+// per limbs of each polynomial of in
+__global__ void k_int_to_limbs(u64* out, const i64* in, int per, LimbMap map, int logN,
                                const ModConst* __restrict__ mc) {
   const u64 N = 1ull << logN;
   u32 i = blockIdx.x * TPB + threadIdx.x;
@@ -2082,11 +2084,11 @@ __global__ void k_int_to_limbs(u64* out, const i64* in, int nlimbs, LimbMap map,
   if (i >= N) return;
   int m = limb_mod(map, k);
   if (m < 0) return;
-  out[(size_t)k * N + i] = reduce_signed(in[i], mc[m]);
+  out[(size_t)k * N + i] = reduce_signed(in[(size_t)(k / per) * N + i], mc[m]);
 }
 void launch_int_to_limbs(const DeviceTables& T, u64* out, const i64* in, int nlimbs, const LimbMap& m,
-                         hipStream_t s) {
-  dim3 grid(cdiv(T.N, TPB), nlimbs);
+                         hipStream_t s, int npoly) {
+  dim3 grid(cdiv(T.N, TPB), nlimbs * npoly);
   hipLaunchKernelGGL(k_int_to_limbs, grid, dim3(TPB), 0, s, out, in, nlimbs, m, T.logN, T.mc);
 }
 
@@ -2787,7 +2789,7 @@ __global__ void __launch_bounds__(2 * TPB) __attribute__((amdgpu_waves_per_eu(4)
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void moddown_fused(const DeviceTables& T, u64* y, const u64* V, const FbcArgs& A, int nq, int npoly,
                           const LimbMap& map, const u64* x, int x_stride, const u64* pinv, u64* out, hipStream_t s,
-                          const u64* cdig, bool pack_out) {
+                          const u64* cdig, bool pack_out, size_t skip) {
   constexpr int R = 1 << (GA + GB), C = TILE / R;
   {
     ProfScope ps("ntt_fwd_cols_fbc", s, 8.0 * T.N * npoly * ((double)A.ns + 1 + nq),
@@ -2821,7 +2823,7 @@ static void moddown_fused(const DeviceTables& T, u64* y, const u64* V, const Fbc
     }
   }
   ntt2_fwd_sub<LOGN, GA, GB, GC, GD>(T, y, nq, npoly, map, x, x_stride, pinv, out, s, false, cdig != nullptr,
-                                     pack_out);
+                                     pack_out, skip);
 }
 // ModDown of npoly polynomials: xp_coef their P limbs in the coefficient
 // domain [npoly][ns][N], x the R_{Q_l P} data ([npoly][x_stride][N]), out
@@ -2856,7 +2858,7 @@ bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq) {
 }
 bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
                           const u64* x, int x_stride, const u64* pinv, u64* out, u64* y, u64* V, hipStream_t s,
-                          int src_stride, int src_off, bool v_ready, bool pack_out) {
+                          int src_stride, int src_off, bool v_ready, bool pack_out, size_t skip) {
   if (T.logN < 12 || T.logN > 16 || tab.ns > 4) return false;
   const FbcArgs A = fbc_args(tab, src_stride > 0 ? src_stride : tab.ns, src_stride > 0 ? src_off : 0);
   const u64* cdig = fbc_digit_path(T, tab, nq) ? tab.cdig : nullptr;
@@ -2877,7 +2879,7 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
   for (int k = 0; k < nq; k++) map.idx[k] = (short)k;
   return ntt_dispatch(T.logN, [&](auto sp) {
     using S = decltype(sp);
-    moddown_fused<NTT_SPLIT_ARGS>(T, y, V, A, nq, npoly, map, x, x_stride, pinv, out, s, cdig, pack_out);
+    moddown_fused<NTT_SPLIT_ARGS>(T, y, V, A, nq, npoly, map, x, x_stride, pinv, out, s, cdig, pack_out, skip);
   });
 }
 
@@ -2906,6 +2908,7 @@ void launch_moddown_final(const DeviceTables& T, u64* out, const u64* x, const u
 // Each key word is read once and applied to every member.
 // digits [B][beta][nqp][N], c0 [B][nq][N], out [2][B][nqp][N]
 #define MS_MAXB 8
+static_assert(MS_MAXB == MR_MEMBERS, "one member limit");
 // Key inner product of MB members, reduced once per output:
 //  * FP64 (q < 2^46): the beta <= 16 signed products a w - k q (each below q
 //    in absolute value) sum exactly in a double and one f64_canon reduces
@@ -3066,6 +3069,11 @@ struct MultiRot {
   const u64* digits2;
   const u64* c02;
   const u64* mask2[MR_MAX];
+  // the launch's members: words from digits (digits2), c0 (c02), out[r] and,
+  // with member_masks, mask[r] (mask2[r]) to member b's, and from an output's
+  // first component to its second
+  size_t dig[MS_MAXB], c0[MS_MAXB], mem[MS_MAXB], msk[MS_MAXB], comp;
+  int member_masks;
 };
 // Limbs of R_{Q_l P} in launch order: the integer limbs (moduli of 47 bits
 // or more, four members at a time to bound their registers) are spread
@@ -3080,9 +3088,8 @@ struct PosList {
 template <int MB, int RPW>
 __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int nr, const u64* __restrict__ digits,
                                                   const u64* __restrict__ c0, const u64* __restrict__ pmod, int nq,
-                                                  int nqp, int beta, int nmods, int B, int b0, int m, int pos,
-                                                  u32 src, int logN, u64 N, const ModConst& mk) {
-  const size_t dstride = (size_t)beta * nqp * N;
+                                                  int nqp, int beta, int nmods, int m, int pos, u32 src, int logN,
+                                                  u64 N, const ModConst& mk) {
   const double q = mk.qf, qi = mk.qinvf;
   u32 idx[RPW];
   const u64* key[RPW];
@@ -3106,7 +3113,7 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
     kan[g] = ldnt(&key[g][((size_t)1 * nmods + m) * N + idx[g]]);
   }
 #pragma unroll
-  for (int b = 0; b < MB; b++) dn[b] = digits[(size_t)(b0 + b) * dstride + (size_t)pos * N + src];
+  for (int b = 0; b < MB; b++) dn[b] = digits[R.dig[b] + (size_t)pos * N + src];
   for (int j = 0; j < beta; j++) {
     double kb[RPW], ka[RPW], d[MB];
 #pragma unroll
@@ -3123,7 +3130,7 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
         kan[g] = ldnt(&key[g][(((size_t)(j + 1) * 2 + 1) * nmods + m) * N + idx[g]]);
       }
 #pragma unroll
-      for (int b = 0; b < MB; b++) dn[b] = digits[(size_t)(b0 + b) * dstride + ((size_t)(j + 1) * nqp + pos) * N + src];
+      for (int b = 0; b < MB; b++) dn[b] = digits[R.dig[b] + ((size_t)(j + 1) * nqp + pos) * N + src];
     }
 #pragma unroll
     for (int g = 0; g < RPW; g++)
@@ -3142,7 +3149,7 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
 #pragma unroll
   for (int b = 0; b < MB; b++)
     cpd[b] = (c0 && pos < nq)
-                 ? u2d(mul_const_any(c0[((size_t)(b0 + b) * nq + pos) * N + src], pmod[2 * m], pmod[2 * m + 1], mk))
+                 ? u2d(mul_const_any(c0[R.c0[b] + (size_t)pos * N + src], pmod[2 * m], pmod[2 * m + 1], mk))
                  : 0.0;
 #pragma unroll
   for (int g = 0; g < RPW; g++) {
@@ -3150,12 +3157,13 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
     const int r = r0 + g;
     const u64* mask = R.mask[r];
     const u32 i = idx[g];
-    const double mv = mask ? u2d(mask[(size_t)pos * N + i]) : 0.0;
+    double mv = mask ? u2d(mask[R.msk[0] + (size_t)pos * N + i]) : 0.0;
 #pragma unroll
     for (int b = 0; b < MB; b++) {
       double a0 = s0[g][b] + cpd[b], a1 = s1[g][b];
-      u64* o0 = &R.out[r][((size_t)(b0 + b) * nqp + pos) * N + i];
-      u64* o1 = &R.out[r][((size_t)(B + b0 + b) * nqp + pos) * N + i];
+      u64* o0 = &R.out[r][R.mem[b] + (size_t)pos * N + i];
+      u64* o1 = o0 + R.comp;
+      if (b > 0 && R.member_masks) mv = u2d(mask[R.msk[b] + (size_t)pos * N + i]);
       if (mask) {
         if (beta > 15) {
           a0 = f64_centre(a0, q, qi);
@@ -3183,10 +3191,9 @@ template <int MB, int RPW>
 __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0, int nr,
                                                        const u64* __restrict__ digits, const u64* __restrict__ c0,
                                                        const u64* __restrict__ pmod, int nq, int nqp, int beta,
-                                                       int nmods, int B, int b0, int m, int pos, u32 src, int logN,
-                                                       u64 N, const ModConst& mk) {
+                                                       int nmods, int m, int pos, u32 src, int logN, u64 N,
+                                                       const ModConst& mk) {
   constexpr int NB = 2 * MB;
-  const size_t dstride = (size_t)beta * nqp * N;
   const double q = mk.qf, qi = mk.qinvf;
   u32 idx[RPW];
   const u64* key[RPW];
@@ -3209,7 +3216,7 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
     kan[g] = ldnt(&key[g][((size_t)1 * nmods + m) * N + idx[g]]);
   }
 #pragma unroll
-  for (int b = 0; b < NB; b++) dn[b] = dg[b / MB][(size_t)(b0 + b % MB) * dstride + (size_t)pos * N + src];
+  for (int b = 0; b < NB; b++) dn[b] = dg[b / MB][R.dig[b % MB] + (size_t)pos * N + src];
   for (int j = 0; j < beta; j++) {
     double kb[RPW], ka[RPW], d[NB];
 #pragma unroll
@@ -3227,7 +3234,7 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
       }
 #pragma unroll
       for (int b = 0; b < NB; b++)
-        dn[b] = dg[b / MB][(size_t)(b0 + b % MB) * dstride + ((size_t)(j + 1) * nqp + pos) * N + src];
+        dn[b] = dg[b / MB][R.dig[b % MB] + ((size_t)(j + 1) * nqp + pos) * N + src];
     }
 #pragma unroll
     for (int g = 0; g < RPW; g++)
@@ -3241,7 +3248,7 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
   double cpd[NB];
 #pragma unroll
   for (int b = 0; b < NB; b++)
-    cpd[b] = pos < nq ? u2d(mul_const_any(cs[b / MB][((size_t)(b0 + b % MB) * nq + pos) * N + src], pmod[2 * m],
+    cpd[b] = pos < nq ? u2d(mul_const_any(cs[b / MB][R.c0[b % MB] + (size_t)pos * N + src], pmod[2 * m],
                                           pmod[2 * m + 1], mk))
                       : 0.0;
 #pragma unroll
@@ -3249,9 +3256,13 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
     if (g >= nr) break;
     const int r = r0 + g;
     const u32 i = idx[g];
-    const double mv1 = u2d(R.mask[r][(size_t)pos * N + i]), mv2 = u2d(R.mask2[r][(size_t)pos * N + i]);
+    double mv1 = u2d(R.mask[r][R.msk[0] + (size_t)pos * N + i]), mv2 = u2d(R.mask2[r][R.msk[0] + (size_t)pos * N + i]);
 #pragma unroll
     for (int b = 0; b < MB; b++) {
+      if (b > 0 && R.member_masks) {
+        mv1 = u2d(R.mask[r][R.msk[b] + (size_t)pos * N + i]);
+        mv2 = u2d(R.mask2[r][R.msk[b] + (size_t)pos * N + i]);
+      }
       double a0 = s0[g][b] + cpd[b], a1 = s1[g][b], e0 = s0[g][MB + b] + cpd[MB + b], e1 = s1[g][MB + b];
       if (beta > 15) {
         a0 = f64_centre(a0, q, qi);
@@ -3261,8 +3272,9 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
       }
       a0 = f64_mulmod_signed(a0, mv1, q, qi) + f64_mulmod_signed(e0, mv2, q, qi);
       a1 = f64_mulmod_signed(a1, mv1, q, qi) + f64_mulmod_signed(e1, mv2, q, qi);
-      stnt(&R.out[r][((size_t)(b0 + b) * nqp + pos) * N + i], d2u(f64_canon(a0, q, qi)));
-      stnt(&R.out[r][((size_t)(B + b0 + b) * nqp + pos) * N + i], d2u(f64_canon(a1, q, qi)));
+      u64* o0 = &R.out[r][R.mem[b] + (size_t)pos * N + i];
+      stnt(o0, d2u(f64_canon(a0, q, qi)));
+      stnt(o0 + R.comp, d2u(f64_canon(a1, q, qi)));
     }
   }
 }
@@ -3332,11 +3344,11 @@ __device__ __forceinline__ void piece_mac(double* S, double d0, double d1, doubl
   S[3] = fma(d2, k1, S[3]);
   S[4] = fma(d2, k2, S[4]);
 }
-template <int MB>
+template <int MB, int B0>
 __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i, const u64* __restrict__ dig,
-                                                 size_t dstride, size_t jstride, const u64* __restrict__ c0,
+                                                 size_t jstride, const u64* __restrict__ c0,
                                                  const u64* __restrict__ pmod, int nq, int nqp, int beta, int nmods,
-                                                 int B, int b0, int m, int pos, u32 src, u64 N, const ModConst& mk) {
+                                                 int m, int pos, u32 src, u64 N, const ModConst& mk) {
   const u64* key = R.key[r];
   double S0[MB][5], S1[MB][5];
 #pragma unroll
@@ -3348,7 +3360,7 @@ __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i
   // next pass over the members, from L2.
   u64 kbn = key[(size_t)m * N + i], kan = key[((size_t)nmods + m) * N + i], dn[MB];
 #pragma unroll
-  for (int b = 0; b < MB; b++) dn[b] = dig[(size_t)b * dstride];
+  for (int b = 0; b < MB; b++) dn[b] = dig[R.dig[B0 + b]];
   for (int j = 0; j < beta; j++) {
     double kb0, kb1, kb2, ka0, ka1, ka2;
     split20(kbn, kb0, kb1, kb2);
@@ -3360,7 +3372,7 @@ __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i
       kbn = key[(((size_t)(j + 1) * 2 + 0) * nmods + m) * N + i];
       kan = key[(((size_t)(j + 1) * 2 + 1) * nmods + m) * N + i];
 #pragma unroll
-      for (int b = 0; b < MB; b++) dn[b] = dig[(size_t)b * dstride + (size_t)(j + 1) * jstride];
+      for (int b = 0; b < MB; b++) dn[b] = dig[R.dig[B0 + b] + (size_t)(j + 1) * jstride];
     }
 #pragma unroll
     for (int b = 0; b < MB; b++) {
@@ -3371,15 +3383,16 @@ __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i
     }
   }
   const u64* mask = R.mask[r];
-  const u64 mv = mask ? mask[(size_t)pos * N + i] : 0;
+  u64 mv = mask ? mask[R.msk[B0] + (size_t)pos * N + i] : 0;
 #pragma unroll
   for (int b = 0; b < MB; b++) {
     u64 v0 = fold_pieces(S0[b], mk), v1 = fold_pieces(S1[b], mk);
     if (c0 && pos < nq)
-      v0 = add_mod(v0, mul_const_any(c0[((size_t)(b0 + b) * nq + pos) * N + src], pmod[2 * m], pmod[2 * m + 1], mk),
+      v0 = add_mod(v0, mul_const_any(c0[R.c0[B0 + b] + (size_t)pos * N + src], pmod[2 * m], pmod[2 * m + 1], mk),
                    mk.q);
-    u64* o0 = &R.out[r][((size_t)(b0 + b) * nqp + pos) * N + i];
-    u64* o1 = &R.out[r][((size_t)(B + b0 + b) * nqp + pos) * N + i];
+    u64* o0 = &R.out[r][R.mem[B0 + b] + (size_t)pos * N + i];
+    u64* o1 = o0 + R.comp;
+    if (b > 0 && R.member_masks) mv = mask[R.msk[B0 + b] + (size_t)pos * N + i];
     if (mask) {
       v0 = mul_mod_any(v0, mv, mk);
       v1 = mul_mod_any(v1, mv, mk);
@@ -3397,25 +3410,24 @@ __device__ __forceinline__ void multsum_int_pass(const MultiRot& R, int r, u32 i
 template <int MB, int MP = 4>
 __device__ __forceinline__ void multsum_rot_group_int(const MultiRot& R, int r0, int nr, const u64* __restrict__ digits,
                                                       const u64* __restrict__ c0, const u64* __restrict__ pmod,
-                                                      int nq, int nqp, int beta, int nmods, int B, int b0, int m,
-                                                      int pos, u32 src, int logN, u64 N, const ModConst& mk) {
-  const size_t dstride = (size_t)beta * nqp * N, jstride = (size_t)nqp * N;
-  const u64* dig = digits + (size_t)b0 * dstride + (size_t)pos * N + src;
+                                                      int nq, int nqp, int beta, int nmods, int m, int pos, u32 src,
+                                                      int logN, u64 N, const ModConst& mk) {
+  const size_t jstride = (size_t)nqp * N;
+  const u64* dig = digits + (size_t)pos * N + src;
   constexpr int M1 = MB > MP ? MP : MB;
   for (int r = r0; r < r0 + nr; r++) {
     const u32 i = automorph_src(src, R.ginv[r], logN);
-    multsum_int_pass<M1>(R, r, i, dig, dstride, jstride, c0, pmod, nq, nqp, beta, nmods, B, b0, m, pos, src, N, mk);
-    if (MB > M1)
-      multsum_int_pass<(MB > M1 ? MB - M1 : 1)>(R, r, i, dig + M1 * dstride, dstride, jstride, c0, pmod, nq, nqp,
-                                                beta, nmods, B, b0 + M1, m, pos, src, N, mk);
+    multsum_int_pass<M1, 0>(R, r, i, dig, jstride, c0, pmod, nq, nqp, beta, nmods, m, pos, src, N, mk);
+    if constexpr (MB > M1)
+      multsum_int_pass<MB - M1, M1>(R, r, i, dig, jstride, c0, pmod, nq, nqp, beta, nmods, m, pos, src, N, mk);
   }
 }
 // RPW: rotations per work-group (their FP64 limbs share the digit loads)
 template <int MB, bool F64, int RPW, bool PAIR = false>
 __global__ void __launch_bounds__(TPB) k_multsum_rot(MultiRot R, PosList P, int nrot, const u64* __restrict__ digits,
                                                      const u64* __restrict__ c0, const u64* __restrict__ pmod,
-                                                     int nq, int nqp, int L, int beta, int nmods, int B, int b0,
-                                                     int logN, const ModConst* __restrict__ mc) {
+                                                     int nq, int nqp, int L, int beta, int nmods, int logN,
+                                                     const ModConst* __restrict__ mc) {
   const u64 N = 1ull << logN;
   const u32 ngroups = (u32)((nrot + RPW - 1) / RPW);
   const u32 x = blockIdx.x, rest = x >> 3;
@@ -3429,13 +3441,12 @@ __global__ void __launch_bounds__(TPB) k_multsum_rot(MultiRot R, PosList P, int 
   const ModConst mk = mc[m];
   if (F64 || mk.bits <= F64_LAZY_BITS) {
     if (PAIR)
-      multsum_rot_group_pair<MB, RPW>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, B, b0, m, pos, src, logN, N,
-                                      mk);
+      multsum_rot_group_pair<MB, RPW>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, m, pos, src, logN, N, mk);
     else
-      multsum_rot_group<MB, RPW>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, B, b0, m, pos, src, logN, N, mk);
+      multsum_rot_group<MB, RPW>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, m, pos, src, logN, N, mk);
     return;
   }
-  multsum_rot_group_int<MB>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, B, b0, m, pos, src, logN, N, mk);
+  multsum_rot_group_int<MB>(R, r0, nr, digits, c0, pmod, nq, nqp, beta, nmods, m, pos, src, logN, N, mk);
 }
 
 // The 60-bit limbs of a multi-rotation launch on their own (knob
@@ -3448,8 +3459,8 @@ template <int MB, int MP>
 __global__ void __launch_bounds__(TPB) k_multsum_rot_int(MultiRot R, PosList P, int nrot, int rc,
                                                          const u64* __restrict__ digits,
                                                          const u64* __restrict__ c0, const u64* __restrict__ pmod,
-                                                         int nq, int nqp, int L, int beta, int nmods, int B, int b0,
-                                                         int logN, const ModConst* __restrict__ mc) {
+                                                         int nq, int nqp, int L, int beta, int nmods, int logN,
+                                                         const ModConst* __restrict__ mc) {
   const u64 N = 1ull << logN;
   const u32 x = blockIdx.x, rest = x >> 3;
   const u32 octets = (u32)((N + 8 * TPB - 1) / (8 * TPB));  // source-block octets
@@ -3463,7 +3474,7 @@ __global__ void __launch_bounds__(TPB) k_multsum_rot_int(MultiRot R, PosList P, 
   const int pos = P.pos[blockIdx.y];
   const int m = pos < nq ? pos : L + 1 + (pos - nq);
   const ModConst mk = mc[m];
-  multsum_rot_group_int<MB, MP>(R, r, 1, digits, c0, pmod, nq, nqp, beta, nmods, B, b0, m, pos, src, logN, N, mk);
+  multsum_rot_group_int<MB, MP>(R, r, 1, digits, c0, pmod, nq, nqp, beta, nmods, m, pos, src, logN, N, mk);
 }
 
 static u64 inv_mod_2n(u64 g, u64 twoN) {
@@ -3504,7 +3515,7 @@ struct KsItem {
   const u64* digits;
   const u64* c0;
   const u64* pmod;
-  int nrot, nq, nqp, beta, B, b0;
+  int nrot, nq, nqp, beta;
 };
 constexpr int KS_RPW = 4;  // rotations per work-group in the merged launch
 thread_local KsSink* tls_ks_sink = nullptr;
@@ -3513,6 +3524,7 @@ KsSink* ks_sink_exchange(KsSink* s) {
   tls_ks_sink = s;
   return old;
 }
+bool ks_sink_active() { return tls_ks_sink != nullptr; }
 
 template <int MB>
 __global__ void __launch_bounds__(TPB) k_multsum_list(const KsItem* __restrict__ items, const u32* __restrict__ start,
@@ -3540,14 +3552,27 @@ __global__ void __launch_bounds__(TPB) k_multsum_list(const KsItem* __restrict__
   const int m = pos < it.nq ? pos : L + 1 + (pos - it.nq);
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
-    multsum_rot_group<MB, KS_RPW>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, it.B,
-                                  it.b0, m, pos, src, logN, N, mk);
+    multsum_rot_group<MB, KS_RPW>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, m, pos,
+                                  src, logN, N, mk);
     return;
   }
-  multsum_rot_group_int<MB>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, it.B, it.b0, m,
-                            pos, src, logN, N, mk);
+  multsum_rot_group_int<MB>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, m, pos, src,
+                            logN, N, mk);
 }
 
+// members b0 .. b0 + mb - 1 of a launch: those of `lay`, or of a batch of B
+// stacked as [.][B][limbs][N] throughout
+static void mr_members(MultiRot& R, const MrLayout* lay, int b0, int mb, int B, int nq, int nqp, int beta, u64 N) {
+  R.member_masks = lay && !lay->msk.empty() ? 1 : 0;
+  R.comp = lay ? lay->comp : (size_t)B * nqp * N;
+  for (int b = 0; b < MS_MAXB; b++) {
+    const size_t x = b0 + (b < mb ? b : 0);
+    R.dig[b] = lay ? lay->dig[x] : x * beta * nqp * N;
+    R.c0[b] = lay ? lay->c0[x] : x * nq * N;
+    R.mem[b] = lay ? lay->mem[x] : x * nqp * N;
+    R.msk[b] = R.member_masks ? lay->msk[x] : 0;
+  }
+}
 // the work's items: rotations in chunks of MR_MAX, members in chunks of
 // MS_MAXB (an item's member count decides the launch it goes to)
 static void ks_items(const DeviceTables& T, const KsWork& w, int L, int alpha, std::vector<std::pair<int, KsItem>>& out) {
@@ -3574,8 +3599,7 @@ static void ks_items(const DeviceTables& T, const KsWork& w, int L, int alpha, s
       it.nq = nq;
       it.nqp = nqp;
       it.beta = w.beta;
-      it.B = w.B;
-      it.b0 = b0;
+      mr_members(it.R, nullptr, b0, std::min(MS_MAXB, w.B - b0), w.B, nq, nqp, w.beta, T.N);
       out.push_back({std::min(MS_MAXB, w.B - b0), it});
     }
   }
@@ -3707,8 +3731,9 @@ static MrCost mr_cost(const DeviceTables& T, const PosList& pl, int n, int nq, i
 void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* const* keys, const u64* gs, int nrot,
                         const u64* digits, const u64* c0, const u64* pmod, int level, int L, int alpha, int beta,
                         int batch, hipStream_t s, const u64* const* masks, bool accumulate,
-                        const ForkStream* fs) {
+                        const ForkStream* fs, const MrLayout* lay) {
   if (tls_ks_sink) {
+    if (lay) throw std::runtime_error("merged key inner products take plainly stacked members");
     KsWork w;
     w.outs.assign(outs, outs + nrot);
     w.keys.assign(keys, keys + nrot);
@@ -3753,6 +3778,7 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
     const bool split = ni > 0 && g_knobs.mr_int_split != 0;
     for (int b0 = 0; b0 < batch; b0 += mstep) {
       const int mb = batch - b0 < mstep ? batch - b0 : mstep;
+      mr_members(R, lay, b0, mb, batch, nq, nqp, beta, T.N);
       const MrCost all = mr_cost(T, P, nqp, nq, L, nr, mb, beta, c0 != nullptr, masks != nullptr, R.accumulate != 0);
       const MrCost fp = split ? mr_cost(T, pf, nf, nq, L, nr, mb, beta, c0 != nullptr, masks != nullptr,
                                         R.accumulate != 0)
@@ -3760,7 +3786,7 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
       // FP64-only kernel when every launched limb is FP64 (the integer branch compiled out)
 #define MR_LAUNCH(K, FP, G, PL, NP)                                                                                \
   hipLaunchKernelGGL((k_multsum_rot<K, FP, G>), dim3(cdiv(nblk, 8) * 8 * cdiv(nr, G), NP), dim3(TPB), 0, s, R, PL, \
-                     nr, digits, c0, pmod, nq, nqp, L, beta, T.nmods, batch, b0, T.logN, T.mc)
+                     nr, digits, c0, pmod, nq, nqp, L, beta, T.nmods, T.logN, T.mc)
 #define MR_GROUPS(K, FP, PL, NP)             \
   if (rpw == 4) MR_LAUNCH(K, FP, 4, PL, NP); \
   else if (rpw == 2) MR_LAUNCH(K, FP, 2, PL, NP); \
@@ -3793,10 +3819,10 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
   case K:                                                                                                        \
     if (g_knobs.mr_int_pass == 8)                                                                                \
       hipLaunchKernelGGL((k_multsum_rot_int<K, 8>), grid, dim3(TPB), 0, si, R, pi, nr, rc, digits, c0, pmod, nq, \
-                         nqp, L, beta, T.nmods, batch, b0, T.logN, T.mc);                                        \
+                         nqp, L, beta, T.nmods, T.logN, T.mc);                                                   \
     else                                                                                                         \
       hipLaunchKernelGGL((k_multsum_rot_int<K, 4>), grid, dim3(TPB), 0, si, R, pi, nr, rc, digits, c0, pmod, nq, \
-                         nqp, L, beta, T.nmods, batch, b0, T.logN, T.mc);                                        \
+                         nqp, L, beta, T.nmods, T.logN, T.mc);                                                   \
     break;
         switch (mb) {
           MRI_CASE(1) MRI_CASE(2) MRI_CASE(3) MRI_CASE(4) MRI_CASE(5) MRI_CASE(6) MRI_CASE(7) MRI_CASE(8)
@@ -3830,7 +3856,7 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
 bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64* const* keys, const u64* gs, int nrot,
                              const u64* digits, const u64* c0, const u64* const* masks, const u64* digits2,
                              const u64* c02, const u64* const* masks2, const u64* pmod, int level, int L, int alpha,
-                             int beta, int batch, hipStream_t s) {
+                             int beta, int batch, hipStream_t s, const MrLayout* lay) {
   if (!g_knobs.mr_pair || tls_ks_sink || !masks || !masks2) return false;
   const int nq = level + 1, nqp = nq + alpha;
   const PosList P = pos_order(T, nq, nqp, L);
@@ -3863,6 +3889,7 @@ bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64*
     }
     for (int b0 = 0; b0 < batch; b0 += mstep) {
       const int mb = batch - b0 < mstep ? batch - b0 : mstep;
+      mr_members(R, lay, b0, mb, batch, nq, nqp, beta, T.N);
       if (ni > 0) {
         // the 60-bit limbs: base 1, then base 2 added on
         MultiRot R2 = R;
@@ -3880,10 +3907,10 @@ bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64*
   case K:                                                                                                             \
     if (g_knobs.mr_int_pass == 8)                                                                                     \
       hipLaunchKernelGGL((k_multsum_rot_int<K, 8>), grid, dim3(TPB), 0, s, RI, pi, nr, rc, dg, cz, pmod, nq, nqp, L, \
-                         beta, T.nmods, batch, b0, T.logN, T.mc);                                                     \
+                         beta, T.nmods, T.logN, T.mc);                                                                \
     else                                                                                                              \
       hipLaunchKernelGGL((k_multsum_rot_int<K, 4>), grid, dim3(TPB), 0, s, RI, pi, nr, rc, dg, cz, pmod, nq, nqp, L, \
-                         beta, T.nmods, batch, b0, T.logN, T.mc);                                                     \
+                         beta, T.nmods, T.logN, T.mc);                                                                \
     break;
           switch (mb) { MRP_INT(1) MRP_INT(2) MRP_INT(3) MRP_INT(4) MRP_INT(5) MRP_INT(6) MRP_INT(7) MRP_INT(8) }
 #undef MRP_INT
@@ -3897,7 +3924,7 @@ bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64*
 #define MRP_FP(K)                                                                                                    \
   case K:                                                                                                            \
     hipLaunchKernelGGL((k_multsum_rot<K, true, RPW, true>), dim3(cdiv(nblk, 8) * 8 * cdiv(nr, RPW), nf), dim3(TPB), \
-                       0, s, R, pf, nr, digits, c0, pmod, nq, nqp, L, beta, T.nmods, batch, b0, T.logN, T.mc);      \
+                       0, s, R, pf, nr, digits, c0, pmod, nq, nqp, L, beta, T.nmods, T.logN, T.mc);                 \
     break;
       switch (mb) { MRP_FP(1) MRP_FP(2) MRP_FP(3) MRP_FP(4) MRP_FP(5) MRP_FP(6) MRP_FP(7) MRP_FP(8) }
 #undef MRP_FP
@@ -4175,6 +4202,37 @@ void launch_multsum_giant(const DeviceTables& T, u64* out, const u64* const* key
 #undef MG_LAUNCH
     }
   }
+}
+
+// Column shifts by a multiple of the block size: the masked P-lifts
+//   out[j][c][b] = P (mask1_j x[c][j][0][b] + mask2_j x[c][j][1][b])
+// of nblk blocks' two bases (x [2][nblk][2][B][nq][N]), out
+// [nblk][2][B][nqp][N], block j's masks j * mstride words on.  One pass in
+// place of the two lifts and a sum over each block.
+__global__ void k_plift_masked(u64* out, const u64* __restrict__ x, const u64* __restrict__ mask1,
+                               const u64* __restrict__ mask2, size_t mstride, int nblk, int B,
+                               const u64* __restrict__ pmod, int nq, int nqp, int logN,
+                               const ModConst* __restrict__ mc) {
+  const u64 N = 1ull << logN;
+  const u32 i = blockIdx.x * TPB + threadIdx.x;
+  const int pos = blockIdx.y, z = blockIdx.z, b = z % B, c = (z / B) & 1, j = z / (2 * B);
+  if (i >= N) return;
+  u64 v = 0;
+  if (pos < nq) {
+    const ModConst mk = mc[pos];
+    const size_t x1 = ((((size_t)c * nblk + j) * 2 * B + b) * nq + pos) * N + i, om = j * mstride + (size_t)pos * N + i;
+    const u64 m1 = mask1[om], m2 = mask2[om], a = x[x1], e = x[x1 + (size_t)B * nq * N];
+    v = mul_const_any(add_mod(mul_mod_any(a, m1, mk), mul_mod_any(e, m2, mk), mk.q), pmod[2 * pos],
+                      pmod[2 * pos + 1], mk);
+  }
+  out[((size_t)z * nqp + pos) * N + i] = v;
+}
+void launch_plift_masked(const DeviceTables& T, u64* out, const u64* x, const u64* mask1, const u64* mask2,
+                         size_t mstride, int nblk, int B, const u64* pmod, int level, int alpha, hipStream_t s) {
+  const int nq = level + 1, nqp = nq + alpha, np = 2 * nblk * B;
+  ProfScope ps("plift", s, 8.0 * T.N * (np * (2.0 * nq + nqp) + 2.0 * nblk * nq), mm_q(T, nq, 3.0 * T.N, np));
+  hipLaunchKernelGGL(k_plift_masked, dim3(cdiv(T.N, TPB), nqp, np), dim3(TPB), 0, s, out, x, mask1, mask2, mstride,
+                     nblk, B, pmod, nq, nqp, T.logN, T.mc);
 }
 
 // P-lift of npoly polys [npoly][nq] -> [npoly][nqp]: P * c on Q limbs, 0 on P limbs

@@ -96,9 +96,9 @@ struct CovState {
 };
 
 // temporaries of one batched stage (elements taken through ModDown, Decompose
-// and the key inner products together): 1 GiB holds every element of a
-// product up to N = 2^14 and the 3 to 20 that fill the chip above
-#define HE_STAGE_BYTES (1ull << 30)
+// and the key inner products together): 768 MiB holds every element of a
+// product up to N = 2^14 and the 2 to 15 that fill the chip above
+#define HE_STAGE_BYTES (768ull << 20)
 
 struct HeCtxImpl {
   int logN = 0;
@@ -131,7 +131,8 @@ struct HeCtxImpl {
   DevBuf s_ntt, pk;
   bool have_sk = false;
   std::map<u64, DevBuf> keys;             // Galois element -> key; 0 = relinearisation (FP64 limbs as doubles)
-  std::map<std::string, DevBuf> ptcache;
+  std::map<std::string, const u64*> ptcache;
+  std::vector<DevBuf> ptbanks;  // plaintexts made together, one after the other
   // a transform's diagonals present (giant, baby step) and their plaintexts
   // (entries of ptcache, kept for the context's life)
   struct LtPlan {
@@ -160,10 +161,13 @@ struct HeCtxImpl {
   size_t stage_count(size_t per_element, size_t elements) const;
   HeCt ct_new(int level, bool qp, double scale, int B = 1);
   HeCt ct_copy(const HeCt& x);
+  // `count` consecutive elements of B members from element `first` of the
+  // elements stacked in `whole` (shaped like `like`)
+  HeCt ct_part(const std::shared_ptr<DevBuf>& whole, const HeCt& like, size_t first, size_t count, int B);
   void copy_limbs(u64* dst, const u64* src, size_t nlimbs, const char* family = "copy_limbs");
 
   DevBuf encode_batch(const double* z_host, int nz, int batch, double delta);
-  void int_to_ntt(u64* out, const i64* m, const LimbMap& map);
+  void int_to_ntt(u64* out, const i64* m, const LimbMap& map, int npoly = 1);
 
   void keygen_secret();
   void swk_gen(const u64* sp, u64 kid, DevBuf& out);
@@ -180,13 +184,9 @@ struct HeCtxImpl {
   HeCt drop(const HeCt& a, int level);
   HeCt rescale(const HeCt& a, int out_level = -1);
   DevBuf decompose(const u64* d, int level, int B = 1);
+  void decompose_to(const u64* d, int level, int B, u64* digits);
   HeCt hoisted(const HeCt& x, const u64* digits, u64 g);
   std::vector<HeCt> hoisted_multi(const HeCt& x, const u64* digits, const std::vector<u64>& gs);
-  void hoisted_masked(const HeCt& x, const u64* digits, const std::vector<u64>& gs, const std::vector<u64*>& outs,
-                      const std::vector<const u64*>& masks, bool accumulate);
-  bool hoisted_masked_pair(const HeCt& x, const u64* dx, const std::vector<const u64*>& m1, const HeCt& y,
-                           const u64* dy, const std::vector<const u64*>& m2, const std::vector<u64>& gs,
-                           const std::vector<u64*>& outs);
   // consume: x's special-prime limbs (and q_l for moddown_rescale) may be
   // overwritten (x is a temporary the caller drops afterwards)
   // pack: the output's FP64 limbs may be stored packed (HeCt::packed says
@@ -194,7 +194,7 @@ struct HeCtxImpl {
   HeCt moddown(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
                const u64* rec = nullptr, bool pack = false);
   bool moddown_to(const HeCt& x, int out_level, u64* out, bool consume = false, bool src_ready = false,
-                  const u64* rec = nullptr, bool pack = false);
+                  const u64* rec = nullptr, bool pack = false, size_t skip = 0);
   // ModDown and Rescale as one rounding by P q_l (a variant)
   HeCt moddown_rescale(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
                        const u64* rec = nullptr, bool pack = false);
@@ -240,6 +240,19 @@ struct HeCtxImpl {
   std::vector<HeCt> run_merged(const std::vector<std::function<HeCt()>>& jobs);
   void accumulate_tensors(DevBuf& acc3, bool& acc_set, const std::vector<HeCt>& Ak, const std::vector<HeCt>& Bk);
   HeCt relin_sum(const DevBuf& acc3, int level, double scale, int B);
+  // A group of consecutive shift blocks' bases, one after the other under the
+  // same rotations: x [2][block][side][B] (`sides` bases a block: the A side
+  // has two) and their digits [block][side][B]
+  struct ShiftBases {
+    int blocks = 0, sides = 1, B = 1;
+    HeCt x;
+    DevBuf dig;
+  };
+  int shift_group(int level, int sides, int B, int blocks) const;
+  ShiftBases shift_bases(const ShiftBases* prev, HeCt& first, long second_step, long step, int sides, int blocks);
+  void shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
+                           const std::vector<const u64*>* masks, int out_level, bool rescale_after, bool fused_rs,
+                           bool pack, double scale, std::vector<HeCt>& out);
   // pack: the A_k (with one rounding) and the ModDown'ed B_k may come out
   // packed, for the tensor sums alone
   std::vector<HeCt> matmul_side_a(const HeCt& ca, int n, int n1z, int npz, int out_level = -1,

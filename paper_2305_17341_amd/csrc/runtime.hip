@@ -176,6 +176,7 @@ HeCtxImpl::~HeCtxImpl() {
   graphs.clear();
   ltplans.clear();
   ptcache.clear();
+  ptbanks.clear();
   keys.clear();
   s_ntt.release();
   pk.release();
@@ -571,6 +572,20 @@ HeCt HeCtxImpl::ct_copy(const HeCt& x) {
   c.packed = x.packed;
   return c;
 }
+HeCt HeCtxImpl::ct_part(const std::shared_ptr<DevBuf>& whole, const HeCt& like, size_t first, size_t count, int B) {
+  HeCt c;
+  c.N = N;
+  c.level = like.level;
+  c.qp = like.qp;
+  c.packed = like.packed;
+  c.nlimbs = like.nlimbs;
+  c.B = (int)count * B;
+  c.scale = like.scale;
+  const size_t words = (size_t)2 * B * c.nlimbs * N;
+  c.d = DevBuf::part(whole->p + first * words, count * words);
+  c.whole = whole;
+  return c;
+}
 void HeCtxImpl::copy_limbs(u64* dst, const u64* src, size_t nlimbs, const char* family) {
   hip_check(copy_async(family, dst, src, nlimbs * N * 8, stream), "copy");
 }
@@ -592,9 +607,9 @@ DevBuf HeCtxImpl::encode_batch(const double* z_host, int nz, int batch, double d
 }
 
 // integer coefficients -> evaluation-domain limbs for the map's moduli
-void HeCtxImpl::int_to_ntt(u64* out, const i64* m, const LimbMap& map) {
-  launch_int_to_limbs(T, out, m, map.n, map, stream);
-  launch_ntt(T, out, map.n, map, false, stream);
+void HeCtxImpl::int_to_ntt(u64* out, const i64* m, const LimbMap& map, int npoly) {
+  launch_int_to_limbs(T, out, m, map.n, map, stream, npoly);
+  launch_ntt(T, out, map.n * npoly, map, false, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -788,13 +803,17 @@ HeCt HeCtxImpl::rescale(const HeCt& a, int out_level) {
 // of moduli below 2^46 as centred doubles (the key inner products' operand
 // form), the others as residues in [0, q)
 DevBuf HeCtxImpl::decompose(const u64* d, int level, int B) {
+  DevBuf dig(&pool, (size_t)B * beta_at(level) * nqp_of(level) * N);
+  decompose_to(d, level, B, dig.p);
+  return dig;
+}
+void HeCtxImpl::decompose_to(const u64* d, int level, int B, u64* dig) {
   int nq = nq_of(level), nqp = nqp_of(level), bl = beta_at(level);
   DevBuf coef(&pool, (size_t)B * nq * N);
   if (!fused_conv) {
     copy_limbs(coef.p, d, (size_t)B * nq, "copy_decompose");
     launch_ntt(T, coef.p, B * nq, qmap(nq), true, stream);
   }
-  DevBuf dig(&pool, (size_t)B * bl * nqp * N);
   LimbMap m;
   m.n = bl * nqp;
   if (m.n > 960) fail(HE_EINVAL, "too many digit limbs");
@@ -817,21 +836,20 @@ DevBuf HeCtxImpl::decompose(const u64* d, int level, int B) {
       launch_ntt(T, coef.p, B * nq, qmap(nq), true, stream);
       launch_mul_const(T, coef.p, coef.p, B * nq, hinv.data(), qmap(nq), stream);
     }
-    if (launch_modup_ntt(T, dig.p, coef.p, d, level, L, alpha, bl, tabs.data(), B, m, stream)) {
+    if (launch_modup_ntt(T, dig, coef.p, d, level, L, alpha, bl, tabs.data(), B, m, stream)) {
       n_decompose += B;
-      return dig;
+      return;
     }
     fail(HE_EINVAL, "fused decomposition unavailable for this ring size");
   }
-  launch_modup(T, dig.p, coef.p, d, level, L, alpha, bl, up[level].data(), B, stream);
-  launch_ntt(T, dig.p, B * m.n, m, false, stream);
+  launch_modup(T, dig, coef.p, d, level, L, alpha, bl, up[level].data(), B, stream);
+  launch_ntt(T, dig, B * m.n, m, false, stream);
   LimbMap all;
   all.n = bl * nqp;
   for (int j = 0; j < bl; j++)
     for (int pos = 0; pos < nqp; pos++) all.idx[j * nqp + pos] = (short)qp_mod(level, pos);
-  launch_digits_f64(T, dig.p, B * all.n, all, stream);
+  launch_digits_f64(T, dig, B * all.n, all, stream);
   n_decompose += B;
-  return dig;
 }
 
 // hoisted rotation left in R_{Q_l P}; g = 1 gives the P-lift
@@ -870,41 +888,6 @@ std::vector<HeCt> HeCtxImpl::hoisted_multi(const HeCt& x, const u64* digits, con
   return out;
 }
 
-// hoisted rotations of one decomposition, each multiplied by its mask (a
-// plaintext in R_{Q_l P}) and written to (or, accumulate, added onto) outs[r]
-void HeCtxImpl::hoisted_masked(const HeCt& x, const u64* digits, const std::vector<u64>& gs,
-                               const std::vector<u64*>& outs, const std::vector<const u64*>& masks, bool accumulate) {
-  if (gs.empty()) return;
-  std::vector<const u64*> ks;
-  for (u64 g : gs) {
-    if (g == 1) fail(HE_EINVAL, "masked hoisted rotation by the identity");
-    ks.push_back(key(g).p);
-  }
-  launch_multsum_rot(T, outs.data(), ks.data(), gs.data(), (int)gs.size(), digits, x.poly(0), pmod.p, x.level, L,
-                     alpha, beta_at(x.level), x.B, stream, masks.data(), accumulate, &fork);
-  n_multsum += (long)x.B * (long)gs.size();
-}
-
-// outs[r] = m1[r] (rotation gs[r] of x) + m2[r] (rotation gs[r] of y): one
-// multi-rotation launch over both decompositions; false where that does not
-// apply (nothing launched)
-bool HeCtxImpl::hoisted_masked_pair(const HeCt& x, const u64* dx, const std::vector<const u64*>& m1, const HeCt& y,
-                                    const u64* dy, const std::vector<const u64*>& m2, const std::vector<u64>& gs,
-                                    const std::vector<u64*>& outs) {
-  if (gs.empty()) return true;
-  if (x.level != y.level || x.B != y.B) fail(HE_EINVAL, "paired bases of unlike elements");
-  std::vector<const u64*> ks;
-  for (u64 g : gs) {
-    if (g == 1) fail(HE_EINVAL, "masked hoisted rotation by the identity");
-    ks.push_back(key(g).p);
-  }
-  if (!launch_multsum_rot_pair(T, outs.data(), ks.data(), gs.data(), (int)gs.size(), dx, x.poly(0), m1.data(), dy,
-                               y.poly(0), m2.data(), pmod.p, x.level, L, alpha, beta_at(x.level), x.B, stream))
-    return false;
-  n_multsum += 2L * x.B * (long)gs.size();
-  return true;
-}
-
 // ModDown: R_{Q_l P}^2 -> R_{Q_l}^2, (x - [x]_P) P^{-1} with [x]_P the exact
 // centred residue; out_level < l keeps (and computes) only the limbs up to it
 HeCt HeCtxImpl::moddown(const HeCt& x, int out_level, bool consume, bool src_ready, const u64* rec, bool pack) {
@@ -919,9 +902,9 @@ HeCt HeCtxImpl::moddown(const HeCt& x, int out_level, bool consume, bool src_rea
 // limbs are brought to the coefficient domain in place (x is left with them
 // so) instead of in a gathered copy; src_ready: that was done already
 // (moddown_sources over a set of elements), and rec, when given, holds their
-// digit records
+// digit records; skip: the second component skip words further on
 bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, u64* out, bool consume, bool src_ready, const u64* rec,
-                           bool pack) {
+                           bool pack, size_t skip) {
   int nq = nq_of(out_level), nqp = nqp_of(x.level);
   const int np = (int)x.polys();
   DevBuf y(&pool, (size_t)np * nq * N);
@@ -936,10 +919,19 @@ bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, u64* out, bool consume,
     DevBuf V;
     if (!rec) V = DevBuf(&pool, (size_t)np * (down.ns + 1) * N);
     if (!launch_moddown_fused(T, x.d.p, nq, np, down, x.d.p, nqp, pinv.p, out, y.p, rec ? (u64*)rec : V.p, stream,
-                              x.nlimbs, nq_of(x.level), rec != nullptr, pack))
+                              x.nlimbs, nq_of(x.level), rec != nullptr, pack, skip))
       fail(HE_EINVAL, "fused ModDown unavailable for this ring size");
     n_moddown += x.B;
     return pack;
+  }
+  if (skip) {
+    // the unfused paths write the two components together
+    DevBuf both(&pool, (size_t)np * nq * N);
+    moddown_to(x, out_level, both.p, false);
+    const size_t half = (size_t)x.B * nq;
+    copy_limbs(out, both.p, half);
+    copy_limbs(out + half * N + skip, both.p + half * N, half);
+    return false;
   }
   DevBuf pc(&pool, (size_t)np * alpha * N);
   gather_limbs(pc.p, x, nq_of(x.level), alpha);
@@ -1207,7 +1199,7 @@ std::vector<const u64*> HeCtxImpl::plaintexts(const std::vector<std::string>& ke
   snprintf(suffix, sizeof suffix, "|L%d|%d|%.17g", level, qp ? 1 : 0, scale);
   for (size_t i = 0; i < keys_.size(); i++) {
     auto it = ptcache.find(keys_[i] + suffix);
-    if (it != ptcache.end()) out[i] = it->second.p;
+    if (it != ptcache.end()) out[i] = it->second;
     else missing.push_back((int)i);
   }
   if (missing.empty()) return out;
@@ -1223,12 +1215,13 @@ std::vector<const u64*> HeCtxImpl::plaintexts(const std::vector<std::string>& ke
       std::copy(v.begin(), v.end(), host.begin() + (size_t)t * n2);
     }
     DevBuf ints = encode_batch(host.data(), n2, b, scale);
+    ptbanks.emplace_back(&pool, (size_t)b * nl * N);
+    u64* bank = ptbanks.back().p;
+    int_to_ntt(bank, (const i64*)ints.p, m, b);
     for (int t = 0; t < b; t++) {
       int i = missing[s0 + t];
-      DevBuf pt(&pool, (size_t)nl * N);
-      int_to_ntt(pt.p, (const i64*)ints.p + (size_t)t * N, m);
-      out[i] = pt.p;
-      ptcache[keys_[i] + suffix] = std::move(pt);
+      out[i] = bank + (size_t)t * nl * N;
+      ptcache[keys_[i] + suffix] = out[i];
     }
   }
   return out;
@@ -1630,93 +1623,32 @@ std::vector<HeCt> HeCtxImpl::matmul_side_a(const HeCt& ca, int n, int n1z, int n
   HeCt A0 = sigma_dcd(ca, n, n1z, npz);
   const int lvl = A0.level;
   if (lvl < 1) fail(HE_ELEVEL, "no level left for the column shifts");
-  const int nqp = nqp_of(lvl);
-  LimbMap qpm = qpmap(lvl);
+  // the masks of every shift, (k, first) then (k, second): block b's are
+  // 2 n1z plaintexts after block b - 1's (one bank).  k = 0 has an all-zero
+  // second mask, so that every block is alike.
   std::vector<std::string> keys_;
-  std::vector<std::pair<int, int>> which;
-  for (int k = 0; k < n; k++) {
+  for (int k = 0; k < n; k++)
     for (int second = 0; second < 2; second++) {
-      if (second && k == 0) continue;
       char key[64];
       snprintf(key, sizeof key, "colmask|n%d|k%d|%d", n, k, second);
       keys_.push_back(key);
-      which.push_back({k, second});
     }
-  }
   // masks encoded at scale q_lvl: each rescale restores the base's scale
-  const double ql = (double)mods[lvl];
-  std::vector<const u64*> masks = plaintexts(
-      keys_, [&](size_t e, std::vector<double>& o) { col_mask(n, which[e].first, which[e].second != 0, o); }, n * n,
-      lvl, true, ql);
-  auto mask_of = [&](int k, int second) { return masks[k == 0 ? 0 : 2 * k - 1 + second]; };
+  const std::vector<const u64*> masks = plaintexts(
+      keys_, [&](size_t e, std::vector<double>& o) { col_mask(n, (int)(e / 2), e % 2 != 0, o); }, n * n, lvl, true,
+      (double)mods[lvl]);
+  std::vector<u64> gs;
+  for (int r = 1; r < n1z; r++) gs.push_back(galois(r));
   std::vector<HeCt> Ak(n);
-  HeCt Bb = ct_copy(A0), Bpb = rotate(A0, -(long)n);
-  A0 = HeCt();
-  for (int b = 0; b * n1z < n; b++) {
-    if (b > 0) {
-      Bb = rotate(Bb, n1z);
-      Bpb = rotate(Bpb, n1z);
-    }
-    // all n1z hoisted rotations of each base in one launch per base; the
-    // masks are applied in the launch's epilogue, the second base's masked
-    // rotations added onto the first's, so that the hoisted rotations
-    // themselves never reach memory.  r = 0 (Galois element 1) is the P-lift.
-    const int nr = std::min(n1z, n - b * n1z);
-    std::vector<HeCt> acc(nr);
-    for (int r = 0; r < nr; r++) acc[r] = ct_new(lvl, true, Bb.scale * ql, Bb.B);
-    std::vector<u64> gs;
-    std::vector<u64*> outs;
-    std::vector<const u64*> m1, m2;
-    for (int r = 1; r < nr; r++) {
-      const int k = b * n1z + r;
-      gs.push_back(galois(r));
-      outs.push_back(acc[r].d.p);
-      m1.push_back(mask_of(k, 0));
-      m2.push_back(mask_of(k, 1));
-    }
-    HeCt lift1, lift2;
-    {
-      // both bases' masked rotations in one launch where it applies (each
-      // key word loaded once), else the second added onto the first
-      DevBuf d1 = decompose(Bb.poly(1), lvl, Bb.B);
-      DevBuf d2 = decompose(Bpb.poly(1), lvl, Bpb.B);
-      if (!hoisted_masked_pair(Bb, d1.p, m1, Bpb, d2.p, m2, gs, outs)) {
-        hoisted_masked(Bb, d1.p, gs, outs, m1, false);
-        hoisted_masked(Bpb, d2.p, gs, outs, m2, true);
-      }
-      lift1 = hoisted(Bb, d1.p, 1);
-      if (b > 0) lift2 = hoisted(Bpb, d2.p, 1);  // k = 0 has no second term
-    }
-    {
-      // r = 0: the P-lifts times their masks
-      const int k = b * n1z;
-      const u64* ta[2] = {lift1.d.p, k > 0 ? lift2.d.p : nullptr};
-      const u64* tp[2] = {mask_of(k, 0), mask_of(k, 1)};
-      launch_mul_sum(T, acc[0].d.p, ta, tp, k > 0 ? 2 : 1, 2 * Bb.B * nqp, nqp, qpm, false, stream);
-      lift1 = HeCt();
-      lift2 = HeCt();
-    }
-    DevBuf rec;
-    size_t rs = 0;
-    {
-      std::vector<HeCt*> srcs;
-      for (auto& a : acc) srcs.push_back(&a);
-      rec = moddown_sources(srcs, fused_rs, &rs);
-    }
-    const bool ready = fused_conv;
-    for (int r = 0; r < nr; r++) {
-      int k = b * n1z + r;
-      HeCt sum = std::move(acc[r]);
-      const int ol = out_level >= 0 ? std::min(out_level, lvl - 1) : -1;
-      const u64* rr = rec.p ? rec.p + r * rs : nullptr;
-      if (fused_rs) {
-        Ak[k] = moddown_rescale(sum, ol, true, ready, rr, pack);
-      } else {
-        HeCt md = moddown(sum, -1, true, ready, rr);
-        Ak[k] = rescale(md, ol);
-      }
-      Ak[k].scale = Bb.scale;
-    }
+  const int nblk = n / n1z, ol = out_level >= 0 ? std::min(out_level, lvl - 1) : lvl - 1;
+  const double scale = A0.scale;
+  int group = shift_group(lvl, 2, A0.B, nblk);
+  for (size_t e = 0; e < masks.size(); e++)
+    if (masks[e] != masks[0] + e * (size_t)nqp_of(lvl) * N) group = 1;  // not one bank
+  ShiftBases sb;
+  for (int b = 0; b < nblk; b += group) {
+    sb = shift_bases(b ? &sb : nullptr, A0, -(long)n, n1z, 2, std::min(group, nblk - b));
+    shift_block_outputs(sb, b, n1z, gs, &masks, ol, true, fused_rs, pack, scale, Ak);
   }
   return Ak;
 }
@@ -1724,34 +1656,193 @@ std::vector<HeCt> HeCtxImpl::matmul_side_a(const HeCt& ca, int n, int n1z, int n
 // B side: B_k = R^k T b.  C_0 = T b, C_b = Rot(C_{b-1}, n n1t), B_k = ModDown(HR(C_b, n r))
 // out_level (if >= 0) caps the level of the B_k, as for the A side
 std::vector<HeCt> HeCtxImpl::matmul_side_b(const HeCt& cb, int n, int n1t, int npt, int out_level, bool pack) {
-  HeCt Cb = tau_dcd(cb, n, n1t, npt);
-  const int lvl = Cb.level;
+  HeCt C0 = tau_dcd(cb, n, n1t, npt);
+  const int lvl = C0.level;
   const int ol = out_level >= 0 ? std::min(out_level, lvl) : lvl;
+  const double scale = C0.scale;
+  std::vector<u64> gs;
+  for (int r = 1; r < n1t; r++) gs.push_back(galois((long)n * r));
   std::vector<HeCt> Bk(n);
-  for (int b = 0; b * n1t < n; b++) {
-    if (b > 0) Cb = rotate(Cb, (long)n * n1t);
-    const int nr = std::min(n1t, n - b * n1t);
-    std::vector<HeCt> hs;
-    {
-      DevBuf d1 = decompose(Cb.poly(1), lvl, Cb.B);
-      std::vector<u64> gs;
-      for (int r = 1; r < nr; r++) gs.push_back(galois((long)n * r));
-      hs = hoisted_multi(Cb, d1.p, gs);
-    }
-    Bk[b * n1t] = ol < lvl ? drop(Cb, ol) : ct_copy(Cb);
-    DevBuf rec;
-    size_t rs = 0;
-    {
-      std::vector<HeCt*> srcs;
-      for (auto& h : hs) srcs.push_back(&h);
-      rec = moddown_sources(srcs, false, &rs);
-    }
-    for (int r = 1; r < nr; r++) {
-      Bk[b * n1t + r] = moddown(hs[r - 1], ol, true, fused_conv, rec.p ? rec.p + (r - 1) * rs : nullptr, pack);
-      hs[r - 1] = HeCt();
-    }
+  const int nblk = n / n1t, group = shift_group(lvl, 1, C0.B, nblk);
+  ShiftBases sb;
+  for (int b = 0; b < nblk; b += group) {
+    sb = shift_bases(b ? &sb : nullptr, C0, 0, (long)n * n1t, 1, std::min(group, nblk - b));
+    shift_block_outputs(sb, b, n1t, gs, nullptr, ol, false, false, pack, scale, Bk);
   }
   return Bk;
+}
+
+// Blocks whose bases stand together: as many as the members of one
+// multi-rotation launch take (each key word is then loaded once for all of
+// them, and the ModDowns of all of them fill the chip together), within
+// 2 HE_STAGE_BYTES of digits; one at a time inside a merged launch, which
+// stacks the members of several products instead.
+int HeCtxImpl::shift_group(int level, int sides, int B, int blocks) const {
+  if (ks_sink_active()) return 1;
+  const size_t per = (size_t)sides * B * ((size_t)beta_at(level) * nqp_of(level) + 2 * nq_of(level)) * N * 8;
+  const size_t fit = std::min<size_t>(std::max(1, MR_MEMBERS / B), 2 * HE_STAGE_BYTES / per);
+  const int most = (int)std::max<size_t>(1, std::min<size_t>(fit, blocks));
+  return ceil_div_i(blocks, ceil_div_i(blocks, most));  // groups of nearly one size
+}
+
+// The bases of the next `blocks` shift blocks and their digits: base 0 of the
+// first block is `first` (and its rotation by second_step, when sides = 2),
+// every other block's bases are the block before's rotated by `step`, from the
+// digits that the block before's shifts use too; both sides take each step
+// together.
+HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first, long second_step, long step,
+                                             int sides, int blocks) {
+  const int B = prev ? prev->B : first.B, level = prev ? prev->x.level : first.level;
+  const double scale = prev ? prev->x.scale : first.scale;
+  const int nq = nq_of(level), M = sides * B;
+  const size_t dstride = (size_t)beta_at(level) * nqp_of(level) * N;
+  ShiftBases sb;
+  sb.blocks = blocks;
+  sb.sides = sides;
+  sb.B = B;
+  sb.x = ct_new(level, false, scale, blocks * M);
+  sb.dig = DevBuf(&pool, (size_t)blocks * M * dstride);
+  // members [at, at + cnt) of x = ModDown(h): the components stand apart
+  auto put = [&](const HeCt& h, int at) {
+    moddown_to(h, level, sb.x.member(0, at), true, false, nullptr, false, (size_t)(blocks * M - h.B) * nq * N);
+  };
+  for (int j = 0; j < blocks; j++) {
+    u64* dj = sb.dig.p + (size_t)j * M * dstride;
+    if (j == 0 && !prev) {
+      for (int p = 0; p < 2; p++) copy_limbs(sb.x.member(p, 0), first.poly(p), (size_t)B * nq, "copy_ct");
+      decompose_to(sb.x.member(1, 0), level, B, dj);
+      if (sides == 2) {
+        put(hoisted(first, dj, galois(second_step)), B);
+        decompose_to(sb.x.member(1, B), level, B, dj + (size_t)B * dstride);
+      }
+      first = HeCt();
+      continue;
+    }
+    const ShiftBases& src = j ? sb : *prev;
+    const int at = ((j ? j : prev->blocks) - 1) * M;
+    HeCt h = ct_new(level, true, scale, M);
+    const u64 g = galois(step);
+    launch_multsum(T, h.d.p, src.dig.p + (size_t)at * dstride, key(g).p, src.x.member(0, at), pmod.p, level, L, alpha,
+                   beta_at(level), g, M, stream);
+    n_multsum += M;
+    put(h, j * M);
+    decompose_to(sb.x.member(1, j * M), level, M, dj);
+  }
+  return sb;
+}
+
+// The shifts of a group of blocks: out[(first_block + j) n1 + r] is the
+// ModDown of the rotation gs[r - 1] of block j's base (r = 0: of the base
+// itself), or with masks (indexed 2 k + side) of the sum over the two bases of
+// mask times rotation, rescaled afterwards (with one rounding if fused_rs).
+void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
+                                    const std::vector<const u64*>* masks, int out_level, bool rescale_after,
+                                    bool fused_rs, bool pack, double scale, std::vector<HeCt>& out) {
+  const int level = sb.x.level, nq = nq_of(level), nqp = nqp_of(level), nb = sb.blocks, B = sb.B, S = sb.sides;
+  const size_t dstride = (size_t)beta_at(level) * nqp * N;
+  const size_t elem = (size_t)2 * B * nqp * N;           // words of one output in R_{Q_l P}
+  const double sc = masks ? sb.x.scale * (double)mods[level] : sb.x.scale;
+  HeCt like;  // the shape of an output before its ModDown
+  like.level = level;
+  like.qp = true;
+  like.nlimbs = nqp;
+  like.scale = sc;
+  MrLayout lay;
+  lay.comp = (size_t)B * nqp * N;
+  for (int j = 0; j < nb; j++)
+    for (int b = 0; b < B; b++) {
+      const size_t x = (size_t)j * S * B + b;
+      lay.dig.push_back(x * dstride);
+      lay.c0.push_back(x * nq * N);
+      lay.mem.push_back(j * elem + (size_t)b * nqp * N);
+      if (masks) lay.msk.push_back((size_t)j * 2 * n1 * nqp * N);
+    }
+  const MrLayout* pl = nb > 1 ? &lay : nullptr;  // one block: plainly stacked members
+  const u64* d1 = sb.dig.p;
+  const u64* d2 = sb.dig.p + (size_t)B * dstride;
+  const u64* c1 = sb.x.poly(0);
+  const u64* c2 = sb.x.poly(0) + (size_t)B * nq * N;
+  auto mask_of = [&](int r, int second) { return (*masks)[2 * (first_block * n1 + r) + second]; };
+  if (!masks)
+    for (int j = 0; j < nb; j++) {  // r = 0: the bases themselves
+      HeCt c = ct_new(out_level, false, scale, B);
+      for (int p = 0; p < 2; p++)
+        hip_check(copy2d_async("copy_gather", c.poly(p), (size_t)(out_level + 1) * N * 8, sb.x.member(p, j * B),
+                               (size_t)nq * N * 8, (size_t)(out_level + 1) * N * 8, B, stream),
+                  "gather");
+      out[(size_t)(first_block + j) * n1] = std::move(c);
+    }
+  // Rotations per launch: the whole block where one block stands alone (its
+  // digits are read once), else as many fours as fit HE_STAGE_BYTES with what
+  // their ModDowns take.  ModDowns go HE_STAGE_BYTES at a time.
+  const size_t down = (size_t)2 * B * (nqp + nq + alpha + 2) * N * 8;
+  const int r_lo = masks ? 0 : 1;
+  const int per = nb == 1 ? n1 : (int)std::max<size_t>(4, stage_count(down * nb, n1) / 4 * 4);
+  for (int r0 = r_lo; r0 < n1; r0 += per) {
+    const int cnt = std::min(per, n1 - r0);
+    const int rd = (int)stage_count(down * nb, cnt);  // rotations per ModDown
+    std::vector<std::shared_ptr<DevBuf>> part;
+    std::vector<HeCt> all;
+    for (int r = 0; r < cnt; r++) {
+      if (r % rd == 0) part.push_back(std::make_shared<DevBuf>(&pool, (size_t)std::min(rd, cnt - r) * nb * elem));
+      for (int j = 0; j < nb; j++) all.push_back(ct_part(part.back(), like, (size_t)(r % rd) * nb + j, 1, B));
+    }
+    std::vector<u64*> outs;
+    std::vector<u64> g2;
+    std::vector<const u64*> ks, m1, m2;
+    for (int r = 0; r < cnt; r++) {
+      if (r0 + r == 0) continue;
+      outs.push_back(all[(size_t)r * nb].d.p);
+      g2.push_back(gs[r0 + r - 1]);
+      ks.push_back(key(g2.back()).p);
+      if (masks) {
+        m1.push_back(mask_of(r0 + r, 0));
+        m2.push_back(mask_of(r0 + r, 1));
+      }
+    }
+    const int nr = (int)outs.size(), bl = beta_at(level);
+    if (nr && !masks) {
+      launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, pmod.p, level, L, alpha, bl, nb * B, stream,
+                         nullptr, false, &fork, pl);
+    } else if (nr && !launch_multsum_rot_pair(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, m1.data(), d2, c2,
+                                              m2.data(), pmod.p, level, L, alpha, bl, nb * B, stream, pl)) {
+      // the second base's masked rotations added onto the first's
+      launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, pmod.p, level, L, alpha, bl, nb * B, stream,
+                         m1.data(), false, &fork, pl);
+      launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d2, c2, pmod.p, level, L, alpha, bl, nb * B, stream,
+                         m2.data(), true, &fork, pl);
+    }
+    n_multsum += (long)S * nb * B * nr;
+    if (masks && r0 == 0)
+      launch_plift_masked(T, all[0].d.p, c1, mask_of(0, 0), mask_of(0, 1), (size_t)2 * n1 * nqp * N, nb, B, pmod.p,
+                          level, alpha, stream);
+    std::vector<HeCt*> srcs;
+    for (HeCt& e : all) srcs.push_back(&e);
+    size_t rs = 0;
+    DevBuf rec = moddown_sources(srcs, masks && fused_rs, &rs);
+    all.clear();
+    for (int r = 0, c = 0; r < cnt; r += rd, c++) {
+      const int nrd = std::min(rd, cnt - r);
+      HeCt x = ct_part(part[c], like, 0, (size_t)nrd * nb, B);
+      const u64* rr = rec.p ? rec.p + (size_t)r * nb * rs : nullptr;
+      HeCt y;
+      if (rescale_after && fused_rs) {
+        y = moddown_rescale(x, out_level, true, fused_conv, rr, pack);
+      } else if (rescale_after) {
+        HeCt md = moddown(x, -1, true, fused_conv, rr);
+        y = rescale(md, out_level);
+      } else {
+        y = moddown(x, out_level, true, fused_conv, rr, pack);
+      }
+      x = HeCt();
+      part[c].reset();
+      y.scale = scale;
+      auto w = std::make_shared<DevBuf>(std::move(y.d));
+      for (int q = 0; q < nrd; q++)
+        for (int j = 0; j < nb; j++)
+          out[(size_t)(first_block + j) * n1 + r0 + r + q] = ct_part(w, y, (size_t)q * nb + j, 1, B);
+    }
+  }
 }
 
 // A side with the masks of C^k folded into Z: phi^k o sigma (output (i, j)

@@ -65,6 +65,21 @@ def _beta(level: int, alpha: int) -> int:
     return -(-(level + 1) // alpha)
 
 
+# temporaries of the library's batched stages (the elements that a product's
+# shifts take through the key inner products and ModDown together, and their
+# bases' digits) stop growing here
+STAGE_BYTES = 1.45 * 2**30
+
+
+def _stage(log_n: int, l: int, alpha: int, d: int, members: int) -> float:
+    """words (of 2^log_n) the stages of `members` stacked d x d products hold: every shift in
+    R_{Q_l P} with its ModDown's temporaries, and the digits of up to eight blocks' two bases"""
+    blocks = min(8, -(-d // default_n1(d)))
+    shifts = d * 2 * (_qp(l, alpha) + l + 1 + alpha + 2)
+    bases = blocks * 2 * (_beta(l, alpha) * _qp(l, alpha) + 2 * (l + 1))
+    return min(members * (shifts + bases), STAGE_BYTES / 8 / (1 << log_n))
+
+
 def product_footprint(log_n: int, top_level: int, alpha: int, d: int, batch: int = 1) -> int:
     """Upper bound on the device bytes one d x d product (inputs at
     `top_level`, no decomposition) allocates beyond what is resident, times
@@ -72,14 +87,14 @@ def product_footprint(log_n: int, top_level: int, alpha: int, d: int, batch: int
     row-shifted B_k (level l-1) held together before the products, plus the
     largest transient of a linear transform (n1 baby-step rotations in
     R_{Q_l P}, or the 2 n1 of the column shifts, the digits of one
-    decomposition and a few accumulators), plus stacked copies of the
-    inputs and the output."""
+    decomposition and a few accumulators) or of the shifts' batched stages,
+    plus stacked copies of the inputs and the output."""
     l = top_level
     n1 = default_n1(d)
     sides = d * 2 * (l - 1) + d * 2 * l
     trans = 2 * (2 * n1 + 4) * _qp(l, alpha) + _beta(l, alpha) * _qp(l, alpha) + 6 * (l + 1)
     io = 4 * (l + 1) + 2 * (l - 2)
-    words = batch * (sides + trans + io) << log_n
+    words = (batch * (sides + io) + max(batch * trans, _stage(log_n, l, alpha, d, batch))) * 2**log_n
     return int(math.ceil(words * 8 * POOL_SLACK))
 
 
@@ -95,7 +110,7 @@ def covariance_footprint(log_n: int, top_level: int, alpha: int, d: int, k: int,
     sides = 2 * k * d * 2 * l * g
     acc = k * k * 2 * l
     trans = g * (2 * (2 * n1 + 4) * _qp(l, alpha) + _beta(l, alpha) * _qp(l, alpha) + 8 * (l + 1))
-    words = (sides + acc + trans) << log_n
+    words = (sides + acc + max(trans, _stage(log_n, l, alpha, d, g))) * 2**log_n
     return int(math.ceil(words * 8 * POOL_SLACK))
 
 

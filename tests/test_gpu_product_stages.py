@@ -51,3 +51,26 @@ def test_batches_match_members_alone(chain, d, n1, batch, flags):
         assert np.array_equal(got[i].export(), alone.export()), i
         err = np.max(np.abs(ctx.decrypt(got[i], d * d) - (I.uniform_matrix(10 + i, d) @ I.uniform_matrix(30 + i, d)).ravel()))
         assert err < 2.0**-15
+
+
+@pytest.mark.parametrize("flags", [0, LAZY, LAZY | FUSED], ids=["paper", "lazy", "lazy-fused"])
+@pytest.mark.parametrize("chain,n1", [(TINY, 2), (TINY, 16), (I.SMALL, 1), (I.SMALL, 4)],
+                         ids=["n11-n1_2", "n11-n1_16", "n13-n1_1", "n13-n1_4"])
+def test_shift_blocks_match_oracle(oracle_mod, chain, n1, flags):
+    """16, 8, 4 and 1 shift blocks: bases stacked in groups of eight, all
+    shifts of a group through one key inner product launch and ModDown; with
+    the ring sizes whose conversions are not fused"""
+    from paper_2305_17341_amd import he
+    n = 16
+    opts = {"n1_z": n1, "n1_t": n1}
+    ctx = he.chain_context(chain, seed=73)
+    steps = ctx.matmul_rot_steps(n, opts)
+    ctx.keygen(steps)
+    o = oracle_mod.Oracle(chain.log_n, chain.q_bits, chain.p_bits, seed=73)
+    o.keygen(rot_steps=steps)
+    A, B = I.uniform_matrix(1, n), I.uniform_matrix(2, n)
+    g = ctx.matmul(ctx.encrypt_matrix(A, nonce=1), ctx.encrypt_matrix(B, nonce=2), n, dict(opts, flags=flags))
+    w = o.matmul(o.encrypt(A.ravel(), nonce=1), o.encrypt(B.ravel(), nonce=2), n, n1, n1, lazy=bool(flags & LAZY),
+                 fused_rescale=bool(flags & FUSED))
+    assert g.level == w.level and g.scale == w.scale
+    assert np.array_equal(g.export(), w.data())
