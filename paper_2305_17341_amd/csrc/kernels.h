@@ -89,6 +89,14 @@ void launch_neg(const DeviceTables& T, u64* out, const u64* a, int nlimbs, const
 void launch_tensor_sum(const DeviceTables& T, u64* out3, const u64* const* a, const u64* const* b, int npairs, int nl,
                        int batch, bool accumulate, hipStream_t s, const bool* a_packed = nullptr,
                        const bool* b_packed = nullptr);
+// products relinearised in batches, pairs a[p], b[p] [2][batch][nl]: the top
+// components out [npairs][batch][nl], and out [2][batch][nl] (+)= the sum of
+// the other two components and of the key switches ks [2][npairs][batch][nl]
+#define RELIN_PAIRS 20
+void launch_tensor_top(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* b, int npairs, int nl,
+                       int batch, hipStream_t s);
+void launch_relin_sum(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* b, const u64* ks,
+                      int npairs, int nl, int batch, bool accumulate, hipStream_t s);
 void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, bool accumulate,
                    hipStream_t s);
 // out [npoly][nlimbs][N] from in [npoly][N]

@@ -2075,6 +2075,97 @@ void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b,
   else hipLaunchKernelGGL(k_tensor<false>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
 }
 
+// Products relinearised in batches: the top tensor components a1 b1 of the
+// pairs, one after the other (what is decomposed), ...
+struct RelinPairs {
+  const u64* a[RELIN_PAIRS];
+  const u64* b[RELIN_PAIRS];
+};
+__global__ void k_tensor_top(u64* out, RelinPairs P, int nl, int nt, int logN, const ModConst* __restrict__ mc) {
+  const u64 N = 1ull << logN;
+  const u32 i = blockIdx.x * TPB + threadIdx.x;
+  const int k = blockIdx.y, p = blockIdx.z;
+  if (i >= N) return;
+  const size_t o1 = (size_t)(nt + k) * N + i;
+  out[((size_t)p * nt + k) * N + i] = mul_mod_any(P.a[p][o1], P.b[p][o1], mc[k % nl]);
+}
+// ... and the sum of the relinearised products: out [2][nt][N] (+)=
+//   sum_p (a0 b0 + ks0_p, a0 b1 + a1 b0 + ks1_p),
+// ks [2][all pairs][nt][N] from the key switches.  One pass where a product at
+// a time wrote its tensor and its sum and read them back; the next pair's
+// loads are in flight while a pair is multiplied.  At most 3 RELIN_PAIRS + 1 = 61
+// terms below q < 2^46 a sum: exact.
+__global__ void __launch_bounds__(TPB) k_relin_sum(u64* out, RelinPairs P, int npairs, const u64* __restrict__ ks,
+                                                   size_t kcomp, int nl, int nt, int accumulate, int logN,
+                                                   const ModConst* __restrict__ mc) {
+  const u64 N = 1ull << logN;
+  const u32 i = blockIdx.x * TPB + threadIdx.x;
+  const int k = blockIdx.y;
+  if (i >= N) return;
+  const ModConst mk = mc[k % nl];
+  const size_t o0 = (size_t)k * N + i, o1 = (size_t)(nt + k) * N + i, step = (size_t)nt * N;
+  struct Six {
+    u64 a0, a1, b0, b1, k0, k1;
+  };
+  auto load = [&](int p) {
+    return Six{P.a[p][o0], P.a[p][o1], P.b[p][o0], P.b[p][o1], ks[p * step + o0], ks[kcomp + p * step + o0]};
+  };
+  Six n = load(0);
+  u64 r0 = accumulate ? out[o0] : 0, r1 = accumulate ? out[o1] : 0;
+  if (mk.bits <= F64_LAZY_BITS) {
+    const double q = mk.qf, qi = mk.qinvf;
+    double s0 = u2d(r0), s1 = u2d(r1);
+    for (int p = 0; p < npairs; p++) {
+      const Six x = n;
+      if (p + 1 < npairs) n = load(p + 1);
+      const double a0 = u2d(x.a0), b0 = u2d(x.b0);
+      s0 += f64_mulmod_signed(a0, b0, q, qi) + u2d(x.k0);
+      s1 += f64_mulmod_signed(a0, u2d(x.b1), q, qi) + f64_mulmod_signed(u2d(x.a1), b0, q, qi) + u2d(x.k1);
+    }
+    r0 = d2u(f64_canon(s0, q, qi));
+    r1 = d2u(f64_canon(s1, q, qi));
+  } else {
+    for (int p = 0; p < npairs; p++) {
+      const Six x = n;
+      if (p + 1 < npairs) n = load(p + 1);
+      r0 = add_mod(r0, add_mod(mul_mod_any(x.a0, x.b0, mk), x.k0, mk.q), mk.q);
+      r1 = add_mod(r1, add_mod(add_mod(mul_mod_any(x.a0, x.b1, mk), mul_mod_any(x.a1, x.b0, mk), mk.q), x.k1, mk.q),
+                   mk.q);
+    }
+  }
+  out[o0] = r0;
+  out[o1] = r1;
+}
+static RelinPairs relin_pairs(const u64* const* a, const u64* const* b, int p0, int np) {
+  RelinPairs P;
+  for (int p = 0; p < RELIN_PAIRS; p++) {
+    P.a[p] = a[p0 + (p < np ? p : 0)];
+    P.b[p] = b[p0 + (p < np ? p : 0)];
+  }
+  return P;
+}
+void launch_tensor_top(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* b, int npairs, int nl,
+                       int batch, hipStream_t s) {
+  const int nt = nl * batch;
+  ProfScope ps("tensor", s, 8.0 * T.N * 3.0 * nt * npairs, mm_q(T, nl, (double)T.N, (double)batch * npairs));
+  for (int p0 = 0; p0 < npairs; p0 += RELIN_PAIRS) {
+    const int np = std::min(RELIN_PAIRS, npairs - p0);
+    hipLaunchKernelGGL(k_tensor_top, dim3(cdiv(T.N, TPB), nt, np), dim3(TPB), 0, s, out + (size_t)p0 * nt * T.N,
+                       relin_pairs(a, b, p0, np), nl, nt, T.logN, T.mc);
+  }
+}
+void launch_relin_sum(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* b, const u64* ks,
+                      int npairs, int nl, int batch, bool accumulate, hipStream_t s) {
+  const int nt = nl * batch;
+  for (int p0 = 0; p0 < npairs; p0 += RELIN_PAIRS) {
+    const int np = std::min(RELIN_PAIRS, npairs - p0);
+    const int acc = accumulate || p0 > 0 ? 1 : 0;
+    ProfScope ps("tensor", s, 8.0 * T.N * nt * (6.0 * np + 2 + 2 * acc), mm_q(T, nl, 3.0 * T.N, (double)batch * np));
+    hipLaunchKernelGGL(k_relin_sum, dim3(cdiv(T.N, TPB), nt), dim3(TPB), 0, s, out, relin_pairs(a, b, p0, np), np,
+                       ks + (size_t)p0 * nt * T.N, (size_t)npairs * nt * T.N, nl, nt, acc, T.logN, T.mc);
+  }
+}
+
 // per limbs of each polynomial of in
 __global__ void k_int_to_limbs(u64* out, const i64* in, int per, LimbMap map, int logN,
                                const ModConst* __restrict__ mc) {

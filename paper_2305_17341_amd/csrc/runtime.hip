@@ -1873,16 +1873,33 @@ void HeCtxImpl::align_sides(std::vector<HeCt>& Ak, std::vector<HeCt>& Bk) {
     if (b.level > lv) b = drop(b, lv);
 }
 
-// acc (+)= sum_k Relin(Tensor(A_k, B_k))
+// acc (+)= sum_k Relin(Tensor(A_k, B_k)), each product relinearised by itself.
+// A batch of products shares the key switch's launches (each had a few
+// work-groups for one product on the smaller rings) and, eight members at a
+// time, the loads of the key: as many products as fit HE_STAGE_BYTES, eight
+// members' worth at least.
 void HeCtxImpl::matmul_accumulate(HeCt& acc, bool& acc_set, const std::vector<HeCt>& Ak, const std::vector<HeCt>& Bk) {
+  const HeCt& a0 = Ak[0];
+  const int level = a0.level, nl = a0.nlimbs, B = a0.B;
+  std::vector<const u64*> pa, pb;
   for (size_t k = 0; k < Ak.size(); k++) {
-    HeCt p = mult(Ak[k], Bk[k]);
-    if (!acc_set) {
-      acc = std::move(p);
-      acc_set = true;
-    } else {
-      add_into(acc, p);
-    }
+    need_same(Ak[k], Bk[k]);
+    need_same(Ak[k], a0);
+    if (Ak[k].packed || Bk[k].packed) fail(HE_EINVAL, "packed limbs are for the lazy tensor sums alone");
+    pa.push_back(Ak[k].d.p);
+    pb.push_back(Bk[k].d.p);
+  }
+  if (!acc_set) acc = ct_new(level, false, a0.scale * Bk[0].scale, B);
+  else if (acc.level != level || acc.B != B) fail(HE_ELEVEL, "operands at different levels");
+  const size_t per = (size_t)B * ((size_t)beta_at(level) * nqp_of(level) + 2 * nqp_of(level) + 6 * nl + 2 * alpha) * N * 8;
+  const size_t cap = std::max(stage_count(per, Ak.size()), std::min<size_t>(Ak.size(), std::max(1, MR_MEMBERS / B)));
+  for (size_t k0 = 0; k0 < Ak.size(); k0 += cap) {
+    const int np = (int)std::min(cap, Ak.size() - k0);
+    DevBuf top(&pool, (size_t)np * B * nl * N);
+    launch_tensor_top(T, top.p, &pa[k0], &pb[k0], np, nl, B, stream);
+    HeCt ks = keyswitch(top.p, level, 0, np * B);
+    launch_relin_sum(T, acc.d.p, &pa[k0], &pb[k0], ks.d.p, np, nl, B, acc_set, stream);
+    acc_set = true;
   }
 }
 
