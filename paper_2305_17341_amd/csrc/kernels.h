@@ -148,9 +148,9 @@ void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int
 // xp_coef: the source limbs in the coefficient domain, [npoly][ns][N]; or,
 // with src_stride > 0, limb a of poly p at slot p * src_stride + src_off + a
 // (the sources transformed in place inside the R_{Q_l P} element)
-// whether a fused ModDown into nq target limbs with this table takes digit
-// records (the int8 lift); only then may V arrive filled (v_ready)
-bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq);
+// whether a fused ModDown of npoly polynomials into nq target limbs with this
+// table takes digit records (the int8 lift); only then may V arrive filled (v_ready)
+bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq, size_t npoly);
 // skip: the second half of the polynomials' outputs lies skip words further on
 // pack_out: out's limbs of FP64 moduli (at most 46 bits) are stored packed in
 // their N-word slots: the low 32 bits of every residue, then one high byte

@@ -678,6 +678,9 @@ __device__ __forceinline__ int lds_rc(int r, int c, int C) { return r * (C + 1) 
 // LDS index of (block b, element e) in the block pass, T1 words per block
 __device__ __forceinline__ int lds_be(int b, int e, int T1) { return b * (T1 + (T1 >> 4) + 1) + e + (e >> 4); }
 #define LDS_WORDS (TILE + TILE / 16 + 64)
+// LDS of a pass with SV values per thread (TPB SV words a work-group): the
+// column pass pads each of at most 256 rows, the block pass one word in 16
+constexpr int lds_words(int sv) { return TPB * sv + 256 + 64; }
 
 // Loads of the forward column pass: the limb itself, or a value computed
 // from other limbs at the same coefficient (ModupLoad).
@@ -805,27 +808,29 @@ struct StoreCentred {
 };
 // x is read into registers when the pass starts (pre), so its loads are in
 // flight during the butterflies; element e = threadIdx.x + k TPB
+template <int SV>
 struct SubScaleShoup {
   u64* out;
   const u64* __restrict__ x;
   u64 c, c_sh, q;
-  u64 xv[TILE / TPB];
+  u64 xv[SV];
   __device__ __forceinline__ void pre() {
 #pragma unroll
-    for (int k = 0; k < TILE / TPB; k++) xv[k] = x[threadIdx.x + k * TPB];
+    for (int k = 0; k < SV; k++) xv[k] = x[threadIdx.x + k * TPB];
   }
   __device__ __forceinline__ void operator()(int e, int k, u64 v) const {
     out[e] = shoup_mul(sub_mod(xv[k], v, q), c, c_sh, q);
   }
 };
+template <int SV>
 struct SubScaleF64 {
   u64* out;
   const u64* __restrict__ x;
   double c, q, qinv;
-  u64 xv[TILE / TPB];
+  u64 xv[SV];
   __device__ __forceinline__ void pre() {
 #pragma unroll
-    for (int k = 0; k < TILE / TPB; k++) xv[k] = x[threadIdx.x + k * TPB];
+    for (int k = 0; k < SV; k++) xv[k] = x[threadIdx.x + k * TPB];
   }
   // v below 9 q in absolute value (eight forward stages): |x - v| < 10 q
   __device__ __forceinline__ void operator()(int e, int k, double v) const {
@@ -834,16 +839,16 @@ struct SubScaleF64 {
 };
 // the same with the output limb stored packed (the layout LoadPacked reads;
 // HB high bytes)
-template <int HB>
+template <int HB, int SV>
 struct SubScalePackedF64 {
   u32* lo;
   void* hi;
   const u64* __restrict__ x;
   double c, q, qinv;
-  u64 xv[TILE / TPB];
+  u64 xv[SV];
   __device__ __forceinline__ void pre() {
 #pragma unroll
-    for (int k = 0; k < TILE / TPB; k++) xv[k] = x[threadIdx.x + k * TPB];
+    for (int k = 0; k < SV; k++) xv[k] = x[threadIdx.x + k * TPB];
   }
   __device__ __forceinline__ void operator()(int e, int k, double v) const {
     const u64 w = d2u(f64_canon(f64_mulmod_signed(u2d(xv[k]) - v, c, q, qinv), q, qinv));
@@ -961,14 +966,256 @@ __device__ __forceinline__ void ntt_rows2_body(u64* a, int blk0, typename A::V* 
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same passes with four values per thread (a work-group takes 1024
+// words): stages in groups of two, each group in place in LDS, every twiddle
+// of the pass loaded before the first group.  A launch of few tiles is bound
+// by the time of one work-group, most of it the 60-bit limbs' integer
+// butterflies (sixteen values a thread: 48 to 64 of them, one after the other);
+// cut into four times as many work-groups it takes about half as long.
+// A rotation at N = 2^13 went from 92 to 45 us (its nine transform passes from
+// 8 to 16 us each to 4 to 7), a PowerMethod round at N = 2^15 from 11.5 to 8.0 ms.
+// ---------------------------------------------------------------------------
+struct TwS {
+  u64 w, wsh;
+};
+__device__ __forceinline__ TwS tw_load(const ShoupArith& ar, u32 i) { return TwS{ar.w[i], ar.wsh[i]}; }
+__device__ __forceinline__ double tw_load(const F64LazyArith& ar, u32 i) { return ar.w[i]; }
+__device__ __forceinline__ u64 tw_mul(const ShoupArith& ar, u64 a, const TwS& t) { return shoup_mul(a, t.w, t.wsh, ar.q); }
+__device__ __forceinline__ double tw_mul(const F64LazyArith& ar, double a, double w) {
+  return f64_mulmod_signed(a, w, ar.q, ar.qinv);
+}
+// group g of an ST-stage pass: two stages, or the last one alone
+template <int ST>
+struct Groups4 {
+  static constexpr int NG = (ST + 1) / 2;
+  static constexpr int size(int g) { return 2 * g + 2 <= ST ? 2 : 1; }
+};
+// item `it` of a group of G index bits above LO others and below ST - G - LO
+// more, the columns (or blocks) of the tile counted apart: the index bits
+// below (lo) and above (hi) the group's
+template <int G, int LO>
+struct Item4 {
+  u32 lo, hi;
+  __device__ __forceinline__ explicit Item4(u32 x) : lo(x & ((1u << LO) - 1)), hi(x >> LO) {}
+  __device__ __forceinline__ u32 at(int mm) const { return (hi << (LO + G)) | ((u32)mm << LO) | lo; }
+};
+template <int G, class A, class TW>
+__device__ __forceinline__ void fwd4(typename A::V* v, const TW* t, const A& ar) {
+  typedef typename A::V V;
+  auto bf = [&](V& x, V& y, const TW& w) {
+    const V p = tw_mul(ar, y, w), u = x;
+    x = ar.add(u, p);
+    y = ar.sub(u, p);
+  };
+  if constexpr (G == 2) {
+    bf(v[0], v[2], t[0]);
+    bf(v[1], v[3], t[0]);
+    bf(v[0], v[1], t[1]);
+    bf(v[2], v[3], t[2]);
+  } else {
+    bf(v[0], v[1], t[0]);
+  }
+}
+template <int G, class A, class TW>
+__device__ __forceinline__ void inv4(typename A::V* v, const TW* t, const A& ar) {
+  typedef typename A::V V;
+  auto bf = [&](V& x, V& y, const TW& w) {
+    const V u = x, d = ar.sub(u, y);
+    x = ar.add(u, y);
+    y = tw_mul(ar, d, w);
+  };
+  if constexpr (G == 2) {
+    bf(v[0], v[1], t[0]);
+    bf(v[2], v[3], t[1]);
+    bf(v[0], v[2], t[2]);
+    bf(v[1], v[3], t[2]);
+  } else {
+    bf(v[0], v[1], t[0]);
+  }
+}
+// twiddles of an item: stage s0 (and s0 + 1) with hi = its index bits above
+template <int G, class A, class TW>
+__device__ __forceinline__ void fwd4_tw(TW* t, int s0, u32 hi, const A& ar) {
+  t[0] = tw_load(ar, (1u << s0) + hi);
+  if constexpr (G == 2) {
+    t[1] = tw_load(ar, (2u << s0) + 2 * hi);
+    t[2] = tw_load(ar, (2u << s0) + 2 * hi + 1);
+  }
+}
+// inverse stages on bits b0 (and b0 + 1)
+template <int G, class A, class TW>
+__device__ __forceinline__ void inv4_tw(TW* t, int b0, int logN, u32 hi, const A& ar) {
+  const u32 h = 1u << (logN - 1 - b0);
+  if constexpr (G == 2) {
+    t[0] = tw_load(ar, h + 2 * hi);
+    t[1] = tw_load(ar, h + 2 * hi + 1);
+    t[2] = tw_load(ar, (h >> 1) + hi);
+  } else {
+    t[0] = tw_load(ar, h + hi);
+  }
+}
+// calls f(integral_constant g) for the groups 0 .. NG - 1
+template <int NG, class F>
+__device__ __forceinline__ void each_group(F&& f) {
+  if constexpr (NG > 0) f(std::integral_constant<int, 0>{});
+  if constexpr (NG > 1) f(std::integral_constant<int, 1>{});
+  if constexpr (NG > 2) f(std::integral_constant<int, 2>{});
+  if constexpr (NG > 3) f(std::integral_constant<int, 3>{});
+  static_assert(NG <= 4, "at most eight stages a pass");
+}
+template <int LOGN, int S1, bool INV, class A, class LD>
+__device__ __forceinline__ void ntt_cols4_body(u64* a, int c0, typename A::V* sh, const A& ar, const LD& ld) {
+  typedef typename A::V V;
+  typedef decltype(tw_load(ar, 0u)) TW;
+  constexpr int R = 1 << S1, T1 = (1 << LOGN) / R, C = TPB * 4 / R, NG = Groups4<S1>::NG, S2 = LOGN - S1;
+  static_assert(C >= 1, "a tile holds whole columns");
+  const int tid = threadIdx.x;
+  TW tw[NG][4];
+  each_group<NG>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, G = Groups4<S1>::size(g), LO = INV ? 2 * g : S1 - 2 * g - G, IT = 4 >> G;
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      const Item4<G, LO> x((u32)((tid + TPB * k) / C));
+      if (INV) inv4_tw<G>(&tw[g][2 * k], S2 + LO, LOGN, x.hi, ar);
+      else fwd4_tw<G>(&tw[g][2 * k], 2 * g, x.hi, ar);
+    }
+  });
+  each_group<NG>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, G = Groups4<S1>::size(g), LO = INV ? 2 * g : S1 - 2 * g - G, IT = 4 >> G,
+                  P = 1 << G;
+    if (g > 0) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      const int it = tid + TPB * k, c = it % C;
+      const Item4<G, LO> x((u32)(it / C));
+      V v[P];
+      if constexpr (g == 0) {
+        if constexpr (INV) {
+#pragma unroll
+          for (int mm = 0; mm < P; mm++) v[mm] = ar.load(a[(size_t)x.at(mm) * T1 + c0 + c]);
+        } else {
+          size_t idx[P];
+#pragma unroll
+          for (int mm = 0; mm < P; mm++) idx[mm] = (size_t)x.at(mm) * T1 + c0 + c;
+          fetch_batch<P>(ar, ld, idx, v);
+        }
+      } else {
+#pragma unroll
+        for (int mm = 0; mm < P; mm++) {
+          v[mm] = sh[lds_rc(x.at(mm), c, C)];
+          if (INV && g % 2 == 0) v[mm] = ar.reduce(v[mm]);  // four inverse stages since the last
+        }
+      }
+      if constexpr (INV) inv4<G>(v, &tw[g][2 * k], ar);
+      else fwd4<G>(v, &tw[g][2 * k], ar);
+#pragma unroll
+      for (int mm = 0; mm < P; mm++) {
+        if constexpr (g + 1 < NG) sh[lds_rc(x.at(mm), c, C)] = v[mm];
+        else a[(size_t)x.at(mm) * T1 + c0 + c] = ar.store(INV ? ar.scale_ninv(v[mm]) : v[mm]);
+      }
+    }
+  });
+}
+template <int LOGN, int S2, bool INV, class A, class ST, class YL = LoadWords>
+__device__ __forceinline__ void ntt_rows4_body(u64* a, int blk0, typename A::V* sh, const A& ar, ST st,
+                                               const YL& yl = YL()) {
+  typedef typename A::V V;
+  typedef decltype(tw_load(ar, 0u)) TW;
+  constexpr int T1 = 1 << S2, S1 = LOGN - S2, NG = Groups4<S2>::NG;
+  static_assert(TPB * 4 >= T1, "a tile holds whole blocks");
+  const int tid = threadIdx.x;
+  TW tw[NG][4];
+  each_group<NG>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, G = Groups4<S2>::size(g), LO = INV ? 2 * g : S2 - 2 * g - G, IT = 4 >> G;
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      // a block's index continues the bits above the item's
+      const Item4<G, LO> x((u32)(tid + TPB * k));
+      const u32 hi = ((u32)blk0 << (S2 - LO - G)) + x.hi;
+      if (INV) inv4_tw<G>(&tw[g][2 * k], LO, LOGN, hi, ar);
+      else fwd4_tw<G>(&tw[g][2 * k], S1 + 2 * g, hi, ar);
+    }
+  });
+  if (!INV) {
+    st.pre();
+  } else {
+    V v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = yl(a, tid + k * TPB, ar);
+#pragma unroll
+    for (int k = 0; k < 4; k++) sh[lds_be((tid + k * TPB) / T1, (tid + k * TPB) % T1, T1)] = v[k];
+  }
+  each_group<NG>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, G = Groups4<S2>::size(g), LO = INV ? 2 * g : S2 - 2 * g - G, IT = 4 >> G,
+                  P = 1 << G;
+    if (INV || g > 0) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < IT; k++) {
+      const Item4<G, LO> x((u32)(tid + TPB * k));
+      V v[P];
+#pragma unroll
+      for (int mm = 0; mm < P; mm++) {
+        const u32 e = x.at(mm);  // position in the tile: block e / T1
+        if (!INV && g == 0) {
+          v[mm] = yl(a, e, ar);
+        } else {
+          v[mm] = sh[lds_be(e / T1, e % T1, T1)];
+          if (INV && g > 0 && g % 2 == 0) v[mm] = ar.reduce(v[mm]);
+        }
+      }
+      if constexpr (INV) inv4<G>(v, &tw[g][2 * k], ar);
+      else fwd4<G>(v, &tw[g][2 * k], ar);
+#pragma unroll
+      for (int mm = 0; mm < P; mm++) {
+        const u32 e = x.at(mm);
+        if (INV && g + 1 == NG) a[e] = ar.store(v[mm]);
+        else sh[lds_be(e / T1, e % T1, T1)] = v[mm];
+      }
+    }
+  });
+  if (!INV) {
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const int e = tid + k * TPB;
+      st(e, k, sh[lds_be(e / T1, e % T1, T1)]);
+    }
+  }
+}
+// a pass with SV values per thread
+template <int LOGN, int GA, int GB, bool INV, int SV, class A, class LD>
+__device__ __forceinline__ void ntt_cols_pass(u64* a, int c0, typename A::V* sh, const A& ar, const LD& ld) {
+  if constexpr (SV == 4) ntt_cols4_body<LOGN, GA + GB, INV>(a, c0, sh, ar, ld);
+  else ntt_cols2_body<LOGN, GA, GB, INV>(a, c0, sh, ar, ld);
+}
+template <int LOGN, int GC, int GD, bool INV, int SV, class A, class ST, class YL = LoadWords>
+__device__ __forceinline__ void ntt_rows_pass(u64* a, int blk0, typename A::V* sh, const A& ar, ST st,
+                                              const YL& yl = YL()) {
+  if constexpr (SV == 4) ntt_rows4_body<LOGN, GC + GD, INV>(a, blk0, sh, ar, st, yl);
+  else ntt_rows2_body<LOGN, GC, GD, INV>(a, blk0, sh, ar, st, yl);
+}
+// Four values per thread where sixteen would give at most 1024 work-groups
+// (four a CU): a PowerMethod round at N = 2^15 takes 9.5, 8.9, 8.6, 7.9 and
+// 8.0 ms with the line at 128, 256, 512, 1024 and 2048, a 64 x 64 product at
+// N = 2^14 3.2, 3.1, 3.0, 3.0 and 3.0 ms.  Above it the larger tile's fewer LDS
+// exchanges and wider rows win.
+static inline bool small_grid(const DeviceTables& T, size_t nlimbs) { return (T.N >> 12) * nlimbs <= 1024; }
+// f(integral_constant SV) for a transform of nlimbs limbs
+template <class F>
+static void by_values(const DeviceTables& T, size_t nlimbs, F&& f) {
+  if (small_grid(T, nlimbs)) f(std::integral_constant<int, 4>{});
+  else f(std::integral_constant<int, 16>{});
+}
+
 // moduli below 2^46 take the lazy FP64 arithmetic
 
-template <int LOGN, int GA, int GB, bool INV>
+template <int LOGN, int GA, int GB, bool INV, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_cols2(u64* data, LimbMap map, const u64* __restrict__ tw,
                                                    const u64* __restrict__ twsh, const double* __restrict__ twf,
                                                    const ModConst* __restrict__ mc) {
-  constexpr int S1 = GA + GB, R = 1 << S1, C = TILE / R;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S1 = GA + GB, R = 1 << S1, C = TPB * SV / R;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = blockIdx.y;
   const int m = limb_mod(map, limb);
   if (m < 0) return;
@@ -978,20 +1225,20 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2(u64* data, LimbMap map, const
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
-    ntt_cols2_body<LOGN, GA, GB, INV>(a, c0, reinterpret_cast<double*>(sh), ar, LoadPlain{a});
+    ntt_cols_pass<LOGN, GA, GB, INV, SV>(a, c0, reinterpret_cast<double*>(sh), ar, LoadPlain{a});
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_cols2_body<LOGN, GA, GB, INV>(a, c0, sh, ar, LoadPlain{a});
+    ntt_cols_pass<LOGN, GA, GB, INV, SV>(a, c0, sh, ar, LoadPlain{a});
   }
 }
 
 // DIG: the forward pass of a decomposition, F64 limbs stored centred as doubles
-template <int LOGN, int GC, int GD, bool INV, bool DIG = false>
+template <int LOGN, int GC, int GD, bool INV, bool DIG = false, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_rows2(u64* data, LimbMap map, const u64* __restrict__ tw,
                                                    const u64* __restrict__ twsh, const double* __restrict__ twf,
                                                    const ModConst* __restrict__ mc, int il) {
-  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TILE / T1;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TPB * SV / T1;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = grid_limb(blockIdx.y, il);
   const int m = limb_mod(map, limb);
   if (m < 0) return;
@@ -1002,12 +1249,12 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2(u64* data, LimbMap map, const
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
     if (DIG)
-      ntt_rows2_body<LOGN, GC, GD, INV>(a, blk0, reinterpret_cast<double*>(sh), ar, StoreCentred{a, ar});
+      ntt_rows_pass<LOGN, GC, GD, INV, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, StoreCentred{a, ar});
     else
-      ntt_rows2_body<LOGN, GC, GD, INV>(a, blk0, reinterpret_cast<double*>(sh), ar, StorePlain<F64LazyArith>{a, ar});
+      ntt_rows_pass<LOGN, GC, GD, INV, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, StorePlain<F64LazyArith>{a, ar});
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_rows2_body<LOGN, GC, GD, INV>(a, blk0, sh, ar, StorePlain<ShoupArith>{a, ar});
+    ntt_rows_pass<LOGN, GC, GD, INV, SV>(a, blk0, sh, ar, StorePlain<ShoupArith>{a, ar});
   }
 }
 
@@ -1068,15 +1315,15 @@ __global__ void __launch_bounds__(TPB) k_intt_rows2_many(LimbBases lb, LimbMap m
 // Forward block pass whose stores are the SubScale tail: data holds npoly x
 // nq limbs y (column pass done), x [npoly][x_stride][N], c pairs (value,
 // Shoup companion) per limb t < nq, out [npoly][nq][N].
-template <int LOGN, int GC, int GD>
+template <int LOGN, int GC, int GD, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, const u64* __restrict__ tw,
                                                        const u64* __restrict__ twsh, const double* __restrict__ twf,
                                                        const ModConst* __restrict__ mc, int nq,
                                                        const u64* __restrict__ x, int x_stride,
                                                        const u64* __restrict__ cpairs, u64* out, int il,
                                                        int packed, int pack_out, int half, size_t skip) {
-  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TILE / T1;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TPB * SV / T1;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = grid_limb(blockIdx.y, il);
   const int m = limb_mod(map, limb);
   if (m < 0) return;
@@ -1091,45 +1338,45 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
-    const SubScaleF64 st{oa, xa, u2d(cpairs[2 * t]), mk.qf, mk.qinvf};
+    const SubScaleF64<SV> st{oa, xa, u2d(cpairs[2 * t]), mk.qf, mk.qinvf};
     if (pack_out) {
       // the output limb packed too (read back by the tensor sums)
       u32* olo = reinterpret_cast<u32*>(out + ((size_t)p * nq + t) * N);
       auto go = [&](auto sto) {
         if (packed && mk.bits <= 40)
-          ntt_rows2_body<LOGN, GC, GD, false>(
+          ntt_rows_pass<LOGN, GC, GD, false, SV>(
               a, blk0, reinterpret_cast<double*>(sh), ar, sto,
               LoadPacked<1>{reinterpret_cast<const u32*>(data + (size_t)limb * N) + off,
                             reinterpret_cast<const u8*>(reinterpret_cast<const u32*>(data + (size_t)limb * N) + N) + off});
         else if (packed)
-          ntt_rows2_body<LOGN, GC, GD, false>(
+          ntt_rows_pass<LOGN, GC, GD, false, SV>(
               a, blk0, reinterpret_cast<double*>(sh), ar, sto,
               LoadPacked<2>{reinterpret_cast<const u32*>(data + (size_t)limb * N) + off,
                             reinterpret_cast<const u16*>(reinterpret_cast<const u32*>(data + (size_t)limb * N) + N) + off});
         else
-          ntt_rows2_body<LOGN, GC, GD, false>(a, blk0, reinterpret_cast<double*>(sh), ar, sto);
+          ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, sto);
       };
       if (mk.bits <= 40)
-        go(SubScalePackedF64<1>{olo + off, reinterpret_cast<u8*>(olo + N) + off, xa, u2d(cpairs[2 * t]), mk.qf,
+        go(SubScalePackedF64<1, SV>{olo + off, reinterpret_cast<u8*>(olo + N) + off, xa, u2d(cpairs[2 * t]), mk.qf,
                                 mk.qinvf});
       else
-        go(SubScalePackedF64<2>{olo + off, reinterpret_cast<u16*>(olo + N) + off, xa, u2d(cpairs[2 * t]), mk.qf,
+        go(SubScalePackedF64<2, SV>{olo + off, reinterpret_cast<u16*>(olo + N) + off, xa, u2d(cpairs[2 * t]), mk.qf,
                                 mk.qinvf});
     } else if (packed) {
       // y of this limb packed by the column pass (the int8 lift's)
       const u32* lo = reinterpret_cast<const u32*>(data + (size_t)limb * N);
       if (mk.bits <= 40)
-        ntt_rows2_body<LOGN, GC, GD, false>(a, blk0, reinterpret_cast<double*>(sh), ar, st,
+        ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, st,
                                             LoadPacked<1>{lo + off, reinterpret_cast<const u8*>(lo + N) + off});
       else
-        ntt_rows2_body<LOGN, GC, GD, false>(a, blk0, reinterpret_cast<double*>(sh), ar, st,
+        ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, st,
                                             LoadPacked<2>{lo + off, reinterpret_cast<const u16*>(lo + N) + off});
     } else {
-      ntt_rows2_body<LOGN, GC, GD, false>(a, blk0, reinterpret_cast<double*>(sh), ar, st);
+      ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, st);
     }
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_rows2_body<LOGN, GC, GD, false>(a, blk0, sh, ar, SubScaleShoup{oa, xa, cpairs[2 * t], cpairs[2 * t + 1], mk.q});
+    ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, sh, ar, SubScaleShoup<SV>{oa, xa, cpairs[2 * t], cpairs[2 * t + 1], mk.q});
   }
 }
 
@@ -1194,13 +1441,13 @@ __device__ __forceinline__ L loader_of(const ModupData& d) {
   static_cast<ModupData&>(l) = d;
   return l;
 }
-template <int LOGN, int GA, int GB>
+template <int LOGN, int GA, int GB, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_cols2_modup(u64* digits, ModupSrc S, const u64* __restrict__ tw,
                                                          const u64* __restrict__ twsh,
                                                          const double* __restrict__ twf, int nmods,
                                                          const ModConst* __restrict__ mc) {
-  constexpr int S1 = GA + GB, R = 1 << S1, T1 = (1 << LOGN) / R, C = TILE / R;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S1 = GA + GB, R = 1 << S1, T1 = (1 << LOGN) / R, C = TPB * SV / R;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = blockIdx.y;
   const int per = S.beta * S.nqp;
   const int b = limb / per, rem = limb - b * per, j = rem / S.nqp, pos = rem - j * S.nqp;
@@ -1211,14 +1458,14 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_modup(u64* digits, ModupSrc S
     // the digit's own limbs: the input itself (centred doubles on F64 moduli)
     const u64* src = S.ntt_in + ((size_t)b * S.nq + pos) * N;
     const bool f64 = mc[pos].bits <= F64_LAZY_BITS;
-    u64 t[TILE / TPB];
+    u64 t[SV];
 #pragma unroll
-    for (int k = 0; k < TILE / TPB; k++) {
+    for (int k = 0; k < SV; k++) {
       const int e = threadIdx.x + k * TPB;
       t[k] = src[(size_t)(e / C) * T1 + c0 + e % C];
     }
 #pragma unroll
-    for (int k = 0; k < TILE / TPB; k++) {
+    for (int k = 0; k < SV; k++) {
       const int e = threadIdx.x + k * TPB;
       a[(size_t)(e / C) * T1 + c0 + e % C] = f64 ? (u64)__double_as_longlong(u2d(t[k])) : t[k];
     }
@@ -1243,23 +1490,21 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_modup(u64* digits, ModupSrc S
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
     double* shd = reinterpret_cast<double*>(sh);
     if (S.srcbits[j] > (int)mk.bits + 1)
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, loader_of<ModupLoad<false>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<false>>(d));
     else if (d.ns == 3)  // a full digit of three limbs: no padding source
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, loader_of<ModupLoad<true, 3>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<true, 3>>(d));
     else
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, loader_of<ModupLoad<true>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<true>>(d));
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_cols2_body<LOGN, GA, GB, false>(a, c0, sh, ar, loader_of<ModupLoad<false>>(d));
+    ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, sh, ar, loader_of<ModupLoad<false>>(d));
   }
 }
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void ntt2_modup(const DeviceTables& T, u64* digits, const ModupSrc& S, int batch, const LimbMap& rows_map,
                        hipStream_t s) {
-  constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
   const int nlimbs = batch * S.beta * S.nqp;
-  dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
   // butterflies of the column stages on every converted digit limb, plus the
   // conversion (ns products per value); the rows pass transforms the same limbs
   Mm mm_cols;
@@ -1269,75 +1514,88 @@ static void ntt2_modup(const DeviceTables& T, u64* digits, const ModupSrc& S, in
   }
   {
     ProfScope ps("ntt_fwd_cols_modup", s, 8.0 * T.N * batch * (2.0 * S.nq + (double)S.beta * S.nqp), mm_cols);
-    hipLaunchKernelGGL((k_ntt_cols2_modup<LOGN, GA, GB>), gc, dim3(TPB), 0, s, digits, S, T.psi, T.psi_sh, T.psi_f,
-                       T.nmods, T.mc);
+    by_values(T, nlimbs, [&](auto sv) {
+      constexpr int SV = decltype(sv)::value;
+      hipLaunchKernelGGL((k_ntt_cols2_modup<LOGN, GA, GB, SV>), dim3((1 << LOGN) / (TPB * SV), nlimbs), dim3(TPB), 0, s,
+                         digits, S, T.psi, T.psi_sh, T.psi_f, T.nmods, T.mc);
+    });
   }
   int active = 0;
   for (int k = 0; k < rows_map.n; k++) active += rows_map.idx[k] >= 0;
   ProfScope ps("ntt_fwd_rows", s, 16.0 * T.N * batch * active,
                mm_map(T, rows_map, S.beta * S.nqp, batch * 0.5 * T.N * (GC + GD)));
-  hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, false, true>), gr, dim3(TPB), 0, s, digits, rows_map, T.psi,
-                     T.psi_sh, T.psi_f, T.mc, interleave_of(nlimbs, modulus_period(rows_map), g_knobs.ntt_interleave));
+  const int il = interleave_of(nlimbs, modulus_period(rows_map), g_knobs.ntt_interleave);
+  by_values(T, nlimbs, [&](auto sv) {
+    constexpr int SV = decltype(sv)::value;
+    hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, false, true, SV>), dim3((1 << LOGN) / (TPB * SV), nlimbs), dim3(TPB),
+                       0, s, digits, rows_map, T.psi, T.psi_sh, T.psi_f, T.mc, il);
+  });
 }
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void ntt2_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const LimbMap& map, const u64* x,
                          int x_stride, const u64* cpairs, u64* out, hipStream_t s, bool do_cols = true,
                          bool packed = false, bool pack_out = false, size_t skip = 0) {
-  constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
-  const int nlimbs = nq * npoly;
-  dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
+  const int nlimbs = nq * npoly, il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
   if (do_cols) {
     ProfScope ps("ntt_fwd_cols", s, 16.0 * nlimbs * T.N, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
-    hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, false>), gc, dim3(TPB), 0, s, y, map, T.psi, T.psi_sh, T.psi_f,
-                       T.mc);
+    by_values(T, nlimbs, [&](auto sv) {
+      constexpr int SV = decltype(sv)::value;
+      hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, false, SV>), dim3((1 << LOGN) / (TPB * SV), nlimbs), dim3(TPB), 0,
+                         s, y, map, T.psi, T.psi_sh, T.psi_f, T.mc);
+    });
   }
   ProfScope ps("ntt_fwd_rows_sub", s, 24.0 * nlimbs * T.N, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD) + T.N));
-  hipLaunchKernelGGL((k_ntt_rows2_sub<LOGN, GC, GD>), gr, dim3(TPB), 0, s, y, map, T.psi, T.psi_sh, T.psi_f, T.mc,
-                     nq, x, x_stride, cpairs, out, interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave),
-                     packed ? 1 : 0, pack_out ? 1 : 0, npoly / 2, skip);
+  by_values(T, nlimbs, [&](auto sv) {
+    constexpr int SV = decltype(sv)::value;
+    hipLaunchKernelGGL((k_ntt_rows2_sub<LOGN, GC, GD, SV>), dim3((1 << LOGN) / (TPB * SV), nlimbs), dim3(TPB), 0, s, y,
+                       map, T.psi, T.psi_sh, T.psi_f, T.mc, nq, x, x_stride, cpairs, out, il, packed ? 1 : 0,
+                       pack_out ? 1 : 0, npoly / 2, skip);
+  });
 }
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void ntt2(const DeviceTables& T, u64* data, int nlimbs, const LimbMap& map, bool inverse, double pass_bytes,
                  hipStream_t s) {
-  constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
   static_assert(GA + GB + GC + GD == LOGN, "stage split");
-  dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
   const int il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
   const Mm mm_c = mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)), mm_r = mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD));
-  if (!inverse) {
-    {
-      ProfScope ps("ntt_fwd_cols", s, pass_bytes, mm_c);
-      hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, false>), gc, dim3(TPB), 0, s, data, map, T.psi, T.psi_sh,
-                         T.psi_f, T.mc);
+  by_values(T, nlimbs, [&](auto sv) {
+    constexpr int SV = decltype(sv)::value;
+    const dim3 grid((1 << LOGN) / (TPB * SV), nlimbs);
+    if (!inverse) {
+      {
+        ProfScope ps("ntt_fwd_cols", s, pass_bytes, mm_c);
+        hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, false, SV>), grid, dim3(TPB), 0, s, data, map, T.psi, T.psi_sh,
+                           T.psi_f, T.mc);
+      }
+      ProfScope ps("ntt_fwd_rows", s, pass_bytes, mm_r);
+      hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, false, false, SV>), grid, dim3(TPB), 0, s, data, map, T.psi, T.psi_sh,
+                         T.psi_f, T.mc, il);
+    } else {
+      {
+        ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_r);
+        hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, true, false, SV>), grid, dim3(TPB), 0, s, data, map, T.ipsi, T.ipsi_sh,
+                           T.ipsi_f, T.mc, il);
+      }
+      ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_c);
+      hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, true, SV>), grid, dim3(TPB), 0, s, data, map, T.ipsi, T.ipsi_sh,
+                         T.ipsi_f, T.mc);
     }
-    ProfScope ps("ntt_fwd_rows", s, pass_bytes, mm_r);
-    hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, false>), gr, dim3(TPB), 0, s, data, map, T.psi, T.psi_sh,
-                       T.psi_f, T.mc, il);
-  } else {
-    {
-      ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_r);
-      hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, true>), gr, dim3(TPB), 0, s, data, map, T.ipsi, T.ipsi_sh,
-                         T.ipsi_f, T.mc, il);
-    }
-    ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_c);
-    hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, true>), gc, dim3(TPB), 0, s, data, map, T.ipsi, T.ipsi_sh,
-                       T.ipsi_f, T.mc);
-  }
+  });
 }
 
 
 // Inverse NTT from src into data whose last stage scales limb k by
 // scales[2 m] (Shoup pair; m its modulus) in place of N^-1: Decompose's
 // coefficient-domain sources times their hat inverses, from the input limbs.
-template <int LOGN, int GC, int GD>
+template <int LOGN, int GC, int GD, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_intt_rows2_src(u64* data, const u64* __restrict__ src, LimbMap map,
                                                         const u64* __restrict__ tw, const u64* __restrict__ twsh,
                                                         const double* __restrict__ twf,
                                                         const ModConst* __restrict__ mc, int il) {
-  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TILE / T1;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S2 = GC + GD, T1 = 1 << S2, K = TPB * SV / T1;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = grid_limb(blockIdx.y, il);
   const int m = limb_mod(map, limb);
   if (m < 0) return;
@@ -1348,20 +1606,20 @@ __global__ void __launch_bounds__(TPB) k_intt_rows2_src(u64* data, const u64* __
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
-    ntt_rows2_body<LOGN, GC, GD, true>(a, blk0, reinterpret_cast<double*>(sh), ar, StorePlain<F64LazyArith>{a, ar},
+    ntt_rows_pass<LOGN, GC, GD, true, SV>(a, blk0, reinterpret_cast<double*>(sh), ar, StorePlain<F64LazyArith>{a, ar},
                                        LoadFrom{src + off});
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_rows2_body<LOGN, GC, GD, true>(a, blk0, sh, ar, StorePlain<ShoupArith>{a, ar}, LoadFrom{src + off});
+    ntt_rows_pass<LOGN, GC, GD, true, SV>(a, blk0, sh, ar, StorePlain<ShoupArith>{a, ar}, LoadFrom{src + off});
   }
 }
-template <int LOGN, int GA, int GB>
+template <int LOGN, int GA, int GB, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_intt_cols2_scaled(u64* data, LimbMap map, const u64* __restrict__ scales,
                                                            const u64* __restrict__ tw, const u64* __restrict__ twsh,
                                                            const double* __restrict__ twf,
                                                            const ModConst* __restrict__ mc) {
-  constexpr int S1 = GA + GB, R = 1 << S1, C = TILE / R;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S1 = GA + GB, R = 1 << S1, C = TPB * SV / R;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = blockIdx.y;
   const int m = limb_mod(map, limb);
   if (m < 0) return;
@@ -1372,10 +1630,10 @@ __global__ void __launch_bounds__(TPB) k_intt_cols2_scaled(u64* data, LimbMap ma
   const u64 c = scales[2 * m], csh = scales[2 * m + 1];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)c};
-    ntt_cols2_body<LOGN, GA, GB, true>(a, c0, reinterpret_cast<double*>(sh), ar, LoadPlain{a});
+    ntt_cols_pass<LOGN, GA, GB, true, SV>(a, c0, reinterpret_cast<double*>(sh), ar, LoadPlain{a});
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, c, csh};
-    ntt_cols2_body<LOGN, GA, GB, true>(a, c0, sh, ar, LoadPlain{a});
+    ntt_cols_pass<LOGN, GA, GB, true, SV>(a, c0, sh, ar, LoadPlain{a});
   }
 }
 bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map,
@@ -1385,18 +1643,20 @@ bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nl
   return ntt_dispatch(T.logN, [&](auto sp) {
     using S = decltype(sp);
     constexpr int LOGN = S::LOGN, GA = S::GA, GB = S::GB, GC = S::GC, GD = S::GD;
-    constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
-    dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
     const int il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
     const double pass_bytes = 16.0 * nlimbs * T.N;
-    {
-      ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD)));
-      hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD>), gr, dim3(TPB), 0, s, data, src, map, T.ipsi, T.ipsi_sh,
-                         T.ipsi_f, T.mc, il);
-    }
-    ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
-    hipLaunchKernelGGL((k_intt_cols2_scaled<LOGN, GA, GB>), gc, dim3(TPB), 0, s, data, map, scales, T.ipsi,
-                       T.ipsi_sh, T.ipsi_f, T.mc);
+    by_values(T, nlimbs, [&](auto sv) {
+      constexpr int SV = decltype(sv)::value;
+      const dim3 grid((1 << LOGN) / (TPB * SV), nlimbs);
+      {
+        ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD)));
+        hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD, SV>), grid, dim3(TPB), 0, s, data, src, map, T.ipsi,
+                           T.ipsi_sh, T.ipsi_f, T.mc, il);
+      }
+      ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
+      hipLaunchKernelGGL((k_intt_cols2_scaled<LOGN, GA, GB, SV>), grid, dim3(TPB), 0, s, data, map, scales, T.ipsi,
+                         T.ipsi_sh, T.ipsi_f, T.mc);
+    });
   });
 }
 
@@ -2459,13 +2719,40 @@ __device__ __forceinline__ L fbc_loader_of(const FbcData& d) {
   static_cast<FbcData&>(l) = d;
   return l;
 }
-template <int LOGN, int GA, int GB>
+// the same from the source limbs x_a: v_a = x_a hatinv_a and the rounded
+// quotient formed by every target (small grids: one launch less)
+template <bool F64>
+struct FbcSrcLoad {
+  typedef typename FbcLoad<F64>::Raw Raw;
+  FbcLoad<F64> ld;
+  const FbcArgs& A;
+  const u64* qs;
+  __device__ __forceinline__ void raw(size_t idx, Raw& w) const {
+#pragma unroll
+    for (int a = 0; a < 4; a++) w.x[a] = ld.v0[(size_t)(a < ld.ns ? a : ld.ns - 1) * ld.N + idx];
+    w.r = 0;
+  }
+  __device__ __forceinline__ Raw quotient(const Raw& x) const {
+    Raw w;
+#pragma unroll
+    for (int a = 0; a < 4; a++) w.x[a] = a < ld.ns ? shoup_mul(x.x[a], A.hatinv[a], A.hatinv_sh[a], qs[a]) : 0;
+    w.r = round_quotient(w.x, A);
+    return w;
+  }
+  __device__ __forceinline__ u64 fin_u(const Raw& w) const { return ld.fin_u(quotient(w)); }
+  __device__ __forceinline__ double fin_d(const Raw& w) const { return ld.fin_d(quotient(w)); }
+};
+__device__ __forceinline__ double fin(const F64LazyArith&, const FbcSrcLoad<true>& ld,
+                                      const typename FbcSrcLoad<true>::Raw& w) {
+  return ld.fin_d(w);
+}
+template <int LOGN, int GA, int GB, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_cols2_fbc(u64* y, const u64* __restrict__ V, int nq, FbcArgs A,
                                                        const u64* __restrict__ tw, const u64* __restrict__ twsh,
                                                        const double* __restrict__ twf, int nmods,
                                                        const ModConst* __restrict__ mc) {
-  constexpr int S1 = GA + GB, R = 1 << S1, C = TILE / R;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S1 = GA + GB, R = 1 << S1, C = TPB * SV / R;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = blockIdx.y;
   const int p = limb / nq, t = limb - p * nq;
   const u64 N = 1ull << LOGN;
@@ -2489,18 +2776,36 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_fbc(u64* y, const u64* __rest
     d.e0[x] = in ? A.hat_f[((size_t)x * nmods + t) * 3] : 0.0;
     d.e1[x] = in ? A.hat_f[((size_t)x * nmods + t) * 3 + 1] : 0.0;
   }
+  if constexpr (SV == 4) {
+    // V is the source limbs themselves: every target's loads form v_a and r
+    d.v0 = V + ((size_t)p * A.src_stride + A.src_off) * N;
+    u64 qs[4];
+    for (int x = 0; x < 4; x++) qs[x] = mc[A.src[x < A.ns ? x : 0]].q;
+    if (mk.bits <= F64_LAZY_BITS) {
+      F64LazyArith ar{twf + (size_t)t * N, mk.qf, mk.qinvf, (double)mk.ninv};
+      double* shd = reinterpret_cast<double*>(sh);
+      if (mk.bits <= 32)
+        ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar, FbcSrcLoad<false>{fbc_loader_of<FbcLoad<false>>(d), A, qs});
+      else
+        ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar, FbcSrcLoad<true>{fbc_loader_of<FbcLoad<true>>(d), A, qs});
+    } else {
+      ShoupArith ar{tw + (size_t)t * N, twsh + (size_t)t * N, mk.q, mk.ninv, mk.ninv_sh};
+      ntt_cols4_body<LOGN, GA + GB, false>(a, c0, sh, ar, FbcSrcLoad<false>{fbc_loader_of<FbcLoad<false>>(d), A, qs});
+    }
+    return;
+  }
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)t * N, mk.qf, mk.qinvf, (double)mk.ninv};
     double* shd = reinterpret_cast<double*>(sh);
     if (mk.bits <= 32)
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, fbc_loader_of<FbcLoad<false>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, fbc_loader_of<FbcLoad<false>>(d));
     else if (d.ns == 3)  // three special primes: no padding source
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, fbc_loader_of<FbcLoad<true, 3>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, fbc_loader_of<FbcLoad<true, 3>>(d));
     else
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, shd, ar, fbc_loader_of<FbcLoad<true>>(d));
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, fbc_loader_of<FbcLoad<true>>(d));
   } else {
     ShoupArith ar{tw + (size_t)t * N, twsh + (size_t)t * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_cols2_body<LOGN, GA, GB, false>(a, c0, sh, ar, fbc_loader_of<FbcLoad<false>>(d));
+    ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, sh, ar, fbc_loader_of<FbcLoad<false>>(d));
   }
 }
 // ModDown's lift as an int8 matrix product.  k_fbc_prep_digits writes, per
@@ -2886,9 +3191,11 @@ static void moddown_fused(const DeviceTables& T, u64* y, const u64* V, const Fbc
     ProfScope ps("ntt_fwd_cols_fbc", s, 8.0 * T.N * npoly * ((double)A.ns + 1 + nq),
                  mm_q(T, nq, 0.5 * T.N * (GA + GB) + (double)T.N * (A.ns + 1), npoly));
     if (!cdig) {
-      dim3 gc((1 << LOGN) / R / C, nq * npoly);
-      hipLaunchKernelGGL((k_ntt_cols2_fbc<LOGN, GA, GB>), gc, dim3(TPB), 0, s, y, V, nq, A, T.psi, T.psi_sh,
-                         T.psi_f, T.nmods, T.mc);
+      by_values(T, (size_t)nq * npoly, [&](auto sv) {
+        constexpr int SV = decltype(sv)::value;
+        hipLaunchKernelGGL((k_ntt_cols2_fbc<LOGN, GA, GB, SV>), dim3((1 << LOGN) / (TPB * SV), nq * npoly), dim3(TPB),
+                           0, s, y, V, nq, A, T.psi, T.psi_sh, T.psi_f, T.nmods, T.mc);
+      });
     } else {
       // FP64 targets in pairs through the MFMA lift, the Shoup-path targets
       // (above 46 bits) two units a work-group, in one launch
@@ -2940,7 +3247,8 @@ static FbcArgs fbc_args(const FbcTable& tab, int src_stride, int src_off) {
 }
 // the MFMA lift takes targets of 33 to 46 bits and, beside them, Shoup-path
 // targets above 46 bits
-bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq) {
+bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq, size_t npoly) {
+  if (small_grid(T, nq * npoly)) return false;  // sources lifted where they are loaded
   if (!g_knobs.fbc_mfma || !tab.cdig || tab.kw <= 0 || nq > 64 || tab.ns > 4 || T.logN < 12 || T.logN > 16)
     return false;
   for (int t = 0; t < nq; t++)
@@ -2952,9 +3260,10 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
                           int src_stride, int src_off, bool v_ready, bool pack_out, size_t skip) {
   if (T.logN < 12 || T.logN > 16 || tab.ns > 4) return false;
   const FbcArgs A = fbc_args(tab, src_stride > 0 ? src_stride : tab.ns, src_stride > 0 ? src_off : 0);
-  const u64* cdig = fbc_digit_path(T, tab, nq) ? tab.cdig : nullptr;
+  const u64* cdig = v_ready || fbc_digit_path(T, tab, nq, npoly) ? tab.cdig : nullptr;
   if (v_ready && !cdig) throw std::runtime_error("digit records given where the ModDown does not take them");
-  if (!v_ready) {
+  const bool from_src = !cdig && small_grid(T, (size_t)nq * npoly);
+  if (!v_ready && !from_src) {
     Mm mm;
     for (int a = 0; a < tab.ns; a++) mm.add(T.bits[tab.src[a]], (double)T.N * npoly);
     ProfScope ps("fbc_prep", s, 8.0 * T.N * npoly * (2.0 * tab.ns + 1), mm);
@@ -2970,7 +3279,7 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
   for (int k = 0; k < nq; k++) map.idx[k] = (short)k;
   return ntt_dispatch(T.logN, [&](auto sp) {
     using S = decltype(sp);
-    moddown_fused<NTT_SPLIT_ARGS>(T, y, V, A, nq, npoly, map, x, x_stride, pinv, out, s, cdig, pack_out, skip);
+    moddown_fused<NTT_SPLIT_ARGS>(T, y, from_src ? xp_coef : V, A, nq, npoly, map, x, x_stride, pinv, out, s, cdig, pack_out, skip);
   });
 }
 
@@ -4419,13 +4728,13 @@ struct LiftLoadF64 {
   __device__ __forceinline__ u64 fin_u(const Raw& r) const { return d2u(f64_canon(fin_d(r), q, qinv)); }
 };
 __device__ __forceinline__ double fin(const F64LazyArith&, const LiftLoadF64& ld, const u64& r) { return ld.fin_d(r); }
-template <int LOGN, int GA, int GB>
+template <int LOGN, int GA, int GB, int SV = 16>
 __global__ void __launch_bounds__(TPB) k_ntt_cols2_lift(u64* t, const u64* __restrict__ top, int l, int nout,
                                                         const u64* __restrict__ tw, const u64* __restrict__ twsh,
                                                         const double* __restrict__ twf,
                                                         const ModConst* __restrict__ mc) {
-  constexpr int S1 = GA + GB, R = 1 << S1, C = TILE / R;
-  __shared__ u64 sh[LDS_WORDS];
+  constexpr int S1 = GA + GB, R = 1 << S1, C = TPB * SV / R;
+  __shared__ u64 sh[lds_words(SV)];
   const int limb = blockIdx.y;
   const int p = limb / nout, k = limb - p * nout;
   const u64 N = 1ull << LOGN;
@@ -4436,24 +4745,25 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_lift(u64* t, const u64* __res
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)k * N, mk.qf, mk.qinvf, (double)mk.ninv};
     if (mc[l].bits <= F64_LAZY_BITS)
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, reinterpret_cast<double*>(sh), ar,
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, reinterpret_cast<double*>(sh), ar,
                                           LiftLoadF64{top + (size_t)p * N, mc[l].qf, mk.qf, mk.qinvf});
     else
-      ntt_cols2_body<LOGN, GA, GB, false>(a, c0, reinterpret_cast<double*>(sh), ar, ld);
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, reinterpret_cast<double*>(sh), ar, ld);
   } else {
     ShoupArith ar{tw + (size_t)k * N, twsh + (size_t)k * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_cols2_body<LOGN, GA, GB, false>(a, c0, sh, ar, ld);
+    ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, sh, ar, ld);
   }
 }
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void rescale_fused(const DeviceTables& T, u64* t, const u64* top, int l, int nout, int npoly, const u64* x,
                           int x_stride, const u64* cpairs, u64* out, hipStream_t s) {
-  constexpr int R = 1 << (GA + GB), C = TILE / R;
-  dim3 gc((1 << LOGN) / R / C, nout * npoly);
   {
     ProfScope ps("ntt_fwd_cols_lift", s, 8.0 * T.N * npoly * (1.0 + nout), mm_q(T, nout, 0.5 * T.N * (GA + GB), npoly));
-    hipLaunchKernelGGL((k_ntt_cols2_lift<LOGN, GA, GB>), gc, dim3(TPB), 0, s, t, top, l, nout, T.psi, T.psi_sh,
-                       T.psi_f, T.mc);
+    by_values(T, (size_t)nout * npoly, [&](auto sv) {
+      constexpr int SV = decltype(sv)::value;
+      hipLaunchKernelGGL((k_ntt_cols2_lift<LOGN, GA, GB, SV>), dim3((1 << LOGN) / (TPB * SV), nout * npoly), dim3(TPB),
+                         0, s, t, top, l, nout, T.psi, T.psi_sh, T.psi_f, T.mc);
+    });
   }
   LimbMap map;
   map.n = nout;

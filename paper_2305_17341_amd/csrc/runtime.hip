@@ -1044,7 +1044,7 @@ DevBuf HeCtxImpl::moddown_sources(const std::vector<HeCt*>& xs, bool with_rescal
     nq = nq_of(l);
   }
   DevBuf rec;
-  if (rec_stride && fbc_digit_path(T, *tab, nq)) {
+  if (rec_stride && fbc_digit_path(T, *tab, nq, xs.size() * np)) {
     *rec_stride = (size_t)np * (per + 1) * N;
     rec = DevBuf(&pool, xs.size() * *rec_stride);
   }

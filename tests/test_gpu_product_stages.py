@@ -74,3 +74,26 @@ def test_shift_blocks_match_oracle(oracle_mod, chain, n1, flags):
                  fused_rescale=bool(flags & FUSED))
     assert g.level == w.level and g.scale == w.scale
     assert np.array_equal(g.export(), w.data())
+
+
+@pytest.mark.parametrize("chain", [I.SMALL, I.MID, I.SERVE15, I.LARGE], ids=lambda c: c.name)
+@pytest.mark.parametrize("inverse", [False, True], ids=["forward", "inverse"])
+def test_transforms_of_few_and_many_limbs(oracle_mod, chain, inverse):
+    """few limbs take four values per thread, more than 1024 tiles of 4096
+    words sixteen: the same residues, the oracle's on a limb of each modulus
+    size (residues 0, 1 and q - 1 among the values)"""
+    from paper_2305_17341_amd import he
+    ctx = he.chain_context(chain, seed=74)
+    N, nm = ctx.N, len(ctx.moduli)
+    many = 1024 * 4096 // N + 3
+    g = np.random.default_rng(9)
+    mods = [k % nm for k in range(many)]
+    x = np.stack([g.integers(0, ctx.moduli[m], size=N, dtype=np.uint64) for m in mods])
+    x[:, 0], x[:, 1], x[:, N - 1] = 0, 1, [ctx.moduli[m] - 1 for m in mods]
+    got = ctx.ntt_limbs(x, mods, inverse)
+    for k0 in range(0, many, 60):
+        few = ctx.ntt_limbs(x[k0:k0 + 60], mods[k0:k0 + 60], inverse)
+        assert np.array_equal(few, got[k0:k0 + 60])
+    o = oracle_mod.Oracle(chain.log_n, chain.q_bits, chain.p_bits, seed=74)
+    for k in (0, 1, nm - 1):
+        assert np.array_equal((o.intt if inverse else o.ntt)(mods[k], x[k]), got[k])
