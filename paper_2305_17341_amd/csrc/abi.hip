@@ -262,8 +262,7 @@ he_status he_decrypt(he_ctx* ctx, const he_ct* ct, double* out, size_t n) {
     auto lk = hold(ctx);
     check_ct(ctx, ct);
     need(out != nullptr && n <= ctx->impl.N / 2, "bad output size");
-    std::vector<double> z = ctx->impl.decrypt(ct->ct);
-    std::copy(z.begin(), z.begin() + n, out);
+    ctx->impl.decrypt(ct->ct, out, n);
   });
 }
 

@@ -29,7 +29,7 @@ struct DeviceTables {
   // double-double FFT tables for the canonical embedding
   double* fft_tw = nullptr;    // [N/2][4] exp(-2 pi i k / N) as (re_hi, re_lo, im_hi, im_lo)
   double* zeta = nullptr;      // [N][4] (cos(pi i/N), sin(pi i/N)) dd
-  u32* rotgroup = nullptr;     // [N/2] 5^j mod 2N
+  u32* slots = nullptr;        // [N] the slot j with +-5^j = 2 t + 1 mod 2N at t, bit 31 set for the minus sign
   u64* cdt = nullptr;          // [38] Gaussian inversion table
 };
 
@@ -261,7 +261,19 @@ void launch_sample_ternary(const DeviceTables& T, i64* out, u64 seed, u64 tag, u
                            hipStream_t s);
 void launch_sample_gauss(const DeviceTables& T, i64* out, u64 seed, u64 tag, u64 c1, u64 c2, u64 c3,
                          hipStream_t s);
-void launch_add_int(i64* out, const i64* a, const i64* b, u64 N, hipStream_t s);
+// an encryption's integer polynomials [3][N]: v (ternary), m + e0, e1 (their
+// streams' tags in that order)
+struct EncTags {
+  u64 t[3];
+};
+void launch_sample_enc(const DeviceTables& T, i64* out, const i64* m, u64 seed, u64 nonce, const EncTags& tags,
+                       hipStream_t s);
+// c [2][nl][N] = e [2][nl][N] + v [nl][N] (pk0, pk1) over q_0 .. q_{nl-1}, pk1
+// comp words after pk0
+void launch_enc_combine(const DeviceTables& T, u64* c, const u64* e, const u64* v, const u64* pk, size_t comp, int nl,
+                        hipStream_t s);
+// out = a + b c on one limb of modulus mod
+void launch_mul_add(const DeviceTables& T, u64* out, const u64* a, const u64* b, const u64* c, int mod, hipStream_t s);
 // m <- round(m * mant / 2^shift) (halves away from zero), 1 <= shift < 128, |m| mant < 2^127
 void launch_scale_int(i64* m, u64 mant, int shift, u64 N, hipStream_t s);
 // switching key b part: b = e - a s (+ pmod s' on the digit's primes)
@@ -276,8 +288,18 @@ void launch_key_f64(const DeviceTables& T, u64* key, int nblocks, int nmods, hip
 void launch_encode(const DeviceTables& T, i64* out, const double* z, int nz, int batch, double delta, void* scratch,
                    hipStream_t s);
 size_t encode_scratch_bytes(const DeviceTables& T, int batch);
-void launch_decode(const DeviceTables& T, double* out, const i64* m, int batch, const double* inv_scale,
-                   void* scratch, hipStream_t s);
+// the encoding of a message made on the device: kind 0 = value in every slot,
+// 1 / 2 / 3 = 1 in column idx / row idx / the diagonal of every n x n block
+// (row-major), 0 elsewhere
+struct EncPattern {
+  int kind, n, idx;
+  double value;
+};
+void launch_encode_pattern(const DeviceTables& T, i64* out, const EncPattern& p, double delta, void* scratch,
+                           hipStream_t s);
+// the N/2 slots of the centred residues of coef mod q
+void launch_decode(const DeviceTables& T, double* out, const u64* coef, u64 q, double inv_scale, void* scratch,
+                   hipStream_t s);
 // decryption helpers
 void launch_centre_to_int(const DeviceTables& T, i64* out, const u64* coef, int mod, hipStream_t s);
 

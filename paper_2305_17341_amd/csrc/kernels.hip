@@ -4817,21 +4817,21 @@ void launch_sample_uniform(const DeviceTables& T, u64* out, int nlimbs, const Li
   hipLaunchKernelGGL(k_sample_uniform, grid, dim3(TPB), 0, s, out, nlimbs, m, seed, tag, c2, c3, T.logN, T.mc);
 }
 
+__device__ __forceinline__ i64 sample_small(int kind, u32 i, u64 seed, u64 tag, u64 c1, u64 c2, u64 c3,
+                                            const u64* __restrict__ cdt) {
+  u64 c[4] = {i, c1, c2, c3};
+  philox4x64(c, seed, tag);
+  if (kind == 0) return (i64)(c[0] % 3) - 1;
+  i64 v = -19;
+  for (int k = 0; k < 38; k++) v += c[0] >= cdt[k] ? 1 : 0;
+  return v;
+}
 __global__ void k_sample_small(i64* out, int kind, u64 seed, u64 tag, u64 c1, u64 c2, u64 c3, int logN,
                                const u64* __restrict__ cdt) {
   const u64 N = 1ull << logN;
   u32 i = blockIdx.x * TPB + threadIdx.x;
   if (i >= N) return;
-  u64 c[4] = {i, c1, c2, c3};
-  philox4x64(c, seed, tag);
-  i64 v;
-  if (kind == 0) {
-    v = (i64)(c[0] % 3) - 1;
-  } else {
-    v = -19;
-    for (int k = 0; k < 38; k++) v += c[0] >= cdt[k] ? 1 : 0;
-  }
-  out[i] = v;
+  out[i] = sample_small(kind, i, seed, tag, c1, c2, c3, cdt);
 }
 void launch_sample_ternary(const DeviceTables& T, i64* out, u64 seed, u64 tag, u64 c1, u64 c2, u64 c3,
                            hipStream_t s) {
@@ -4843,12 +4843,50 @@ void launch_sample_gauss(const DeviceTables& T, i64* out, u64 seed, u64 tag, u64
   hipLaunchKernelGGL(k_sample_small, dim3(cdiv(T.N, TPB)), dim3(TPB), 0, s, out, 1, seed, tag, c1, c2, c3, T.logN,
                      T.cdt);
 }
-__global__ void k_add_int(i64* out, const i64* a, const i64* b, u64 N) {
-  u64 i = (u64)blockIdx.x * TPB + threadIdx.x;
-  if (i < N) out[i] = a[i] + b[i];
+// an encryption's integer polynomials [3][N]: v (ternary), m + e0, e1
+__global__ void k_sample_enc(i64* out, const i64* m, u64 seed, u64 nonce, EncTags tags, int logN,
+                             const u64* __restrict__ cdt) {
+  const u64 N = 1ull << logN;
+  const u32 i = blockIdx.x * TPB + threadIdx.x;
+  const int p = blockIdx.y;
+  if (i >= N) return;
+  const i64 v = sample_small(p == 0 ? 0 : 1, i, seed, tags.t[p], 0, nonce, 0, cdt);
+  out[(size_t)p * N + i] = p == 1 ? v + m[i] : v;
 }
-void launch_add_int(i64* out, const i64* a, const i64* b, u64 N, hipStream_t s) {
-  hipLaunchKernelGGL(k_add_int, dim3(cdiv(N, TPB)), dim3(TPB), 0, s, out, a, b, N);
+void launch_sample_enc(const DeviceTables& T, i64* out, const i64* m, u64 seed, u64 nonce, const EncTags& tags,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(k_sample_enc, dim3(cdiv(T.N, TPB), 3), dim3(TPB), 0, s, out, m, seed, nonce, tags, T.logN, T.cdt);
+}
+// c [2][nl][N] = e [2][nl][N] + v [nl][N] (pk0, pk1), limbs q_0 .. q_{nl-1}, the
+// second half of the key comp words after the first
+__global__ void k_enc_combine(u64* c, const u64* __restrict__ e, const u64* __restrict__ v,
+                              const u64* __restrict__ pk, size_t comp, int nl, int logN,
+                              const ModConst* __restrict__ mc) {
+  const u64 N = 1ull << logN;
+  const u32 i = blockIdx.x * TPB + threadIdx.x;
+  const int k = blockIdx.y;
+  if (i >= N) return;
+  const ModConst mk = mc[k];
+  const size_t o0 = (size_t)k * N + i, o1 = (size_t)(nl + k) * N + i;
+  const u64 x = v[o0];
+  c[o0] = add_mod(e[o0], mul_mod_any(x, pk[o0], mk), mk.q);
+  c[o1] = add_mod(e[o1], mul_mod_any(x, pk[comp + o0], mk), mk.q);
+}
+void launch_enc_combine(const DeviceTables& T, u64* c, const u64* e, const u64* v, const u64* pk, size_t comp, int nl,
+                        hipStream_t s) {
+  ProfScope ps("elementwise", s, 8.0 * T.N * 7.0 * nl, mm_q(T, nl, 2.0 * T.N));
+  hipLaunchKernelGGL(k_enc_combine, dim3(cdiv(T.N, TPB), nl), dim3(TPB), 0, s, c, e, v, pk, comp, nl, T.logN, T.mc);
+}
+// out = a + b c on one limb
+__global__ void k_mul_add(u64* out, const u64* a, const u64* b, const u64* c, int m, u64 N,
+                          const ModConst* __restrict__ mc) {
+  const u64 i = (u64)blockIdx.x * TPB + threadIdx.x;
+  if (i >= N) return;
+  const ModConst mk = mc[m];
+  out[i] = add_mod(a[i], mul_mod_any(b[i], c[i], mk), mk.q);
+}
+void launch_mul_add(const DeviceTables& T, u64* out, const u64* a, const u64* b, const u64* c, int mod, hipStream_t s) {
+  hipLaunchKernelGGL(k_mul_add, dim3(cdiv(T.N, TPB)), dim3(TPB), 0, s, out, a, b, c, mod, T.N, T.mc);
 }
 
 // m <- round(m * mant / 2^shift), halves away from zero, exact (128-bit product)
@@ -4965,96 +5003,141 @@ __device__ __forceinline__ cdd cdd_mul(cdd a, cdd b) {
 __device__ __forceinline__ cdd cdd_add(cdd a, cdd b) { return {dd_add(a.re, b.re), dd_add(a.im, b.im)}; }
 __device__ __forceinline__ cdd cdd_sub(cdd a, cdd b) { return {dd_add(a.re, dd_neg(b.re)), dd_add(a.im, dd_neg(b.im))}; }
 
-// scatter the message into bit-reversed FFT input order
-__global__ void k_enc_scatter(cdd* x, const double* z, int nz, int batch, int logN, const u32* rotgroup) {
-  const u64 N = 1ull << logN, S = N >> 1;
-  u64 j = (u64)blockIdx.x * TPB + threadIdx.x;
-  int b = blockIdx.y;
-  if (j >= S) return;
-  double v = z[(size_t)b * nz + (j % nz)];
-  u32 e = rotgroup[j];
-  u32 t1 = (e - 1) >> 1, t2 = (u32)((2 * N - e - 1) >> 1);
-  cdd val = {{v, 0.0}, {0.0, 0.0}};
-  x[(size_t)b * N + brv(t1, logN)] = val;
-  x[(size_t)b * N + brv(t2, logN)] = val;
-}
-
-// one radix-2 stage of an in-place DIT FFT (input in bit-reversed order);
-// sign = -1 uses exp(-2 pi i k/N), +1 its conjugate
-__global__ void k_fft_stage(cdd* x, int logN, int len, int sign, const double* tw) {
-  const u64 N = 1ull << logN;
-  u64 t = (u64)blockIdx.x * TPB + threadIdx.x;
-  int b = blockIdx.y;
-  if (t >= N / 2) return;
-  int half = len >> 1;
-  u64 blk = t / half, k = t % half;
-  u64 i0 = blk * len + k, i1 = i0 + half;
-  u64 ti = k * (N / len);
+// The in-place DIT FFT of N points (input in bit-reversed order; sign = -1
+// uses exp(-2 pi i k/N), +1 its conjugate) in two passes of FFT_TILE points
+// in LDS, one butterfly per thread and stage: the first FFT_LOW stages on
+// contiguous tiles, the others on tiles of whole columns (rows 2^FFT_LOW
+// apart).  The first pass forms its input as it loads it, the second ends in
+// what is wanted of the result.  A launch per radix-2 stage spent 3 us on
+// each of 13 to 16 stages, nearly all of it latency.
+#define FFT_TILE (2 * TPB)
+#define FFT_LOW 9
+static_assert(FFT_TILE == 1 << FFT_LOW, "the low pass takes a whole tile");
+__device__ __forceinline__ void fft_bf(cdd& x0, cdd& x1, u64 ti, int sign, const double* __restrict__ tw) {
   const double* w4 = tw + 4 * ti;
-  cdd w = {{w4[0], w4[1]}, {sign < 0 ? w4[2] : -w4[2], sign < 0 ? w4[3] : -w4[3]}};
-  cdd* xb = x + (size_t)b * N;
-  cdd a = xb[i0], c = cdd_mul(xb[i1], w);
-  xb[i0] = cdd_add(a, c);
-  xb[i1] = cdd_sub(a, c);
+  const cdd w = {{w4[0], w4[1]}, {sign < 0 ? w4[2] : -w4[2], sign < 0 ? w4[3] : -w4[3]}};
+  const cdd a = x0, c = cdd_mul(x1, w);
+  x0 = cdd_add(a, c);
+  x1 = cdd_sub(a, c);
+}
+template <class IN>
+__global__ void __launch_bounds__(TPB) k_fft_low(cdd* x, IN in, int logN, int sign, const double* __restrict__ tw) {
+  __shared__ cdd sh[FFT_TILE];
+  const u64 N = 1ull << logN;
+  const u32 p0 = blockIdx.x * FFT_TILE;
+  const int b = blockIdx.y;
+  for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) sh[e] = in(b, brv(p0 + e, logN), N);
+  for (int st = 0; st < FFT_LOW; st++) {
+    __syncthreads();
+    const u32 half = 1u << st, k = threadIdx.x & (half - 1), i0 = ((threadIdx.x >> st) << (st + 1)) + k;
+    fft_bf(sh[i0], sh[i0 + half], (u64)k << (logN - st - 1), sign, tw);
+  }
+  __syncthreads();
+  for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) x[(size_t)b * N + p0 + e] = sh[e];
+}
+template <class OUT>
+__global__ void __launch_bounds__(TPB) k_fft_high(const cdd* __restrict__ x, OUT out, int logN, int sign,
+                                                  const double* __restrict__ tw) {
+  __shared__ cdd sh[FFT_TILE];
+  const u64 N = 1ull << logN;
+  const int lr = logN - FFT_LOW, lc = FFT_LOW - lr;  // log2 of the rows, of the tile's columns
+  const u32 C = 1u << lc, c0 = blockIdx.x * C;
+  const int b = blockIdx.y;
+  for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
+    sh[e] = x[(size_t)b * N + ((size_t)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1))];
+  const u32 c = threadIdx.x & (C - 1), rr = threadIdx.x >> lc;
+  for (int st = 0; st < lr; st++) {
+    __syncthreads();
+    const u32 half = 1u << st, k = rr & (half - 1), r0 = ((rr >> st) << (st + 1)) + k;
+    const u64 kk = ((u64)k << FFT_LOW) + c0 + c;
+    fft_bf(sh[(r0 << lc) + c], sh[((r0 + half) << lc) + c], kk << (lr - st - 1), sign, tw);
+  }
+  __syncthreads();
+  for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
+    out(b, ((u64)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1)), sh[e], N);
+}
+template <class IN, class OUT>
+static void fft_passes(const DeviceTables& T, cdd* x, const IN& in, const OUT& out, int batch, int sign, hipStream_t s) {
+  const dim3 grid((unsigned)(T.N / FFT_TILE), batch);
+  hipLaunchKernelGGL(k_fft_low<IN>, grid, dim3(TPB), 0, s, x, in, T.logN, sign, T.fft_tw);
+  hipLaunchKernelGGL(k_fft_high<OUT>, grid, dim3(TPB), 0, s, x, out, T.logN, sign, T.fft_tw);
 }
 
-__global__ void k_enc_finish(i64* out, const cdd* x, double delta_over_n, int logN, const double* zeta) {
-  const u64 N = 1ull << logN;
-  u64 i = (u64)blockIdx.x * TPB + threadIdx.x;
-  int b = blockIdx.y;
-  if (i >= N) return;
-  cdd U = x[(size_t)b * N + i];
-  dd c = {zeta[4 * i], zeta[4 * i + 1]}, s = {zeta[4 * i + 2], zeta[4 * i + 3]};
-  // Re(zeta^-i U) = Re(U) cos + Im(U) sin
-  dd re = dd_add(dd_mul(U.re, c), dd_mul(U.im, s));
-  dd v = dd_mul_d(re, delta_over_n);
-  dd w = dd_add(v, dd{0.500000000931322574615478515625, 0.0});  // 1/2 + 2^-30, exact
-  double f = floor(w.hi);
-  i64 r = (i64)f;
-  if (f == w.hi && w.lo < 0.0) r -= 1;
-  out[(size_t)b * N + i] = r;
-}
+// encoder input: u[t] = z_j at the exponents 2 t + 1 = +-5^j mod 2N
+struct EncSlots {
+  const double* z;
+  int nz;
+  const u32* slots;
+  __device__ __forceinline__ cdd operator()(int b, u32 t, u64) const {
+    const u32 j = slots[t] & 0x7fffffffu;
+    return {{z[(size_t)b * nz + j % (u32)nz], 0.0}, {0.0, 0.0}};
+  }
+};
+// a constant, or 1s in one column, one row or the diagonal of every n x n block
+struct EncPatternIn {
+  EncPattern p;
+  const u32* slots;
+  __device__ __forceinline__ cdd operator()(int, u32 t, u64) const {
+    const u32 j = (slots[t] & 0x7fffffffu) % (u32)(p.n * p.n), r = j / (u32)p.n, c = j - r * (u32)p.n;
+    const bool on = p.kind == 1 ? c == (u32)p.idx : p.kind == 2 ? r == (u32)p.idx : r == c;
+    const double v = p.kind == 0 ? p.value : on ? 1.0 : 0.0;
+    return {{v, 0.0}, {0.0, 0.0}};
+  }
+};
+struct EncFinish {
+  i64* out;
+  double delta_over_n;
+  const double* zeta;
+  __device__ __forceinline__ void operator()(int b, u64 i, const cdd& U, u64 N) const {
+    dd c = {zeta[4 * i], zeta[4 * i + 1]}, s = {zeta[4 * i + 2], zeta[4 * i + 3]};
+    // Re(zeta^-i U) = Re(U) cos + Im(U) sin
+    dd re = dd_add(dd_mul(U.re, c), dd_mul(U.im, s));
+    dd v = dd_mul_d(re, delta_over_n);
+    dd w = dd_add(v, dd{0.500000000931322574615478515625, 0.0});  // 1/2 + 2^-30, exact
+    double f = floor(w.hi);
+    i64 r = (i64)f;
+    if (f == w.hi && w.lo < 0.0) r -= 1;
+    out[(size_t)b * N + i] = r;
+  }
+};
 
 size_t encode_scratch_bytes(const DeviceTables& T, int batch) { return (size_t)batch * T.N * sizeof(cdd); }
 
 void launch_encode(const DeviceTables& T, i64* out, const double* z, int nz, int batch, double delta, void* scratch,
                    hipStream_t s) {
-  cdd* x = (cdd*)scratch;  // every entry is written by the scatter (+-5^j cover all odd residues)
-  hipLaunchKernelGGL(k_enc_scatter, dim3(cdiv(T.N / 2, TPB), batch), dim3(TPB), 0, s, x, z, nz, batch, T.logN,
-                     T.rotgroup);
-  for (int len = 2; len <= (int)T.N; len <<= 1)
-    hipLaunchKernelGGL(k_fft_stage, dim3(cdiv(T.N / 2, TPB), batch), dim3(TPB), 0, s, x, T.logN, len, -1, T.fft_tw);
-  hipLaunchKernelGGL(k_enc_finish, dim3(cdiv(T.N, TPB), batch), dim3(TPB), 0, s, out, x, delta / (double)T.N,
-                     T.logN, T.zeta);
+  fft_passes(T, (cdd*)scratch, EncSlots{z, nz, T.slots}, EncFinish{out, delta / (double)T.N, T.zeta}, batch, -1, s);
+}
+void launch_encode_pattern(const DeviceTables& T, i64* out, const EncPattern& p, double delta, void* scratch,
+                           hipStream_t s) {
+  fft_passes(T, (cdd*)scratch, EncPatternIn{p, T.slots}, EncFinish{out, delta / (double)T.N, T.zeta}, 1, -1, s);
 }
 
-// decoding: y[t] = sum_i (m_i zeta^i) w^(t i); z_j = Re(y[(5^j - 1)/2]) / scale
-__global__ void k_dec_scatter(cdd* x, const i64* m, int logN, const double* zeta) {
-  const u64 N = 1ull << logN;
-  u64 i = (u64)blockIdx.x * TPB + threadIdx.x;
-  int b = blockIdx.y;
-  if (i >= N) return;
-  i64 v = m[(size_t)b * N + i];
-  double hi = (double)v;
-  double lo = (double)(v - (i64)hi);
-  dd mv = quick_two_sum(hi, lo);
-  dd c = {zeta[4 * i], zeta[4 * i + 1]}, s = {zeta[4 * i + 2], zeta[4 * i + 3]};
-  x[(size_t)b * N + brv((u32)i, logN)] = {dd_mul(mv, c), dd_mul(mv, s)};
-}
-__global__ void k_dec_gather(double* out, const cdd* x, int logN, const u32* rotgroup, const double* inv_scale) {
-  const u64 N = 1ull << logN, S = N >> 1;
-  u64 j = (u64)blockIdx.x * TPB + threadIdx.x;
-  int b = blockIdx.y;
-  if (j >= S) return;
-  cdd y = x[(size_t)b * N + ((rotgroup[j] - 1) >> 1)];
-  out[(size_t)b * S + j] = (y.re.hi + y.re.lo) * inv_scale[b];
-}
-void launch_decode(const DeviceTables& T, double* out, const i64* m, int batch, const double* inv_scale,
-                   void* scratch, hipStream_t s) {
-  cdd* x = (cdd*)scratch;
-  hipLaunchKernelGGL(k_dec_scatter, dim3(cdiv(T.N, TPB), batch), dim3(TPB), 0, s, x, m, T.logN, T.zeta);
-  for (int len = 2; len <= (int)T.N; len <<= 1)
-    hipLaunchKernelGGL(k_fft_stage, dim3(cdiv(T.N / 2, TPB), batch), dim3(TPB), 0, s, x, T.logN, len, +1, T.fft_tw);
-  hipLaunchKernelGGL(k_dec_gather, dim3(cdiv(T.N / 2, TPB), batch), dim3(TPB), 0, s, out, x, T.logN, T.rotgroup,
-                     inv_scale);
+// decoding: y[t] = sum_i (m_i zeta^i) w^(t i), m the centred residues of a
+// coefficient-domain limb; z_j = Re(y[(5^j - 1)/2]) / scale
+struct DecIn {
+  const u64* coef;
+  u64 q;
+  const double* zeta;
+  __device__ __forceinline__ cdd operator()(int, u32 i, u64) const {
+    const u64 x = coef[i];
+    const i64 v = x > (q >> 1) ? -(i64)(q - x) : (i64)x;
+    double hi = (double)v;
+    double lo = (double)(v - (i64)hi);
+    dd mv = quick_two_sum(hi, lo);
+    dd c = {zeta[4 * (size_t)i], zeta[4 * (size_t)i + 1]}, s = {zeta[4 * (size_t)i + 2], zeta[4 * (size_t)i + 3]};
+    return {dd_mul(mv, c), dd_mul(mv, s)};
+  }
+};
+struct DecOut {
+  double* out;
+  double inv_scale;
+  const u32* slots;
+  __device__ __forceinline__ void operator()(int, u64 t, const cdd& y, u64) const {
+    const u32 j = slots[t];
+    if (!(j >> 31)) out[j] = (y.re.hi + y.re.lo) * inv_scale;
+  }
+};
+void launch_decode(const DeviceTables& T, double* out, const u64* coef, u64 q, double inv_scale, void* scratch,
+                   hipStream_t s) {
+  fft_passes(T, (cdd*)scratch, DecIn{coef, q, T.zeta}, DecOut{out, inv_scale, T.slots}, 1, +1, s);
 }

@@ -39,8 +39,7 @@ DevBuf HeCtxImpl::decrypt_int(const HeCt& c) {
   if (c.qp || c.B != 1) fail(HE_EINVAL, "decrypt takes one ciphertext over Q");
   DevBuf t(&pool, N);
   LimbMap m0 = one(0);
-  launch_mul(T, t.p, c.limb(1, 0), s_ntt.p, 1, m0, stream);
-  launch_add(T, t.p, t.p, c.limb(0, 0), 1, m0, stream);
+  launch_mul_add(T, t.p, c.limb(0, 0), c.limb(1, 0), s_ntt.p, 0, stream);
   launch_ntt(T, t.p, 1, m0, true, stream);
   DevBuf mi(&pool, N);
   launch_centre_to_int(T, (i64*)mi.p, t.p, 0, stream);
@@ -75,20 +74,15 @@ struct Circuit {
   int n;
   const RefreshFn& refresh;
 
-  DevBuf const_pt(double v, double scale) {
-    std::vector<double> z((size_t)n * n, v);
-    return c.encode_batch(z.data(), n * n, 1, scale);
-  }
+  DevBuf const_pt(double v, double scale) { return c.encode_pattern(EncPattern{0, n, 0, v}, scale); }
+  // column 0, or the diagonal
   DevBuf mask_pt(bool col0, double scale) {
-    std::vector<double> z((size_t)n * n, 0.0);
-    for (int i = 0; i < n; i++) z[(size_t)i * n + (col0 ? 0 : i)] = 1.0;
-    return c.encode_batch(z.data(), n * n, 1, scale);
+    if (col0) return line_pt(true, 0, scale);
+    return c.encode_pattern(EncPattern{3, n, 0, 1.0}, scale);
   }
   // 0/1 mask keeping column idx (col) or row idx of an n x n block
   DevBuf line_pt(bool col, int idx, double scale) {
-    std::vector<double> z((size_t)n * n, 0.0);
-    for (int i = 0; i < n; i++) z[col ? (size_t)i * n + idx : (size_t)idx * n + i] = 1.0;
-    return c.encode_batch(z.data(), n * n, 1, scale);
+    return c.encode_pattern(EncPattern{col ? 1 : 2, n, idx, 1.0}, scale);
   }
   void ready(HeCt& x) {
     if (x.level < 1) refresh(x);

@@ -167,6 +167,7 @@ struct HeCtxImpl {
   void copy_limbs(u64* dst, const u64* src, size_t nlimbs, const char* family = "copy_limbs");
 
   DevBuf encode_batch(const double* z_host, int nz, int batch, double delta);
+  DevBuf encode_pattern(const EncPattern& p, double delta);
   void int_to_ntt(u64* out, const i64* m, const LimbMap& map, int npoly = 1);
 
   void keygen_secret();
@@ -177,7 +178,8 @@ struct HeCtxImpl {
 
   HeCt encrypt_int(const i64* m_dev, int level, double scale, u64 nonce);
   HeCt encrypt(const double* z, int nz, int level, u64 nonce);
-  std::vector<double> decrypt(const HeCt& c);
+  // the first n slots, to host memory
+  void decrypt(const HeCt& c, double* out, size_t n);
 
   HeCt add(const HeCt& a, const HeCt& b, bool sub);
   void add_into(HeCt& acc, const HeCt& b);

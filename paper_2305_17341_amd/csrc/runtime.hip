@@ -448,13 +448,14 @@ void HeCtxImpl::init(const he_params* p, const he_device* dev, u64 seed_) {
   he_host_dd_tables(logN, tw.data(), zt.data());
   T.fft_tw = (double*)table_upload(tw.data(), tw.size() * 8);
   T.zeta = (double*)table_upload(zt.data(), zt.size() * 8);
-  std::vector<u32> rg(N / 2);
+  std::vector<u32> slots(N);
   u64 g = 1;
   for (u64 j = 0; j < N / 2; j++) {
-    rg[j] = (u32)g;
+    slots[(g - 1) >> 1] = (u32)j;
+    slots[(2 * N - g - 1) >> 1] = (u32)j | 0x80000000u;
     g = (g * 5) % (2 * N);
   }
-  T.rotgroup = (u32*)table_upload(rg.data(), rg.size() * 4);
+  T.slots = (u32*)table_upload(slots.data(), slots.size() * 4);
 
   // Gaussian inversion table for chi_e: cumulative discrete Gaussian, |e| <= 19
   {
@@ -606,6 +607,13 @@ DevBuf HeCtxImpl::encode_batch(const double* z_host, int nz, int batch, double d
   return out;
 }
 
+// a message made on the device: nothing uploaded, nothing waited for
+DevBuf HeCtxImpl::encode_pattern(const EncPattern& p, double dlt) {
+  DevBuf out(&pool, N), scratch(&pool, encode_scratch_bytes(T, 1) / 8);
+  launch_encode_pattern(T, (i64*)out.p, p, dlt, scratch.p, stream);
+  return out;
+}
+
 // integer coefficients -> evaluation-domain limbs for the map's moduli
 void HeCtxImpl::int_to_ntt(u64* out, const i64* m, const LimbMap& map, int npoly) {
   launch_int_to_limbs(T, out, m, map.n, map, stream, npoly);
@@ -686,19 +694,12 @@ HeCt HeCtxImpl::encrypt_int(const i64* m_dev, int level, double scale, u64 nonce
   if (level < 0 || level > L) fail(HE_ELEVEL, "level out of range");
   int nl = level + 1;
   LimbMap qm = qmap(nl);
-  DevBuf v(&pool, N), e0(&pool, N), e1(&pool, N);
-  launch_sample_ternary(T, (i64*)v.p, seed, TAG_ENC_V, 0, nonce, 0, stream);
-  launch_sample_gauss(T, (i64*)e0.p, seed, TAG_ENC_E0, 0, nonce, 0, stream);
-  launch_sample_gauss(T, (i64*)e1.p, seed, TAG_ENC_E1, 0, nonce, 0, stream);
-  launch_add_int((i64*)e0.p, (const i64*)e0.p, m_dev, N, stream);
-  DevBuf vn(&pool, (size_t)nl * N);
-  int_to_ntt(vn.p, (const i64*)v.p, qm);
+  DevBuf small(&pool, 3 * N), ntt(&pool, (size_t)3 * nl * N);
+  launch_sample_enc(T, (i64*)small.p, m_dev, seed, nonce, EncTags{{TAG_ENC_V, TAG_ENC_E0, TAG_ENC_E1}}, stream);
+  int_to_ntt(ntt.p, (const i64*)small.p, qm, 3);
   HeCt c = ct_new(level, false, scale);
-  int_to_ntt(c.poly(0), (const i64*)e0.p, qm);
-  int_to_ntt(c.poly(1), (const i64*)e1.p, qm);
-  // c0 += v pk0 ; c1 += v pk1  (pk rows restricted to the first nl limbs)
-  launch_mul_acc(T, c.poly(0), vn.p, pk.p, nl, nl, qm, stream);
-  launch_mul_acc(T, c.poly(1), vn.p, pk.p + (size_t)(L + 1) * N, nl, nl, qm, stream);
+  // c0 = m + e0 + v pk0 ; c1 = e1 + v pk1  (pk rows restricted to the first nl limbs)
+  launch_enc_combine(T, c.d.p, ntt.p + (size_t)nl * N, ntt.p, pk.p, (size_t)(L + 1) * N, nl, stream);
   return c;
 }
 
@@ -707,27 +708,18 @@ HeCt HeCtxImpl::encrypt(const double* z, int nz, int level, u64 nonce) {
   return encrypt_int((const i64*)m.p, level, delta, nonce);
 }
 
-std::vector<double> HeCtxImpl::decrypt(const HeCt& c) {
+void HeCtxImpl::decrypt(const HeCt& c, double* out, size_t n) {
   if (!have_sk) fail(HE_EKEY, "keys not generated");
   if (c.qp) fail(HE_EINVAL, "cannot decrypt an R_QP element");
   if (c.B != 1) fail(HE_EINVAL, "decrypt takes a single ciphertext, not a batch");
   DevBuf t(&pool, N);
-  LimbMap m0 = one(0);
-  launch_mul(T, t.p, c.limb(1, 0), s_ntt.p, 1, m0, stream);
-  launch_add(T, t.p, t.p, c.limb(0, 0), 1, m0, stream);
-  launch_ntt(T, t.p, 1, m0, true, stream);
-  DevBuf mi(&pool, N);
-  launch_centre_to_int(T, (i64*)mi.p, t.p, 0, stream);
-  double inv = 1.0 / c.scale;
-  DevBuf invd(&pool, 1);
-  hip_check(hipMemcpyAsync(invd.p, &inv, 8, hipMemcpyHostToDevice, stream), "scale");
-  DevBuf out(&pool, N / 2);
+  launch_mul_add(T, t.p, c.limb(0, 0), c.limb(1, 0), s_ntt.p, 0, stream);
+  launch_ntt(T, t.p, 1, one(0), true, stream);
+  DevBuf slots(&pool, N / 2);
   DevBuf scratch(&pool, encode_scratch_bytes(T, 1) / 8);
-  launch_decode(T, (double*)out.p, (const i64*)mi.p, 1, (const double*)invd.p, scratch.p, stream);
-  std::vector<double> h(N / 2);
-  hip_check(hipMemcpyAsync(h.data(), out.p, (N / 2) * 8, hipMemcpyDeviceToHost, stream), "download");
+  launch_decode(T, (double*)slots.p, t.p, mods[0], 1.0 / c.scale, scratch.p, stream);
+  if (n) hip_check(hipMemcpyAsync(out, slots.p, n * 8, hipMemcpyDeviceToHost, stream), "download");
   hip_check(hipStreamSynchronize(stream), "decrypt");
-  return h;
 }
 
 // ---------------------------------------------------------------------------

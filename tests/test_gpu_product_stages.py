@@ -97,3 +97,19 @@ def test_transforms_of_few_and_many_limbs(oracle_mod, chain, inverse):
     o = oracle_mod.Oracle(chain.log_n, chain.q_bits, chain.p_bits, seed=74)
     for k in (0, 1, nm - 1):
         assert np.array_equal((o.intt if inverse else o.ntt)(mods[k], x[k]), got[k])
+
+
+@pytest.mark.parametrize("log_n", [10, 11, 13, 16])
+def test_embedding_passes_match_oracle(oracle_mod, log_n):
+    """the encoder's two FFT passes from one to seven stages in the second,
+    messages of one slot to all of them; decryption returns the message"""
+    from paper_2305_17341_amd import he
+    ch = I.Chain("emb", log_n, (60, 40), (60,))
+    ctx = he.chain_context(ch, seed=75)
+    ctx.keygen([])
+    o = oracle_mod.Oracle(log_n, ch.q_bits, ch.p_bits, seed=75)
+    for n in (1, 2, 64, ctx.slots):
+        z = np.random.default_rng(n).uniform(-1, 1, n)
+        assert np.array_equal(ctx.encode(z, 2.0**40), o.encode(z, 2.0**40))
+        got = ctx.decrypt(ctx.encrypt(z, nonce=n))
+        assert np.max(np.abs(got - np.resize(z, ctx.slots))) < 2.0**-15
