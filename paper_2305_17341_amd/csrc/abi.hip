@@ -359,23 +359,16 @@ he_status he_rotate_many(he_ctx* ctx, const he_ct* const* a, size_t count, const
       xs.push_back(&a[i]->ct);
     }
     HeCtxImpl& c = ctx->impl;
-    HeCt x = count == 1 ? c.ct_copy(*xs[0]) : c.stack(xs);
-    std::vector<HeCt> rot = c.rotate_many(x, std::vector<long>(steps, steps + nsteps));
+    const std::vector<long> st(steps, steps + nsteps);
+    std::vector<HeCt> rot = count == 1 && xs[0]->B == 1 ? c.rotate_many(*xs[0], st) : c.rotate_many(c.stack(xs), st);
     std::vector<he_ct*> made;
     try {
-      for (size_t r = 0; r < nsteps; r++) {
-        std::vector<HeCt> parts = count == 1 ? std::vector<HeCt>{} : c.unstack(rot[r]);
-        if (count == 1) parts.push_back(std::move(rot[r]));
-        rot[r] = HeCt();
-        for (size_t i = 0; i < count; i++) {
-          made.push_back(wrap(ctx, std::move(parts[i])));
-          out[i * nsteps + r] = made.back();
-        }
-      }
+      for (size_t k = 0; k < count * nsteps; k++) made.push_back(wrap(ctx, std::move(rot[k])));
     } catch (...) {
       for (he_ct* m : made) delete m;
       throw;
     }
+    std::copy(made.begin(), made.end(), out);
   });
 }
 he_status he_rotate_noalloc(he_ctx* ctx, const he_ct* a, int32_t step, he_ct* out) {

@@ -40,6 +40,27 @@ void launch_ntt(const DeviceTables& T, u64* data, int nlimbs, const LimbMap& map
 // launched) without the register-blocked NTT
 bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map,
                         const u64* scales, hipStream_t s);
+// Inverse NTT of src, whose limbs lie in the map's slots, into data, one limb
+// after the other; false (nothing launched) without the register-blocked NTT
+bool launch_intt_from(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map, hipStream_t s);
+// Where a fused ModDown writes its polynomials: out [npoly][nq][N], the second
+// half of them skip words further on; or, with tab, elements of per members
+// and two components, [element][2][per], to tab[element per + member] (at
+// most RD_MAX), [2][nq][N] each.  add, laid out as out, is added on.
+#define RD_MAX 64
+struct SubDst {
+  u64* out = nullptr;
+  size_t skip = 0;
+  const u64* add = nullptr;
+  std::vector<u64*> tab;
+  int per = 0;
+  SubDst(u64* o, size_t sk = 0, const u64* a = nullptr) : out(o), skip(sk), add(a) {}
+  SubDst(std::vector<u64*> t, int members) : tab(std::move(t)), per(members) {}
+  bool plain() const { return !skip && !add && tab.empty(); }
+};
+// ciphertexts [2][nl][N] into a batch [2][B][nl][N], and back
+void launch_stack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s);
+void launch_unstack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s);
 // forward NTT of npoly x nq limbs y, then out = (x - y) c mod q_t with x
 // [npoly][x_stride][N] and c pairs (value, Shoup companion) per t < nq
 void launch_ntt_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const LimbMap& map, const u64* x,
@@ -151,14 +172,13 @@ void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int
 // whether a fused ModDown of npoly polynomials into nq target limbs with this
 // table takes digit records (the int8 lift); only then may V arrive filled (v_ready)
 bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq, size_t npoly);
-// skip: the second half of the polynomials' outputs lies skip words further on
 // pack_out: out's limbs of FP64 moduli (at most 46 bits) are stored packed in
 // their N-word slots: the low 32 bits of every residue, then one high byte
 // each (moduli of at most 40 bits) or two
 bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
-                          const u64* x, int x_stride, const u64* pinv, u64* out, u64* y, u64* V, hipStream_t s,
-                          int src_stride = 0, int src_off = 0, bool v_ready = false, bool pack_out = false,
-                          size_t skip = 0);
+                          const u64* x, int x_stride, const u64* pinv, const SubDst& dst, u64* y, u64* V,
+                          hipStream_t s, int src_stride = 0, int src_off = 0, bool v_ready = false,
+                          bool pack_out = false);
 // y[npoly][nq] = exact centred lift of the source limbs xp[npoly][ns] to each q_t
 void launch_fbc_to_q(const DeviceTables& T, u64* y, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
                      hipStream_t s);

@@ -117,8 +117,12 @@ static bool ntt_dispatch(int logN, F&& f) {
 // ---------------------------------------------------------------------------
 // Algorithmic modular products of a launch by arithmetic: moduli below 2^46
 // take the lazy FP64 product, the others 64-bit integer products.
+namespace {
+bool g_prof_on = false;  // the counts below are wanted
+}
 Mm mm_map(const DeviceTables& T, const LimbMap& m, int nlimbs, double per_limb) {
   Mm r;
+  if (!g_prof_on) return r;
   for (int k = 0; k < nlimbs; k++) {
     const int idx = m.idx[k % m.n];
     if (idx >= 0) r.add(T.bits[idx], per_limb);
@@ -128,12 +132,14 @@ Mm mm_map(const DeviceTables& T, const LimbMap& m, int nlimbs, double per_limb) 
 // limbs of q_0 .. q_{nq-1}, `reps` times
 static Mm mm_q(const DeviceTables& T, int nq, double per_limb, double reps = 1.0) {
   Mm r;
+  if (!g_prof_on) return r;
   for (int k = 0; k < nq; k++) r.add(T.bits[k], per_limb * reps);
   return r;
 }
 // an R_{Q_l P} element's positions: q_0 .. q_{nq-1}, then the special primes
 static Mm mm_qp(const DeviceTables& T, int nq, int nqp, int L, double per_q, double per_p, double reps = 1.0) {
   Mm r;
+  if (!g_prof_on) return r;
   for (int pos = 0; pos < nqp; pos++) {
     const int m = pos < nq ? pos : L + 1 + (pos - nq);
     r.add(T.bits[m], (pos < nq ? per_q : per_p) * reps);
@@ -150,7 +156,6 @@ namespace {
 struct ProfPair {
   hipEvent_t a, b;
 };
-bool g_prof_on = false;
 std::map<std::string, std::vector<ProfPair>> g_prof;
 struct ProfTotal {
   double ms = 0, bytes = 0, mm_f64 = 0, mm_int = 0, unit_bytes = 0;
@@ -806,12 +811,24 @@ struct StoreCentred {
     a[e] = (u64)__double_as_longlong(ar.reduce(v));
   }
 };
+// Where the subtracting block pass writes: out [npoly][nq][N], the second half
+// of the polynomials skip words further on; or, with per > 0, polynomial p =
+// (r, component, b) of elements r of per members to (*tab)[r per + b], two
+// components each.  add (laid out as out): added onto the result.
+struct RowsDst {
+  u64* out;
+  size_t skip;
+  int half, per;
+  const u64* add;
+  u64* tab[RD_MAX];
+};
 // x is read into registers when the pass starts (pre), so its loads are in
 // flight during the butterflies; element e = threadIdx.x + k TPB
 template <int SV>
 struct SubScaleShoup {
   u64* out;
   const u64* __restrict__ x;
+  const u64* add;
   u64 c, c_sh, q;
   u64 xv[SV];
   __device__ __forceinline__ void pre() {
@@ -819,13 +836,15 @@ struct SubScaleShoup {
     for (int k = 0; k < SV; k++) xv[k] = x[threadIdx.x + k * TPB];
   }
   __device__ __forceinline__ void operator()(int e, int k, u64 v) const {
-    out[e] = shoup_mul(sub_mod(xv[k], v, q), c, c_sh, q);
+    const u64 r = shoup_mul(sub_mod(xv[k], v, q), c, c_sh, q);
+    out[e] = add ? add_mod(r, add[e], q) : r;
   }
 };
 template <int SV>
 struct SubScaleF64 {
   u64* out;
   const u64* __restrict__ x;
+  const u64* add;
   double c, q, qinv;
   u64 xv[SV];
   __device__ __forceinline__ void pre() {
@@ -834,7 +853,9 @@ struct SubScaleF64 {
   }
   // v below 9 q in absolute value (eight forward stages): |x - v| < 10 q
   __device__ __forceinline__ void operator()(int e, int k, double v) const {
-    out[e] = d2u(f64_canon(f64_mulmod_signed(u2d(xv[k]) - v, c, q, qinv), q, qinv));
+    double r = f64_mulmod_signed(u2d(xv[k]) - v, c, q, qinv);
+    if (add) r += u2d(add[e]);
+    out[e] = d2u(f64_canon(r, q, qinv));
   }
 };
 // the same with the output limb stored packed (the layout LoadPacked reads;
@@ -1320,8 +1341,8 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
                                                        const u64* __restrict__ twsh, const double* __restrict__ twf,
                                                        const ModConst* __restrict__ mc, int nq,
                                                        const u64* __restrict__ x, int x_stride,
-                                                       const u64* __restrict__ cpairs, u64* out, int il,
-                                                       int packed, int pack_out, int half, size_t skip) {
+                                                       const u64* __restrict__ cpairs, RowsDst D, int il, int packed,
+                                                       int pack_out) {
   constexpr int S2 = GC + GD, T1 = 1 << S2, K = TPB * SV / T1;
   __shared__ u64 sh[lds_words(SV)];
   const int limb = grid_limb(blockIdx.y, il);
@@ -1332,16 +1353,19 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
   const int blk0 = blockIdx.x * K;
   const size_t off = (size_t)blk0 * T1;
   u64* a = data + (size_t)limb * N + off;
-  if (p >= half) out += skip;
+  u64* out;  // this limb
+  if (D.per > 0) out = D.tab[p / (2 * D.per) * D.per + p % D.per] + ((size_t)(p / D.per % 2) * nq + t) * N;
+  else out = D.out + ((size_t)p * nq + t) * N + (p >= D.half ? D.skip : 0);
   const u64* xa = x + ((size_t)p * x_stride + t) * N + off;
-  u64* oa = out + ((size_t)p * nq + t) * N + off;
+  u64* oa = out + off;
+  const u64* da = D.add ? D.add + ((size_t)p * nq + t) * N + off : nullptr;
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
-    const SubScaleF64<SV> st{oa, xa, u2d(cpairs[2 * t]), mk.qf, mk.qinvf};
+    const SubScaleF64<SV> st{oa, xa, da, u2d(cpairs[2 * t]), mk.qf, mk.qinvf};
     if (pack_out) {
       // the output limb packed too (read back by the tensor sums)
-      u32* olo = reinterpret_cast<u32*>(out + ((size_t)p * nq + t) * N);
+      u32* olo = reinterpret_cast<u32*>(out);
       auto go = [&](auto sto) {
         if (packed && mk.bits <= 40)
           ntt_rows_pass<LOGN, GC, GD, false, SV>(
@@ -1376,7 +1400,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows2_sub(u64* data, LimbMap map, c
     }
   } else {
     ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
-    ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, sh, ar, SubScaleShoup<SV>{oa, xa, cpairs[2 * t], cpairs[2 * t + 1], mk.q});
+    ntt_rows_pass<LOGN, GC, GD, false, SV>(a, blk0, sh, ar, SubScaleShoup<SV>{oa, xa, da, cpairs[2 * t], cpairs[2 * t + 1], mk.q});
   }
 }
 
@@ -1534,8 +1558,8 @@ static void ntt2_modup(const DeviceTables& T, u64* digits, const ModupSrc& S, in
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void ntt2_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const LimbMap& map, const u64* x,
-                         int x_stride, const u64* cpairs, u64* out, hipStream_t s, bool do_cols = true,
-                         bool packed = false, bool pack_out = false, size_t skip = 0) {
+                         int x_stride, const u64* cpairs, const SubDst& dst, hipStream_t s, bool do_cols = true,
+                         bool packed = false, bool pack_out = false) {
   const int nlimbs = nq * npoly, il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
   if (do_cols) {
     ProfScope ps("ntt_fwd_cols", s, 16.0 * nlimbs * T.N, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
@@ -1546,11 +1570,19 @@ static void ntt2_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const
     });
   }
   ProfScope ps("ntt_fwd_rows_sub", s, 24.0 * nlimbs * T.N, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD) + T.N));
+  RowsDst D;
+  D.out = dst.out;
+  D.skip = dst.skip;
+  D.half = npoly / 2;
+  D.add = dst.add;
+  D.per = dst.tab.empty() ? 0 : dst.per;
+  if (dst.tab.size() > RD_MAX) throw std::runtime_error("too many separate outputs");
+  for (size_t k = 0; k < dst.tab.size(); k++) D.tab[k] = dst.tab[k];
   by_values(T, nlimbs, [&](auto sv) {
     constexpr int SV = decltype(sv)::value;
     hipLaunchKernelGGL((k_ntt_rows2_sub<LOGN, GC, GD, SV>), dim3((1 << LOGN) / (TPB * SV), nlimbs), dim3(TPB), 0, s, y,
-                       map, T.psi, T.psi_sh, T.psi_f, T.mc, nq, x, x_stride, cpairs, out, il, packed ? 1 : 0,
-                       pack_out ? 1 : 0, npoly / 2, skip);
+                       map, T.psi, T.psi_sh, T.psi_f, T.mc, nq, x, x_stride, cpairs, D, il, packed ? 1 : 0,
+                       pack_out ? 1 : 0);
   });
 }
 
@@ -1601,8 +1633,9 @@ __global__ void __launch_bounds__(TPB) k_intt_rows2_src(u64* data, const u64* __
   if (m < 0) return;
   const u64 N = 1ull << LOGN;
   const int blk0 = blockIdx.x * K;
+  // the source's limbs in the map's slots, the result's one after the other
   const size_t off = limb_slot(map, limb) * N + (size_t)blk0 * T1;
-  u64* a = data + off;
+  u64* a = data + (size_t)limb * N + (size_t)blk0 * T1;
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
@@ -1660,6 +1693,29 @@ bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nl
   });
 }
 
+bool launch_intt_from(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map, hipStream_t s) {
+  LimbMap flat = map;
+  flat.slot_per = 0;
+  return ntt_dispatch(T.logN, [&](auto sp) {
+    using S = decltype(sp);
+    constexpr int LOGN = S::LOGN, GA = S::GA, GB = S::GB, GC = S::GC, GD = S::GD;
+    const int il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
+    const double pass_bytes = 16.0 * nlimbs * T.N;
+    by_values(T, nlimbs, [&](auto sv) {
+      constexpr int SV = decltype(sv)::value;
+      const dim3 grid((1 << LOGN) / (TPB * SV), nlimbs);
+      {
+        ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD)));
+        hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD, SV>), grid, dim3(TPB), 0, s, data, src, map, T.ipsi,
+                           T.ipsi_sh, T.ipsi_f, T.mc, il);
+      }
+      ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
+      hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, true, SV>), grid, dim3(TPB), 0, s, data, flat, T.ipsi, T.ipsi_sh,
+                         T.ipsi_f, T.mc);
+    });
+  });
+}
+
 static bool ntt_register_blocked(const DeviceTables& T, u64* data, int nlimbs, const LimbMap& map, bool inverse,
                                  double pass_bytes, hipStream_t s) {
   return ntt_dispatch(T.logN, [&](auto sp) {
@@ -1710,7 +1766,7 @@ void launch_ntt_fwd_sub(const DeviceTables& T, u64* y, int nq, int npoly, const 
   if (nq <= 0 || npoly <= 0) return;
   if (ntt_dispatch(T.logN, [&](auto sp) {
         using S = decltype(sp);
-        ntt2_fwd_sub<NTT_SPLIT_ARGS>(T, y, nq, npoly, map, x, x_stride, cpairs, out, s);
+        ntt2_fwd_sub<NTT_SPLIT_ARGS>(T, y, nq, npoly, map, x, x_stride, cpairs, SubDst(out), s);
       }))
     return;
   launch_ntt(T, y, nq * npoly, map, false, s);
@@ -2333,6 +2389,40 @@ void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b,
   dim3 grid(cdiv(T.N, TPB), nt);
   if (accumulate) hipLaunchKernelGGL(k_tensor<true>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
   else hipLaunchKernelGGL(k_tensor<false>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
+}
+
+// Ciphertexts [2][nl][N] gathered into a batch [2][B][nl][N], or a batch
+// scattered: one launch for up to RD_MAX members, two words a thread
+struct Members {
+  u64* p[RD_MAX];
+};
+template <bool GATHER>
+__global__ void k_members(u64* batch, Members M, int m0, int B, int nl, u64 N) {
+  const u64 i = ((u64)blockIdx.x * TPB + threadIdx.x) * 2;
+  const int k = blockIdx.y % nl, c = blockIdx.y / nl, b = blockIdx.z;
+  if (i >= N) return;
+  ulonglong2* x = reinterpret_cast<ulonglong2*>(batch + (((size_t)c * B + m0 + b) * nl + k) * N + i);
+  ulonglong2* y = reinterpret_cast<ulonglong2*>(M.p[b] + ((size_t)c * nl + k) * N + i);
+  if (GATHER) *x = *y;
+  else *y = *x;
+}
+static void launch_members(const DeviceTables& T, bool gather, u64* batch, u64* const* members, int B, int nl,
+                           hipStream_t s) {
+  ProfScope ps(gather ? "copy_stack" : "copy_unstack", s, 32.0 * T.N * B * nl);
+  for (int m0 = 0; m0 < B; m0 += RD_MAX) {
+    const int nb = std::min(RD_MAX, B - m0);
+    Members M;
+    for (int b = 0; b < RD_MAX; b++) M.p[b] = members[m0 + (b < nb ? b : 0)];
+    const dim3 grid(cdiv(T.N, 2 * TPB), 2 * nl, nb);
+    if (gather) hipLaunchKernelGGL(k_members<true>, grid, dim3(TPB), 0, s, batch, M, m0, B, nl, T.N);
+    else hipLaunchKernelGGL(k_members<false>, grid, dim3(TPB), 0, s, batch, M, m0, B, nl, T.N);
+  }
+}
+void launch_stack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s) {
+  launch_members(T, true, batch, members, B, nl, s);
+}
+void launch_unstack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s) {
+  launch_members(T, false, batch, members, B, nl, s);
 }
 
 // Products relinearised in batches: the top tensor components a1 b1 of the
@@ -3184,8 +3274,8 @@ __global__ void __launch_bounds__(2 * TPB) __attribute__((amdgpu_waves_per_eu(4)
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void moddown_fused(const DeviceTables& T, u64* y, const u64* V, const FbcArgs& A, int nq, int npoly,
-                          const LimbMap& map, const u64* x, int x_stride, const u64* pinv, u64* out, hipStream_t s,
-                          const u64* cdig, bool pack_out, size_t skip) {
+                          const LimbMap& map, const u64* x, int x_stride, const u64* pinv, const SubDst& dst,
+                          hipStream_t s, const u64* cdig, bool pack_out) {
   constexpr int R = 1 << (GA + GB), C = TILE / R;
   {
     ProfScope ps("ntt_fwd_cols_fbc", s, 8.0 * T.N * npoly * ((double)A.ns + 1 + nq),
@@ -3220,8 +3310,8 @@ static void moddown_fused(const DeviceTables& T, u64* y, const u64* V, const Fbc
       }
     }
   }
-  ntt2_fwd_sub<LOGN, GA, GB, GC, GD>(T, y, nq, npoly, map, x, x_stride, pinv, out, s, false, cdig != nullptr,
-                                     pack_out, skip);
+  ntt2_fwd_sub<LOGN, GA, GB, GC, GD>(T, y, nq, npoly, map, x, x_stride, pinv, dst, s, false, cdig != nullptr,
+                                     pack_out);
 }
 // ModDown of npoly polynomials: xp_coef their P limbs in the coefficient
 // domain [npoly][ns][N], x the R_{Q_l P} data ([npoly][x_stride][N]), out
@@ -3256,8 +3346,8 @@ bool fbc_digit_path(const DeviceTables& T, const FbcTable& tab, int nq, size_t n
   return true;
 }
 bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
-                          const u64* x, int x_stride, const u64* pinv, u64* out, u64* y, u64* V, hipStream_t s,
-                          int src_stride, int src_off, bool v_ready, bool pack_out, size_t skip) {
+                          const u64* x, int x_stride, const u64* pinv, const SubDst& dst, u64* y, u64* V,
+                          hipStream_t s, int src_stride, int src_off, bool v_ready, bool pack_out) {
   if (T.logN < 12 || T.logN > 16 || tab.ns > 4) return false;
   const FbcArgs A = fbc_args(tab, src_stride > 0 ? src_stride : tab.ns, src_stride > 0 ? src_off : 0);
   const u64* cdig = v_ready || fbc_digit_path(T, tab, nq, npoly) ? tab.cdig : nullptr;
@@ -3279,7 +3369,7 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
   for (int k = 0; k < nq; k++) map.idx[k] = (short)k;
   return ntt_dispatch(T.logN, [&](auto sp) {
     using S = decltype(sp);
-    moddown_fused<NTT_SPLIT_ARGS>(T, y, from_src ? xp_coef : V, A, nq, npoly, map, x, x_stride, pinv, out, s, cdig, pack_out, skip);
+    moddown_fused<NTT_SPLIT_ARGS>(T, y, from_src ? xp_coef : V, A, nq, npoly, map, x, x_stride, pinv, dst, s, cdig, pack_out);
   });
 }
 
@@ -4114,6 +4204,7 @@ struct MrCost {
 static MrCost mr_cost(const DeviceTables& T, const PosList& pl, int n, int nq, int L, int nr, int mb, int beta,
                       bool c0, bool masks, bool acc) {
   MrCost c;
+  if (!g_prof_on) return c;
   double w = 0, u = 0;
   for (int x = 0; x < n; x++) {
     const int pos = pl.pos[x];
@@ -4768,7 +4859,7 @@ static void rescale_fused(const DeviceTables& T, u64* t, const u64* top, int l, 
   LimbMap map;
   map.n = nout;
   for (int k = 0; k < nout; k++) map.idx[k] = (short)k;
-  ntt2_fwd_sub<LOGN, GA, GB, GC, GD>(T, t, nout, npoly, map, x, x_stride, cpairs, out, s, false);
+  ntt2_fwd_sub<LOGN, GA, GB, GC, GD>(T, t, nout, npoly, map, x, x_stride, cpairs, SubDst(out), s, false);
 }
 bool launch_rescale_fused(const DeviceTables& T, u64* t, const u64* top_coef, int l, int nout, int npoly,
                           const u64* x, int x_stride, const u64* cpairs, u64* out, hipStream_t s) {

@@ -124,12 +124,12 @@ struct Circuit {
   }
   HeCt aggregate(HeCt A, int axis) {
     if (axis == 0) {
-      for (long i = n; i < (long)n * n; i <<= 1) A = c.add(A, c.rotate(A, i), false);
+      for (long i = n; i < (long)n * n; i <<= 1) A = c.rotate_add(A, i);
       return A;
     }
-    for (long i = 1; i < n; i <<= 1) A = c.add(A, c.rotate(A, i), false);
+    for (long i = 1; i < n; i <<= 1) A = c.rotate_add(A, i);
     A = pmul_mask(A, true);
-    for (long i = -1; i > -n; i *= 2) A = c.add(A, c.rotate(A, i), false);
+    for (long i = -1; i > -n; i *= 2) A = c.rotate_add(A, i);
     return A;
   }
   HeCt axis_flip(HeCt& V, int axis) { return aggregate(pmul_mask(V, false), 1 - axis); }
@@ -209,7 +209,7 @@ struct Circuit {
       DevBuf m = line_pt(axis == 1, 0, ql);
       HeCt M = c.rescale(c.pmult_int(R, (const i64*)m.p, ql));
       if (axis == 1) {
-        for (long st = -1; st > -n; st *= 2) M = c.add(M, c.rotate(M, st), false);
+        for (long st = -1; st > -n; st *= 2) M = c.rotate_add(M, st);
       } else {
         M = aggregate(std::move(M), 0);
       }

@@ -195,17 +195,21 @@ struct HeCtxImpl {
   // whether they were: only on the fused, consuming path)
   HeCt moddown(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
                const u64* rec = nullptr, bool pack = false);
-  bool moddown_to(const HeCt& x, int out_level, u64* out, bool consume = false, bool src_ready = false,
-                  const u64* rec = nullptr, bool pack = false, size_t skip = 0);
+  bool moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool consume = false, bool src_ready = false,
+                  const u64* rec = nullptr, bool pack = false);
+  void intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map);
   // ModDown and Rescale as one rounding by P q_l (a variant)
   HeCt moddown_rescale(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
                        const u64* rec = nullptr, bool pack = false);
   // returns the digit records of the elements' ModDown sources when the
   // int8 lift takes them (element e's at rec + e * rec_stride), else empty
   DevBuf moddown_sources(const std::vector<HeCt*>& xs, bool with_rescale, size_t* rec_stride = nullptr);
-  HeCt keyswitch(const u64* d, int level, u64 g_key, int B = 1);
+  // add: a ciphertext batch of the result's layout added onto it
+  HeCt keyswitch(const u64* d, int level, u64 g_key, int B = 1, const u64* add = nullptr);
   HeCt mult(const HeCt& a, const HeCt& b);
   HeCt rotate(const HeCt& x, long step);
+  HeCt rotate_add(const HeCt& x, long step);  // x + its rotation
+  // single ciphertexts: member b's rotation by steps[r] at [b * steps + r]
   std::vector<HeCt> rotate_many(const HeCt& x, const std::vector<long>& steps);
   size_t rotate_workspace_bytes(int level, int B) const;
   void rotate_into(const HeCt& x, long step, u64* out, void* ws, size_t ws_bytes);

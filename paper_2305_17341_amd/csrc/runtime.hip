@@ -761,6 +761,19 @@ HeCt HeCtxImpl::drop(const HeCt& a, int level) {
   return c;
 }
 
+// limbs first .. first + count - 1 of every poly of x in the coefficient
+// domain, [polys][count][N] (moduli by map, of period count)
+void HeCtxImpl::intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map) {
+  LimbMap m = map;
+  m.slot_per = (short)count;
+  m.slot_stride = (short)x.nlimbs;
+  m.slot_off = (short)first;
+  const int n = (int)x.polys() * count;
+  if (launch_intt_from(T, dst, x.d.p, n, m, stream)) return;
+  gather_limbs(dst, x, first, count);
+  launch_ntt(T, dst, n, map, true, stream);
+}
+
 // Rescale by q_l; out_level < l - 1 also drops the limbs above it (only the
 // kept limbs are computed: the same residues as Rescale followed by a drop)
 HeCt HeCtxImpl::rescale(const HeCt& a, int out_level) {
@@ -772,8 +785,7 @@ HeCt HeCtxImpl::rescale(const HeCt& a, int out_level) {
   if (out_level > l - 1) fail(HE_ELEVEL, "rescale cannot raise the level");
   const int np = (int)a.polys(), nout = out_level + 1;
   DevBuf top(&pool, (size_t)np * N);
-  gather_limbs(top.p, a, l, 1);
-  launch_ntt(T, top.p, np, one(l), true, stream);
+  intt_from(top.p, a, l, 1, one(l));
   DevBuf t(&pool, (size_t)np * nout * N);
   HeCt c = ct_new(out_level, false, a.scale / (double)mods[l], a.B);
   const u64* ql_inv = qlinv.p + (size_t)l * nmods * 2;
@@ -894,9 +906,9 @@ HeCt HeCtxImpl::moddown(const HeCt& x, int out_level, bool consume, bool src_rea
 // limbs are brought to the coefficient domain in place (x is left with them
 // so) instead of in a gathered copy; src_ready: that was done already
 // (moddown_sources over a set of elements), and rec, when given, holds their
-// digit records; skip: the second component skip words further on
-bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, u64* out, bool consume, bool src_ready, const u64* rec,
-                           bool pack, size_t skip) {
+// digit records; dst may place the components apart, or add something on
+bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool consume, bool src_ready,
+                           const u64* rec, bool pack) {
   int nq = nq_of(out_level), nqp = nqp_of(x.level);
   const int np = (int)x.polys();
   DevBuf y(&pool, (size_t)np * nq * N);
@@ -910,31 +922,35 @@ bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, u64* out, bool consume,
     if (!src_ready) launch_ntt(T, x.d.p, np * alpha, pm, true, stream);
     DevBuf V;
     if (!rec) V = DevBuf(&pool, (size_t)np * (down.ns + 1) * N);
-    if (!launch_moddown_fused(T, x.d.p, nq, np, down, x.d.p, nqp, pinv.p, out, y.p, rec ? (u64*)rec : V.p, stream,
-                              x.nlimbs, nq_of(x.level), rec != nullptr, pack, skip))
+    if (!launch_moddown_fused(T, x.d.p, nq, np, down, x.d.p, nqp, pinv.p, dst, y.p, rec ? (u64*)rec : V.p, stream,
+                              x.nlimbs, nq_of(x.level), rec != nullptr, pack))
       fail(HE_EINVAL, "fused ModDown unavailable for this ring size");
     n_moddown += x.B;
     return pack;
   }
-  if (skip) {
-    // the unfused paths write the two components together
-    DevBuf both(&pool, (size_t)np * nq * N);
-    moddown_to(x, out_level, both.p, false);
+  if (!dst.plain()) {
+    // the unfused paths write one block
+    DevBuf all(&pool, (size_t)np * nq * N);
+    moddown_to(x, out_level, all.p);
     const size_t half = (size_t)x.B * nq;
-    copy_limbs(out, both.p, half);
-    copy_limbs(out + half * N + skip, both.p + half * N, half);
+    for (size_t k = 0; k < dst.tab.size(); k++)
+      for (size_t p = 0; p < 2; p++)
+        copy_limbs(dst.tab[k] + p * nq * N, all.p + ((k / dst.per * 2 + p) * dst.per + k % dst.per) * nq * N, nq);
+    if (!dst.tab.empty()) return false;
+    if (dst.add) launch_add(T, all.p, all.p, dst.add, np * nq, qmap(nq), stream);
+    copy_limbs(dst.out, all.p, half);
+    copy_limbs(dst.out + half * N + dst.skip, all.p + half * N, half);
     return false;
   }
   DevBuf pc(&pool, (size_t)np * alpha * N);
-  gather_limbs(pc.p, x, nq_of(x.level), alpha);
-  launch_ntt(T, pc.p, np * alpha, pm, true, stream);
+  intt_from(pc.p, x, nq_of(x.level), alpha, pm);
   if (fused_conv) {
     DevBuf V(&pool, (size_t)np * (down.ns + 1) * N);
-    if (!launch_moddown_fused(T, pc.p, nq, np, down, x.d.p, nqp, pinv.p, out, y.p, V.p, stream))
+    if (!launch_moddown_fused(T, pc.p, nq, np, down, x.d.p, nqp, pinv.p, dst, y.p, V.p, stream))
       fail(HE_EINVAL, "fused ModDown unavailable for this ring size");
   } else {
     launch_fbc_to_q(T, y.p, pc.p, nq, np, down, stream);
-    launch_ntt_fwd_sub(T, y.p, nq, np, qmap(nq), x.d.p, nqp, pinv.p, out, stream);
+    launch_ntt_fwd_sub(T, y.p, nq, np, qmap(nq), x.d.p, nqp, pinv.p, dst.out, stream);
   }
   n_moddown += x.B;
   return false;
@@ -1044,13 +1060,15 @@ DevBuf HeCtxImpl::moddown_sources(const std::vector<HeCt*>& xs, bool with_rescal
   return rec;
 }
 
-HeCt HeCtxImpl::keyswitch(const u64* d, int level, u64 g_key, int B) {
+HeCt HeCtxImpl::keyswitch(const u64* d, int level, u64 g_key, int B, const u64* add) {
   DevBuf dig = decompose(d, level, B);
   HeCt h = ct_new(level, true, 1.0, B);
   const DevBuf& k = key(g_key);
   launch_multsum(T, h.d.p, dig.p, k.p, nullptr, pmod.p, level, L, alpha, beta_at(level), 1, B, stream);
   n_multsum += B;
-  return moddown(h, -1, true);
+  HeCt c = ct_new(level, false, 1.0, B);
+  moddown_to(h, level, SubDst(c.d.p, 0, add), true);
+  return c;
 }
 
 HeCt HeCtxImpl::mult(const HeCt& a, const HeCt& b) {
@@ -1060,9 +1078,8 @@ HeCt HeCtxImpl::mult(const HeCt& a, const HeCt& b) {
   int nl = a.nlimbs, nt = a.B * nl;
   DevBuf t3(&pool, (size_t)3 * nt * N);
   launch_tensor(T, t3.p, a.d.p, b.d.p, nl, a.B, false, stream);
-  HeCt ks = keyswitch(t3.p + (size_t)2 * nt * N, a.level, 0, a.B);
-  HeCt c = ct_new(a.level, false, a.scale * b.scale, a.B);
-  launch_add(T, c.d.p, t3.p, ks.d.p, 2 * nt, qmap(nl), stream);
+  HeCt c = keyswitch(t3.p + (size_t)2 * nt * N, a.level, 0, a.B, t3.p);
+  c.scale = a.scale * b.scale;
   return c;
 }
 
@@ -1075,33 +1092,78 @@ HeCt HeCtxImpl::rotate(const HeCt& x, long step) {
   return moddown(h, -1, true);
 }
 
+// x + Rot(x, step): the sum formed where the rotation's ModDown ends
+HeCt HeCtxImpl::rotate_add(const HeCt& x, long step) {
+  if (x.qp || x.packed) fail(HE_EINVAL, "rotation of an unpacked ciphertext only");
+  const u64 g = galois(step);
+  if (g == 1) return add(x, x, false);
+  DevBuf dig = decompose(x.poly(1), x.level, x.B);
+  HeCt h = hoisted(x, dig.p, g), c = ct_new(x.level, false, x.scale, x.B);
+  moddown_to(h, x.level, SubDst(c.d.p, 0, x.d.p), true);
+  return c;
+}
+
 // Rotations of a batch x (one level and scale) by several steps, hoisted
 // (section 3.3.1): one Decompose of the whole batch, the key inner products
 // of every step in one multi-rotation launch, one ModDown per step.  out[r]
 // is x rotated by steps[r], with the residues rotate() gives.
 std::vector<HeCt> HeCtxImpl::rotate_many(const HeCt& x, const std::vector<long>& steps) {
   if (x.qp) fail(HE_EINVAL, "rotation of an R_QP element");
-  std::vector<HeCt> out(steps.size());
+  const int level = x.level, nq = nq_of(level), nqp = nqp_of(level), B = x.B;
+  const size_t ns = steps.size();
+  std::vector<HeCt> out(ns * B);
   std::vector<u64> gs;
   std::vector<size_t> where;
-  for (size_t r = 0; r < steps.size(); r++) {
+  std::vector<u64*> same;
+  for (size_t r = 0; r < ns; r++) {
     const u64 g = galois(steps[r]);
-    if (g == 1) {
-      out[r] = ct_copy(x);
-    } else {
+    if (g != 1) {
       key(g);  // a missing key fails before anything is launched
       gs.push_back(g);
       where.push_back(r);
     }
   }
+  for (HeCt& c : out) c = ct_new(level, false, x.scale);
+  for (size_t r = 0; r < ns; r++) {
+    if (galois(steps[r]) != 1) continue;
+    for (int b = 0; b < B; b++) same.push_back(out[b * ns + r].d.p);
+    launch_unstack(T, x.d.p, same.data(), B, nq, stream);
+    same.clear();
+  }
   if (gs.empty()) return out;
-  DevBuf dig = decompose(x.poly(1), x.level, x.B);
+  DevBuf dig = decompose(x.poly(1), level, B);
+  // every rotation of a launch reads the same digits; their ModDowns go
+  // HE_STAGE_BYTES at a time, straight into the results
+  const size_t elem = (size_t)2 * B * nqp * N;
   for (size_t r0 = 0; r0 < gs.size(); r0 += MR_MAX) {
-    const size_t nr = std::min(gs.size() - r0, (size_t)MR_MAX);
-    std::vector<HeCt> h = hoisted_multi(x, dig.p, std::vector<u64>(gs.begin() + r0, gs.begin() + r0 + nr));
-    for (size_t r = 0; r < nr; r++) {
-      out[where[r0 + r]] = moddown(h[r], -1, true);
-      h[r] = HeCt();
+    const int nr = (int)std::min(gs.size() - r0, (size_t)MR_MAX);
+    const int rd = (int)std::min<size_t>(stage_count((size_t)2 * B * (nqp + nq + alpha + 2) * N * 8, nr),
+                                         std::max(1, RD_MAX / B));
+    std::vector<DevBuf> part;
+    std::vector<u64*> outs;
+    std::vector<const u64*> ks;
+    for (int r = 0; r < nr; r++) {
+      if (r % rd == 0) part.emplace_back(&pool, (size_t)std::min(rd, nr - r) * elem);
+      outs.push_back(part.back().p + (size_t)(r % rd) * elem);
+      ks.push_back(key(gs[r0 + r]).p);
+    }
+    launch_multsum_rot(T, outs.data(), ks.data(), gs.data() + r0, nr, dig.p, x.poly(0), pmod.p, level, L, alpha,
+                       beta_at(level), B, stream, nullptr, false, &fork);
+    n_multsum += (long)B * nr;
+    for (int r = 0; r < nr; r += rd) {
+      const int cnt = std::min(rd, nr - r);
+      HeCt h;
+      h.N = N;
+      h.level = level;
+      h.qp = true;
+      h.nlimbs = nqp;
+      h.B = cnt * B;
+      h.d = DevBuf::part(part[r / rd].p, (size_t)cnt * elem);
+      std::vector<u64*> tab;
+      for (int q = 0; q < cnt; q++)
+        for (int b = 0; b < B; b++) tab.push_back(out[b * ns + where[r0 + r + q]].d.p);
+      moddown_to(h, level, SubDst(std::move(tab), B), true);
+      part[r / rd].release();
     }
   }
   return out;
@@ -1164,17 +1226,19 @@ HeCt HeCtxImpl::stack(const std::vector<const HeCt*>& xs) {
     if (x->level != x0.level || x->qp || x->B != 1 || x->scale != x0.scale)
       fail(HE_EINVAL, "batched members must share level and scale");
   HeCt c = ct_new(x0.level, false, x0.scale, (int)xs.size());
-  for (size_t b = 0; b < xs.size(); b++)
-    for (int p = 0; p < 2; p++) copy_limbs(c.member(p, (int)b), xs[b]->poly(p), x0.nlimbs, "copy_stack");
+  std::vector<u64*> ms;
+  for (auto* x : xs) ms.push_back(x->d.p);
+  launch_stack(T, c.d.p, ms.data(), c.B, c.nlimbs, stream);
   return c;
 }
 std::vector<HeCt> HeCtxImpl::unstack(const HeCt& x) {
   std::vector<HeCt> out;
+  std::vector<u64*> ms;
   for (int b = 0; b < x.B; b++) {
-    HeCt c = ct_new(x.level, x.qp, x.scale, 1);
-    for (int p = 0; p < 2; p++) copy_limbs(c.poly(p), x.member(p, b), x.nlimbs, "copy_unstack");
-    out.push_back(std::move(c));
+    out.push_back(ct_new(x.level, x.qp, x.scale, 1));
+    ms.push_back(out.back().d.p);
   }
+  launch_unstack(T, x.d.p, ms.data(), x.B, x.nlimbs, stream);
   return out;
 }
 
@@ -1696,7 +1760,7 @@ HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first
   sb.dig = DevBuf(&pool, (size_t)blocks * M * dstride);
   // members [at, at + cnt) of x = ModDown(h): the components stand apart
   auto put = [&](const HeCt& h, int at) {
-    moddown_to(h, level, sb.x.member(0, at), true, false, nullptr, false, (size_t)(blocks * M - h.B) * nq * N);
+    moddown_to(h, level, SubDst(sb.x.member(0, at), (size_t)(blocks * M - h.B) * nq * N), true);
   };
   for (int j = 0; j < blocks; j++) {
     u64* dj = sb.dig.p + (size_t)j * M * dstride;
@@ -1918,9 +1982,8 @@ void HeCtxImpl::accumulate_tensors(DevBuf& acc3, bool& acc_set, const std::vecto
 // ... and relinearised once
 HeCt HeCtxImpl::relin_sum(const DevBuf& acc3, int level, double scale, int B) {
   const int nl = level + 1, nt = B * nl;
-  HeCt ks = keyswitch(acc3.p + (size_t)2 * nt * N, level, 0, B);
-  HeCt c = ct_new(level, false, scale, B);
-  launch_add(T, c.d.p, acc3.p, ks.d.p, 2 * nt, qmap(nl), stream);
+  HeCt c = keyswitch(acc3.p + (size_t)2 * nt * N, level, 0, B, acc3.p);
+  c.scale = scale;
   return c;
 }
 
