@@ -35,14 +35,12 @@ struct DeviceTables {
 
 // transforms
 void launch_ntt(const DeviceTables& T, u64* data, int nlimbs, const LimbMap& map, bool inverse, hipStream_t s);
-// Inverse NTT of src into data (same layout) with limb k's result times
-// scales[2 m] (Shoup pairs by modulus m) in place of N^-1; false (nothing
-// launched) without the register-blocked NTT
+// Inverse NTT of src, whose limbs lie in the map's slots, into data (in place,
+// or one limb after the other) with limb k's result times scales[2 m] (Shoup
+// pairs by modulus m) in place of N^-1 (null: N^-1); false (nothing launched)
+// without the register-blocked NTT
 bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map,
                         const u64* scales, hipStream_t s);
-// Inverse NTT of src, whose limbs lie in the map's slots, into data, one limb
-// after the other; false (nothing launched) without the register-blocked NTT
-bool launch_intt_from(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map, hipStream_t s);
 // Where a fused ModDown writes its polynomials: out [npoly][nq][N], the second
 // half of them skip words further on; or, with tab, elements of per members
 // and two components, [element][2][per], to tab[element per + member] (at
@@ -158,15 +156,15 @@ void launch_modup(const DeviceTables& T, u64* digits, const u64* coef, const u64
 // Inverse NTT, in place, of the same limbs of many R_{Q_l P} elements (the
 // ModDown sources of a set of hoisted rotations): in element e (bases[e]),
 // limb j < per_elem lives at slot (j / per) * stride + off + j % per; map
-// gives the modulus of limb j by j % map.n (map.n = per).  One launch per 64
-// elements.
+// gives the modulus of limb j by j % map.n (map.n = per), scales the factor
+// in place of N^-1 (launch_intt_scaled).  One launch per 64 elements.
 // With rec_tab and rec: the sources are those of the ModDown table rec_tab
 // (per = its ns) and the last pass writes their digit records to rec
 // ([element][per_elem / per][per + 1][N]) instead of the limbs.
 void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int per_elem, int per, int stride,
-                      int off, const LimbMap& map, hipStream_t s, const FbcTable* rec_tab = nullptr,
-                      u64* rec = nullptr);
-// xp_coef: the source limbs in the coefficient domain, [npoly][ns][N]; or,
+                      int off, const LimbMap& map, const u64* scales, hipStream_t s,
+                      const FbcTable* rec_tab = nullptr, u64* rec = nullptr);
+// xp_coef: the source limbs in the coefficient domain times their hat inverses, [npoly][ns][N]; or,
 // with src_stride > 0, limb a of poly p at slot p * src_stride + src_off + a
 // (the sources transformed in place inside the R_{Q_l P} element)
 // whether a fused ModDown of npoly polynomials into nq target limbs with this

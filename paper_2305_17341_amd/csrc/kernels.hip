@@ -1291,8 +1291,9 @@ __device__ __forceinline__ u64* limb_base_addr(const LimbBases& lb, int k, u64 N
   return lb.base[e] + ((size_t)(j / lb.per) * lb.stride + lb.off + j % lb.per) * N;
 }
 template <int LOGN, int GA, int GB>
-__global__ void __launch_bounds__(TPB) k_intt_cols2_many(LimbBases lb, LimbMap map, const u64* __restrict__ tw,
-                                                         const u64* __restrict__ twsh, const double* __restrict__ twf,
+__global__ void __launch_bounds__(TPB) k_intt_cols2_many(LimbBases lb, LimbMap map, const u64* __restrict__ scales,
+                                                         const u64* __restrict__ tw, const u64* __restrict__ twsh,
+                                                         const double* __restrict__ twf,
                                                          const ModConst* __restrict__ mc) {
   constexpr int S1 = GA + GB, R = 1 << S1, C = TILE / R;
   __shared__ u64 sh[LDS_WORDS];
@@ -1304,10 +1305,10 @@ __global__ void __launch_bounds__(TPB) k_intt_cols2_many(LimbBases lb, LimbMap m
   const int c0 = blockIdx.x * C;
   const ModConst mk = mc[m];
   if (mk.bits <= F64_LAZY_BITS) {
-    F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
+    F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)scales[2 * m]};
     ntt_cols2_body<LOGN, GA, GB, true>(a, c0, reinterpret_cast<double*>(sh), ar, LoadPlain{a});
   } else {
-    ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
+    ShoupArith ar{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, scales[2 * m], scales[2 * m + 1]};
     ntt_cols2_body<LOGN, GA, GB, true>(a, c0, sh, ar, LoadPlain{a});
   }
 }
@@ -1415,11 +1416,15 @@ struct ModupSrc {
   const u64* ntt_in;  // [B][nq][N]
   int nq, nqp, alpha, beta, L;
   int ns[16], srcbits[16];
+  u8 bits[16][4];           // of each source
   const u64* hat_t[16];     // [ns][nmods]
   const u64* hat_t_sh[16];
+  const double* hat_f[16];  // [ns][nmods][3]: hat, 2^32 hat
 };
-// F64: every source below 4 q (signed exact products, one reduction);
-// otherwise Shoup products.  The source loop has a compile-time length NS
+// F64: every source below 4 q (signed exact products, one reduction), or
+// (SPLIT) any size, the larger ones cut at bit 32 with both halves below q:
+// the digit of q0 took Shoup products for every target, three times the
+// issue cycles of its four exact FP64 ones.  Otherwise Shoup products.  The source loop has a compile-time length NS
 // without branches: 3 for a full digit of three limbs, else 4 with sources
 // past ns repeating the last one against zero constants; so the loads of a
 // tile's values can all be in flight together.
@@ -1428,9 +1433,10 @@ struct ModupData {
   u64 N;
   int ns;
   u64 q, h[4], hs[4];
-  double qf, qinvf, hf[4];
+  double qf, qinvf, hf[4], h32[4];
+  u32 big;  // bit a: source a is cut
 };
-template <bool F64, int NS = 4>
+template <bool F64, int NS = 4, bool SPLIT = false>
 struct ModupLoad : ModupData {
   struct Raw {
     u64 x[NS];
@@ -1442,7 +1448,11 @@ struct ModupLoad : ModupData {
   __device__ __forceinline__ double sum_f64(const Raw& r) const {
     double acc = 0.0;
 #pragma unroll
-    for (int a = 0; a < NS; a++) acc += f64_mulmod_signed(u2d(r.x[a]), hf[a], qf, qinvf);
+    for (int a = 0; a < NS; a++) {
+      const bool cut = SPLIT && ((big >> a) & 1u);
+      acc += f64_mulmod_signed(u2d(cut ? r.x[a] & 0xffffffffull : r.x[a]), hf[a], qf, qinvf);
+      if (cut) acc += f64_mulmod_signed(u2d(r.x[a] >> 32), h32[a], qf, qinvf);
+    }
     return acc;
   }
   __device__ __forceinline__ u64 fin_u(const Raw& r) const {
@@ -1454,9 +1464,9 @@ struct ModupLoad : ModupData {
   }
   __device__ __forceinline__ double fin_d(const Raw& r) const { return f64_centre(sum_f64(r), qf, qinvf); }
 };
-template <int NS>
-__device__ __forceinline__ double fin(const F64LazyArith&, const ModupLoad<true, NS>& ld,
-                                      const typename ModupLoad<true, NS>::Raw& r) {
+template <int NS, bool SPLIT>
+__device__ __forceinline__ double fin(const F64LazyArith&, const ModupLoad<true, NS, SPLIT>& ld,
+                                      const typename ModupLoad<true, NS, SPLIT>::Raw& r) {
   return ld.fin_d(r);
 }
 template <class L>
@@ -1504,17 +1514,22 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_modup(u64* digits, ModupSrc S
   d.q = mk.q;
   d.qf = mk.qf;
   d.qinvf = mk.qinvf;
+  d.big = 0;
   for (int x = 0; x < 4; x++) {
     const bool in = x < d.ns;
     d.h[x] = in ? S.hat_t[j][(size_t)x * nmods + m] : 0;
     d.hs[x] = in ? S.hat_t_sh[j][(size_t)x * nmods + m] : 0;
     d.hf[x] = u2d(d.h[x]);
+    d.h32[x] = in ? S.hat_f[j][((size_t)x * nmods + m) * 3 + 1] : 0.0;
+    if (in && S.bits[j][x] > mk.bits + 1) d.big |= 1u << x;
   }
   if (mk.bits <= F64_LAZY_BITS) {
     F64LazyArith ar{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
     double* shd = reinterpret_cast<double*>(sh);
-    if (S.srcbits[j] > (int)mk.bits + 1)
+    if (S.srcbits[j] > (int)mk.bits + 1 && mk.bits <= 32)
       ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<false>>(d));
+    else if (S.srcbits[j] > (int)mk.bits + 1)
+      ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<true, 4, true>>(d));
     else if (d.ns == 3)  // a full digit of three limbs: no padding source
       ntt_cols_pass<LOGN, GA, GB, false, SV>(a, c0, shd, ar, loader_of<ModupLoad<true, 3>>(d));
     else
@@ -1672,7 +1687,9 @@ __global__ void __launch_bounds__(TPB) k_intt_cols2_scaled(u64* data, LimbMap ma
 bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map,
                         const u64* scales, hipStream_t s) {
   if (nlimbs <= 0) return true;
-  if (map.slot_per > 0) return false;
+  const bool in_place = data == src;
+  LimbMap out = map;  // where the first pass leaves the limbs
+  if (!in_place) out.slot_per = 0;
   return ntt_dispatch(T.logN, [&](auto sp) {
     using S = decltype(sp);
     constexpr int LOGN = S::LOGN, GA = S::GA, GB = S::GB, GC = S::GC, GD = S::GD;
@@ -1683,35 +1700,20 @@ bool launch_intt_scaled(const DeviceTables& T, u64* data, const u64* src, int nl
       const dim3 grid((1 << LOGN) / (TPB * SV), nlimbs);
       {
         ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD)));
-        hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD, SV>), grid, dim3(TPB), 0, s, data, src, map, T.ipsi,
-                           T.ipsi_sh, T.ipsi_f, T.mc, il);
+        if (in_place)
+          hipLaunchKernelGGL((k_ntt_rows2<LOGN, GC, GD, true, false, SV>), grid, dim3(TPB), 0, s, data, map, T.ipsi,
+                             T.ipsi_sh, T.ipsi_f, T.mc, il);
+        else
+          hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD, SV>), grid, dim3(TPB), 0, s, data, src, map, T.ipsi,
+                             T.ipsi_sh, T.ipsi_f, T.mc, il);
       }
       ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
-      hipLaunchKernelGGL((k_intt_cols2_scaled<LOGN, GA, GB, SV>), grid, dim3(TPB), 0, s, data, map, scales, T.ipsi,
-                         T.ipsi_sh, T.ipsi_f, T.mc);
-    });
-  });
-}
-
-bool launch_intt_from(const DeviceTables& T, u64* data, const u64* src, int nlimbs, const LimbMap& map, hipStream_t s) {
-  LimbMap flat = map;
-  flat.slot_per = 0;
-  return ntt_dispatch(T.logN, [&](auto sp) {
-    using S = decltype(sp);
-    constexpr int LOGN = S::LOGN, GA = S::GA, GB = S::GB, GC = S::GC, GD = S::GD;
-    const int il = interleave_of(nlimbs, modulus_period(map), g_knobs.ntt_interleave);
-    const double pass_bytes = 16.0 * nlimbs * T.N;
-    by_values(T, nlimbs, [&](auto sv) {
-      constexpr int SV = decltype(sv)::value;
-      const dim3 grid((1 << LOGN) / (TPB * SV), nlimbs);
-      {
-        ProfScope ps("ntt_inv_rows", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GC + GD)));
-        hipLaunchKernelGGL((k_intt_rows2_src<LOGN, GC, GD, SV>), grid, dim3(TPB), 0, s, data, src, map, T.ipsi,
-                           T.ipsi_sh, T.ipsi_f, T.mc, il);
-      }
-      ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
-      hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, true, SV>), grid, dim3(TPB), 0, s, data, flat, T.ipsi, T.ipsi_sh,
-                         T.ipsi_f, T.mc);
+      if (scales)
+        hipLaunchKernelGGL((k_intt_cols2_scaled<LOGN, GA, GB, SV>), grid, dim3(TPB), 0, s, data, out, scales, T.ipsi,
+                           T.ipsi_sh, T.ipsi_f, T.mc);
+      else
+        hipLaunchKernelGGL((k_ntt_cols2<LOGN, GA, GB, true, SV>), grid, dim3(TPB), 0, s, data, out, T.ipsi, T.ipsi_sh,
+                           T.ipsi_f, T.mc);
     });
   });
 }
@@ -1807,7 +1809,9 @@ bool launch_modup_ntt(const DeviceTables& T, u64* digits, const u64* y, const u6
   for (int j = 0; j < beta; j++) {
     S.ns[j] = tabs[j].ns;
     S.srcbits[j] = 0;
+    for (int a = 0; a < 4; a++) S.bits[j][a] = a < tabs[j].ns ? (u8)T.bits[tabs[j].src[a]] : 0;
     for (int a = 0; a < tabs[j].ns; a++) S.srcbits[j] = std::max(S.srcbits[j], (int)T.bits[tabs[j].src[a]]);
+    S.hat_f[j] = tabs[j].hat_f;
     S.hat_t[j] = tabs[j].hat_t;
     S.hat_t_sh[j] = tabs[j].hat_t_sh;
   }
@@ -2660,18 +2664,20 @@ __device__ __forceinline__ int w4_cmp(const u64 a[4], const u64 b[4]) {
 // of sum_a y_a / q_a (products with the rounded reciprocals: error below
 // ns 2^-52), replaced by an exact multiword comparison when the estimate lies
 // within 2^-40 of a rounding boundary.
+template <int NS = 0>
 __device__ __forceinline__ u64 round_quotient(const u64* y, const FbcArgs& A) {
+  const int n = NS ? NS : A.ns;
   double f = 0.0;
-  for (int a = 0; a < A.ns; a++) f += (double)y[a] * A.qrecip[a];
+  for (int a = 0; a < n; a++) f += (double)y[a] * A.qrecip[a];
   double t = f + 0.5;
   double fl = floor(t);
   double fr = t - fl;
   if (fr > 9.094947017729282e-13 && fr < 1.0 - 9.094947017729282e-13) return (u64)fl;
   // exact: v = #{ w >= 1 : 2 S > (2w - 1) D }
   u64 S2[4] = {0, 0, 0, 0};
-  for (int a = 0; a < A.ns; a++) w4_muladd(S2, A.Hw[a], 2 * y[a]);
+  for (int a = 0; a < n; a++) w4_muladd(S2, A.Hw[a], 2 * y[a]);
   u64 v = 0;
-  for (u64 w = 1; w <= (u64)A.ns; w++) {
+  for (u64 w = 1; w <= (u64)n; w++) {
     u64 T[4] = {0, 0, 0, 0};
     w4_muladd(T, A.Dw, 2 * w - 1);
     if (w4_cmp(S2, T) > 0) v = w;
@@ -2738,14 +2744,16 @@ void launch_fbc_to_q(const DeviceTables& T, u64* y, const u64* xp_coef, int nq, 
   hipLaunchKernelGGL(k_fbc_to_q, grid, dim3(TPB), 0, s, y, xp_coef, nq, A, T.logN, T.nmods, T.mc);
 }
 
-// ModDown with the basis conversion fused into the forward column pass.
-// k_fbc_prep stores, per coefficient, v_a = x_a hatinv_a mod p_a and the
-// rounded quotient r of the exact centred lift ([npoly][ns + 1][N]); the
+// ModDown with the basis conversion fused into the forward column pass.  Its
+// sources are v_a = x_a hatinv_a mod p_a: the inverse transform that brings
+// them to the coefficient domain ends with N^-1 hatinv_a in place of N^-1.
+// k_fbc_prep stores, per coefficient, the v_a and the rounded quotient r of
+// the exact centred lift ([npoly][ns + 1][N]); the
 // column pass of target limb t then loads
 //   sum_a v_a hat_(a,t) - r D mod q_t
 // (the value k_fbc_to_q writes) while filling its tile, and the block pass
 // ends with (x - y) P^-1: no converted limb goes to memory.
-__global__ void k_fbc_prep(u64* V, const u64* xp, FbcArgs A, int logN, const ModConst* __restrict__ mc) {
+__global__ void k_fbc_prep(u64* V, const u64* xp, FbcArgs A, int logN) {
   const u64 N = 1ull << logN;
   u32 i = blockIdx.x * TPB + threadIdx.x;
   if (i >= N) return;
@@ -2753,7 +2761,7 @@ __global__ void k_fbc_prep(u64* V, const u64* xp, FbcArgs A, int logN, const Mod
   const u64* x = xp + ((size_t)poly * A.src_stride + A.src_off) * N;
   u64* o = V + (size_t)poly * (A.ns + 1) * N;
   u64 v[4];
-  for (int a = 0; a < A.ns; a++) v[a] = shoup_mul(x[(size_t)a * N + i], A.hatinv[a], A.hatinv_sh[a], mc[A.src[a]].q);
+  for (int a = 0; a < A.ns; a++) v[a] = x[(size_t)a * N + i];
   const u64 r = round_quotient(v, A);
   for (int a = 0; a < A.ns; a++) o[(size_t)a * N + i] = v[a];
   o[(size_t)A.ns * N + i] = r;
@@ -2809,31 +2817,32 @@ __device__ __forceinline__ L fbc_loader_of(const FbcData& d) {
   static_cast<FbcData&>(l) = d;
   return l;
 }
-// the same from the source limbs x_a: v_a = x_a hatinv_a and the rounded
-// quotient formed by every target (small grids: one launch less)
-template <bool F64>
+// the same from the sources themselves, every target forming the rounded
+// quotient as it loads (small grids: one launch less)
+template <bool F64, int NS>
 struct FbcSrcLoad {
-  typedef typename FbcLoad<F64>::Raw Raw;
-  FbcLoad<F64> ld;
+  struct Raw {
+    u64 x[NS];
+  };
+  FbcLoad<F64, NS> ld;
   const FbcArgs& A;
-  const u64* qs;
   __device__ __forceinline__ void raw(size_t idx, Raw& w) const {
 #pragma unroll
-    for (int a = 0; a < 4; a++) w.x[a] = ld.v0[(size_t)(a < ld.ns ? a : ld.ns - 1) * ld.N + idx];
-    w.r = 0;
+    for (int a = 0; a < NS; a++) w.x[a] = ld.v0[(size_t)a * ld.N + idx];
   }
-  __device__ __forceinline__ Raw quotient(const Raw& x) const {
-    Raw w;
+  __device__ __forceinline__ typename FbcLoad<F64, NS>::Raw quotient(const Raw& x) const {
+    typename FbcLoad<F64, NS>::Raw w;
 #pragma unroll
-    for (int a = 0; a < 4; a++) w.x[a] = a < ld.ns ? shoup_mul(x.x[a], A.hatinv[a], A.hatinv_sh[a], qs[a]) : 0;
-    w.r = round_quotient(w.x, A);
+    for (int a = 0; a < NS; a++) w.x[a] = x.x[a];
+    w.r = round_quotient<NS>(x.x, A);
     return w;
   }
   __device__ __forceinline__ u64 fin_u(const Raw& w) const { return ld.fin_u(quotient(w)); }
   __device__ __forceinline__ double fin_d(const Raw& w) const { return ld.fin_d(quotient(w)); }
 };
-__device__ __forceinline__ double fin(const F64LazyArith&, const FbcSrcLoad<true>& ld,
-                                      const typename FbcSrcLoad<true>::Raw& w) {
+template <int NS>
+__device__ __forceinline__ double fin(const F64LazyArith&, const FbcSrcLoad<true, NS>& ld,
+                                      const typename FbcSrcLoad<true, NS>::Raw& w) {
   return ld.fin_d(w);
 }
 template <int LOGN, int GA, int GB, int SV = 16>
@@ -2867,21 +2876,29 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols2_fbc(u64* y, const u64* __rest
     d.e1[x] = in ? A.hat_f[((size_t)x * nmods + t) * 3 + 1] : 0.0;
   }
   if constexpr (SV == 4) {
-    // V is the source limbs themselves: every target's loads form v_a and r
+    // V is the sources themselves
     d.v0 = V + ((size_t)p * A.src_stride + A.src_off) * N;
-    u64 qs[4];
-    for (int x = 0; x < 4; x++) qs[x] = mc[A.src[x < A.ns ? x : 0]].q;
-    if (mk.bits <= F64_LAZY_BITS) {
-      F64LazyArith ar{twf + (size_t)t * N, mk.qf, mk.qinvf, (double)mk.ninv};
-      double* shd = reinterpret_cast<double*>(sh);
-      if (mk.bits <= 32)
-        ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar, FbcSrcLoad<false>{fbc_loader_of<FbcLoad<false>>(d), A, qs});
-      else
-        ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar, FbcSrcLoad<true>{fbc_loader_of<FbcLoad<true>>(d), A, qs});
-    } else {
-      ShoupArith ar{tw + (size_t)t * N, twsh + (size_t)t * N, mk.q, mk.ninv, mk.ninv_sh};
-      ntt_cols4_body<LOGN, GA + GB, false>(a, c0, sh, ar, FbcSrcLoad<false>{fbc_loader_of<FbcLoad<false>>(d), A, qs});
-    }
+    auto go = [&](auto ns) {
+      constexpr int NS = decltype(ns)::value;
+      if (mk.bits <= F64_LAZY_BITS) {
+        F64LazyArith ar{twf + (size_t)t * N, mk.qf, mk.qinvf, (double)mk.ninv};
+        double* shd = reinterpret_cast<double*>(sh);
+        if (mk.bits <= 32)
+          ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar,
+                                               FbcSrcLoad<false, NS>{fbc_loader_of<FbcLoad<false, NS>>(d), A});
+        else
+          ntt_cols4_body<LOGN, GA + GB, false>(a, c0, shd, ar,
+                                               FbcSrcLoad<true, NS>{fbc_loader_of<FbcLoad<true, NS>>(d), A});
+      } else {
+        ShoupArith ar{tw + (size_t)t * N, twsh + (size_t)t * N, mk.q, mk.ninv, mk.ninv_sh};
+        ntt_cols4_body<LOGN, GA + GB, false>(a, c0, sh, ar,
+                                             FbcSrcLoad<false, NS>{fbc_loader_of<FbcLoad<false, NS>>(d), A});
+      }
+    };
+    if (A.ns == 1) go(std::integral_constant<int, 1>{});
+    else if (A.ns == 2) go(std::integral_constant<int, 2>{});
+    else if (A.ns == 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
     return;
   }
   if (mk.bits <= F64_LAZY_BITS) {
@@ -2929,7 +2946,7 @@ struct FbcRec {
   static_assert(KU == NS + 1, "a record takes the words of the sources and the quotient");
 };
 template <int NS>
-__global__ void k_fbc_prep_digits(u64* V, const u64* xp, FbcArgs A, int logN, const ModConst* __restrict__ mc) {
+__global__ void k_fbc_prep_digits(u64* V, const u64* xp, FbcArgs A, int logN) {
   constexpr int KU = FbcRec<NS>::KU;
   const u64 N = 1ull << logN;
   u32 i = blockIdx.x * TPB + threadIdx.x;
@@ -2939,8 +2956,8 @@ __global__ void k_fbc_prep_digits(u64* V, const u64* xp, FbcArgs A, int logN, co
   u64* o = V + (size_t)poly * KU * N;
   u64 v[4];
 #pragma unroll
-  for (int a = 0; a < NS; a++) v[a] = shoup_mul(x[(size_t)a * N + i], A.hatinv[a], A.hatinv_sh[a], mc[A.src[a]].q);
-  const u64 r = round_quotient(v, A);
+  for (int a = 0; a < NS; a++) v[a] = x[(size_t)a * N + i];
+  const u64 r = round_quotient<NS>(v, A);
   u64 w[KU];
 #pragma unroll
   for (int k = 0; k < KU; k++) w[k] = 0;
@@ -3024,7 +3041,8 @@ __device__ __forceinline__ void intt_cols_last_lds(typename A::V* sh, const A& a
 }
 template <int LOGN, int GA, int GB, int NS>
 __global__ void __launch_bounds__(NS * TPB)
-    k_intt_cols2_rec(LimbBases lb, LimbMap map, FbcArgs A, u64* rec, const u64* __restrict__ tw,
+    k_intt_cols2_rec(LimbBases lb, LimbMap map, FbcArgs A, const u64* __restrict__ scales, u64* rec,
+                     const u64* __restrict__ tw,
                      const u64* __restrict__ twsh, const double* __restrict__ twf, const ModConst* __restrict__ mc) {
   constexpr int S1 = GA + GB, R = 1 << S1, T1 = (1 << LOGN) / R, C = TILE / R, KU = FbcRec<NS>::KU;
   __shared__ u64 sh[NS][LDS_WORDS];
@@ -3036,8 +3054,8 @@ __global__ void __launch_bounds__(NS * TPB)
   const ModConst mk = mc[map.idx[src]];
   const int m = map.idx[src];
   const bool f64 = mk.bits <= F64_LAZY_BITS;
-  const F64LazyArith af{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)mk.ninv};
-  const ShoupArith as{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, mk.ninv, mk.ninv_sh};
+  const F64LazyArith af{twf + (size_t)m * N, mk.qf, mk.qinvf, (double)scales[2 * m]};
+  const ShoupArith as{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, scales[2 * m], scales[2 * m + 1]};
   if (f64) intt_cols_first<LOGN, GA, GB>(a, c0, reinterpret_cast<double*>(sh[src]), af, tid);
   else intt_cols_first<LOGN, GA, GB>(a, c0, sh[src], as, tid);
   __syncthreads();
@@ -3049,9 +3067,8 @@ __global__ void __launch_bounds__(NS * TPB)
     const int row = e / C, col = e % C;
     u64 v[4];
 #pragma unroll
-    for (int x = 0; x < NS; x++)
-      v[x] = shoup_mul(sh[x][lds_rc(row, col, C)], A.hatinv[x], A.hatinv_sh[x], mc[A.src[x]].q);
-    const u64 r = round_quotient(v, A);
+    for (int x = 0; x < NS; x++) v[x] = sh[x][lds_rc(row, col, C)];
+    const u64 r = round_quotient<NS>(v, A);
     u64 w[KU];
 #pragma unroll
     for (int k = 0; k < KU; k++) w[k] = 0;
@@ -3071,7 +3088,7 @@ __global__ void __launch_bounds__(NS * TPB)
 
 template <int LOGN, int GA, int GB, int GC, int GD>
 static void intt2_many(const DeviceTables& T, const LimbBases& lb, int nelem, const LimbMap& map, hipStream_t s,
-                       const FbcArgs* fa, u64* rec) {
+                       const FbcArgs* fa, u64* rec, const u64* scales) {
   constexpr int R = 1 << (GA + GB), C = TILE / R, T1 = 1 << (GC + GD), K = TILE / T1;
   const int nlimbs = nelem * lb.per_elem;
   dim3 gc((1 << LOGN) / R / C, nlimbs), gr(((1 << LOGN) / T1) / K, nlimbs);
@@ -3085,8 +3102,8 @@ static void intt2_many(const DeviceTables& T, const LimbBases& lb, int nelem, co
   }
   if (!rec) {
     ProfScope ps("ntt_inv_cols", s, pass_bytes, mm_map(T, map, nlimbs, 0.5 * T.N * (GA + GB)));
-    hipLaunchKernelGGL((k_intt_cols2_many<LOGN, GA, GB>), gc, dim3(TPB), 0, s, lb, map, T.ipsi, T.ipsi_sh, T.ipsi_f,
-                       T.mc);
+    hipLaunchKernelGGL((k_intt_cols2_many<LOGN, GA, GB>), gc, dim3(TPB), 0, s, lb, map, scales, T.ipsi, T.ipsi_sh,
+                       T.ipsi_f, T.mc);
     return;
   }
   // the last pass ends in the digit records: the sources are read once and
@@ -3097,16 +3114,17 @@ static void intt2_many(const DeviceTables& T, const LimbBases& lb, int nelem, co
   ProfScope ps("ntt_inv_cols", s, 8.0 * T.N * (nlimbs + (double)npoly * (fa->ns + 1)), mm);
   dim3 g((1 << LOGN) / R / C, npoly);
   switch (lb.per) {
-    case 1: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 1>), g, dim3(1 * TPB), 0, s, lb, map, *fa, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
-    case 2: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 2>), g, dim3(2 * TPB), 0, s, lb, map, *fa, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
-    case 3: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 3>), g, dim3(3 * TPB), 0, s, lb, map, *fa, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
-    default: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 4>), g, dim3(4 * TPB), 0, s, lb, map, *fa, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
+    case 1: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 1>), g, dim3(1 * TPB), 0, s, lb, map, *fa, scales, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
+    case 2: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 2>), g, dim3(2 * TPB), 0, s, lb, map, *fa, scales, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
+    case 3: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 3>), g, dim3(3 * TPB), 0, s, lb, map, *fa, scales, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
+    default: hipLaunchKernelGGL((k_intt_cols2_rec<LOGN, GA, GB, 4>), g, dim3(4 * TPB), 0, s, lb, map, *fa, scales, rec, T.ipsi, T.ipsi_sh, T.ipsi_f, T.mc); break;
   }
 }
 
 static FbcArgs fbc_args(const FbcTable& tab, int src_stride, int src_off);
 void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int per_elem, int per, int stride,
-                      int off, const LimbMap& map, hipStream_t s, const FbcTable* rec_tab, u64* rec) {
+                      int off, const LimbMap& map, const u64* scales, hipStream_t s, const FbcTable* rec_tab,
+                      u64* rec) {
   if (map.n != per || per_elem % per != 0) throw std::runtime_error("launch_intt_many: bad limb pattern");
   if (rec && (!rec_tab || rec_tab->ns != per || per > 4))
     throw std::runtime_error("launch_intt_many: records need the ModDown table of the sources");
@@ -3123,7 +3141,7 @@ void launch_intt_many(const DeviceTables& T, const std::vector<u64*>& bases, int
     u64* rc = rec ? rec + (size_t)e0 * (per_elem / per) * (per + 1) * T.N : nullptr;
     if (!ntt_dispatch(T.logN, [&](auto sp) {
           using S = decltype(sp);
-          intt2_many<NTT_SPLIT_ARGS>(T, lb, ne, map, s, rec ? &fa : nullptr, rc);
+          intt2_many<NTT_SPLIT_ARGS>(T, lb, ne, map, s, rec ? &fa : nullptr, rc, scales);
         }))
       throw std::runtime_error("launch_intt_many needs the register-blocked NTT (log N 12..16)");
   }
@@ -3358,11 +3376,11 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
     for (int a = 0; a < tab.ns; a++) mm.add(T.bits[tab.src[a]], (double)T.N * npoly);
     ProfScope ps("fbc_prep", s, 8.0 * T.N * npoly * (2.0 * tab.ns + 1), mm);
     dim3 gp(cdiv(T.N, TPB), npoly);
-    if (!cdig) hipLaunchKernelGGL(k_fbc_prep, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN, T.mc);
-    else if (tab.ns == 1) hipLaunchKernelGGL(k_fbc_prep_digits<1>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN, T.mc);
-    else if (tab.ns == 2) hipLaunchKernelGGL(k_fbc_prep_digits<2>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN, T.mc);
-    else if (tab.ns == 3) hipLaunchKernelGGL(k_fbc_prep_digits<3>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN, T.mc);
-    else hipLaunchKernelGGL(k_fbc_prep_digits<4>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN, T.mc);
+    if (!cdig) hipLaunchKernelGGL(k_fbc_prep, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN);
+    else if (tab.ns == 1) hipLaunchKernelGGL(k_fbc_prep_digits<1>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN);
+    else if (tab.ns == 2) hipLaunchKernelGGL(k_fbc_prep_digits<2>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN);
+    else if (tab.ns == 3) hipLaunchKernelGGL(k_fbc_prep_digits<3>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN);
+    else hipLaunchKernelGGL(k_fbc_prep_digits<4>, gp, dim3(TPB), 0, s, V, xp_coef, A, T.logN);
   }
   LimbMap map;
   map.n = nq;

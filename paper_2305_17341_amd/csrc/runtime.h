@@ -127,6 +127,9 @@ struct HeCtxImpl {
   FbcTable down;                          // P -> Q
   DevBuf pmod, pinv, qlinv;
   DevBuf pqlinv;  // [level][nmods][2]: (P q_l)^-1 mod q_k with Shoup companions
+  // N^-1 hatinv of ModDown's sources in their modulus (Shoup pairs by
+  // modulus): of P, and of q_l and P by level
+  DevBuf down_scale, down_rs_scale;
   DevBuf up_scale;  // [level][nmods][2]: N^-1 hatinv_t mod q_t (Decompose's digit sources)
   DevBuf s_ntt, pk;
   bool have_sk = false;
@@ -197,7 +200,7 @@ struct HeCtxImpl {
                const u64* rec = nullptr, bool pack = false);
   bool moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool consume = false, bool src_ready = false,
                   const u64* rec = nullptr, bool pack = false);
-  void intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map);
+  void intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map, const u64* scales = nullptr);
   // ModDown and Rescale as one rounding by P q_l (a variant)
   HeCt moddown_rescale(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
                        const u64* rec = nullptr, bool pack = false);

@@ -545,6 +545,22 @@ void HeCtxImpl::init(const he_params* p, const he_device* dev, u64 seed_) {
     up_scale = DevBuf(&pool, us.size());
     hip_check(hipMemcpy(up_scale.p, us.data(), us.size() * 8, hipMemcpyHostToDevice), "up_scale");
   }
+  auto source_scale = [&](const FbcTable& t, u64* to) {
+    for (int a = 0; a < t.ns; a++) {
+      const u64 q = mods[t.src[a]], v = hmul(hinv(N % q, q), t.hatinv[a], q);
+      to[2 * t.src[a]] = v;
+      to[2 * t.src[a] + 1] = shoup_pre(v, q);
+    }
+  };
+  {
+    std::vector<u64> ds((size_t)2 * nmods, 0), rs((size_t)(L + 1) * nmods * 2, 0);
+    source_scale(down, ds.data());
+    for (size_t l = 1; l < down_rs.size(); l++) source_scale(down_rs[l], &rs[l * nmods * 2]);
+    down_scale = DevBuf(&pool, ds.size());
+    hip_check(hipMemcpy(down_scale.p, ds.data(), ds.size() * 8, hipMemcpyHostToDevice), "down_scale");
+    down_rs_scale = DevBuf(&pool, rs.size());
+    hip_check(hipMemcpy(down_rs_scale.p, rs.data(), rs.size() * 8, hipMemcpyHostToDevice), "down_rs_scale");
+  }
   hip_check(hipDeviceSynchronize(), "init");
 }
 
@@ -762,14 +778,15 @@ HeCt HeCtxImpl::drop(const HeCt& a, int level) {
 }
 
 // limbs first .. first + count - 1 of every poly of x in the coefficient
-// domain, [polys][count][N] (moduli by map, of period count)
-void HeCtxImpl::intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map) {
+// domain, [polys][count][N] (moduli by map, of period count), times scales in
+// place of N^-1 where the conversions are fused
+void HeCtxImpl::intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map, const u64* scales) {
   LimbMap m = map;
   m.slot_per = (short)count;
   m.slot_stride = (short)x.nlimbs;
   m.slot_off = (short)first;
   const int n = (int)x.polys() * count;
-  if (launch_intt_from(T, dst, x.d.p, n, m, stream)) return;
+  if (launch_intt_scaled(T, dst, x.d.p, n, m, scales, stream)) return;
   gather_limbs(dst, x, first, count);
   launch_ntt(T, dst, n, map, true, stream);
 }
@@ -919,7 +936,7 @@ bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool
     pm.slot_per = (short)alpha;
     pm.slot_stride = (short)x.nlimbs;
     pm.slot_off = (short)nq_of(x.level);
-    if (!src_ready) launch_ntt(T, x.d.p, np * alpha, pm, true, stream);
+    if (!src_ready) launch_intt_scaled(T, x.d.p, x.d.p, np * alpha, pm, down_scale.p, stream);
     DevBuf V;
     if (!rec) V = DevBuf(&pool, (size_t)np * (down.ns + 1) * N);
     if (!launch_moddown_fused(T, x.d.p, nq, np, down, x.d.p, nqp, pinv.p, dst, y.p, rec ? (u64*)rec : V.p, stream,
@@ -943,7 +960,7 @@ bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool
     return false;
   }
   DevBuf pc(&pool, (size_t)np * alpha * N);
-  intt_from(pc.p, x, nq_of(x.level), alpha, pm);
+  intt_from(pc.p, x, nq_of(x.level), alpha, pm, down_scale.p);
   if (fused_conv) {
     DevBuf V(&pool, (size_t)np * (down.ns + 1) * N);
     if (!launch_moddown_fused(T, pc.p, nq, np, down, x.d.p, nqp, pinv.p, dst, y.p, V.p, stream))
@@ -982,7 +999,8 @@ HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool
     sm.slot_per = (short)ns;
     sm.slot_stride = (short)x.nlimbs;
     sm.slot_off = (short)l;
-    if (!src_ready) launch_ntt(T, x.d.p, np * ns, sm, true, stream);
+    if (!src_ready)
+      launch_intt_scaled(T, x.d.p, x.d.p, np * ns, sm, down_rs_scale.p + (size_t)l * nmods * 2, stream);
     DevBuf y(&pool, (size_t)np * nout * N);
     HeCt c = ct_new(out_level, false, x.scale / (double)mods[l], x.B);
     DevBuf V;
@@ -994,15 +1012,10 @@ HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool
     n_moddown += x.B;
     return c;
   }
-  // sources [np][q_l, p_1..p_alpha] in the coefficient domain
+  // sources [np][q_l, p_1..p_alpha] in the coefficient domain: they are the
+  // consecutive limbs l .. l + alpha of each poly
   DevBuf pc(&pool, (size_t)np * ns * N);
-  hip_check(copy2d_async("copy_gather", pc.p, (size_t)ns * N * 8, x.d.p + (size_t)l * N, (size_t)x.nlimbs * N * 8,
-                         (size_t)N * 8, np, stream),
-            "gather");
-  hip_check(copy2d_async("copy_gather", pc.p + N, (size_t)ns * N * 8, x.d.p + (size_t)nqx * N,
-                         (size_t)x.nlimbs * N * 8, (size_t)alpha * N * 8, np, stream),
-            "gather");
-  launch_ntt(T, pc.p, np * ns, sm, true, stream);
+  intt_from(pc.p, x, l, ns, sm, down_rs_scale.p + (size_t)l * nmods * 2);
   DevBuf y(&pool, (size_t)np * nout * N);
   HeCt c = ct_new(out_level, false, x.scale / (double)mods[l], x.B);
   if (fused_conv) {
@@ -1056,7 +1069,9 @@ DevBuf HeCtxImpl::moddown_sources(const std::vector<HeCt*>& xs, bool with_rescal
     *rec_stride = (size_t)np * (per + 1) * N;
     rec = DevBuf(&pool, xs.size() * *rec_stride);
   }
-  launch_intt_many(T, bases, np * per, per, x0.nlimbs, off, m, stream, rec.p ? tab : nullptr, rec.p);
+  launch_intt_many(T, bases, np * per, per, x0.nlimbs, off, m,
+                   with_rescale ? down_rs_scale.p + (size_t)l * nmods * 2 : down_scale.p, stream,
+                   rec.p ? tab : nullptr, rec.p);
   return rec;
 }
 
