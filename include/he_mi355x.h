@@ -136,13 +136,11 @@ typedef struct {
 #define HE_MM_FOLDED 32u
 /* he_matmul_batch only: products of any sizes and levels run together.
  * Products of equal d, level and scales are stacked (up to 8, wherever they
- * stand in the list); the stacks run concurrently on the context's stream,
- * taking turns, and their key inner products (the hoisted rotations of every
- * transform and shift, the relinearisations) are merged: each merged launch
- * (one per member count) serves one key-switch step of every product at
- * once, items of different levels and rotation sets side by side.  Results
- * are residue-for-residue those of each product computed alone.  Not with
- * HE_MM_GRAPH. */
+ * stand in the list): each of their launches serves the whole stack.  The
+ * stacks run side by side on streams of the context's own, forked from its
+ * stream and joined to it, so the call is ordered on the context's stream
+ * like any other.  Results are residue-for-residue those of each product
+ * computed alone.  Not with HE_MM_GRAPH. */
 #define HE_MM_MERGED 64u
 
 /* Host only (no device needed): the moduli a context with these parameters

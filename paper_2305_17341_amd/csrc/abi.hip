@@ -498,8 +498,7 @@ he_status he_matmul_batch(he_ctx* ctx, const he_ct* const* a, const he_ct* const
     try {
       if (opts && (opts->flags & HE_MM_MERGED)) {
         // products of equal d, level and scales stacked (up to 8, wherever
-        // they stand in the list); the stacks run together with their key
-        // inner products merged into shared launches
+        // they stand in the list); the stacks run side by side
         std::vector<std::vector<size_t>> stacks;
         for (size_t i = 0; i < count; i++) {
           bool placed = false;
@@ -515,9 +514,9 @@ he_status he_matmul_batch(he_ctx* ctx, const he_ct* const* a, const he_ct* const
           }
           if (!placed) stacks.push_back({i});
         }
-        std::vector<std::function<HeCt()>> jobs;
+        std::vector<HeCtxImpl::Job> jobs;
         for (const auto& st : stacks) {
-          jobs.push_back([&, st]() {
+          jobs.push_back({(double)d[st[0]] * (4.0 + st.size()), [&, st]() {
             std::vector<const HeCt*> xa, xb;
             for (size_t k : st) {
               xa.push_back(&a[k]->ct);
@@ -527,9 +526,9 @@ he_status he_matmul_batch(he_ctx* ctx, const he_ct* const* a, const he_ct* const
             HeCt sa = st.size() == 1 ? c.ct_copy(*xa[0]) : c.stack(xa);
             HeCt sb = st.size() == 1 ? c.ct_copy(*xb[0]) : c.stack(xb);
             return c.matmul(sa, sb, (int)d[st[0]], m.n1z, m.n1t, m.npz, m.npt, m.lazy, m.fused, m.folded);
-          });
+          }});
         }
-        std::vector<HeCt> res = c.run_merged(jobs);
+        std::vector<HeCt> res = c.run_lanes(jobs);
         for (size_t s_ = 0; s_ < stacks.size(); s_++) {
           std::vector<HeCt> parts = stacks[s_].size() == 1 ? std::vector<HeCt>{} : c.unstack(res[s_]);
           if (stacks[s_].size() == 1) parts.push_back(std::move(res[s_]));
@@ -783,8 +782,8 @@ he_status he_mem_info(const he_ctx* ctx, size_t* live, size_t* cached, size_t* p
   return guard([&] {
     auto lk = hold(ctx);
     need(ctx != nullptr, "null context");
-    if (live) *live = ctx->impl.pool.bytes_live;
-    if (cached) *cached = ctx->impl.pool.bytes_cached;
+    if (live) *live = ctx->impl.pool.total_live();
+    if (cached) *cached = ctx->impl.pool.total_cached();
     if (peak) *peak = ctx->impl.pool.peak;
   });
 }
@@ -810,7 +809,7 @@ he_status he_trim(he_ctx* ctx) {
     hip_check(hipStreamSynchronize(ctx->impl.stream), "sync");
     ctx->impl.drop_graphs();
     ctx->impl.pool.trim();
-    ctx->impl.pool.peak = ctx->impl.pool.bytes_live;
+    ctx->impl.pool.peak = ctx->impl.pool.total_live();
   });
 }
 

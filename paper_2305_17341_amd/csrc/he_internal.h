@@ -172,10 +172,20 @@ struct DevPool {
   // workspace of the allocation-free entry points; reset by the caller)
   char* bump_base = nullptr;
   size_t bump_cap = 0, bump_off = 0;
+  // The pools of the context's side streams (Lane): blocks taken from them
+  // come back to them through this pool.  A lane's block may have been read
+  // on either stream when it is released: the lane's next work waits for the
+  // context's stream first, and giving blocks back waits for both.
+  std::vector<DevPool*> subs;
+  DevPool* parent = nullptr;
   void* get(size_t bytes);
   void put(void* p);
   void trim();
   void wait();
+  // with the side streams' pools
+  size_t total_live() const;
+  size_t total_cached() const;
+  void note_peak();
   ~DevPool();
 };
 

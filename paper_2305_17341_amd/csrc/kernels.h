@@ -227,31 +227,6 @@ bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64*
                              const u64* digits, const u64* c0, const u64* const* masks, const u64* digits2,
                              const u64* c02, const u64* const* masks2, const u64* pmod, int level, int L, int alpha,
                              int beta, int batch, hipStream_t s, const MrLayout* lay = nullptr);
-// Key inner products handed to a sink instead of being launched (merged
-// launches of several products): the arguments of one launch_multsum_rot or
-// launch_multsum call
-struct KsWork {
-  std::vector<u64*> outs;
-  std::vector<const u64*> keys;
-  std::vector<u64> gs;
-  std::vector<const u64*> masks;  // empty: plain outputs
-  bool accumulate = false;
-  const u64* digits = nullptr;
-  const u64* c0 = nullptr;
-  const u64* pmod = nullptr;
-  int level = 0, beta = 0, B = 1;
-};
-using KsSink = std::function<void(KsWork&&)>;
-// set the calling thread's sink (null: launch as usual); returns the previous one
-KsSink* ks_sink_exchange(KsSink* s);
-bool ks_sink_active();
-// one launch per member count over every item of `works` (any levels): the
-// same residues as their own launch_multsum_rot calls.  `table` is device
-// memory of multsum_list_table_bytes() bytes for the work table (uploaded
-// from pageable memory: not for use under stream capture).
-size_t multsum_list_table_bytes(const DeviceTables& T, const std::vector<KsWork>& works, int L, int alpha);
-void launch_multsum_list(const DeviceTables& T, const std::vector<KsWork>& works, void* table, size_t table_bytes,
-                         int L, int alpha, hipStream_t s);
 // out[j][c][b] = P (mask1_j x[c][j][0][b] + mask2_j x[c][j][1][b]) for nblk
 // shift blocks' two bases, x [2][nblk][2][B][nq][N], out [nblk][2][B][nqp][N],
 // block j's masks j * mstride words after mask1 and mask2

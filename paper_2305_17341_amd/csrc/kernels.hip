@@ -4012,62 +4012,6 @@ static PosList pos_order(const DeviceTables& T, int nq, int nqp, int L) {
   return P;
 }
 
-// ---------------------------------------------------------------------------
-// Merged key inner products: one launch over a list of work items of any
-// level, members and rotations (of different products), read from a device
-// table.  Each item runs exactly the arithmetic of k_multsum_rot.
-// ---------------------------------------------------------------------------
-struct KsItem {
-  MultiRot R;
-  PosList P;
-  const u64* digits;
-  const u64* c0;
-  const u64* pmod;
-  int nrot, nq, nqp, beta;
-};
-constexpr int KS_RPW = 4;  // rotations per work-group in the merged launch
-thread_local KsSink* tls_ks_sink = nullptr;
-KsSink* ks_sink_exchange(KsSink* s) {
-  KsSink* old = tls_ks_sink;
-  tls_ks_sink = s;
-  return old;
-}
-bool ks_sink_active() { return tls_ks_sink != nullptr; }
-
-template <int MB>
-__global__ void __launch_bounds__(TPB) k_multsum_list(const KsItem* __restrict__ items, const u32* __restrict__ start,
-                                                      int nitems, int L, int nmods, int logN,
-                                                      const ModConst* __restrict__ mc) {
-  const u32 x = blockIdx.x;
-  int lo = 0, hi = nitems;  // start[lo] <= x < start[lo + 1]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (start[mid] <= x) lo = mid;
-    else hi = mid;
-  }
-  const KsItem& it = items[lo];
-  if ((int)blockIdx.y >= it.nqp) return;
-  const u64 N = 1ull << logN;
-  const u32 xl = x - start[lo];
-  const u32 ngroups = (u32)((it.nrot + KS_RPW - 1) / KS_RPW);
-  const u32 rest = xl >> 3;
-  const int r0 = (int)(rest % ngroups) * KS_RPW;
-  const int nr = it.nrot - r0 < KS_RPW ? it.nrot - r0 : KS_RPW;
-  const u32 S = (rest / ngroups) * 8 + (xl & 7);
-  if ((u64)S * TPB >= N) return;
-  const u32 src = S * TPB + threadIdx.x;
-  const int pos = it.P.pos[blockIdx.y];
-  const int m = pos < it.nq ? pos : L + 1 + (pos - it.nq);
-  const ModConst mk = mc[m];
-  if (mk.bits <= F64_LAZY_BITS) {
-    multsum_rot_group<MB, KS_RPW>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, m, pos,
-                                  src, logN, N, mk);
-    return;
-  }
-  multsum_rot_group_int<MB>(it.R, r0, nr, it.digits, it.c0, it.pmod, it.nq, it.nqp, it.beta, nmods, m, pos, src,
-                            logN, N, mk);
-}
-
 // members b0 .. b0 + mb - 1 of a launch: those of `lay`, or of a batch of B
 // stacked as [.][B][limbs][N] throughout
 static void mr_members(MultiRot& R, const MrLayout* lay, int b0, int mb, int B, int nq, int nqp, int beta, u64 N) {
@@ -4081,132 +4025,6 @@ static void mr_members(MultiRot& R, const MrLayout* lay, int b0, int mb, int B, 
     R.msk[b] = R.member_masks ? lay->msk[x] : 0;
   }
 }
-// the work's items: rotations in chunks of MR_MAX, members in chunks of
-// MS_MAXB (an item's member count decides the launch it goes to)
-static void ks_items(const DeviceTables& T, const KsWork& w, int L, int alpha, std::vector<std::pair<int, KsItem>>& out) {
-  const int nq = w.level + 1, nqp = nq + alpha, nrot = (int)w.gs.size();
-  const u64 twoN = 2 * T.N;
-  const PosList P = pos_order(T, nq, nqp, L);
-  for (int r0 = 0; r0 < nrot; r0 += MR_MAX) {
-    const int nr = std::min(nrot - r0, MR_MAX);
-    for (int b0 = 0; b0 < w.B; b0 += MS_MAXB) {
-      KsItem it;
-      std::memset(&it, 0, sizeof it);
-      it.R.accumulate = !w.masks.empty() && w.accumulate ? 1 : 0;
-      for (int r = 0; r < nr; r++) {
-        it.R.out[r] = w.outs[r0 + r];
-        it.R.key[r] = w.keys[r0 + r];
-        it.R.mask[r] = w.masks.empty() ? nullptr : w.masks[r0 + r];
-        it.R.ginv[r] = inv_mod_2n(w.gs[r0 + r], twoN);
-      }
-      it.P = P;
-      it.digits = w.digits;
-      it.c0 = w.c0;
-      it.pmod = w.pmod;
-      it.nrot = nr;
-      it.nq = nq;
-      it.nqp = nqp;
-      it.beta = w.beta;
-      mr_members(it.R, nullptr, b0, std::min(MS_MAXB, w.B - b0), w.B, nq, nqp, w.beta, T.N);
-      out.push_back({std::min(MS_MAXB, w.B - b0), it});
-    }
-  }
-}
-
-// bytes of the table launch_multsum_list lays out: per distinct member count
-// a 256-aligned run of items, then a 256-aligned prefix array of its
-// work-group counts (one more entry than items)
-static size_t ks_table_bytes(std::vector<std::pair<int, KsItem>>& items) {
-  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first < b.first; });
-  size_t bytes = 0;
-  for (size_t i = 0; i < items.size();) {
-    size_t j = i;
-    while (j < items.size() && items[j].first == items[i].first) j++;
-    bytes = ((bytes + 255) & ~(size_t)255) + (j - i) * sizeof(KsItem);
-    bytes = ((bytes + 255) & ~(size_t)255) + (j - i + 1) * sizeof(u32);
-    i = j;
-  }
-  return bytes;
-}
-size_t multsum_list_table_bytes(const DeviceTables& T, const std::vector<KsWork>& works, int L, int alpha) {
-  std::vector<std::pair<int, KsItem>> items;
-  for (const KsWork& w : works) ks_items(T, w, L, alpha, items);
-  return ks_table_bytes(items);
-}
-
-void launch_multsum_list(const DeviceTables& T, const std::vector<KsWork>& works, void* table, size_t table_bytes,
-                         int L, int alpha, hipStream_t s) {
-  std::vector<std::pair<int, KsItem>> items;
-  for (const KsWork& w : works) ks_items(T, w, L, alpha, items);
-  if (items.empty()) return;
-  // one launch per member count: items sorted by it, each group's table
-  // (items, then the prefix of their work-group counts) laid out in turn
-  const size_t need = ks_table_bytes(items);
-  if (need > table_bytes) throw std::runtime_error("merged key-switch table larger than its buffer");
-  std::vector<char> host;
-  host.reserve(need);
-  struct Launch {
-    int mb, n, nqp_max;
-    size_t items_off, start_off;
-    u32 tiles;
-    double bytes, unit;
-    Mm mm;
-  };
-  std::vector<Launch> launches;
-  const u32 nblk = (u32)cdiv(T.N, TPB), per_rot_group = (u32)cdiv(nblk, 8) * 8;
-  for (size_t i = 0; i < items.size();) {
-    size_t j = i;
-    while (j < items.size() && items[j].first == items[i].first) j++;
-    Launch L_;
-    L_.mb = items[i].first;
-    L_.n = (int)(j - i);
-    L_.nqp_max = 0;
-    L_.bytes = L_.unit = 0;
-    L_.items_off = (host.size() + 255) & ~(size_t)255;
-    host.resize(L_.items_off + (size_t)L_.n * sizeof(KsItem));
-    std::vector<u32> start;
-    u32 t = 0;
-    for (size_t k = i; k < j; k++) {
-      const KsItem& it = items[k].second;
-      std::memcpy(host.data() + L_.items_off + (k - i) * sizeof(KsItem), &it, sizeof(KsItem));
-      start.push_back(t);
-      t += per_rot_group * (u32)((it.nrot + KS_RPW - 1) / KS_RPW);
-      L_.nqp_max = std::max(L_.nqp_max, it.nqp);
-      const bool masked = it.R.mask[0] != nullptr;
-      const double mb = L_.mb, nr = it.nrot;
-      L_.bytes += 8.0 * T.N * it.nqp *
-                  (nr * 2.0 * it.beta + mb * it.beta + (masked ? nr : 0.0) + mb * nr * 2.0 * (1 + it.R.accumulate)) +
-                  (it.c0 ? 8.0 * T.N * mb * it.nq : 0.0);
-      L_.unit += 8.0 * T.N * (nr * 2.0 * it.beta * it.nqp + nr * mb * 4.0 * it.nq);
-      L_.mm = L_.mm + mm_qp(T, it.nq, it.nqp, L, (double)T.N * (2.0 * it.beta + (it.c0 ? 1 : 0) + (masked ? 2 : 0)),
-                            (double)T.N * (2.0 * it.beta + (masked ? 2 : 0)), mb * nr);
-    }
-    start.push_back(t);
-    L_.tiles = t;
-    L_.start_off = (host.size() + 255) & ~(size_t)255;
-    host.resize(L_.start_off + start.size() * sizeof(u32));
-    std::memcpy(host.data() + L_.start_off, start.data(), start.size() * sizeof(u32));
-    launches.push_back(L_);
-    i = j;
-  }
-  if (host.size() != need) throw std::runtime_error("merged key-switch table layout mismatch");
-  // pageable source: the copy has read it when the call returns
-  if (hipMemcpyAsync(table, host.data(), host.size(), hipMemcpyHostToDevice, s) != hipSuccess)
-    throw std::runtime_error("merged key-switch table upload failed");
-  for (const Launch& l : launches) {
-    const KsItem* it = (const KsItem*)((char*)table + l.items_off);
-    const u32* st = (const u32*)((char*)table + l.start_off);
-    ProfScope ps("multsum_rot", s, l.bytes, l.mm, l.unit);
-    const dim3 grid(l.tiles, l.nqp_max);
-#define ML_CASE(K)                                                                                            \
-  case K:                                                                                                     \
-    hipLaunchKernelGGL(k_multsum_list<K>, grid, dim3(TPB), 0, s, it, st, l.n, L, T.nmods, T.logN, T.mc); \
-    break;
-    switch (l.mb) { ML_CASE(1) ML_CASE(2) ML_CASE(3) ML_CASE(4) ML_CASE(5) ML_CASE(6) ML_CASE(7) ML_CASE(8) }
-#undef ML_CASE
-  }
-}
-
 // HBM bytes (each rotation's key once, the members' digits and c0 once,
 // outputs once, the masks, the outputs read back when accumulating),
 // modular products (2 beta key products per member, rotation and value, P c0
@@ -4241,23 +4059,6 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
                         const u64* digits, const u64* c0, const u64* pmod, int level, int L, int alpha, int beta,
                         int batch, hipStream_t s, const u64* const* masks, bool accumulate,
                         const ForkStream* fs, const MrLayout* lay) {
-  if (tls_ks_sink) {
-    if (lay) throw std::runtime_error("merged key inner products take plainly stacked members");
-    KsWork w;
-    w.outs.assign(outs, outs + nrot);
-    w.keys.assign(keys, keys + nrot);
-    w.gs.assign(gs, gs + nrot);
-    if (masks) w.masks.assign(masks, masks + nrot);
-    w.accumulate = accumulate;
-    w.digits = digits;
-    w.c0 = c0;
-    w.pmod = pmod;
-    w.level = level;
-    w.beta = beta;
-    w.B = batch;
-    (*tls_ks_sink)(std::move(w));
-    return;
-  }
   const int nq = level + 1, nqp = nq + alpha;
   const u64 twoN = 2 * T.N;
   const int nblk = cdiv(T.N, TPB);
@@ -4360,13 +4161,13 @@ void launch_multsum_rot(const DeviceTables& T, u64* const* outs, const u64* cons
 // hoisted sums): outs[r] = masks[r] (rotation of base 1) + masks2[r]
 // (rotation of base 2).  The 60-bit limbs run the two launches of their own
 // kernel (the second accumulating).  False (nothing launched) where the pair
-// launch does not apply: knob mr_pair off, a merged-launch sink, or 60-bit
-// limbs that do not run in a kernel of their own.
+// launch does not apply: knob mr_pair off, or 60-bit limbs that do not run in
+// a kernel of their own.
 bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64* const* keys, const u64* gs, int nrot,
                              const u64* digits, const u64* c0, const u64* const* masks, const u64* digits2,
                              const u64* c02, const u64* const* masks2, const u64* pmod, int level, int L, int alpha,
                              int beta, int batch, hipStream_t s, const MrLayout* lay) {
-  if (!g_knobs.mr_pair || tls_ks_sink || !masks || !masks2) return false;
+  if (!g_knobs.mr_pair || !masks || !masks2) return false;
   const int nq = level + 1, nqp = nq + alpha;
   const PosList P = pos_order(T, nq, nqp, L);
   PosList pf, pi;
@@ -4444,10 +4245,6 @@ bool launch_multsum_rot_pair(const DeviceTables& T, u64* const* outs, const u64*
 
 void launch_multsum(const DeviceTables& T, u64* out, const u64* digits, const u64* key, const u64* c0,
                     const u64* pmod, int level, int L, int alpha, int beta, u64 g, int batch, hipStream_t s) {
-  if (tls_ks_sink) {
-    launch_multsum_rot(T, &out, &key, &g, 1, digits, c0, pmod, level, L, alpha, beta, batch, s);
-    return;
-  }
   int nq = level + 1, nqp = nq + alpha;
   dim3 grid(cdiv(T.N, TPB), nqp);
   const int mstep = std::min(MS_MAXB, g_knobs.ms_members);

@@ -146,6 +146,18 @@ struct HeCtxImpl {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   double last_ms = 0;
   long n_decompose = 0, n_multsum = 0, n_moddown = 0;
+  // Side streams with pools of their own (default priority; made when first
+  // used, kept for the context's life): work that does not depend on each
+  // other runs side by side, forked from the context's stream and joined to it
+  // before the call returns.
+  struct Lane {
+    hipStream_t stream = nullptr;
+    hipEvent_t done = nullptr;
+    DevPool pool;
+    ~Lane();
+  };
+  std::vector<std::unique_ptr<Lane>> lanes;
+  hipEvent_t lane_fork = nullptr;
   std::list<MmGraph> graphs;  // most recently used first (declared after the pool: destroyed before it)
 
   ~HeCtxImpl();
@@ -242,11 +254,13 @@ struct HeCtxImpl {
   std::vector<HeCt> matmul_graph(const std::vector<const HeCt*>& a, const std::vector<const HeCt*>& b, int n,
                                  int n1z, int n1t, int npz, int npt, bool lazy, bool fused_rs, bool folded = false);
   void drop_graphs();
-  // Products run together, one host thread each, taking turns on the
-  // context: their key inner products are collected and launched as one
-  // merged launch (launch_multsum_list) once every unfinished job has handed
-  // one over.  Each job's residues are those it has alone.
-  std::vector<HeCt> run_merged(const std::vector<std::function<HeCt()>>& jobs);
+  // Products run together, spread over side streams by weight.  Each job's
+  // residues are those it has alone.
+  struct Job {
+    double weight;
+    std::function<HeCt()> run;
+  };
+  std::vector<HeCt> run_lanes(const std::vector<Job>& jobs);
   void accumulate_tensors(DevBuf& acc3, bool& acc_set, const std::vector<HeCt>& Ak, const std::vector<HeCt>& Bk);
   HeCt relin_sum(const DevBuf& acc3, int level, double scale, int B);
   // A group of consecutive shift blocks' bases, one after the other under the

@@ -7,10 +7,7 @@
 
 #include <algorithm>
 #include <cmath>
-#include <condition_variable>
-#include <exception>
 #include <mutex>
-#include <thread>
 #include <cstdio>
 #include <set>
 #include <unordered_map>
@@ -47,7 +44,7 @@ void* DevPool::get(size_t bytes) {
     bytes_cached -= sz;
     live_[p] = sz;
     bytes_live += sz;
-    peak = std::max(peak, bytes_live);
+    note_peak();
     return p;
   }
   if (frozen) fail(HE_ENOMEM, "graph arena exhausted while recording");
@@ -60,13 +57,27 @@ void* DevPool::get(size_t bytes) {
       p = nullptr;
     }
     if (p) break;
-    trim();
+    (parent ? parent : this)->trim();
   }
   if (!p) fail(HE_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
   live_[p] = bytes;
   bytes_live += bytes;
-  peak = std::max(peak, bytes_live);
+  note_peak();
   return p;
+}
+size_t DevPool::total_live() const {
+  size_t n = bytes_live;
+  for (const DevPool* s : subs) n += s->bytes_live;
+  return n;
+}
+size_t DevPool::total_cached() const {
+  size_t n = bytes_cached;
+  for (const DevPool* s : subs) n += s->bytes_cached;
+  return n;
+}
+void DevPool::note_peak() {
+  DevPool* root = parent ? parent : this;
+  root->peak = std::max(root->peak, root->total_live());
 }
 void DevPool::put(void* p) {
   if (redirect && redirect->live_.count(p)) {
@@ -74,7 +85,11 @@ void DevPool::put(void* p) {
     return;
   }
   auto it = live_.find(p);
-  if (it == live_.end()) return;
+  if (it == live_.end()) {
+    for (DevPool* s : subs)
+      if (s->live_.count(p)) return s->put(p);
+    return;
+  }
   size_t sz = it->second;
   live_.erase(it);
   bytes_live -= sz;
@@ -82,10 +97,13 @@ void DevPool::put(void* p) {
   bytes_cached += sz;
 }
 void DevPool::wait() {
+  if (parent && parent->stream) (void)hipStreamSynchronize(parent->stream);
+  for (DevPool* s : subs) (void)hipStreamSynchronize(s->stream);
   if (stream) (void)hipStreamSynchronize(stream);
   else (void)hipDeviceSynchronize();
 }
 void DevPool::trim() {
+  for (DevPool* s : subs) s->trim();
   if (free_.empty()) return;
   wait();
   for (auto& kv : free_) {
@@ -171,7 +189,15 @@ static u32 brv_host(u32 x, int bits) {
 // ---------------------------------------------------------------------------
 // context construction
 // ---------------------------------------------------------------------------
+HeCtxImpl::Lane::~Lane() {
+  if (stream) (void)hipStreamSynchronize(stream);
+  pool.trim();
+  pool.stream = nullptr;
+  if (done) (void)hipEventDestroy(done);
+  if (stream) (void)hipStreamDestroy(stream);
+}
 HeCtxImpl::~HeCtxImpl() {
+  for (auto& l : lanes) (void)hipStreamSynchronize(l->stream);
   if (stream) (void)hipStreamSynchronize(stream);
   graphs.clear();
   ltplans.clear();
@@ -183,6 +209,9 @@ HeCtxImpl::~HeCtxImpl() {
   tables.clear();
   for (auto& row : up)
     for (auto& t : row) (void)t;
+  pool.subs.clear();
+  lanes.clear();
+  if (lane_fork) (void)hipEventDestroy(lane_fork);
   if (ev0) (void)hipEventDestroy(ev0);
   if (ev1) (void)hipEventDestroy(ev1);
   // the pool is destroyed after this body: its last trim must not wait on a
@@ -847,16 +876,7 @@ void HeCtxImpl::decompose_to(const u64* d, int level, int B, u64* dig) {
     // sources times their hat inverses (the inverse transform's last scaling,
     // read from d directly), then conversion + NTT in one pass pair
     const std::vector<FbcTable>& tabs = up[level];
-    if (!launch_intt_scaled(T, coef.p, d, B * nq, qmap(nq), up_scale.p + (size_t)level * nmods * 2, stream)) {
-      std::vector<u64> hinv((size_t)2 * nq);
-      for (int t = 0; t < nq; t++) {
-        hinv[2 * t] = tabs[t / alpha].hatinv[t % alpha];
-        hinv[2 * t + 1] = tabs[t / alpha].hatinv_sh[t % alpha];
-      }
-      copy_limbs(coef.p, d, (size_t)B * nq, "copy_decompose");
-      launch_ntt(T, coef.p, B * nq, qmap(nq), true, stream);
-      launch_mul_const(T, coef.p, coef.p, B * nq, hinv.data(), qmap(nq), stream);
-    }
+    launch_intt_scaled(T, coef.p, d, B * nq, qmap(nq), up_scale.p + (size_t)level * nmods * 2, stream);
     if (launch_modup_ntt(T, dig, coef.p, d, level, L, alpha, bl, tabs.data(), B, m, stream)) {
       n_decompose += B;
       return;
@@ -985,7 +1005,7 @@ HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool
   if (down_rs.empty()) fail(HE_EINVAL, "one rounding for ModDown and Rescale needs at most 3 special primes");
   if (out_level < 0) out_level = l - 1;
   if (out_level > l - 1) fail(HE_ELEVEL, "rescale cannot raise the level");
-  const int nqx = nq_of(l), nqp = nqp_of(l), nout = out_level + 1, ns = alpha + 1;
+  const int nqp = nqp_of(l), nout = out_level + 1, ns = alpha + 1;
   const int np = (int)x.polys();
   const FbcTable& tab = down_rs[l];
   LimbMap sm;
@@ -1295,6 +1315,8 @@ std::vector<const u64*> HeCtxImpl::plaintexts(const std::vector<std::string>& ke
       ptcache[keys_[i] + suffix] = out[i];
     }
   }
+  // made on a side stream: another may use them next
+  if (!lanes.empty()) hip_check(hipStreamSynchronize(stream), "plaintexts");
   return out;
 }
 
@@ -1746,10 +1768,8 @@ std::vector<HeCt> HeCtxImpl::matmul_side_b(const HeCt& cb, int n, int n1t, int n
 // Blocks whose bases stand together: as many as the members of one
 // multi-rotation launch take (each key word is then loaded once for all of
 // them, and the ModDowns of all of them fill the chip together), within
-// 2 HE_STAGE_BYTES of digits; one at a time inside a merged launch, which
-// stacks the members of several products instead.
+// 2 HE_STAGE_BYTES of digits.
 int HeCtxImpl::shift_group(int level, int sides, int B, int blocks) const {
-  if (ks_sink_active()) return 1;
   const size_t per = (size_t)sides * B * ((size_t)beta_at(level) * nqp_of(level) + 2 * nq_of(level)) * N * 8;
   const size_t fit = std::min<size_t>(std::max(1, MR_MEMBERS / B), 2 * HE_STAGE_BYTES / per);
   const int most = (int)std::max<size_t>(1, std::min<size_t>(fit, blocks));
@@ -2112,68 +2132,62 @@ std::vector<HeCt> HeCtxImpl::matmul_graph(const std::vector<const HeCt*>& a, con
   return out;
 }
 
-namespace {
-struct KsGroup {
-  std::mutex mu;  // held by the job that is running
-  std::condition_variable cv;
-  int active = 0, waiting = 0;
-  u64 generation = 0;
-  bool failed = false;
-  std::string error;
-  std::vector<KsWork> pending;
-};
-}  // namespace
-
-std::vector<HeCt> HeCtxImpl::run_merged(const std::vector<std::function<HeCt()>>& jobs) {
-  KsGroup g;
-  g.active = (int)jobs.size();
+// Jobs from the heaviest down, each to the stream with the least to do: a
+// product's launches fill the chip only on the larger rings, and two or three
+// of them side by side take little longer than one.  (Merging only their key
+// inner products into shared launches, a host thread a product, left the
+// other nine tenths of the launches one after the other: seven products of
+// three sizes at N = 2^14 took 11.3 ms so, and take 6.3 ms side by side.)
+std::vector<HeCt> HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
+  constexpr size_t LANES = 3;
   std::vector<HeCt> res(jobs.size());
-  std::vector<std::exception_ptr> errs(jobs.size());
-  // with g.mu held: launch what is pending and release the waiting jobs
-  auto flush = [&]() {
-    if (!g.pending.empty() && !g.failed) {
-      try {
-        DevBuf tab(&pool, (multsum_list_table_bytes(T, g.pending, L, alpha) + 7) / 8);
-        launch_multsum_list(T, g.pending, tab.p, tab.words * 8, L, alpha, stream);
-      } catch (const HeError& e) {
-        g.failed = true;
-        g.error = e.msg;
-      } catch (const std::exception& e) {
-        g.failed = true;
-        g.error = e.what();
-      }
+  // a caller's allocator or stream knows nothing of other streams
+  if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect) {
+    for (size_t t = 0; t < jobs.size(); t++) res[t] = jobs[t].run();
+    return res;
+  }
+  if (!lane_fork) hip_check(hipEventCreateWithFlags(&lane_fork, hipEventDisableTiming), "event");
+  while (lanes.size() < std::min(LANES, jobs.size())) {
+    std::unique_ptr<Lane> l(new Lane);
+    hip_check(hipStreamCreateWithFlags(&l->stream, hipStreamNonBlocking), "stream");
+    hip_check(hipEventCreateWithFlags(&l->done, hipEventDisableTiming), "event");
+    l->pool.user_alloc = pool.user_alloc;
+    l->pool.user_release = pool.user_release;
+    l->pool.user = pool.user;
+    l->pool.stream = l->stream;
+    l->pool.parent = &pool;
+    lanes.push_back(std::move(l));
+    pool.subs.push_back(&lanes.back()->pool);
+  }
+  const size_t nl = std::min(LANES, jobs.size());
+  const hipStream_t main = stream;
+  hip_check(hipEventRecord(lane_fork, main), "fork");
+  for (size_t i = 0; i < nl; i++) hip_check(hipStreamWaitEvent(lanes[i]->stream, lane_fork, 0), "fork");
+  // whatever happens, the context's stream goes on after the lanes
+  struct Join {
+    HeCtxImpl& c;
+    hipStream_t main;
+    size_t nl;
+    ~Join() {
+      c.stream = main;
+      c.pool.redirect = nullptr;
+      for (size_t i = 0; i < nl; i++)
+        if (hipEventRecord(c.lanes[i]->done, c.lanes[i]->stream) != hipSuccess ||
+            hipStreamWaitEvent(main, c.lanes[i]->done, 0) != hipSuccess)
+          (void)hipStreamSynchronize(c.lanes[i]->stream);
     }
-    g.pending.clear();
-    g.waiting = 0;
-    g.generation++;
-    g.cv.notify_all();
-  };
-  auto worker = [&](size_t t) {
-    std::unique_lock<std::mutex> lk(g.mu);
-    KsSink sink = [&](KsWork&& w) {
-      if (g.failed) fail(HE_EDEVICE, "merged key switch failed: " + g.error);
-      g.pending.push_back(std::move(w));
-      g.waiting++;
-      const u64 gen = g.generation;
-      if (g.waiting == g.active) flush();
-      else g.cv.wait(lk, [&] { return g.generation != gen; });
-      if (g.failed) fail(HE_EDEVICE, "merged key switch failed: " + g.error);
-    };
-    KsSink* prev = ks_sink_exchange(&sink);
-    try {
-      res[t] = jobs[t]();
-    } catch (...) {
-      errs[t] = std::current_exception();
-    }
-    ks_sink_exchange(prev);
-    g.active--;
-    if (g.active > 0 && g.waiting == g.active) flush();
-  };
-  std::vector<std::thread> threads;
-  for (size_t t = 0; t < jobs.size(); t++) threads.emplace_back(worker, t);
-  for (auto& th : threads) th.join();
-  for (auto& e : errs)
-    if (e) std::rethrow_exception(e);
+  } join{*this, main, nl};
+  std::vector<size_t> order(jobs.size());
+  for (size_t t = 0; t < order.size(); t++) order[t] = t;
+  std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return jobs[x].weight > jobs[y].weight; });
+  std::vector<double> load(nl, 0.0);
+  for (size_t t : order) {
+    const size_t i = std::min_element(load.begin(), load.end()) - load.begin();
+    load[i] += jobs[t].weight;
+    stream = lanes[i]->stream;
+    pool.redirect = &lanes[i]->pool;
+    res[t] = jobs[t].run();
+  }
   return res;
 }
 

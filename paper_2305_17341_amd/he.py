@@ -244,7 +244,7 @@ class Ciphertext:
     def export(self) -> np.ndarray:
         """Residues u64[2][level+1][N] (synchronises)."""
         lv = self.level
-        out = np.zeros(2 * (lv + 1) * self.ctx.N, dtype=np.uint64)
+        out = np.empty(2 * (lv + 1) * self.ctx.N, dtype=np.uint64)
         _check(load().he_ct_export(self.ptr, out.ctypes.data_as(u64p), out.size, None, None))
         return out.reshape(2, lv + 1, self.ctx.N)
 

@@ -16,8 +16,8 @@ Scheduling
     it takes the oldest admitted request of its N together with the other
     admitted products of that N, of any size (up to `max_batch`), and runs
     them as one merged batch: products of equal d are stacked, and the
-    stacks of different d run together with their key inner products merged
-    into shared launches (HE_MM_MERGED).  Requests that arrived while earlier
+    stacks of different d run side by side on streams of the context
+    (HE_MM_MERGED).  Requests that arrived while earlier
     work was on the device join the next batch.  Workers of different N run
     concurrently, each on its context's stream, so their kernels overlap on
     the GPU.  Memory freed by a finished batch admits waiting requests.
@@ -221,9 +221,10 @@ class HeBackend:
 
 class Server:
     def __init__(self, backend, hbm_budget: int, max_batch: int = 8, trim_when_idle: bool = True,
-                 cov_yield: int = 4):
+                 cov_yield: int = 4, join_s: float = 0.0005):
         self.backend = backend
         self.cov_yield = cov_yield
+        self.join_s = join_s
         self.budget = int(hbm_budget)
         self.max_batch = max_batch
         self.trim_when_idle = trim_when_idle
@@ -340,6 +341,13 @@ class Server:
                     if self._stop and not any(p.log_n == log_n for p in self._pending):
                         return
                     self._cv.wait()
+                # a lone product lets others join for join_s from its
+                # submission: a small one takes about as long itself, and two
+                # stacked little longer than one
+                lone = self._ready[log_n][0]
+                left = self.join_s - (time.perf_counter() - lone.t_submit)
+                if left > 0 and lone.kind == "matmul":
+                    self._cv.wait_for(lambda: self._stop or len(self._ready[log_n]) > 1, left)
                 group = self._take(log_n)
             t0 = time.perf_counter()
             err, out = None, None
