@@ -4916,6 +4916,9 @@ __device__ __forceinline__ cdd cdd_sub(cdd a, cdd b) { return {dd_add(a.re, dd_n
 // apart).  The first pass forms its input as it loads it, the second ends in
 // what is wanted of the result.  A launch per radix-2 stage spent 3 us on
 // each of 13 to 16 stages, nearly all of it latency.
+// The stage loops end in their barrier: with it at the loop's head the compiler
+// (ROCm 7.2) leaves out the wait for the LDS writes of the stage before, and
+// one tile in some 250 000 then read a value too early.
 #define FFT_TILE (2 * TPB)
 #define FFT_LOW 9
 static_assert(FFT_TILE == 1 << FFT_LOW, "the low pass takes a whole tile");
@@ -4933,12 +4936,12 @@ __global__ void __launch_bounds__(TPB) k_fft_low(cdd* x, IN in, int logN, int si
   const u32 p0 = blockIdx.x * FFT_TILE;
   const int b = blockIdx.y;
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) sh[e] = in(b, brv(p0 + e, logN), N);
+  __syncthreads();
   for (int st = 0; st < FFT_LOW; st++) {
-    __syncthreads();
     const u32 half = 1u << st, k = threadIdx.x & (half - 1), i0 = ((threadIdx.x >> st) << (st + 1)) + k;
     fft_bf(sh[i0], sh[i0 + half], (u64)k << (logN - st - 1), sign, tw);
+    __syncthreads();
   }
-  __syncthreads();
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) x[(size_t)b * N + p0 + e] = sh[e];
 }
 template <class OUT>
@@ -4952,13 +4955,13 @@ __global__ void __launch_bounds__(TPB) k_fft_high(const cdd* __restrict__ x, OUT
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
     sh[e] = x[(size_t)b * N + ((size_t)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1))];
   const u32 c = threadIdx.x & (C - 1), rr = threadIdx.x >> lc;
+  __syncthreads();
   for (int st = 0; st < lr; st++) {
-    __syncthreads();
     const u32 half = 1u << st, k = rr & (half - 1), r0 = ((rr >> st) << (st + 1)) + k;
     const u64 kk = ((u64)k << FFT_LOW) + c0 + c;
     fft_bf(sh[(r0 << lc) + c], sh[((r0 + half) << lc) + c], kk << (lr - st - 1), sign, tw);
+    __syncthreads();
   }
-  __syncthreads();
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
     out(b, ((u64)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1)), sh[e], N);
 }

@@ -113,3 +113,25 @@ def test_embedding_passes_match_oracle(oracle_mod, log_n):
         assert np.array_equal(ctx.encode(z, 2.0**40), o.encode(z, 2.0**40))
         got = ctx.decrypt(ctx.encrypt(z, nonce=n))
         assert np.max(np.abs(got - np.resize(z, ctx.slots))) < 2.0**-15
+
+
+def test_plaintexts_encoded_together():
+    """some nine thousand messages encoded in batches (the diagonals of three
+    permutations at twelve levels): every transform returns the permuted matrix"""
+    from paper_2305_17341_amd import he
+    n = 128
+    ch = I.Chain("emb16", 16, (60,) + (40,) * 12, (60,))
+    ctx = he.chain_context(ch, seed=76)
+    steps = set()
+    for kind in "ZTG":
+        steps |= set(he.lintrans_rot_steps(kind, n, 16))
+    ctx.keygen(sorted(steps))
+    A = I.uniform_matrix(8, n)
+    i, j = np.meshgrid(np.arange(n), np.arange(n), indexing="ij")
+    want = {"sigma": A[i, (i + j) % n], "tau": A[(i + j) % n, j], "transpose": A.T}
+    x = ctx.encrypt_matrix(A, nonce=3)
+    for level in range(1, 13):
+        at = ctx.drop(x, level)
+        for kind, w in want.items():
+            got = ctx.decrypt(ctx.lintrans(at, kind, n, 16), n * n)
+            assert np.max(np.abs(got - w.ravel())) < 2.0**-15, (kind, level)
