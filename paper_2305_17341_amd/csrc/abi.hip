@@ -281,8 +281,7 @@ he_status he_ct_export(const he_ct* ct, uint64_t* host, size_t words, uint32_t* 
     need(ct != nullptr && host != nullptr, "null argument");
     need(words >= ct->ct.d.words, "host buffer too small");
     HeCtxImpl& c = ct->ctx->impl;
-    hip_check(hipMemcpyAsync(host, ct->ct.d.p, ct->ct.d.words * 8, hipMemcpyDeviceToHost, c.stream), "export");
-    hip_check(hipStreamSynchronize(c.stream), "export");
+    c.download(host, ct->ct.d.p, ct->ct.d.words * 8);
     if (level) *level = (uint32_t)ct->ct.level;
     if (scale) *scale = ct->ct.scale;
   });
@@ -859,8 +858,7 @@ he_status he_hoisted_rotate_export(he_ctx* ctx, const he_ct* a, int32_t step, ui
     if (g != 1) dig = c.decompose(a->ct.poly(1), a->ct.level);
     HeCt h = c.hoisted(a->ct, dig.p, g);
     need(words >= h.d.words, "host buffer too small");
-    hip_check(hipMemcpyAsync(host, h.d.p, h.d.words * 8, hipMemcpyDeviceToHost, c.stream), "download");
-    hip_check(hipStreamSynchronize(c.stream), "hoisted");
+    c.download(host, h.d.p, h.d.words * 8);
   });
 }
 

@@ -58,6 +58,7 @@ struct SubDst {
 };
 // ciphertexts [2][nl][N] into a batch [2][B][nl][N], and back
 void launch_stack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s);
+void launch_copy(void* out, const void* in, size_t bytes, hipStream_t s);  // to pinned memory; whole 16 bytes
 void launch_unstack(const DeviceTables& T, u64* batch, u64* const* members, int B, int nl, hipStream_t s);
 // forward NTT of npoly x nq limbs y, then out = (x - y) c mod q_t with x
 // [npoly][x_stride][N] and c pairs (value, Shoup companion) per t < nq

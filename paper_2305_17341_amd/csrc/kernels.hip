@@ -2395,6 +2395,16 @@ void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b,
   else hipLaunchKernelGGL(k_tensor<false>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
 }
 
+// Words to a pinned host buffer (the link bounds it at 55 GB/s): two a thread
+__global__ void k_copy(ulonglong2* out, const ulonglong2* in, u64 n) {
+  const u64 i = (u64)blockIdx.x * TPB + threadIdx.x;
+  if (i < n) out[i] = in[i];
+}
+void launch_copy(void* out, const void* in, size_t bytes, hipStream_t s) {
+  hipLaunchKernelGGL(k_copy, dim3(cdiv(bytes / 16, TPB)), dim3(TPB), 0, s, (ulonglong2*)out, (const ulonglong2*)in,
+                     bytes / 16);
+}
+
 // Ciphertexts [2][nl][N] gathered into a batch [2][B][nl][N], or a batch
 // scattered: one launch for up to RD_MAX members, two words a thread
 struct Members {

@@ -261,6 +261,15 @@ struct HeCtxImpl {
     std::function<HeCt()> run;
   };
   std::vector<HeCt> run_lanes(const std::vector<Job>& jobs);
+  // device memory to a caller's host buffer, waited for
+  void download(void* host, const void* dev, size_t bytes);
+  struct Staging {
+    static constexpr size_t CHUNK = 1 << 19, COUNT = 8;
+    char* mem = nullptr;  // pinned, COUNT chunks (made when first used)
+    hipEvent_t done[COUNT] = {};
+    bool failed = false;
+    ~Staging();
+  } staging;
   void accumulate_tensors(DevBuf& acc3, bool& acc_set, const std::vector<HeCt>& Ak, const std::vector<HeCt>& Bk);
   HeCt relin_sum(const DevBuf& acc3, int level, double scale, int B);
   // A group of consecutive shift blocks' bases, one after the other under the
