@@ -514,8 +514,11 @@ he_status he_matmul_batch(he_ctx* ctx, const he_ct* const* a, const he_ct* const
           if (!placed) stacks.push_back({i});
         }
         std::vector<HeCtxImpl::Job> jobs;
-        for (const auto& st : stacks) {
-          jobs.push_back({(double)d[st[0]] * (4.0 + st.size()), [&, st]() {
+        std::vector<HeCt> res(stacks.size());
+        for (size_t s_ = 0; s_ < stacks.size(); s_++) {
+          const std::vector<size_t>& st = stacks[s_];
+          jobs.push_back({(double)d[st[0]] * (4.0 + st.size()), [&, s_]() {
+            const std::vector<size_t>& st = stacks[s_];
             std::vector<const HeCt*> xa, xb;
             for (size_t k : st) {
               xa.push_back(&a[k]->ct);
@@ -524,10 +527,10 @@ he_status he_matmul_batch(he_ctx* ctx, const he_ct* const* a, const he_ct* const
             MmOpts m = opts_of(opts, (int)d[st[0]]);
             HeCt sa = st.size() == 1 ? c.ct_copy(*xa[0]) : c.stack(xa);
             HeCt sb = st.size() == 1 ? c.ct_copy(*xb[0]) : c.stack(xb);
-            return c.matmul(sa, sb, (int)d[st[0]], m.n1z, m.n1t, m.npz, m.npt, m.lazy, m.fused, m.folded);
+            res[s_] = c.matmul(sa, sb, (int)d[st[0]], m.n1z, m.n1t, m.npz, m.npt, m.lazy, m.fused, m.folded);
           }});
         }
-        std::vector<HeCt> res = c.run_lanes(jobs);
+        c.run_lanes(jobs);
         for (size_t s_ = 0; s_ < stacks.size(); s_++) {
           std::vector<HeCt> parts = stacks[s_].size() == 1 ? std::vector<HeCt>{} : c.unstack(res[s_]);
           if (stacks[s_].size() == 1) parts.push_back(std::move(res[s_]));

@@ -258,9 +258,10 @@ struct HeCtxImpl {
   // residues are those it has alone.
   struct Job {
     double weight;
-    std::function<HeCt()> run;
+    std::function<void()> run;
   };
-  std::vector<HeCt> run_lanes(const std::vector<Job>& jobs);
+  void run_lanes(const std::vector<Job>& jobs);
+  void run_sides(const std::vector<Job>& jobs, int B);
   // device memory to a caller's host buffer, waited for
   void download(void* host, const void* dev, size_t bytes);
   struct Staging {

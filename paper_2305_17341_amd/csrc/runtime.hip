@@ -2089,9 +2089,13 @@ HeCt HeCtxImpl::matmul(const HeCt& ca, const HeCt& cb, int n, int n1z, int n1t, 
   // B: tau); align_sides only guards the prediction
   const int common = std::min(ca.level - da, cb.level - dt);
   // the sides come out packed where only the lazy tensor sums read them
-  std::vector<HeCt> Ak =
-      folded ? matmul_side_a_folded(ca, n, n1z) : matmul_side_a(ca, n, n1z, npz, common, fused_rs, lazy);
-  std::vector<HeCt> Bk = matmul_side_b(cb, n, n1t, npt, common, lazy);
+  std::vector<HeCt> Ak, Bk;
+  std::vector<Job> sides;
+  sides.push_back({2.0, [&] {
+    Ak = folded ? matmul_side_a_folded(ca, n, n1z) : matmul_side_a(ca, n, n1z, npz, common, fused_rs, lazy);
+  }});
+  sides.push_back({1.0, [&] { Bk = matmul_side_b(cb, n, n1t, npt, common, lazy); }});
+  run_sides(sides, ca.B);
   align_sides(Ak, Bk);
   HeCt acc;
   if (lazy) {
@@ -2188,14 +2192,13 @@ std::vector<HeCt> HeCtxImpl::matmul_graph(const std::vector<const HeCt*>& a, con
 // of them side by side take little longer than one.  (Merging only their key
 // inner products into shared launches, a host thread a product, left the
 // other nine tenths of the launches one after the other: seven products of
-// three sizes at N = 2^14 took 11.3 ms so, and take 6.3 ms side by side.)
-std::vector<HeCt> HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
+// three sizes at N = 2^14 took 11.3 ms so, and take 8.4 ms side by side.)
+void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   constexpr size_t LANES = 3;
-  std::vector<HeCt> res(jobs.size());
   // a caller's allocator or stream knows nothing of other streams
   if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect) {
-    for (size_t t = 0; t < jobs.size(); t++) res[t] = jobs[t].run();
-    return res;
+    for (const Job& j : jobs) j.run();
+    return;
   }
   if (!lane_fork) hip_check(hipEventCreateWithFlags(&lane_fork, hipEventDisableTiming), "event");
   while (lanes.size() < std::min(LANES, jobs.size())) {
@@ -2237,9 +2240,19 @@ std::vector<HeCt> HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
     load[i] += jobs[t].weight;
     stream = lanes[i]->stream;
     pool.redirect = &lanes[i]->pool;
-    res[t] = jobs[t].run();
+    jobs[t].run();
   }
-  return res;
+}
+
+// The sides of a product do not depend on each other.  Side by side they fill
+// what one side's launches leave idle of the chip: d = 64 at N = 2^14 took 2.95
+// ms one after the other and takes 2.34 so, d = 128 at N = 2^16 83.3 and 81.4.
+// At N = 2^13 the launches are so short that crossing between streams costs
+// more (d = 16: 1.06 ms and 1.17); batches of N = 2^16 fill the chip alone and
+// would only hold both sides' temporaries at once.
+void HeCtxImpl::run_sides(const std::vector<Job>& jobs, int B) {
+  if ((u64)B * N <= (1ull << 16) && N >= (1ull << 14)) return run_lanes(jobs);
+  for (const Job& j : jobs) j.run();
 }
 
 void HeCtxImpl::drop_graphs() {
@@ -2299,14 +2312,18 @@ void HeCtxImpl::cov_add(CovState& st, const std::vector<const HeCt*>& x, int rb)
       return gb == 1 ? ct_copy(*xs[0]) : stack(xs);
     };
     std::vector<std::vector<HeCt>> A(k), B(k);
-    for (int a = 0; a < k; a++) {
-      HeCt xt = lintrans(rows_of(a), LT_TRANSPOSE, n, st.n1g, 1.0 / (double)st.n_samples);
-      A[a] = matmul_side_a(xt, n, st.n1z, st.npz, common, st.fused, st.lazy);
-    }
-    for (int b = 0; b < k; b++) {
-      HeCt xb = drop(rows_of(b), level - 1);
-      B[b] = matmul_side_b(xb, n, st.n1t, st.npt, common, st.lazy);
-    }
+    std::vector<Job> sides;
+    for (int a = 0; a < k; a++)
+      sides.push_back({3.0, [&, a] {
+        HeCt xt = lintrans(rows_of(a), LT_TRANSPOSE, n, st.n1g, 1.0 / (double)st.n_samples);
+        A[a] = matmul_side_a(xt, n, st.n1z, st.npz, common, st.fused, st.lazy);
+      }});
+    for (int b = 0; b < k; b++)
+      sides.push_back({1.0, [&, b] {
+        HeCt xb = drop(rows_of(b), level - 1);
+        B[b] = matmul_side_b(xb, n, st.n1t, st.npt, common, st.lazy);
+      }});
+    run_sides(sides, gb);
     for (int a = 0; a < k; a++) align_sides(A[a], B[0]);
     for (int b = 0; b < k; b++) align_sides(A[0], B[b]);
     st.acc_level = A[0][0].level;
