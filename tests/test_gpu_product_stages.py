@@ -135,3 +135,32 @@ def test_plaintexts_encoded_together():
         for kind, w in want.items():
             got = ctx.decrypt(ctx.lintrans(at, kind, n, 16), n * n)
             assert np.max(np.abs(got - w.ravel())) < 2.0**-15, (kind, level)
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("level,v_level", [(4, 4), (3, 4), (2, 2)])
+def test_power_blocks_together_match_oracle(oracle_mod, axis, level, v_level):
+    """three by three blocks alike (one batch a stage), the vector's level
+    above the blocks', and too low for a batch along one of the axes"""
+    from oracle import power as P
+    from paper_2305_17341_amd import he
+    n, k, ch = 4, 3, TINY
+    ctx = he.chain_context(ch, seed=77)
+    ctx.keygen(he.power_rot_steps(n))
+    o = oracle_mod.Oracle(ch.log_n, ch.q_bits, ch.p_bits, seed=77)
+    o.keygen(rot_steps=he.power_rot_steps(n))
+    X = I.uniform_matrix(3, n * k)
+    cov = X @ X.T / (n * k)
+    blocks = [cov[r * n:(r + 1) * n, c * n:(c + 1) * n] for r in range(k) for c in range(k)]
+    reps = P.replicate(I.rng(4).uniform(-0.3, 0.3, n * k), k, n, axis)
+    gC = [ctx.encrypt_matrix(b, level, nonce=100 + i) for i, b in enumerate(blocks)]
+    oC = [P.Box(o.encrypt(b.ravel(), level, nonce=100 + i)) for i, b in enumerate(blocks)]
+    gV = [ctx.encrypt_matrix(b, v_level, nonce=200 + i) for i, b in enumerate(reps)]
+    oV = [P.Box(o.encrypt(b.ravel(), v_level, nonce=200 + i)) for i, b in enumerate(reps)]
+    ref, hp = he.Refresher(ctx, 1 << 40), P.HePower(o, n, nonce0=1 << 40)
+    gV, g_axis = ctx.power_step(gC, k, n, gV, axis, 1, 2.0, False, ref)
+    oV, o_axis = hp.step(oC, k, oV, axis, 1, 2.0, False)
+    assert g_axis == o_axis and ref.count == hp.refreshes
+    for i in range(k):
+        assert gV[i].level == oV[i].ct.level and gV[i].scale == oV[i].ct.scale
+        assert np.array_equal(gV[i].export(), oV[i].ct.data()), i
