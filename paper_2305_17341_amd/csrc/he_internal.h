@@ -178,6 +178,10 @@ struct DevPool {
   // context's stream first, and giving blocks back waits for both.
   std::vector<DevPool*> subs;
   DevPool* parent = nullptr;
+  // while the streams run side by side, blocks released on another one than
+  // their own are kept until they have met again
+  bool lanes_on = false;
+  std::vector<void*> deferred;
   void* get(size_t bytes);
   void put(void* p);
   void trim();

@@ -114,6 +114,7 @@ struct HeCtxImpl {
   bool own_stream = false;
   // second stream of the multi-rotation launches (see ForkStream)
   ForkStream fork;
+  const ForkStream* fork_stream() const { return pool.lanes_on ? nullptr : &fork; }  // it is a lane then
   // device the context was created on, and that device's copy of the
   // allocation-free entry points' workspace
   int device = 0;
@@ -148,10 +149,11 @@ struct HeCtxImpl {
   long n_decompose = 0, n_multsum = 0, n_moddown = 0;
   // Side streams with pools of their own (default priority; made when first
   // used, kept for the context's life): work that does not depend on each
-  // other runs side by side, forked from the context's stream and joined to it
-  // before the call returns.
+  // other runs on them and the context's stream side by side, forked from that
+  // and joined to it before the call returns.
   struct Lane {
     hipStream_t stream = nullptr;
+    bool own = true;  // else the ForkStream's
     hipEvent_t done = nullptr;
     DevPool pool;
     ~Lane();

@@ -85,6 +85,10 @@ void DevPool::put(void* p) {
     return;
   }
   auto it = live_.find(p);
+  if (lanes_on && (redirect || it == live_.end())) {
+    deferred.push_back(p);
+    return;
+  }
   if (it == live_.end()) {
     for (DevPool* s : subs)
       if (s->live_.count(p)) return s->put(p);
@@ -245,7 +249,7 @@ HeCtxImpl::Lane::~Lane() {
   pool.trim();
   pool.stream = nullptr;
   if (done) (void)hipEventDestroy(done);
-  if (stream) (void)hipStreamDestroy(stream);
+  if (stream && own) (void)hipStreamDestroy(stream);
 }
 HeCtxImpl::~HeCtxImpl() {
   for (auto& l : lanes) (void)hipStreamSynchronize(l->stream);
@@ -975,7 +979,7 @@ std::vector<HeCt> HeCtxImpl::hoisted_multi(const HeCt& x, const u64* digits, con
   }
   if (!outs.empty())
     launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), (int)outs.size(), digits, x.poly(0), pmod.p, x.level,
-                       L, alpha, beta_at(x.level), x.B, stream, nullptr, false, &fork);
+                       L, alpha, beta_at(x.level), x.B, stream, nullptr, false, fork_stream());
   n_multsum += (long)x.B * (long)outs.size();
   return out;
 }
@@ -1234,7 +1238,7 @@ std::vector<HeCt> HeCtxImpl::rotate_many(const HeCt& x, const std::vector<long>&
       ks.push_back(key(gs[r0 + r]).p);
     }
     launch_multsum_rot(T, outs.data(), ks.data(), gs.data() + r0, nr, dig.p, x.poly(0), pmod.p, level, L, alpha,
-                       beta_at(level), B, stream, nullptr, false, &fork);
+                       beta_at(level), B, stream, nullptr, false, fork_stream());
     n_multsum += (long)B * nr;
     for (int r = 0; r < nr; r += rd) {
       const int cnt = std::min(rd, nr - r);
@@ -1945,14 +1949,14 @@ void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n
     const int nr = (int)outs.size(), bl = beta_at(level);
     if (nr && !masks) {
       launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, pmod.p, level, L, alpha, bl, nb * B, stream,
-                         nullptr, false, &fork, pl);
+                         nullptr, false, fork_stream(), pl);
     } else if (nr && !launch_multsum_rot_pair(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, m1.data(), d2, c2,
                                               m2.data(), pmod.p, level, L, alpha, bl, nb * B, stream, pl)) {
       // the second base's masked rotations added onto the first's
       launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d1, c1, pmod.p, level, L, alpha, bl, nb * B, stream,
-                         m1.data(), false, &fork, pl);
+                         m1.data(), false, fork_stream(), pl);
       launch_multsum_rot(T, outs.data(), ks.data(), g2.data(), nr, d2, c2, pmod.p, level, L, alpha, bl, nb * B, stream,
-                         m2.data(), true, &fork, pl);
+                         m2.data(), true, fork_stream(), pl);
     }
     n_multsum += (long)S * nb * B * nr;
     if (masks && r0 == 0)
@@ -2192,18 +2196,25 @@ std::vector<HeCt> HeCtxImpl::matmul_graph(const std::vector<const HeCt*>& a, con
 // of them side by side take little longer than one.  (Merging only their key
 // inner products into shared launches, a host thread a product, left the
 // other nine tenths of the launches one after the other: seven products of
-// three sizes at N = 2^14 took 11.3 ms so, and take 8.4 ms side by side.)
+// three sizes at N = 2^14 took 11.3 ms so, and take 7.3 ms side by side.)  The
+// streams are the context's own, its ForkStream's and one more: a process has
+// four hardware queues, and streams that share one run one after the other
+// (with two new streams a context's product of d = 64 took 2.3 or 2.9 ms,
+// whichever queues they had met).
 void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   constexpr size_t LANES = 3;
   // a caller's allocator or stream knows nothing of other streams
-  if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect) {
+  if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect || pool.lanes_on) {
     for (const Job& j : jobs) j.run();
     return;
   }
   if (!lane_fork) hip_check(hipEventCreateWithFlags(&lane_fork, hipEventDisableTiming), "event");
-  while (lanes.size() < std::min(LANES, jobs.size())) {
+  const size_t nl = std::min(LANES, jobs.size());
+  while (lanes.size() + 1 < nl) {
     std::unique_ptr<Lane> l(new Lane);
-    hip_check(hipStreamCreateWithFlags(&l->stream, hipStreamNonBlocking), "stream");
+    l->own = !lanes.empty();
+    if (l->own) hip_check(hipStreamCreateWithFlags(&l->stream, hipStreamNonBlocking), "stream");
+    else l->stream = fork.aux;
     hip_check(hipEventCreateWithFlags(&l->done, hipEventDisableTiming), "event");
     l->pool.user_alloc = pool.user_alloc;
     l->pool.user_release = pool.user_release;
@@ -2213,10 +2224,10 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
     lanes.push_back(std::move(l));
     pool.subs.push_back(&lanes.back()->pool);
   }
-  const size_t nl = std::min(LANES, jobs.size());
   const hipStream_t main = stream;
   hip_check(hipEventRecord(lane_fork, main), "fork");
-  for (size_t i = 0; i < nl; i++) hip_check(hipStreamWaitEvent(lanes[i]->stream, lane_fork, 0), "fork");
+  for (size_t i = 0; i + 1 < nl; i++) hip_check(hipStreamWaitEvent(lanes[i]->stream, lane_fork, 0), "fork");
+  pool.lanes_on = true;
   // whatever happens, the context's stream goes on after the lanes
   struct Join {
     HeCtxImpl& c;
@@ -2225,10 +2236,13 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
     ~Join() {
       c.stream = main;
       c.pool.redirect = nullptr;
-      for (size_t i = 0; i < nl; i++)
+      for (size_t i = 0; i + 1 < nl; i++)
         if (hipEventRecord(c.lanes[i]->done, c.lanes[i]->stream) != hipSuccess ||
             hipStreamWaitEvent(main, c.lanes[i]->done, 0) != hipSuccess)
           (void)hipStreamSynchronize(c.lanes[i]->stream);
+      c.pool.lanes_on = false;
+      for (void* p : c.pool.deferred) c.pool.put(p);
+      c.pool.deferred.clear();
     }
   } join{*this, main, nl};
   std::vector<size_t> order(jobs.size());
@@ -2238,20 +2252,19 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   for (size_t t : order) {
     const size_t i = std::min_element(load.begin(), load.end()) - load.begin();
     load[i] += jobs[t].weight;
-    stream = lanes[i]->stream;
-    pool.redirect = &lanes[i]->pool;
+    stream = i ? lanes[i - 1]->stream : main;
+    pool.redirect = i ? &lanes[i - 1]->pool : nullptr;
     jobs[t].run();
   }
 }
 
 // The sides of a product do not depend on each other.  Side by side they fill
-// what one side's launches leave idle of the chip: d = 64 at N = 2^14 took 2.95
-// ms one after the other and takes 2.34 so, d = 128 at N = 2^16 83.3 and 81.4.
-// At N = 2^13 the launches are so short that crossing between streams costs
-// more (d = 16: 1.06 ms and 1.17); batches of N = 2^16 fill the chip alone and
+// what one side's launches leave idle of the chip: d = 16 at N = 2^13 took 1.09
+// ms one after the other and takes 0.93 so, d = 64 at N = 2^14 2.95 and 2.29, d
+// = 128 at N = 2^16 83.3 and 81.5.  Batches of N = 2^16 fill the chip alone and
 // would only hold both sides' temporaries at once.
 void HeCtxImpl::run_sides(const std::vector<Job>& jobs, int B) {
-  if ((u64)B * N <= (1ull << 16) && N >= (1ull << 14)) return run_lanes(jobs);
+  if ((u64)B * N <= (1ull << 16)) return run_lanes(jobs);
   for (const Job& j : jobs) j.run();
 }
 
