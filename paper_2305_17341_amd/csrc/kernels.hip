@@ -3454,6 +3454,30 @@ __device__ __forceinline__ u64 u128_reduce(const U128& x, const ModConst& m) {
 __device__ __forceinline__ u64 ldnt(const u64* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void stnt(u64* p, u64 v) { __builtin_nontemporal_store(v, p); }
 
+// A switching key's limbs of moduli below 2^46 are stored packed
+// (launch_key_pack): residue i of a limb as its low 32 bits in word i of the
+// limb's first 4 N bytes and the rest in a byte (16 bits above 2^40) of those
+// that follow, so that 5 (6) of every 8 bytes are read.  Whole words as
+// doubles needed no conversion, but the products of few members read little
+// else: d = 128 at N = 2^16 took 80.3 ms and takes 77.7, at N = 2^15
+// (dual-component) 12.8 and 12.6; batches of eight members, where the loads of
+// keys, digits and sums wait for each other, take as long (200.9 and 201.5).
+struct KeyWord {
+  u32 lo, hi;
+};
+__device__ __forceinline__ KeyWord ldkey(const u64* limb, u32 i, u64 N, bool wide) {
+  const unsigned char* hi = reinterpret_cast<const unsigned char*>(limb) + 4 * N;
+  KeyWord w;
+  w.lo = __builtin_nontemporal_load(reinterpret_cast<const u32*>(limb) + i);
+  w.hi = wide ? (u32) reinterpret_cast<const unsigned short*>(hi)[i] : (u32)hi[i];
+  return w;
+}
+// its double, from the bits of 2^52 + w
+__device__ __forceinline__ double key_f64(const KeyWord& w) {
+  return __hiloint2double((int)(0x43300000u | w.hi), (int)w.lo) - 0x1p52;
+}
+__device__ __forceinline__ bool key_wide(const ModConst& mk) { return mk.bits > 40; }
+
 template <int MB, bool F64>
 __device__ __forceinline__ void multsum_body(u64* out, const u64* __restrict__ digits, const u64* __restrict__ key,
                                              const u64* __restrict__ c0, const u64* __restrict__ pmod, int nq,
@@ -3468,18 +3492,19 @@ __device__ __forceinline__ void multsum_body(u64* out, const u64* __restrict__ d
 #pragma unroll
     for (int b = 0; b < MB; b++) s0[b] = s1[b] = 0.0;
     // software-pipelined: the loads of digit j + 1 are in flight while j is multiplied
-    u64 kbn = ldnt(&key[((size_t)0 * nmods + m) * N + i]), kan = ldnt(&key[((size_t)1 * nmods + m) * N + i]), dn[MB];
+    const bool wide = key_wide(mk);
+    KeyWord kbn = ldkey(key + (size_t)m * N, i, N, wide), kan = ldkey(key + ((size_t)nmods + m) * N, i, N, wide);
+    u64 dn[MB];
 #pragma unroll
     for (int b = 0; b < MB; b++) dn[b] = digits[(size_t)(b0 + b) * dstride + (size_t)pos * N + src];
     for (int j = 0; j < beta; j++) {
-      // FP64 limbs of a switching key hold doubles (launch_key_f64)
-      const double kb = __longlong_as_double((long long)kbn), ka = __longlong_as_double((long long)kan);
+      const double kb = key_f64(kbn), ka = key_f64(kan);
       double d[MB];
 #pragma unroll
       for (int b = 0; b < MB; b++) d[b] = __longlong_as_double((long long)dn[b]);  // centred double digits
       if (j + 1 < beta) {
-        kbn = ldnt(&key[(((size_t)(j + 1) * 2 + 0) * nmods + m) * N + i]);
-        kan = ldnt(&key[(((size_t)(j + 1) * 2 + 1) * nmods + m) * N + i]);
+        kbn = ldkey(key + (((size_t)(j + 1) * 2 + 0) * nmods + m) * N, i, N, wide);
+        kan = ldkey(key + (((size_t)(j + 1) * 2 + 1) * nmods + m) * N, i, N, wide);
 #pragma unroll
         for (int b = 0; b < MB; b++)
           dn[b] = digits[(size_t)(b0 + b) * dstride + ((size_t)(j + 1) * nqp + pos) * N + src];
@@ -3624,11 +3649,13 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
     for (int b = 0; b < MB; b++) s0[g][b] = s1[g][b] = 0.0;
   // software-pipelined as multsum_body: digit j + 1 and the keys at j + 1 in
   // flight while j is multiplied
-  u64 kbn[RPW], kan[RPW], dn[MB];
+  const bool wide = key_wide(mk);
+  KeyWord kbn[RPW], kan[RPW];
+  u64 dn[MB];
 #pragma unroll
   for (int g = 0; g < RPW; g++) {
-    kbn[g] = ldnt(&key[g][((size_t)0 * nmods + m) * N + idx[g]]);
-    kan[g] = ldnt(&key[g][((size_t)1 * nmods + m) * N + idx[g]]);
+    kbn[g] = ldkey(key[g] + (size_t)m * N, idx[g], N, wide);
+    kan[g] = ldkey(key[g] + ((size_t)nmods + m) * N, idx[g], N, wide);
   }
 #pragma unroll
   for (int b = 0; b < MB; b++) dn[b] = digits[R.dig[b] + (size_t)pos * N + src];
@@ -3636,16 +3663,16 @@ __device__ __forceinline__ void multsum_rot_group(const MultiRot& R, int r0, int
     double kb[RPW], ka[RPW], d[MB];
 #pragma unroll
     for (int g = 0; g < RPW; g++) {
-      kb[g] = __longlong_as_double((long long)kbn[g]);  // key limbs stored as doubles
-      ka[g] = __longlong_as_double((long long)kan[g]);
+      kb[g] = key_f64(kbn[g]);
+      ka[g] = key_f64(kan[g]);
     }
 #pragma unroll
     for (int b = 0; b < MB; b++) d[b] = __longlong_as_double((long long)dn[b]);  // centred double digits
     if (j + 1 < beta) {
 #pragma unroll
       for (int g = 0; g < RPW; g++) {
-        kbn[g] = ldnt(&key[g][(((size_t)(j + 1) * 2 + 0) * nmods + m) * N + idx[g]]);
-        kan[g] = ldnt(&key[g][(((size_t)(j + 1) * 2 + 1) * nmods + m) * N + idx[g]]);
+        kbn[g] = ldkey(key[g] + (((size_t)(j + 1) * 2 + 0) * nmods + m) * N, idx[g], N, wide);
+        kan[g] = ldkey(key[g] + (((size_t)(j + 1) * 2 + 1) * nmods + m) * N, idx[g], N, wide);
       }
 #pragma unroll
       for (int b = 0; b < MB; b++) dn[b] = digits[R.dig[b] + ((size_t)(j + 1) * nqp + pos) * N + src];
@@ -3727,11 +3754,13 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
   for (int g = 0; g < RPW; g++)
 #pragma unroll
     for (int b = 0; b < NB; b++) s0[g][b] = s1[g][b] = 0.0;
-  u64 kbn[RPW], kan[RPW], dn[NB];
+  const bool wide = key_wide(mk);
+  KeyWord kbn[RPW], kan[RPW];
+  u64 dn[NB];
 #pragma unroll
   for (int g = 0; g < RPW; g++) {
-    kbn[g] = ldnt(&key[g][((size_t)0 * nmods + m) * N + idx[g]]);
-    kan[g] = ldnt(&key[g][((size_t)1 * nmods + m) * N + idx[g]]);
+    kbn[g] = ldkey(key[g] + (size_t)m * N, idx[g], N, wide);
+    kan[g] = ldkey(key[g] + ((size_t)nmods + m) * N, idx[g], N, wide);
   }
 #pragma unroll
   for (int b = 0; b < NB; b++) dn[b] = dg[b / MB][R.dig[b % MB] + (size_t)pos * N + src];
@@ -3739,16 +3768,16 @@ __device__ __forceinline__ void multsum_rot_group_pair(const MultiRot& R, int r0
     double kb[RPW], ka[RPW], d[NB];
 #pragma unroll
     for (int g = 0; g < RPW; g++) {
-      kb[g] = __longlong_as_double((long long)kbn[g]);  // key limbs stored as doubles
-      ka[g] = __longlong_as_double((long long)kan[g]);
+      kb[g] = key_f64(kbn[g]);
+      ka[g] = key_f64(kan[g]);
     }
 #pragma unroll
     for (int b = 0; b < NB; b++) d[b] = __longlong_as_double((long long)dn[b]);  // centred double digits
     if (j + 1 < beta) {
 #pragma unroll
       for (int g = 0; g < RPW; g++) {
-        kbn[g] = ldnt(&key[g][(((size_t)(j + 1) * 2 + 0) * nmods + m) * N + idx[g]]);
-        kan[g] = ldnt(&key[g][(((size_t)(j + 1) * 2 + 1) * nmods + m) * N + idx[g]]);
+        kbn[g] = ldkey(key[g] + (((size_t)(j + 1) * 2 + 0) * nmods + m) * N, idx[g], N, wide);
+        kan[g] = ldkey(key[g] + (((size_t)(j + 1) * 2 + 1) * nmods + m) * N, idx[g], N, wide);
       }
 #pragma unroll
       for (int b = 0; b < NB; b++)
@@ -4301,18 +4330,20 @@ __device__ __forceinline__ void giant_f64(const GiantKeys& K, int t0, int dt, in
   const u64 N = 1ull << logN;
   const size_t dstride = (size_t)beta * nqp * N;
   const double q = mk.qf, qi = mk.qinvf;
-  u64 kbn[U], kan[U], dn[U][MB];
+  const bool wide = key_wide(mk);
+  KeyWord kbn[U], kan[U];
+  u64 dn[U][MB];
   u32 src = 0;
   auto load = [&](int t, int j0) {
     if (j0 == 0) src = automorph_src(i, K.g[t], logN);
-    const u64* key = K.key[t] + (size_t)m * N + i;
+    const u64* key = K.key[t] + (size_t)m * N;
     const u64* dg = digits + ((size_t)t * B + b0) * dstride + (size_t)pos * N + src;
 #pragma unroll
     for (int u = 0; u < U; u++) {
       const int j = j0 + u;
       if (U > 1 && j >= beta) break;
-      kbn[u] = ldnt(key + (size_t)(2 * j) * nmods * N);
-      kan[u] = ldnt(key + (size_t)(2 * j + 1) * nmods * N);
+      kbn[u] = ldkey(key + (size_t)(2 * j) * nmods * N, i, N, wide);
+      kan[u] = ldkey(key + (size_t)(2 * j + 1) * nmods * N, i, N, wide);
 #pragma unroll
       for (int b = 0; b < MB; b++) dn[u][b] = dg[(size_t)b * dstride + (size_t)j * nqp * N];
     }
@@ -4323,7 +4354,8 @@ __device__ __forceinline__ void giant_f64(const GiantKeys& K, int t0, int dt, in
 #pragma unroll
     for (int b = 0; b < MB; b++) cw[b] = pos < nq ? c0[(((size_t)t * B + b0 + b) * nq + pos) * N + src] : 0;
     for (int j0 = 0; j0 < beta; j0 += U) {
-      u64 kb[U], ka[U], d[U][MB];
+      KeyWord kb[U], ka[U];
+      u64 d[U][MB];
 #pragma unroll
       for (int u = 0; u < U; u++) {
         kb[u] = kbn[u];
@@ -4336,7 +4368,7 @@ __device__ __forceinline__ void giant_f64(const GiantKeys& K, int t0, int dt, in
 #pragma unroll
       for (int u = 0; u < U; u++) {
         if (U > 1 && j0 + u >= beta) break;
-        const double fb = __longlong_as_double((long long)kb[u]), fa = __longlong_as_double((long long)ka[u]);
+        const double fb = key_f64(kb[u]), fa = key_f64(ka[u]);
 #pragma unroll
         for (int b = 0; b < MB; b++) {
           const double fd = __longlong_as_double((long long)d[u][b]);  // centred double digits
@@ -4847,21 +4879,26 @@ void launch_swk_b(const DeviceTables& T, u64* b, const u64* a, const u64* e, con
   hipLaunchKernelGGL(k_swk_b, grid, dim3(TPB), 0, s, b, a, e, s_ntt, sp_ntt, pmod, digit, alpha, L, T.logN, T.mc);
 }
 
-// A switching key's limbs of at most F64_LAZY_BITS bits rewritten in place as
-// the IEEE doubles of their residues (exact below 2^53): the key inner
-// products read them as FP64 operands with no conversion.  The 60-bit limbs
-// stay integers.
-__global__ void k_key_f64(u64* key, int nmods, int logN, const ModConst* __restrict__ mc) {
+// limbs of a switching key in the form the key inner products read them
+// (KeyWord; the 60-bit limbs stay whole words)
+__global__ void k_key_pack(u64* key, const u64* __restrict__ in, int nmods, int logN, const ModConst* __restrict__ mc) {
   const u64 N = 1ull << logN;
   const u32 i = blockIdx.x * TPB + threadIdx.x;
-  const int m = (int)blockIdx.y % nmods;
-  if (i >= N || mc[m].bits > F64_LAZY_BITS) return;
-  u64* p = key + (size_t)blockIdx.y * N + i;
-  *p = (u64)__double_as_longlong((double)*p);
+  if (i >= N) return;
+  const ModConst mk = mc[(int)blockIdx.y % nmods];
+  u64* limb = key + (size_t)blockIdx.y * N;
+  const u64 w = in[(size_t)blockIdx.y * N + i];
+  if (mk.bits > F64_LAZY_BITS) {
+    limb[i] = w;
+    return;
+  }
+  unsigned char* hi = reinterpret_cast<unsigned char*>(limb) + 4 * N;
+  reinterpret_cast<u32*>(limb)[i] = (u32)w;
+  if (key_wide(mk)) reinterpret_cast<unsigned short*>(hi)[i] = (unsigned short)(w >> 32);
+  else hi[i] = (unsigned char)(w >> 32);
 }
-void launch_key_f64(const DeviceTables& T, u64* key, int nblocks, int nmods, hipStream_t s) {
-  dim3 grid(cdiv(T.N, TPB), nblocks * nmods);
-  hipLaunchKernelGGL(k_key_f64, grid, dim3(TPB), 0, s, key, nmods, T.logN, T.mc);
+void launch_key_pack(const DeviceTables& T, u64* key, const u64* in, int nblocks, int nmods, hipStream_t s) {
+  hipLaunchKernelGGL(k_key_pack, dim3(cdiv(T.N, TPB), nblocks * nmods), dim3(TPB), 0, s, key, in, nmods, T.logN, T.mc);
 }
 
 // centred integer of one coefficient-domain limb

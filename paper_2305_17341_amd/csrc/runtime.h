@@ -134,7 +134,7 @@ struct HeCtxImpl {
   DevBuf up_scale;  // [level][nmods][2]: N^-1 hatinv_t mod q_t (Decompose's digit sources)
   DevBuf s_ntt, pk;
   bool have_sk = false;
-  std::map<u64, DevBuf> keys;             // Galois element -> key; 0 = relinearisation (FP64 limbs as doubles)
+  std::map<u64, DevBuf> keys;             // Galois element -> key; 0 = relinearisation (FP64 limbs packed: launch_key_pack)
   std::map<std::string, const u64*> ptcache;
   std::vector<DevBuf> ptbanks;  // plaintexts made together, one after the other
   // a transform's diagonals present (giant, baby step) and their plaintexts

@@ -750,16 +750,15 @@ void HeCtxImpl::swk_gen(const u64* sp, u64 kid, DevBuf& out) {
   LimbMap all;
   all.n = nmods;
   for (int m = 0; m < nmods; m++) all.idx[m] = (short)m;
-  DevBuf e(&pool, N), en(&pool, (size_t)nmods * N);
+  DevBuf e(&pool, N), en(&pool, (size_t)nmods * N), ba(&pool, (size_t)2 * nmods * N);
+  u64 *bj = ba.p, *aj = ba.p + (size_t)nmods * N;
   for (int j = 0; j < beta; j++) {
-    u64* bj = out.p + ((size_t)j * 2 + 0) * nmods * N;
-    u64* aj = out.p + ((size_t)j * 2 + 1) * nmods * N;
     launch_sample_uniform(T, aj, nmods, all, seed, TAG_SWK_A, (u64)j, kid, stream);
     launch_sample_gauss(T, (i64*)e.p, seed, TAG_SWK_E, 0, (u64)j, kid, stream);
     int_to_ntt(en.p, (const i64*)e.p, all);
     launch_swk_b(T, bj, aj, en.p, s_ntt.p, sp, pmod.p, nmods, j, alpha, L, stream);
+    launch_key_pack(T, out.p + (size_t)j * 2 * nmods * N, ba.p, 2, nmods, stream);
   }
-  launch_key_f64(T, out.p, beta * 2, nmods, stream);
 }
 
 void HeCtxImpl::keygen_relin() {

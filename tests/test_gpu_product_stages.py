@@ -164,3 +164,25 @@ def test_power_blocks_together_match_oracle(oracle_mod, axis, level, v_level):
     for i in range(k):
         assert gV[i].level == oV[i].ct.level and gV[i].scale == oV[i].ct.scale
         assert np.array_equal(gV[i].export(), oV[i].ct.data()), i
+
+
+@pytest.mark.parametrize("bits", [(60, 46, 41, 40, 33), (45, 45, 45, 45, 45), (60, 40, 32, 38, 46)], ids=str)
+def test_key_words_of_all_sizes_match_oracle(oracle_mod, bits):
+    """switching keys over moduli of 32 to 46 bits (packed in a byte or two
+    above 32) and 60: a rotation, a product, hoisted rotations and a transform"""
+    from paper_2305_17341_amd import he
+    n, ch = 16, I.Chain("keys", 12, bits, (60, 46))
+    steps = sorted(set(he.lintrans_rot_steps("Z", n, 4)) | {1, 3, -5})
+    ctx = he.Context(ch.log_n, ch.q_bits, ch.p_bits, 30.0, seed=78)
+    ctx.keygen(steps)
+    o = oracle_mod.Oracle(ch.log_n, ch.q_bits, ch.p_bits, log2_scale=30.0, seed=78)
+    o.keygen(rot_steps=steps)
+    A = I.uniform_matrix(6, n)
+    x, y = ctx.encrypt_matrix(A, nonce=1), o.encrypt(A.ravel(), nonce=1)
+    assert np.array_equal(ctx.rotate(x, 3).export(), o.rotate(y, 3).data())
+    assert np.array_equal(ctx.mult(x, x).export(), o.mult(y, y).data())
+    many = ctx.rotate_many([x, x], [1, 3, -5])
+    for r, s in enumerate([1, 3, -5]):
+        for member in many:
+            assert np.array_equal(member[r].export(), o.rotate(y, s).data())
+    assert np.array_equal(ctx.lintrans(x, "sigma", n, 4).export(), o.lt_sigma(y, n, 4).data())
