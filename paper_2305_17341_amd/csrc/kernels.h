@@ -82,9 +82,6 @@ void launch_mul(const DeviceTables& T, u64* out, const u64* a, const u64* b, int
 // out = a * b where b has period b_limbs (b limb = k % b_limbs)
 void launch_mul_bcast(const DeviceTables& T, u64* out, const u64* a, const u64* b, int nlimbs, int b_limbs,
                       const LimbMap& m, hipStream_t s);
-// acc += a * b (b broadcast with period b_limbs)
-void launch_mul_acc(const DeviceTables& T, u64* acc, const u64* a, const u64* b, int nlimbs, int b_limbs,
-                    const LimbMap& m, hipStream_t s);
 // out (+)= sum_t a[t] * p[t] (p[t] broadcast with period b_limbs), nterms pairs;
 // the second half of the output limbs lies `skip` words further on (an
 // element of a batch whose two components stand apart)
@@ -97,11 +94,6 @@ void launch_mul_sum(const DeviceTables& T, u64* out, const u64* const* a, const 
 bool launch_mul_sum_multi(const DeviceTables& T, u64* const* outs, int nouts, const u64* const* a,
                           const u64* const* p, int nterms, int nlimbs, int b_limbs, const LimbMap& m,
                           hipStream_t s, const size_t* skips = nullptr);
-// out = a * c_k for a per-limb constant (host array, Shoup)
-void launch_mul_const(const DeviceTables& T, u64* out, const u64* a, int nlimbs, const u64* consts /*[map.n]*/,
-                      const LimbMap& m, hipStream_t s);
-void launch_neg(const DeviceTables& T, u64* out, const u64* a, int nlimbs, const LimbMap& m, hipStream_t s);
-// batch pairs of ciphertexts [2][batch][nl] -> [3][batch][nl] (accumulate: added onto out3)
 // sum of npairs tensors (a[p], b[p] over Q_l, [2][B][nl] each) into the
 // three-component [3][B][nl] out3, or added onto it; a_packed[p] (b_packed)
 // set: a[p]'s limbs of FP64 moduli are stored packed (the fused ModDown's
@@ -117,8 +109,8 @@ void launch_tensor_top(const DeviceTables& T, u64* out, const u64* const* a, con
                        int batch, hipStream_t s);
 void launch_relin_sum(const DeviceTables& T, u64* out, const u64* const* a, const u64* const* b, const u64* ks,
                       int npairs, int nl, int batch, bool accumulate, hipStream_t s);
-void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, bool accumulate,
-                   hipStream_t s);
+// the tensors of batch pairs of ciphertexts, [2][batch][nl] each: [3][batch][nl]
+void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, hipStream_t s);
 // out [npoly][nlimbs][N] from in [npoly][N]
 void launch_int_to_limbs(const DeviceTables& T, u64* out, const i64* in, int nlimbs, const LimbMap& m, hipStream_t s,
                          int npoly = 1);
@@ -181,9 +173,6 @@ bool launch_moddown_fused(const DeviceTables& T, const u64* xp_coef, int nq, int
 // y[npoly][nq] = exact centred lift of the source limbs xp[npoly][ns] to each q_t
 void launch_fbc_to_q(const DeviceTables& T, u64* y, const u64* xp_coef, int nq, int npoly, const FbcTable& tab,
                      hipStream_t s);
-void launch_moddown_final(const DeviceTables& T, u64* out, const u64* x, const u64* y, int nq,
-                          const u64* pinv /*device [nmods] Shoup pairs*/, int npoly, int x_stride_limbs,
-                          hipStream_t s);
 // hoisted rotation: out[2][nqp][N] = sum_j pi_g(d_j) * key_j (+ P pi_g(c0) on Q limbs)
 void launch_multsum(const DeviceTables& T, u64* out, const u64* digits, const u64* key, const u64* c0,
                     const u64* pmod /*device [nmods][2]*/, int level, int L, int alpha, int beta, u64 g,
@@ -245,8 +234,6 @@ void launch_rescale_lift(const DeviceTables& T, u64* t, const u64* top_coef, int
 // register-blocked NTT
 bool launch_rescale_fused(const DeviceTables& T, u64* t, const u64* top_coef, int l, int nout, int npoly,
                           const u64* x, int x_stride, const u64* cpairs, u64* out, hipStream_t s);
-void launch_rescale_final(const DeviceTables& T, u64* out, const u64* x, const u64* t, int l, int npoly,
-                          int x_stride_limbs, const u64* qlinv /*device [l][2]*/, hipStream_t s);
 
 // randomness (Philox4x64-10, counter = (coefficient, c1, c2, c3), key = (seed, tag))
 void launch_sample_uniform(const DeviceTables& T, u64* out, int nlimbs, const LimbMap& m, u64 seed, u64 tag,

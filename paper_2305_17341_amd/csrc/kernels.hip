@@ -1848,7 +1848,7 @@ void launch_automorph(const DeviceTables& T, u64* out, const u64* in, int nlimbs
 // ---------------------------------------------------------------------------
 // Elementwise
 // ---------------------------------------------------------------------------
-enum { EW_ADD = 0, EW_SUB, EW_MUL, EW_MULACC, EW_NEG };
+enum { EW_ADD = 0, EW_SUB, EW_MUL };
 
 __global__ void k_elementwise(int op, u64* out, const u64* a, const u64* b, int nlimbs, int b_limbs, LimbMap map,
                               int logN, const ModConst* __restrict__ mc, int il) {
@@ -1866,18 +1866,15 @@ __global__ void k_elementwise(int op, u64* out, const u64* a, const u64* b, int 
     case EW_ADD: out[o] = add_mod(a[o], b[ob], mk.q); break;
     case EW_SUB: out[o] = sub_mod(a[o], b[ob], mk.q); break;
     case EW_MUL: out[o] = mul_mod_any(a[o], b[ob], mk); break;
-    case EW_MULACC: out[o] = add_mod(out[o], mul_mod_any(a[o], b[ob], mk), mk.q); break;
-    case EW_NEG: out[o] = a[o] ? mk.q - a[o] : 0; break;
   }
 }
 
 static void ew(const DeviceTables& T, int op, u64* out, const u64* a, const u64* b, int nlimbs, int b_limbs,
                const LimbMap& m, hipStream_t s) {
   if (nlimbs <= 0) return;
-  // reads a (and b once per distinct limb), writes out; the accumulate also reads out
-  double words = (double)nlimbs * (op == EW_MULACC ? 3 : (op == EW_NEG ? 2 : 2)) + (op == EW_NEG ? 0 : b_limbs);
-  ProfScope ps("elementwise", s, 8.0 * T.N * words,
-               op == EW_MUL || op == EW_MULACC ? mm_map(T, m, nlimbs, (double)T.N) : Mm());
+  // reads a (and b once per distinct limb), writes out
+  ProfScope ps("elementwise", s, 8.0 * T.N * (2.0 * nlimbs + b_limbs),
+               op == EW_MUL ? mm_map(T, m, nlimbs, (double)T.N) : Mm());
   int il;
   dim3 grid = sum_grid((int)cdiv(T.N, TPB), nlimbs, b_limbs, g_knobs.ew_interleave, il);
   hipLaunchKernelGGL(k_elementwise, grid, dim3(TPB), 0, s, op, out, a, b, nlimbs, b_limbs, m, T.logN, T.mc, il);
@@ -1890,8 +1887,6 @@ void launch_mul(const DeviceTables& T, u64* out, const u64* a, const u64* b, int
                 hipStream_t s) { ew(T, EW_MUL, out, a, b, nl, nl, m, s); }
 void launch_mul_bcast(const DeviceTables& T, u64* out, const u64* a, const u64* b, int nl, int bl,
                       const LimbMap& m, hipStream_t s) { ew(T, EW_MUL, out, a, b, nl, bl, m, s); }
-void launch_mul_acc(const DeviceTables& T, u64* acc, const u64* a, const u64* b, int nl, int bl, const LimbMap& m,
-                    hipStream_t s) { ew(T, EW_MULACC, acc, a, b, nl, bl, m, s); }
 // out = sum_t a_t (.) p_t (p_t broadcast with period b_limbs), one pass over
 // every operand; `accumulate` adds onto out
 struct SumTerms {
@@ -2140,40 +2135,8 @@ bool launch_mul_sum_multi(const DeviceTables& T, u64* const* outs, int nouts, co
   return true;
 }
 
-void launch_neg(const DeviceTables& T, u64* out, const u64* a, int nl, const LimbMap& m, hipStream_t s) {
-  ew(T, EW_NEG, out, a, a, nl, nl, m, s);
-}
-
-struct ConstPairs {
-  u64 w[HE_MAXMOD * 2];
-};
-__global__ void k_mul_const(u64* out, const u64* a, int nlimbs, ConstPairs c, LimbMap map, int logN,
-                            const ModConst* __restrict__ mc) {
-  const u64 N = 1ull << logN;
-  u32 i = blockIdx.x * TPB + threadIdx.x;
-  int k = blockIdx.y;
-  if (i >= N || k >= nlimbs) return;
-  int m = limb_mod(map, k);
-  if (m < 0) return;
-  int ci = k % map.n;
-  size_t o = (size_t)k * N + i;
-  out[o] = mul_const_any(a[o], c.w[2 * ci], c.w[2 * ci + 1], mc[m]);
-}
-void launch_mul_const(const DeviceTables& T, u64* out, const u64* a, int nlimbs, const u64* consts,
-                      const LimbMap& m, hipStream_t s) {
-  ConstPairs c;
-  for (int k = 0; k < m.n && k < HE_MAXMOD; k++) {
-    c.w[2 * k] = consts[2 * k];
-    c.w[2 * k + 1] = consts[2 * k + 1];
-  }
-  dim3 grid(cdiv(T.N, TPB), nlimbs);
-  ProfScope ps("elementwise", s, 16.0 * T.N * nlimbs, mm_map(T, m, nlimbs, (double)T.N));
-  hipLaunchKernelGGL(k_mul_const, grid, dim3(TPB), 0, s, out, a, nlimbs, c, m, T.logN, T.mc);
-}
-
 // Tensor of B pairs of ciphertexts over Q_l ([2][B][nl] each):
-// (a0 b0, a0 b1 + a1 b0, a1 b1) into [3][B][nl], or added onto it (ACC)
-template <bool ACC>
+// (a0 b0, a0 b1 + a1 b0, a1 b1) into [3][B][nl]
 __global__ void k_tensor(u64* out, const u64* a, const u64* b, int nl, int nt, int logN,
                          const ModConst* __restrict__ mc) {
   const u64 N = 1ull << logN;
@@ -2190,11 +2153,6 @@ __global__ void k_tensor(u64* out, const u64* a, const u64* b, int nl, int nt, i
     double s0 = f64_mulmod_signed(x0, y0, q, qi);
     double s1 = f64_mulmod_signed(x0, y1, q, qi) + f64_mulmod_signed(x1, y0, q, qi);
     double s2 = f64_mulmod_signed(x1, y1, q, qi);
-    if (ACC) {
-      s0 += u2d(out[o0]);
-      s1 += u2d(out[o1]);
-      s2 += u2d(out[o2]);
-    }
     out[o0] = d2u(f64_canon(s0, q, qi));
     out[o1] = d2u(f64_canon(s1, q, qi));
     out[o2] = d2u(f64_canon(s2, q, qi));
@@ -2203,11 +2161,6 @@ __global__ void k_tensor(u64* out, const u64* a, const u64* b, int nl, int nt, i
   u64 t0 = mul_mod_any(a0, b0, mk);
   u64 t1 = add_mod(mul_mod_any(a0, b1, mk), mul_mod_any(a1, b0, mk), mk.q);
   u64 t2 = mul_mod_any(a1, b1, mk);
-  if (ACC) {
-    t0 = add_mod(t0, out[o0], mk.q);
-    t1 = add_mod(t1, out[o1], mk.q);
-    t2 = add_mod(t2, out[o2], mk.q);
-  }
   out[o0] = t0;
   out[o1] = t1;
   out[o2] = t2;
@@ -2386,13 +2339,10 @@ void launch_tensor_sum(const DeviceTables& T, u64* out3, const u64* const* a, co
   }
 }
 
-void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, bool accumulate,
-                   hipStream_t s) {
+void launch_tensor(const DeviceTables& T, u64* out3, const u64* a, const u64* b, int nl, int batch, hipStream_t s) {
   const int nt = nl * batch;
-  ProfScope ps("tensor", s, 8.0 * T.N * (accumulate ? 10 : 7) * nt, mm_q(T, nl, 4.0 * T.N, batch));
-  dim3 grid(cdiv(T.N, TPB), nt);
-  if (accumulate) hipLaunchKernelGGL(k_tensor<true>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
-  else hipLaunchKernelGGL(k_tensor<false>, grid, dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
+  ProfScope ps("tensor", s, 8.0 * T.N * 7 * nt, mm_q(T, nl, 4.0 * T.N, batch));
+  hipLaunchKernelGGL(k_tensor, dim3(cdiv(T.N, TPB), nt), dim3(TPB), 0, s, out3, a, b, nl, nt, T.logN, T.mc);
 }
 
 // Words to a pinned host buffer (the link bounds it at 55 GB/s): two a thread
@@ -3412,12 +3362,6 @@ __global__ void k_moddown_final(u64* out, const u64* x, const u64* y, int nq, co
   u64 q = mc[t].q;
   u64 d = sub_mod(x[((size_t)p * x_stride_limbs + t) * N + i], y[((size_t)p * nq + t) * N + i], q);
   out[((size_t)p * nq + t) * N + i] = mul_const_any(d, pinv[2 * t], pinv[2 * t + 1], mc[t]);
-}
-void launch_moddown_final(const DeviceTables& T, u64* out, const u64* x, const u64* y, int nq, const u64* pinv,
-                          int npoly, int x_stride_limbs, hipStream_t s) {
-  ProfScope ps("moddown_final", s, 8.0 * T.N * 3.0 * npoly * nq, mm_q(T, nq, (double)T.N, npoly));
-  dim3 grid(cdiv(T.N, TPB), nq, npoly);
-  hipLaunchKernelGGL(k_moddown_final, grid, dim3(TPB), 0, s, out, x, y, nq, pinv, x_stride_limbs, T.logN, T.mc);
 }
 
 // Hoisted rotation in R_{Q_l P} of MB batch members sharing one key: for each
@@ -4629,23 +4573,6 @@ void launch_rescale_lift(const DeviceTables& T, u64* t, const u64* top_coef, int
   dim3 grid(cdiv(T.N, TPB), nout, npoly);
   hipLaunchKernelGGL(k_rescale_lift, grid, dim3(TPB), 0, s, t, top_coef, l, nout, T.logN, T.mc);
 }
-__global__ void k_rescale_final(u64* out, const u64* x, const u64* t, int l, int x_stride_limbs, const u64* qlinv,
-                                int logN, const ModConst* __restrict__ mc) {
-  const u64 N = 1ull << logN;
-  u32 i = blockIdx.x * TPB + threadIdx.x;
-  int k = blockIdx.y, p = blockIdx.z;
-  if (i >= N) return;
-  u64 q = mc[k].q;
-  u64 d = sub_mod(x[((size_t)p * x_stride_limbs + k) * N + i], t[((size_t)p * l + k) * N + i], q);
-  out[((size_t)p * l + k) * N + i] = mul_const_any(d, qlinv[2 * k], qlinv[2 * k + 1], mc[k]);
-}
-void launch_rescale_final(const DeviceTables& T, u64* out, const u64* x, const u64* t, int l, int npoly,
-                          int x_stride_limbs, const u64* qlinv, hipStream_t s) {
-  ProfScope ps("rescale_final", s, 8.0 * T.N * npoly * 3.0 * l, mm_q(T, l, (double)T.N, npoly));
-  dim3 grid(cdiv(T.N, TPB), l, npoly);
-  hipLaunchKernelGGL(k_rescale_final, grid, dim3(TPB), 0, s, out, x, t, l, x_stride_limbs, qlinv, T.logN, T.mc);
-}
-
 // Rescale with the lift fused into the forward column pass: the value of
 // limb k at a coefficient is the centred top-limb residue reduced mod q_k,
 // computed while filling the tile; the block pass ends with (x - t) q_l^-1.

@@ -1166,7 +1166,7 @@ HeCt HeCtxImpl::mult(const HeCt& a, const HeCt& b) {
   if (a.qp) fail(HE_EINVAL, "mult of R_QP elements");
   int nl = a.nlimbs, nt = a.B * nl;
   DevBuf t3(&pool, (size_t)3 * nt * N);
-  launch_tensor(T, t3.p, a.d.p, b.d.p, nl, a.B, false, stream);
+  launch_tensor(T, t3.p, a.d.p, b.d.p, nl, a.B, stream);
   HeCt c = keyswitch(t3.p + (size_t)2 * nt * N, a.level, 0, a.B, t3.p);
   c.scale = a.scale * b.scale;
   return c;
