@@ -36,17 +36,24 @@ void* DevPool::get(size_t bytes) {
     peak = std::max(peak, bump_off);
     return p;
   }
-  auto it = free_.lower_bound(bytes);
-  if (it != free_.end() && it->first <= (exact ? bytes : bytes + bytes / 4)) {
+  auto take = [&](DevPool& from) -> void* {
+    auto it = from.free_.lower_bound(bytes);
+    if (it == from.free_.end() || it->first > (exact ? bytes : bytes + bytes / 4)) return nullptr;
     void* p = it->second;
     size_t sz = it->first;
-    free_.erase(it);
-    bytes_cached -= sz;
+    from.free_.erase(it);
+    from.bytes_cached -= sz;
     live_[p] = sz;
     bytes_live += sz;
     note_peak();
     return p;
-  }
+  };
+  if (void* p = take(*this)) return p;
+  // the context's stream has met the side streams: their free blocks are its
+  // own as well then
+  if (!lanes_on)
+    for (DevPool* s : subs)
+      if (void* p = take(*s)) return p;
   if (frozen) fail(HE_ENOMEM, "graph arena exhausted while recording");
   void* p = nullptr;
   for (int attempt = 0; attempt < 2; attempt++) {
