@@ -182,6 +182,10 @@ struct DevPool {
   // their own are kept until they have met again
   bool lanes_on = false;
   std::vector<void*> deferred;
+  // the blocks that were free when the streams parted: any of them may take one
+  std::multimap<size_t, void*> common_;
+  void part();  // from now on the streams run side by side
+  void meet();  // the context's stream has waited for the others
   void* get(size_t bytes);
   void put(void* p);
   void trim();

@@ -36,24 +36,28 @@ void* DevPool::get(size_t bytes) {
     peak = std::max(peak, bump_off);
     return p;
   }
-  auto take = [&](DevPool& from) -> void* {
-    auto it = from.free_.lower_bound(bytes);
-    if (it == from.free_.end() || it->first > (exact ? bytes : bytes + bytes / 4)) return nullptr;
+  auto take = [&](DevPool& from, std::multimap<size_t, void*>& blocks) -> void* {
+    auto it = blocks.lower_bound(bytes);
+    if (it == blocks.end() || it->first > (exact ? bytes : bytes + bytes / 4)) return nullptr;
     void* p = it->second;
     size_t sz = it->first;
-    from.free_.erase(it);
+    blocks.erase(it);
     from.bytes_cached -= sz;
     live_[p] = sz;
     bytes_live += sz;
     note_peak();
     return p;
   };
-  if (void* p = take(*this)) return p;
-  // the context's stream has met the side streams: their free blocks are its
-  // own as well then
-  if (!lanes_on)
+  if (void* p = take(*this, free_)) return p;
+  DevPool& root = parent ? *parent : *this;
+  if (root.lanes_on) {
+    if (void* p = take(root, root.common_)) return p;
+  } else {
+    // the context's stream has met the side streams: their free blocks are its
+    // own as well then
     for (DevPool* s : subs)
-      if (void* p = take(*s)) return p;
+      if (void* p = take(*s, s->free_)) return p;
+  }
   if (frozen) fail(HE_ENOMEM, "graph arena exhausted while recording");
   void* p = nullptr;
   for (int attempt = 0; attempt < 2; attempt++) {
@@ -107,6 +111,23 @@ void DevPool::put(void* p) {
   free_.insert({sz, p});
   bytes_cached += sz;
 }
+void DevPool::part() {
+  for (DevPool* s : subs) {
+    for (auto& kv : s->free_) free_.insert(kv);
+    bytes_cached += s->bytes_cached;
+    s->free_.clear();
+    s->bytes_cached = 0;
+  }
+  common_.swap(free_);
+  lanes_on = true;
+}
+void DevPool::meet() {
+  lanes_on = false;
+  for (auto& kv : common_) free_.insert(kv);
+  common_.clear();
+  for (void* p : deferred) put(p);
+  deferred.clear();
+}
 void DevPool::wait() {
   if (parent && parent->stream) (void)hipStreamSynchronize(parent->stream);
   for (DevPool* s : subs) (void)hipStreamSynchronize(s->stream);
@@ -115,6 +136,8 @@ void DevPool::wait() {
 }
 void DevPool::trim() {
   for (DevPool* s : subs) s->trim();
+  for (auto& kv : common_) free_.insert(kv);
+  common_.clear();
   if (free_.empty()) return;
   wait();
   for (auto& kv : free_) {
@@ -2233,7 +2256,7 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   const hipStream_t main = stream;
   hip_check(hipEventRecord(lane_fork, main), "fork");
   for (size_t i = 0; i + 1 < nl; i++) hip_check(hipStreamWaitEvent(lanes[i]->stream, lane_fork, 0), "fork");
-  pool.lanes_on = true;
+  pool.part();
   // whatever happens, the context's stream goes on after the lanes
   struct Join {
     HeCtxImpl& c;
@@ -2246,9 +2269,7 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
         if (hipEventRecord(c.lanes[i]->done, c.lanes[i]->stream) != hipSuccess ||
             hipStreamWaitEvent(main, c.lanes[i]->done, 0) != hipSuccess)
           (void)hipStreamSynchronize(c.lanes[i]->stream);
-      c.pool.lanes_on = false;
-      for (void* p : c.pool.deferred) c.pool.put(p);
-      c.pool.deferred.clear();
+      c.pool.meet();
     }
   } join{*this, main, nl};
   std::vector<size_t> order(jobs.size());
