@@ -424,7 +424,9 @@ he_status he_knob_get(const char* name, int32_t* value);
 
 /* wait for all work of the context */
 he_status he_sync(he_ctx* ctx);
-/* device bytes held by the context (live, cached, peak) */
+/* device bytes held by the context: in use (live), free but kept (cached), and
+ * the largest number in use at once since he_trim (peak; where parts of a call
+ * run side by side on streams of the context, the sum of what each needs) */
 he_status he_mem_info(const he_ctx* ctx, size_t* live, size_t* cached, size_t* peak);
 /* free and total bytes of the current HIP device */
 he_status he_device_memory(size_t* free_bytes, size_t* total_bytes);

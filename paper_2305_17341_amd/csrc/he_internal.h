@@ -151,7 +151,10 @@ __device__ __forceinline__ u64 reduce_signed(i64 v, const ModConst& m) {
 struct DevPool {
   std::multimap<size_t, void*> free_;
   std::map<void*, size_t> live_;
-  size_t bytes_live = 0, bytes_cached = 0, peak = 0;
+  // peak (the context's pool): the largest number of bytes in use at once.
+  // Streams side by side reach their own largest numbers (high, since they
+  // parted) at any time, whatever the order they were queued in: their sum then.
+  size_t bytes_live = 0, bytes_cached = 0, peak = 0, high = 0;
   void* (*user_alloc)(size_t, void*) = nullptr;
   void (*user_release)(void*, void*) = nullptr;
   void* user = nullptr;
@@ -186,6 +189,22 @@ struct DevPool {
   std::multimap<size_t, void*> common_;
   void part();  // from now on the streams run side by side
   void meet();  // the context's stream has waited for the others
+  // Scratch: while a ScratchScope stands, blocks are cut out of segments kept
+  // for that, and parts that are free again are joined.  A stage's temporaries
+  // have other sizes at each step, so whole blocks kept by size added up to
+  // twice what a product needs at once (one of d = 128 at N = 2^16 took 18.0
+  // GiB from the device, and takes 11.4 for the 11.0 of its two sides; one of
+  // d = 16 there 8.4 and 4.4; the times are the same).  Not over a caller's
+  // allocator (it may do the same itself), nor in a recording's arena.
+  int scratch = 0;                  // ScratchScopes standing (of the context's pool)
+  std::map<char*, size_t> segs_;    // segment -> bytes
+  std::map<char*, size_t> gaps_;    // free part of a segment -> bytes
+  std::map<void*, size_t> cut_;     // block cut out -> bytes
+  void* cut(size_t bytes);          // out of a gap; null if none is large enough
+  bool rejoin(void* p);             // false: not a block cut out here
+  void reserve(size_t bytes);       // a gap of so many bytes, where the device has them
+  void drop_segments(bool all);     // those that nothing is cut out of (or all)
+  void* obtain(size_t bytes);       // from the device or the caller's allocator
   void* get(size_t bytes);
   void put(void* p);
   void trim();
@@ -195,6 +214,25 @@ struct DevPool {
   size_t total_cached() const;
   void note_peak();
   ~DevPool();
+};
+
+// temporaries of a stage come from scratch (see DevPool) until the scope ends
+struct ScratchScope {
+  DevPool& pool;
+  explicit ScratchScope(DevPool& p, size_t bytes = 0) : pool(p) {
+    if (bytes) pool.reserve(bytes);
+    pool.scratch++;
+  }
+  ~ScratchScope() { pool.scratch--; }
+  ScratchScope(const ScratchScope&) = delete;
+};
+// ... but what outlives it comes from the pool's blocks
+struct KeepScope {
+  DevPool& pool;
+  int was;
+  explicit KeepScope(DevPool& p) : pool(p), was(p.scratch) { pool.scratch = 0; }
+  ~KeepScope() { pool.scratch = was; }
+  KeepScope(const KeepScope&) = delete;
 };
 
 struct DevBuf {

@@ -1,5 +1,6 @@
 // Host runtime declarations (internal).
 #pragma once
+#include <algorithm>
 #include <functional>
 #include <list>
 #include <memory>
@@ -176,7 +177,21 @@ struct HeCtxImpl {
   u64* table_upload(const void* host, size_t bytes);
 
   size_t stage_count(size_t per_element, size_t elements) const;
+  // scratch of a transform (babies, giant: its steps present) and of a side's
+  // shifts (sides bases a block, n1 shifts a block), in bytes
+  size_t giant_count(int level, int B, size_t giant) const;
+  size_t lintrans_scratch(int level, int B, size_t babies, size_t giant) const;
+  size_t shift_scratch(int level, int sides, int B, int blocks, int n1, bool rescale_apart) const;
+  // device bytes of a product's side: its results, kept until the tensors are
+  // summed, and its temporaries
+  struct SideBytes {
+    size_t keep = 0, scratch = 0;
+    SideBytes operator+(const SideBytes& o) const { return {keep + o.keep, std::max(scratch, o.scratch)}; }
+  };
+  SideBytes side_bytes(bool a_side, int level, int out_level, int B, int n, int n1, int nprime, bool fused_rs = false,
+                       bool folded = false) const;
   HeCt ct_new(int level, bool qp, double scale, int B = 1);
+  HeCt ct_at(u64* at, int level, double scale, int B);
   HeCt ct_copy(const HeCt& x);
   // `count` consecutive elements of B members from element `first` of the
   // elements stacked in `whole` (shaped like `like`)
@@ -201,7 +216,8 @@ struct HeCtxImpl {
   HeCt add(const HeCt& a, const HeCt& b, bool sub);
   void add_into(HeCt& acc, const HeCt& b);
   HeCt drop(const HeCt& a, int level);
-  HeCt rescale(const HeCt& a, int out_level = -1);
+  // to: where the result goes (null: a block of its own)
+  HeCt rescale(const HeCt& a, int out_level = -1, u64* to = nullptr);
   DevBuf decompose(const u64* d, int level, int B = 1);
   void decompose_to(const u64* d, int level, int B, u64* digits);
   HeCt hoisted(const HeCt& x, const u64* digits, u64 g);
@@ -211,18 +227,19 @@ struct HeCtxImpl {
   // pack: the output's FP64 limbs may be stored packed (HeCt::packed says
   // whether they were: only on the fused, consuming path)
   HeCt moddown(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
-               const u64* rec = nullptr, bool pack = false);
+               const u64* rec = nullptr, bool pack = false, u64* to = nullptr);
   bool moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool consume = false, bool src_ready = false,
                   const u64* rec = nullptr, bool pack = false);
   void intt_from(u64* dst, const HeCt& x, int first, int count, const LimbMap& map, const u64* scales = nullptr);
   // ModDown and Rescale as one rounding by P q_l (a variant)
   HeCt moddown_rescale(const HeCt& x, int out_level = -1, bool consume = false, bool src_ready = false,
-                       const u64* rec = nullptr, bool pack = false);
+                       const u64* rec = nullptr, bool pack = false, u64* to = nullptr);
   // returns the digit records of the elements' ModDown sources when the
   // int8 lift takes them (element e's at rec + e * rec_stride), else empty
   DevBuf moddown_sources(const std::vector<HeCt*>& xs, bool with_rescale, size_t* rec_stride = nullptr);
   // add: a ciphertext batch of the result's layout added onto it
   HeCt keyswitch(const u64* d, int level, u64 g_key, int B = 1, const u64* add = nullptr);
+  void keyswitch_to(u64* out, const u64* d, int level, u64 g_key, int B, const u64* add);
   HeCt mult(const HeCt& a, const HeCt& b);
   HeCt rotate(const HeCt& x, long step);
   HeCt rotate_add(const HeCt& x, long step);  // x + its rotation
@@ -261,8 +278,10 @@ struct HeCtxImpl {
   struct Job {
     double weight;
     std::function<void()> run;
+    SideBytes bytes = {};
   };
   void run_lanes(const std::vector<Job>& jobs);
+  void run_in_order(const std::vector<Job>& jobs);
   void run_sides(const std::vector<Job>& jobs, int B);
   // device memory to a caller's host buffer, waited for
   void download(void* host, const void* dev, size_t bytes);
@@ -284,10 +303,12 @@ struct HeCtxImpl {
     DevBuf dig;
   };
   int shift_group(int level, int sides, int B, int blocks) const;
-  ShiftBases shift_bases(const ShiftBases* prev, HeCt& first, long second_step, long step, int sides, int blocks);
+  size_t shift_rotations(int level, int B, int nb, int n1) const;
+  size_t shift_downs(int level, int B, int nb, size_t cnt) const;
+  ShiftBases shift_bases(ShiftBases&& prev, HeCt& first, long second_step, long step, int sides, int blocks);
   void shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
                            const std::vector<const u64*>* masks, int out_level, bool rescale_after, bool fused_rs,
-                           bool pack, double scale, std::vector<HeCt>& out);
+                           bool pack, double scale, const std::shared_ptr<DevBuf>& side, std::vector<HeCt>& out);
   // pack: the A_k (with one rounding) and the ModDown'ed B_k may come out
   // packed, for the tensor sums alone
   std::vector<HeCt> matmul_side_a(const HeCt& ca, int n, int n1z, int npz, int out_level = -1,

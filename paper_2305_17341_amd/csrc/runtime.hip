@@ -36,6 +36,21 @@ void* DevPool::get(size_t bytes) {
     peak = std::max(peak, bump_off);
     return p;
   }
+  DevPool& root = parent ? *parent : *this;
+  if (root.scratch > 0 && !user_alloc && !exact) {
+    bytes = (bytes + 4095) & ~(size_t)4095;
+    if (void* p = cut(bytes)) return p;
+    if (!root.lanes_on)
+      for (DevPool* s : subs)
+        if (void* p = s->cut(bytes)) return p;
+    void* p = obtain(bytes);
+    if (!p) fail(HE_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
+    segs_[(char*)p] = bytes;
+    cut_[p] = bytes;
+    bytes_live += bytes;
+    note_peak();
+    return p;
+  }
   auto take = [&](DevPool& from, std::multimap<size_t, void*>& blocks) -> void* {
     auto it = blocks.lower_bound(bytes);
     if (it == blocks.end() || it->first > (exact ? bytes : bytes + bytes / 4)) return nullptr;
@@ -49,7 +64,6 @@ void* DevPool::get(size_t bytes) {
     return p;
   };
   if (void* p = take(*this, free_)) return p;
-  DevPool& root = parent ? *parent : *this;
   if (root.lanes_on) {
     if (void* p = take(root, root.common_)) return p;
   } else {
@@ -59,6 +73,14 @@ void* DevPool::get(size_t bytes) {
       if (void* p = take(*s, s->free_)) return p;
   }
   if (frozen) fail(HE_ENOMEM, "graph arena exhausted while recording");
+  void* p = obtain(bytes);
+  if (!p) fail(HE_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
+  live_[p] = bytes;
+  bytes_live += bytes;
+  note_peak();
+  return p;
+}
+void* DevPool::obtain(size_t bytes) {
   void* p = nullptr;
   for (int attempt = 0; attempt < 2; attempt++) {
     if (user_alloc) {
@@ -70,11 +92,88 @@ void* DevPool::get(size_t bytes) {
     if (p) break;
     (parent ? parent : this)->trim();
   }
-  if (!p) fail(HE_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
-  live_[p] = bytes;
+  return p;
+}
+void* DevPool::cut(size_t bytes) {
+  auto best = gaps_.end();
+  for (auto it = gaps_.begin(); it != gaps_.end(); ++it)
+    if (it->second >= bytes && (best == gaps_.end() || it->second < best->second)) best = it;
+  if (best == gaps_.end()) return nullptr;
+  char* p = best->first;
+  const size_t left = best->second - bytes;
+  gaps_.erase(best);
+  if (left) gaps_[p + bytes] = left;
+  cut_[p] = bytes;
+  bytes_cached -= bytes;
   bytes_live += bytes;
   note_peak();
   return p;
+}
+bool DevPool::rejoin(void* p) {
+  auto it = cut_.find(p);
+  if (it == cut_.end()) return false;
+  char* at = (char*)p;
+  size_t bytes = it->second;
+  cut_.erase(it);
+  bytes_live -= bytes;
+  bytes_cached += bytes;
+  // with the gaps on both sides, within the segment
+  auto next = gaps_.find(at + bytes);
+  if (next != gaps_.end() && !segs_.count(at + bytes)) {
+    bytes += next->second;
+    gaps_.erase(next);
+  }
+  auto prev = gaps_.lower_bound(at);
+  if (prev != gaps_.begin() && !segs_.count(at)) {
+    --prev;
+    if (prev->first + prev->second == at) {
+      prev->second += bytes;
+      return true;
+    }
+  }
+  gaps_[at] = bytes;
+  return true;
+}
+void DevPool::drop_segments(bool all) {
+  for (auto it = segs_.begin(); it != segs_.end();) {
+    auto gap = gaps_.find(it->first);
+    const bool unused = gap != gaps_.end() && gap->second == it->second;
+    if (unused) {
+      gaps_.erase(gap);
+      bytes_cached -= it->second;
+    }
+    if (unused || all) {
+      if (user_release) user_release(it->first, user);
+      else (void)hipFree(it->first);
+      it = segs_.erase(it);
+    } else {
+      ++it;
+    }
+  }
+}
+void DevPool::reserve(size_t bytes) {
+  if (redirect) return redirect->reserve(bytes);
+  if (user_alloc || bump_base || exact) return;
+  bytes = (bytes + 4095) & ~(size_t)4095;
+  auto fits = [&](const DevPool& d) {
+    for (auto& kv : d.gaps_)
+      if (kv.second >= bytes) return true;
+    return false;
+  };
+  if (fits(*this)) return;
+  if (!parent && !lanes_on)
+    for (DevPool* s : subs)
+      if (fits(*s)) return;
+  // a larger segment in place of those that nothing uses
+  if (!segs_.empty()) {
+    wait();
+    drop_segments(false);
+  }
+  if (void* p = obtain(bytes)) {  // else the blocks are obtained one by one
+    segs_[(char*)p] = bytes;
+    gaps_[(char*)p] = bytes;
+    bytes_cached += bytes;
+  }
 }
 size_t DevPool::total_live() const {
   size_t n = bytes_live;
@@ -88,13 +187,19 @@ size_t DevPool::total_cached() const {
 }
 void DevPool::note_peak() {
   DevPool* root = parent ? parent : this;
-  root->peak = std::max(root->peak, root->total_live());
+  high = std::max(high, bytes_live);
+  size_t n = root->lanes_on ? root->high : root->total_live();
+  if (root->lanes_on)
+    for (const DevPool* s : root->subs) n += s->high;
+  root->peak = std::max(root->peak, n);
 }
 void DevPool::put(void* p) {
-  if (redirect && redirect->live_.count(p)) {
+  if (redirect && (redirect->live_.count(p) || redirect->cut_.count(p))) {
     redirect->put(p);
     return;
   }
+  // (a block cut out here and released on a side stream waits as well)
+  if (!(lanes_on && redirect) && rejoin(p)) return;
   auto it = live_.find(p);
   if (lanes_on && (redirect || it == live_.end())) {
     deferred.push_back(p);
@@ -102,7 +207,7 @@ void DevPool::put(void* p) {
   }
   if (it == live_.end()) {
     for (DevPool* s : subs)
-      if (s->live_.count(p)) return s->put(p);
+      if (s->live_.count(p) || s->cut_.count(p)) return s->put(p);
     return;
   }
   size_t sz = it->second;
@@ -119,6 +224,8 @@ void DevPool::part() {
     s->bytes_cached = 0;
   }
   common_.swap(free_);
+  high = bytes_live;
+  for (DevPool* s : subs) s->high = s->bytes_live;
   lanes_on = true;
 }
 void DevPool::meet() {
@@ -138,19 +245,21 @@ void DevPool::trim() {
   for (DevPool* s : subs) s->trim();
   for (auto& kv : common_) free_.insert(kv);
   common_.clear();
-  if (free_.empty()) return;
+  if (free_.empty() && gaps_.empty()) return;
   wait();
+  drop_segments(false);
   for (auto& kv : free_) {
     if (user_release) user_release(kv.second, user);
     else (void)hipFree(kv.second);
+    bytes_cached -= kv.first;
   }
   free_.clear();
-  bytes_cached = 0;
 }
 DevPool::~DevPool() {
-  if (free_.empty() && live_.empty()) return;
+  if (free_.empty() && live_.empty() && segs_.empty()) return;
   wait();
   trim();
+  drop_segments(true);
   for (auto& kv : live_) {
     if (user_release) user_release(kv.first, user);
     else (void)hipFree(kv.first);
@@ -686,6 +795,45 @@ void HeCtxImpl::init(const he_params* p, const he_device* dev, u64 seed_) {
 size_t HeCtxImpl::stage_count(size_t per_element, size_t elements) const {
   return std::max<size_t>(1, std::min(elements, (size_t)HE_STAGE_BYTES / per_element));
 }
+static int ceil_div_i(int a, int b) { return (a + b - 1) / b; }
+
+// limbs of B members' elements while they go through Decompose (coefficients
+// and digits) and through a fused ModDown (lift, quotient records, result)
+static size_t split_limbs(const HeCtxImpl& c, int level, size_t B) {
+  return B * (c.nq_of(level) + (size_t)c.beta_at(level) * c.nqp_of(level));
+}
+static size_t down_limbs(const HeCtxImpl& c, int level, size_t B) { return B * (4 * c.nq_of(level) + 2 * (c.alpha + 1)); }
+size_t HeCtxImpl::giant_count(int level, int B, size_t giant) const {
+  const size_t nq = nq_of(level), nqp = nqp_of(level);
+  return stage_count(B * (2 * nqp + 5 * nq + 2 * (alpha + 1) + beta_at(level) * nqp) * N * 8, giant);
+}
+size_t HeCtxImpl::lintrans_scratch(int level, int B, size_t babies, size_t giant) const {
+  const size_t nq = nq_of(level), nqp = nqp_of(level), el = (size_t)2 * B * nqp;  // an R_{Q_l P} element
+  const size_t gcap = giant_count(level, B, giant), nb = std::min(giant, std::max<size_t>(gcap, SUM_MAX_OUTS));
+  // the giant steps' sums through ModDown, then through Decompose
+  const size_t sums = std::max(nb * (el + down_limbs(*this, level, B)),
+                               nb * 2 * B * nq + split_limbs(*this, level, std::min(gcap, nb) * B));
+  const size_t limbs = (babies + 1) * el + std::max(sums, split_limbs(*this, level, B));
+  // blocks of several sizes leave gaps: a sixteenth more
+  return (limbs + limbs / 16 + 2) * N * 8;
+}
+size_t HeCtxImpl::shift_scratch(int level, int sides, int B, int blocks, int n1, bool rescale_apart) const {
+  const size_t nq = nq_of(level), nqp = nqp_of(level), M = (size_t)sides * B, g = shift_group(level, sides, B, blocks);
+  const size_t base = g * M * (2 * nq + (size_t)beta_at(level) * nqp);
+  const size_t step = 2 * M * nqp + std::max(down_limbs(*this, level, M), M * nq);  // a block's bases made
+  const size_t per = shift_rotations(level, B, (int)g, n1), rd = shift_downs(level, B, (int)g, per);
+  const size_t outs = g * B * (per * (2 * nqp + 2 * (alpha + 2)) + rd * (rescale_apart ? 4 * nq + 2 : 2 * nq));
+  const size_t limbs = base + std::max(step, outs);
+  return (limbs + limbs / 16 + 2) * N * 8;
+}
+HeCtxImpl::SideBytes HeCtxImpl::side_bytes(bool a_side, int level, int out_level, int B, int n, int n1, int nprime,
+                                           bool fused_rs, bool folded) const {
+  const int low = level - (nprime >= n - 1 ? 1 : ceil_div_i(n - 1, nprime));  // after Z (T)
+  const size_t turns = lintrans_scratch(level, B, n1, (a_side ? 2 : 1) * ceil_div_i(n, n1));
+  if (folded || low < 0) return {0, turns};
+  return {(size_t)n * 2 * B * nq_of(out_level) * N * 8,
+          std::max(turns, shift_scratch(low, a_side ? 2 : 1, B, n / n1, n1, a_side && !fused_rs))};
+}
 HeCt HeCtxImpl::ct_new(int level, bool qp, double scale, int B) {
   HeCt c;
   c.N = N;
@@ -695,6 +843,18 @@ HeCt HeCtxImpl::ct_new(int level, bool qp, double scale, int B) {
   c.B = B;
   c.scale = scale;
   c.d = DevBuf(&pool, (size_t)2 * B * c.nlimbs * N);
+  return c;
+}
+// a ciphertext batch in words owned elsewhere, or (at null) in a block of its own
+HeCt HeCtxImpl::ct_at(u64* at, int level, double scale, int B) {
+  if (!at) return ct_new(level, false, scale, B);
+  HeCt c;
+  c.N = N;
+  c.level = level;
+  c.nlimbs = nq_of(level);
+  c.B = B;
+  c.scale = scale;
+  c.d = DevBuf::part(at, (size_t)2 * B * c.nlimbs * N);
   return c;
 }
 HeCt HeCtxImpl::ct_copy(const HeCt& x) {
@@ -906,7 +1066,7 @@ void HeCtxImpl::intt_from(u64* dst, const HeCt& x, int first, int count, const L
 
 // Rescale by q_l; out_level < l - 1 also drops the limbs above it (only the
 // kept limbs are computed: the same residues as Rescale followed by a drop)
-HeCt HeCtxImpl::rescale(const HeCt& a, int out_level) {
+HeCt HeCtxImpl::rescale(const HeCt& a, int out_level, u64* to) {
   if (a.qp) fail(HE_EINVAL, "rescale of an R_QP element");
   if (a.packed) fail(HE_EINVAL, "packed limbs are for the tensor sums alone");
   int l = a.level;
@@ -917,7 +1077,7 @@ HeCt HeCtxImpl::rescale(const HeCt& a, int out_level) {
   DevBuf top(&pool, (size_t)np * N);
   intt_from(top.p, a, l, 1, one(l));
   DevBuf t(&pool, (size_t)np * nout * N);
-  HeCt c = ct_new(out_level, false, a.scale / (double)mods[l], a.B);
+  HeCt c = ct_at(to, out_level, a.scale / (double)mods[l], a.B);
   const u64* ql_inv = qlinv.p + (size_t)l * nmods * 2;
   if (fused_conv) {
     if (!launch_rescale_fused(T, t.p, top.p, l, nout, np, a.d.p, l + 1, ql_inv, c.d.p, stream))
@@ -1015,11 +1175,12 @@ std::vector<HeCt> HeCtxImpl::hoisted_multi(const HeCt& x, const u64* digits, con
 
 // ModDown: R_{Q_l P}^2 -> R_{Q_l}^2, (x - [x]_P) P^{-1} with [x]_P the exact
 // centred residue; out_level < l keeps (and computes) only the limbs up to it
-HeCt HeCtxImpl::moddown(const HeCt& x, int out_level, bool consume, bool src_ready, const u64* rec, bool pack) {
+HeCt HeCtxImpl::moddown(const HeCt& x, int out_level, bool consume, bool src_ready, const u64* rec, bool pack,
+                        u64* to) {
   if (!x.qp) fail(HE_EINVAL, "moddown of an R_Q element");
   if (out_level < 0) out_level = x.level;
   if (out_level > x.level) fail(HE_ELEVEL, "moddown cannot raise the level");
-  HeCt c = ct_new(out_level, false, x.scale, x.B);
+  HeCt c = ct_at(to, out_level, x.scale, x.B);
   c.packed = moddown_to(x, out_level, c.d.p, consume, src_ready, rec, pack);
   return c;
 }
@@ -1082,7 +1243,7 @@ bool HeCtxImpl::moddown_to(const HeCt& x, int out_level, const SubDst& dst, bool
 // limbs are computed): the exact centred lift of x mod P q_l from the limbs
 // q_l, p_1..p_alpha, then (x - lift) (P q_l)^-1 on the limbs below q_l.
 HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool src_ready, const u64* rec,
-                                 bool pack) {
+                                 bool pack, u64* to) {
   if (!x.qp) fail(HE_EINVAL, "moddown of an R_Q element");
   const int l = x.level;
   if (l < 1) fail(HE_ELEVEL, "no level left to rescale");
@@ -1106,7 +1267,7 @@ HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool
     if (!src_ready)
       launch_intt_scaled(T, x.d.p, x.d.p, np * ns, sm, down_rs_scale.p + (size_t)l * nmods * 2, stream);
     DevBuf y(&pool, (size_t)np * nout * N);
-    HeCt c = ct_new(out_level, false, x.scale / (double)mods[l], x.B);
+    HeCt c = ct_at(to, out_level, x.scale / (double)mods[l], x.B);
     DevBuf V;
     if (!rec) V = DevBuf(&pool, (size_t)np * (ns + 1) * N);
     if (!launch_moddown_fused(T, x.d.p, nout, np, tab, x.d.p, nqp, cp, c.d.p, y.p, rec ? (u64*)rec : V.p, stream,
@@ -1121,7 +1282,7 @@ HeCt HeCtxImpl::moddown_rescale(const HeCt& x, int out_level, bool consume, bool
   DevBuf pc(&pool, (size_t)np * ns * N);
   intt_from(pc.p, x, l, ns, sm, down_rs_scale.p + (size_t)l * nmods * 2);
   DevBuf y(&pool, (size_t)np * nout * N);
-  HeCt c = ct_new(out_level, false, x.scale / (double)mods[l], x.B);
+  HeCt c = ct_at(to, out_level, x.scale / (double)mods[l], x.B);
   if (fused_conv) {
     DevBuf V(&pool, (size_t)np * (ns + 1) * N);
     if (!launch_moddown_fused(T, pc.p, nout, np, tab, x.d.p, nqp, cp, c.d.p, y.p, V.p, stream))
@@ -1180,14 +1341,17 @@ DevBuf HeCtxImpl::moddown_sources(const std::vector<HeCt*>& xs, bool with_rescal
 }
 
 HeCt HeCtxImpl::keyswitch(const u64* d, int level, u64 g_key, int B, const u64* add) {
+  HeCt c = ct_new(level, false, 1.0, B);
+  keyswitch_to(c.d.p, d, level, g_key, B, add);
+  return c;
+}
+void HeCtxImpl::keyswitch_to(u64* out, const u64* d, int level, u64 g_key, int B, const u64* add) {
   DevBuf dig = decompose(d, level, B);
   HeCt h = ct_new(level, true, 1.0, B);
   const DevBuf& k = key(g_key);
   launch_multsum(T, h.d.p, dig.p, k.p, nullptr, pmod.p, level, L, alpha, beta_at(level), 1, B, stream);
   n_multsum += B;
-  HeCt c = ct_new(level, false, 1.0, B);
-  moddown_to(h, level, SubDst(c.d.p, 0, add), true);
-  return c;
+  moddown_to(h, level, SubDst(out, 0, add), true);
 }
 
 HeCt HeCtxImpl::mult(const HeCt& a, const HeCt& b) {
@@ -1444,8 +1608,6 @@ static bool diag_vec(const DiagGroups& groups, long n2, long l, long shift, doub
   return true;
 }
 
-static int ceil_div_i(int a, int b) { return (a + b - 1) / b; }
-
 LtGeom lt_geom(int kind, int n, int n1) {
   LtGeom g;
   g.n1 = n1;
@@ -1537,7 +1699,12 @@ HeCt HeCtxImpl::lintrans_perm(const HeCt& x, const std::vector<int>& perm, const
   const std::vector<std::pair<int, int>>& ij = pit->second.ij;
   const std::vector<const u64*>& pts = pit->second.pts;
   std::vector<bool> used(n1, false);
-  for (auto& p : ij) used[p.second] = true;
+  std::set<int> steps;
+  for (auto& p : ij) {
+    used[p.second] = true;
+    if (p.first) steps.insert(p.first);
+  }
+  ScratchScope scratch(pool, lintrans_scratch(level, x.B, std::count(used.begin(), used.end(), true), steps.size()));
   // Decompose once, baby-step hoisted rotations kept in R_{Q_l P}.  With the
   // simple key substitution (section 4.2.1, 2 <= n1p < n1) the baby steps
   // a (b n1p + j') come in blocks of n1p, each hoisted from its own base
@@ -1588,8 +1755,7 @@ HeCt HeCtxImpl::lintrans_perm(const HeCt& x, const std::vector<int>& perm, const
   // HE_STAGE_BYTES (on the largest ring a few steps fill the chip already), but
   // the sums always run SUM_MAX_OUTS at a time: each pass reads every baby.
   const int B = x.B, nq = nq_of(level), nl = 2 * B * nqp;
-  const size_t per_step = (size_t)B * (2 * nqp + 5 * nq + 2 * (alpha + 1) + (size_t)beta_at(level) * nqp) * N * 8;
-  const size_t gcap = stage_count(per_step, gi.size());
+  const size_t gcap = giant_count(level, B, gi.size());
   for (size_t c0 = 0; c0 < gi.size();) {
     const int lone = gi[c0] == 0 ? 1 : 0;  // step 0 joins the first batch
     const int nb = (int)std::min(std::max<size_t>(gcap, SUM_MAX_OUTS - lone), gi.size() - c0 - lone);
@@ -1652,6 +1818,7 @@ HeCt HeCtxImpl::lintrans_perm(const HeCt& x, const std::vector<int>& perm, const
     c0 += lone + nb;
   }
   HeCt md = moddown(acc, -1, true);
+  KeepScope keep(pool);
   HeCt r = rescale(md);
   r.scale = x.scale;
   return r;
@@ -1822,10 +1989,12 @@ std::vector<HeCt> HeCtxImpl::matmul_side_a(const HeCt& ca, int n, int n1z, int n
   int group = shift_group(lvl, 2, A0.B, nblk);
   for (size_t e = 0; e < masks.size(); e++)
     if (masks[e] != masks[0] + e * (size_t)nqp_of(lvl) * N) group = 1;  // not one bank
+  ScratchScope scratch(pool);
+  auto side = std::make_shared<DevBuf>(&pool, (size_t)n * 2 * A0.B * nq_of(ol) * N);
   ShiftBases sb;
   for (int b = 0; b < nblk; b += group) {
-    sb = shift_bases(b ? &sb : nullptr, A0, -(long)n, n1z, 2, std::min(group, nblk - b));
-    shift_block_outputs(sb, b, n1z, gs, &masks, ol, true, fused_rs, pack, scale, Ak);
+    sb = shift_bases(std::move(sb), A0, -(long)n, n1z, 2, std::min(group, nblk - b));
+    shift_block_outputs(sb, b, n1z, gs, &masks, ol, true, fused_rs, pack, scale, side, Ak);
   }
   return Ak;
 }
@@ -1841,10 +2010,12 @@ std::vector<HeCt> HeCtxImpl::matmul_side_b(const HeCt& cb, int n, int n1t, int n
   for (int r = 1; r < n1t; r++) gs.push_back(galois((long)n * r));
   std::vector<HeCt> Bk(n);
   const int nblk = n / n1t, group = shift_group(lvl, 1, C0.B, nblk);
+  ScratchScope scratch(pool);
+  auto side = std::make_shared<DevBuf>(&pool, (size_t)n * 2 * C0.B * nq_of(ol) * N);
   ShiftBases sb;
   for (int b = 0; b < nblk; b += group) {
-    sb = shift_bases(b ? &sb : nullptr, C0, 0, (long)n * n1t, 1, std::min(group, nblk - b));
-    shift_block_outputs(sb, b, n1t, gs, nullptr, ol, false, false, pack, scale, Bk);
+    sb = shift_bases(std::move(sb), C0, 0, (long)n * n1t, 1, std::min(group, nblk - b));
+    shift_block_outputs(sb, b, n1t, gs, nullptr, ol, false, false, pack, scale, side, Bk);
   }
   return Bk;
 }
@@ -1859,18 +2030,42 @@ int HeCtxImpl::shift_group(int level, int sides, int B, int blocks) const {
   const int most = (int)std::max<size_t>(1, std::min<size_t>(fit, blocks));
   return ceil_div_i(blocks, ceil_div_i(blocks, most));  // groups of nearly one size
 }
+// Rotations of a group of nb blocks per launch: the whole block where one block
+// stands alone (its digits are read once), else as many fours as fit
+// HE_STAGE_BYTES with what their ModDowns take.
+size_t HeCtxImpl::shift_rotations(int level, int B, int nb, int n1) const {
+  const size_t down = (size_t)2 * B * (nqp_of(level) + nq_of(level) + alpha + 2) * N * 8;
+  return nb == 1 ? n1 : std::min<size_t>(n1, std::max<size_t>(4, stage_count(down * nb, n1) / 4 * 4));
+}
+// ... and rotations per ModDown, of cnt
+size_t HeCtxImpl::shift_downs(int level, int B, int nb, size_t cnt) const {
+  return stage_count((size_t)2 * B * (nqp_of(level) + nq_of(level) + alpha + 2) * N * 8 * nb, cnt);
+}
 
 // The bases of the next `blocks` shift blocks and their digits: base 0 of the
 // first block is `first` (and its rotation by second_step, when sides = 2),
 // every other block's bases are the block before's rotated by `step`, from the
 // digits that the block before's shifts use too; both sides take each step
 // together.
-HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first, long second_step, long step,
-                                             int sides, int blocks) {
-  const int B = prev ? prev->B : first.B, level = prev ? prev->x.level : first.level;
-  const double scale = prev ? prev->x.scale : first.scale;
+HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(ShiftBases&& prev, HeCt& first, long second_step, long step, int sides,
+                                             int blocks) {
+  const bool start = prev.blocks == 0;
+  const int B = start ? first.B : prev.B, level = start ? first.level : prev.x.level;
+  const double scale = start ? first.scale : prev.x.scale;
   const int nq = nq_of(level), M = sides * B;
   const size_t dstride = (size_t)beta_at(level) * nqp_of(level) * N;
+  // the bases of the block after block j of src, in R_{Q_l P}
+  auto turn = [&](const ShiftBases& src, int j) {
+    HeCt h = ct_new(level, true, scale, M);
+    const u64 g = galois(step);
+    launch_multsum(T, h.d.p, src.dig.p + (size_t)j * M * dstride, key(g).p, src.x.member(0, j * M), pmod.p, level, L,
+                   alpha, beta_at(level), g, M, stream);
+    n_multsum += M;
+    return h;
+  };
+  HeCt h;
+  if (!start) h = turn(prev, prev.blocks - 1);
+  prev = ShiftBases();  // nothing else of it is needed: room for this group
   ShiftBases sb;
   sb.blocks = blocks;
   sb.sides = sides;
@@ -1878,12 +2073,12 @@ HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first
   sb.x = ct_new(level, false, scale, blocks * M);
   sb.dig = DevBuf(&pool, (size_t)blocks * M * dstride);
   // members [at, at + cnt) of x = ModDown(h): the components stand apart
-  auto put = [&](const HeCt& h, int at) {
-    moddown_to(h, level, SubDst(sb.x.member(0, at), (size_t)(blocks * M - h.B) * nq * N), true);
+  auto put = [&](const HeCt& e, int at) {
+    moddown_to(e, level, SubDst(sb.x.member(0, at), (size_t)(blocks * M - e.B) * nq * N), true);
   };
   for (int j = 0; j < blocks; j++) {
     u64* dj = sb.dig.p + (size_t)j * M * dstride;
-    if (j == 0 && !prev) {
+    if (j == 0 && start) {
       for (int p = 0; p < 2; p++) copy_limbs(sb.x.member(p, 0), first.poly(p), (size_t)B * nq, "copy_ct");
       decompose_to(sb.x.member(1, 0), level, B, dj);
       if (sides == 2) {
@@ -1893,14 +2088,9 @@ HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first
       first = HeCt();
       continue;
     }
-    const ShiftBases& src = j ? sb : *prev;
-    const int at = ((j ? j : prev->blocks) - 1) * M;
-    HeCt h = ct_new(level, true, scale, M);
-    const u64 g = galois(step);
-    launch_multsum(T, h.d.p, src.dig.p + (size_t)at * dstride, key(g).p, src.x.member(0, at), pmod.p, level, L, alpha,
-                   beta_at(level), g, M, stream);
-    n_multsum += M;
+    if (j) h = turn(sb, j - 1);
     put(h, j * M);
+    h = HeCt();
     decompose_to(sb.x.member(1, j * M), level, M, dj);
   }
   return sb;
@@ -1912,7 +2102,8 @@ HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(const ShiftBases* prev, HeCt& first
 // mask times rotation, rescaled afterwards (with one rounding if fused_rs).
 void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
                                     const std::vector<const u64*>* masks, int out_level, bool rescale_after,
-                                    bool fused_rs, bool pack, double scale, std::vector<HeCt>& out) {
+                                    bool fused_rs, bool pack, double scale, const std::shared_ptr<DevBuf>& side,
+                                    std::vector<HeCt>& out) {
   const int level = sb.x.level, nq = nq_of(level), nqp = nqp_of(level), nb = sb.blocks, B = sb.B, S = sb.sides;
   const size_t dstride = (size_t)beta_at(level) * nqp * N;
   const size_t elem = (size_t)2 * B * nqp * N;           // words of one output in R_{Q_l P}
@@ -1938,24 +2129,24 @@ void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n
   const u64* c1 = sb.x.poly(0);
   const u64* c2 = sb.x.poly(0) + (size_t)B * nq * N;
   auto mask_of = [&](int r, int second) { return (*masks)[2 * (first_block * n1 + r) + second]; };
+  // results, [2][B][out_level + 1][N] each, go to `side` in the order they come
+  const size_t one = (size_t)2 * B * nq_of(out_level) * N;
+  size_t at = (size_t)first_block * n1;
   if (!masks)
     for (int j = 0; j < nb; j++) {  // r = 0: the bases themselves
-      HeCt c = ct_new(out_level, false, scale, B);
+      HeCt c = ct_at(side->p + at++ * one, out_level, scale, B);
       for (int p = 0; p < 2; p++)
         hip_check(copy2d_async("copy_gather", c.poly(p), (size_t)(out_level + 1) * N * 8, sb.x.member(p, j * B),
                                (size_t)nq * N * 8, (size_t)(out_level + 1) * N * 8, B, stream),
                   "gather");
+      c.whole = side;
       out[(size_t)(first_block + j) * n1] = std::move(c);
     }
-  // Rotations per launch: the whole block where one block stands alone (its
-  // digits are read once), else as many fours as fit HE_STAGE_BYTES with what
-  // their ModDowns take.  ModDowns go HE_STAGE_BYTES at a time.
-  const size_t down = (size_t)2 * B * (nqp + nq + alpha + 2) * N * 8;
   const int r_lo = masks ? 0 : 1;
-  const int per = nb == 1 ? n1 : (int)std::max<size_t>(4, stage_count(down * nb, n1) / 4 * 4);
+  const int per = (int)shift_rotations(level, B, nb, n1);
   for (int r0 = r_lo; r0 < n1; r0 += per) {
     const int cnt = std::min(per, n1 - r0);
-    const int rd = (int)stage_count(down * nb, cnt);  // rotations per ModDown
+    const int rd = (int)shift_downs(level, B, nb, cnt);
     std::vector<std::shared_ptr<DevBuf>> part;
     std::vector<HeCt> all;
     for (int r = 0; r < cnt; r++) {
@@ -2001,21 +2192,21 @@ void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n
       HeCt x = ct_part(part[c], like, 0, (size_t)nrd * nb, B);
       const u64* rr = rec.p ? rec.p + (size_t)r * nb * rs : nullptr;
       HeCt y;
+      u64* to = side->p + at * one;
       if (rescale_after && fused_rs) {
-        y = moddown_rescale(x, out_level, true, fused_conv, rr, pack);
+        y = moddown_rescale(x, out_level, true, fused_conv, rr, pack, to);
       } else if (rescale_after) {
         HeCt md = moddown(x, -1, true, fused_conv, rr);
-        y = rescale(md, out_level);
+        y = rescale(md, out_level, to);
       } else {
-        y = moddown(x, out_level, true, fused_conv, rr, pack);
+        y = moddown(x, out_level, true, fused_conv, rr, pack, to);
       }
       x = HeCt();
       part[c].reset();
       y.scale = scale;
-      auto w = std::make_shared<DevBuf>(std::move(y.d));
       for (int q = 0; q < nrd; q++)
         for (int j = 0; j < nb; j++)
-          out[(size_t)(first_block + j) * n1 + r0 + r + q] = ct_part(w, y, (size_t)q * nb + j, 1, B);
+          out[(size_t)(first_block + j) * n1 + r0 + r + q] = ct_part(side, y, at++, 1, B);
     }
   }
 }
@@ -2068,6 +2259,7 @@ void HeCtxImpl::matmul_accumulate(HeCt& acc, bool& acc_set, const std::vector<He
   else if (acc.level != level || acc.B != B) fail(HE_ELEVEL, "operands at different levels");
   const size_t per = (size_t)B * ((size_t)beta_at(level) * nqp_of(level) + 2 * nqp_of(level) + 6 * nl + 2 * alpha) * N * 8;
   const size_t cap = std::max(stage_count(per, Ak.size()), std::min<size_t>(Ak.size(), std::max(1, MR_MEMBERS / B)));
+  ScratchScope scratch(pool);
   for (size_t k0 = 0; k0 < Ak.size(); k0 += cap) {
     const int np = (int)std::min(cap, Ak.size() - k0);
     DevBuf top(&pool, (size_t)np * B * nl * N);
@@ -2101,8 +2293,9 @@ void HeCtxImpl::accumulate_tensors(DevBuf& acc3, bool& acc_set, const std::vecto
 // ... and relinearised once
 HeCt HeCtxImpl::relin_sum(const DevBuf& acc3, int level, double scale, int B) {
   const int nl = level + 1, nt = B * nl;
-  HeCt c = keyswitch(acc3.p + (size_t)2 * nt * N, level, 0, B, acc3.p);
-  c.scale = scale;
+  HeCt c = ct_new(level, false, scale, B);
+  ScratchScope scratch(pool);
+  keyswitch_to(c.d.p, acc3.p + (size_t)2 * nt * N, level, 0, B, acc3.p);
   return c;
 }
 
@@ -2126,8 +2319,9 @@ HeCt HeCtxImpl::matmul(const HeCt& ca, const HeCt& cb, int n, int n1z, int n1t, 
   std::vector<Job> sides;
   sides.push_back({2.0, [&] {
     Ak = folded ? matmul_side_a_folded(ca, n, n1z) : matmul_side_a(ca, n, n1z, npz, common, fused_rs, lazy);
-  }});
-  sides.push_back({1.0, [&] { Bk = matmul_side_b(cb, n, n1t, npt, common, lazy); }});
+  }, side_bytes(true, ca.level, common, ca.B, n, n1z, npz, fused_rs, folded)});
+  sides.push_back({1.0, [&] { Bk = matmul_side_b(cb, n, n1t, npt, common, lazy); },
+                   side_bytes(false, cb.level, common, cb.B, n, n1t, npt)});
   run_sides(sides, ca.B);
   align_sides(Ak, Bk);
   HeCt acc;
@@ -2233,10 +2427,7 @@ std::vector<HeCt> HeCtxImpl::matmul_graph(const std::vector<const HeCt*>& a, con
 void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   constexpr size_t LANES = 3;
   // a caller's allocator or stream knows nothing of other streams
-  if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect || pool.lanes_on) {
-    for (const Job& j : jobs) j.run();
-    return;
-  }
+  if (jobs.size() == 1 || pool.user_alloc || !own_stream || pool.redirect || pool.lanes_on) return run_in_order(jobs);
   if (!lane_fork) hip_check(hipEventCreateWithFlags(&lane_fork, hipEventDisableTiming), "event");
   const size_t nl = std::min(LANES, jobs.size());
   while (lanes.size() + 1 < nl) {
@@ -2272,17 +2463,32 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
       c.pool.meet();
     }
   } join{*this, main, nl};
-  std::vector<size_t> order(jobs.size());
+  std::vector<size_t> order(jobs.size()), lane(jobs.size());
   for (size_t t = 0; t < order.size(); t++) order[t] = t;
   std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return jobs[x].weight > jobs[y].weight; });
   std::vector<double> load(nl, 0.0);
   for (size_t t : order) {
-    const size_t i = std::min_element(load.begin(), load.end()) - load.begin();
-    load[i] += jobs[t].weight;
+    lane[t] = std::min_element(load.begin(), load.end()) - load.begin();
+    load[lane[t]] += jobs[t].weight;
+  }
+  for (size_t i = 0; i < nl; i++) {
+    SideBytes all;
+    for (size_t t = 0; t < jobs.size(); t++)
+      if (lane[t] == i) all = all + jobs[t].bytes;
+    (i ? lanes[i - 1]->pool : pool).reserve(all.keep + all.scratch);
+  }
+  for (size_t t : order) {
+    const size_t i = lane[t];
     stream = i ? lanes[i - 1]->stream : main;
     pool.redirect = i ? &lanes[i - 1]->pool : nullptr;
     jobs[t].run();
   }
+}
+void HeCtxImpl::run_in_order(const std::vector<Job>& jobs) {
+  SideBytes all;
+  for (const Job& j : jobs) all = all + j.bytes;
+  pool.reserve(all.keep + all.scratch);
+  for (const Job& j : jobs) j.run();
 }
 
 // The sides of a product do not depend on each other.  Side by side they fill
@@ -2291,8 +2497,8 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
 // = 128 at N = 2^16 83.3 and 81.5.  Batches of N = 2^16 fill the chip alone and
 // would only hold both sides' temporaries at once.
 void HeCtxImpl::run_sides(const std::vector<Job>& jobs, int B) {
-  if ((u64)B * N <= (1ull << 16)) return run_lanes(jobs);
-  for (const Job& j : jobs) j.run();
+  if ((u64)B * N <= (1ull << 16)) run_lanes(jobs);
+  else run_in_order(jobs);
 }
 
 void HeCtxImpl::drop_graphs() {
@@ -2352,17 +2558,18 @@ void HeCtxImpl::cov_add(CovState& st, const std::vector<const HeCt*>& x, int rb)
       return gb == 1 ? ct_copy(*xs[0]) : stack(xs);
     };
     std::vector<std::vector<HeCt>> A(k), B(k);
+    const SideBytes turned{0, lintrans_scratch(level, gb, st.n1g, 2 * ceil_div_i(n, st.n1g))};
     std::vector<Job> sides;
     for (int a = 0; a < k; a++)
       sides.push_back({3.0, [&, a] {
         HeCt xt = lintrans(rows_of(a), LT_TRANSPOSE, n, st.n1g, 1.0 / (double)st.n_samples);
         A[a] = matmul_side_a(xt, n, st.n1z, st.npz, common, st.fused, st.lazy);
-      }});
+      }, turned + side_bytes(true, level - 1, common, gb, n, st.n1z, st.npz, st.fused)});
     for (int b = 0; b < k; b++)
       sides.push_back({1.0, [&, b] {
         HeCt xb = drop(rows_of(b), level - 1);
         B[b] = matmul_side_b(xb, n, st.n1t, st.npt, common, st.lazy);
-      }});
+      }, side_bytes(false, level - 1, common, gb, n, st.n1t, st.npt)});
     run_sides(sides, gb);
     for (int a = 0; a < k; a++) align_sides(A[a], B[0]);
     for (int b = 0; b < k; b++) align_sides(A[0], B[b]);

@@ -65,37 +65,70 @@ def _beta(level: int, alpha: int) -> int:
     return -(-(level + 1) // alpha)
 
 
-# temporaries of the library's batched stages (the elements that a product's
-# shifts take through the key inner products and ModDown together, and their
-# bases' digits) stop growing here
-STAGE_BYTES = 1.45 * 2**30
+# The library's batched stages (the elements that go through ModDown, Decompose
+# and the key inner products together) take as many elements as fit this, one
+# at least; a multi-rotation launch takes this many members.
+STAGE_BYTES = 768 << 20
+MEMBERS = 8
+LANES = 3             # streams that parts of one call run on side by side, ...
+LANE_WORDS = 1 << 16  # ... while (members of a batch) * N is at most this
 
 
-def _stage(log_n: int, l: int, alpha: int, d: int, members: int) -> float:
-    """words (of 2^log_n) the stages of `members` stacked d x d products hold: every shift in
-    R_{Q_l P} with its ModDown's temporaries, and the digits of up to eight blocks' two bases"""
-    blocks = min(8, -(-d // default_n1(d)))
-    shifts = d * 2 * (_qp(l, alpha) + l + 1 + alpha + 2)
-    bases = blocks * 2 * (_beta(l, alpha) * _qp(l, alpha) + 2 * (l + 1))
-    return min(members * (shifts + bases), STAGE_BYTES / 8 / (1 << log_n))
+def _fit(log_n: int, limbs: float, n: int) -> int:
+    """elements of `limbs` limbs a stage takes at once, of n"""
+    return max(1, min(n, STAGE_BYTES // int(limbs * 8 << log_n)))
+
+
+def _turns(log_n: int, l: int, alpha: int, members: int, babies: int, giants: int) -> float:
+    """limbs a double-hoisted transform at level l holds: its baby steps, their sum, and the
+    giant steps' sums on their way through ModDown and Decompose"""
+    nq, nqp, digits = l + 1, _qp(l, alpha), _beta(l, alpha) * _qp(l, alpha)
+    cap = _fit(log_n, members * (2 * nqp + 5 * nq + 2 * (alpha + 1) + digits), giants)
+    steps = min(giants, max(cap, 4))
+    sums = max(steps * (2 * nqp + 4 * nq + 2 * (alpha + 1)), steps * 2 * nq + min(cap, steps) * (nq + digits))
+    return members * ((babies + 1) * 2 * nqp + max(sums, nq + digits)) * 17 / 16 + 2
+
+
+def _shifts(log_n: int, l: int, alpha: int, members: int, sides: int, d: int, n1: int) -> float:
+    """limbs the shifts of one side of a product hold at level l: a group of blocks' bases and
+    digits, and their rotations on their way through ModDown (and, on the A side, Rescale)"""
+    nq, nqp, digits, blocks = l + 1, _qp(l, alpha), _beta(l, alpha) * _qp(l, alpha), -(-d // n1)
+    base = sides * members * (digits + 2 * nq)
+    most = max(1, min(max(1, MEMBERS // members), 2 * STAGE_BYTES // (base * 8 << log_n), blocks))
+    group = -(-blocks // -(-blocks // most))
+    down = 2 * members * (nqp + nq + alpha + 2) * group
+    per = n1 if group == 1 else min(n1, max(4, _fit(log_n, down, n1) // 4 * 4))
+    lifts = _fit(log_n, down, per) * (4 * nq + 2 if sides == 2 else 2 * nq)
+    step = sides * members * (2 * nqp + 4 * nq + 2 * (alpha + 1))
+    return (group * base + max(step, group * members * (per * (2 * nqp + 2 * (alpha + 2)) + lifts))) * 17 / 16 + 2
+
+
+def _sides(log_n: int, l: int, alpha: int, members: int, d: int):
+    """limbs of the temporaries of the A side and of the B side of a product at level l"""
+    n1 = default_n1(d)
+    return [max(_turns(log_n, l, alpha, members, n1, sides * -(-d // n1)),
+                _shifts(log_n, l - 1, alpha, members, sides, d, n1)) for sides in (2, 1)]
 
 
 def product_footprint(log_n: int, top_level: int, alpha: int, d: int, batch: int = 1) -> int:
     """Upper bound on the device bytes one d x d product (inputs at
-    `top_level`, no decomposition) allocates beyond what is resident, times
-    `batch` stacked members: the n column-shifted A_k (level l-2) and the n
-    row-shifted B_k (level l-1) held together before the products, plus the
-    largest transient of a linear transform (n1 baby-step rotations in
-    R_{Q_l P}, or the 2 n1 of the column shifts, the digits of one
-    decomposition and a few accumulators) or of the shifts' batched stages,
-    plus stacked copies of the inputs and the output."""
+    `top_level`, no decomposition, either order of relinearisation) takes
+    beyond what is resident, times `batch` stacked members: the d
+    column-shifted A_k and the d row-shifted B_k (level l-2) held together
+    before the products; the temporaries of both sides, which run side by
+    side, or of the relinearisations after them; and stacked copies of the
+    inputs, the sums and the output, in blocks that may be a quarter larger."""
     l = top_level
-    n1 = default_n1(d)
-    sides = d * 2 * (l - 1) + d * 2 * l
-    trans = 2 * (2 * n1 + 4) * _qp(l, alpha) + _beta(l, alpha) * _qp(l, alpha) + 6 * (l + 1)
-    io = 4 * (l + 1) + 2 * (l - 2)
-    words = (batch * (sides + io) + max(batch * trans, _stage(log_n, l, alpha, d, batch))) * 2**log_n
-    return int(math.ceil(words * 8 * POOL_SLACK))
+    keep = 2 * d * 2 * (l - 1)
+    relin = min(d, max(MEMBERS, _fit(log_n, _relin(l - 2, alpha), d))) * _relin(l - 2, alpha)
+    io = 4 * (l + 1) + 17 * l
+    words = (keep + max(sum(_sides(log_n, l, alpha, 1, d)), relin) + POOL_SLACK * io) * 2**log_n
+    return int(batch * math.ceil(words * 8))
+
+
+def _relin(l: int, alpha: int) -> int:
+    """limbs of a product's relinearisation at level l"""
+    return (_beta(l, alpha) + 2) * _qp(l, alpha) + 6 * (l + 1) + 2 * alpha
 
 
 def covariance_footprint(log_n: int, top_level: int, alpha: int, d: int, k: int, row_blocks: int = 1,
@@ -103,15 +136,18 @@ def covariance_footprint(log_n: int, top_level: int, alpha: int, d: int, k: int,
     """Upper bound for the block covariance of k feature blocks: the A and B
     sides of all k blocks are held for the row blocks stacked into one batch
     (min(row_blocks, stacked): the library's "cov_row_blocks"; one-to-many
-    reuse), plus the k^2 accumulators and one batch's transient."""
+    reuse), plus the k^2 accumulators, the temporaries of the sides that run
+    side by side, and the blocks' copies."""
     l = top_level
     n1 = default_n1(d)
     g = max(1, min(row_blocks, stacked))
-    sides = 2 * k * d * 2 * l * g
-    acc = k * k * 2 * l
-    trans = g * (2 * (2 * n1 + 4) * _qp(l, alpha) + _beta(l, alpha) * _qp(l, alpha) + 8 * (l + 1))
-    words = (sides + acc + max(trans, _stage(log_n, l, alpha, d, g))) * 2**log_n
-    return int(math.ceil(words * 8 * POOL_SLACK))
+    lanes = min(LANES, 2 * k) if g << log_n <= LANE_WORDS else 1
+    keep = 2 * k * d * 2 * (l - 2) * g
+    scratch = max([_turns(log_n, l, alpha, g, n1, 2 * -(-d // n1))] + _sides(log_n, l - 1, alpha, g, d))
+    relin = min(d, max(-(-MEMBERS // g), _fit(log_n, g * _relin(l - 3, alpha), d))) * g * _relin(l - 3, alpha)
+    io = k * k * 5 * l + g * (3 * l + lanes * 8 * (l + 1))
+    words = (keep + max(lanes * scratch, relin) + POOL_SLACK * io) * 2**log_n
+    return int(math.ceil(words * 8))
 
 
 @dataclass

@@ -1,0 +1,112 @@
+"""What a context reports of its device memory, and what a product takes."""
+import ctypes as C
+
+import pytest
+
+from paper_2305_17341_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+BATCHED, LAZY, FUSED, MERGED = 1, 2, 4, 64
+
+
+def _peak(ctx, a, b, d, opts):
+    for _ in range(2):      # the plaintext diagonals are cached by the first
+        ctx.sync()
+        ctx.trim()
+        live, _, _ = ctx.mem_info()
+        out = ctx.matmul(a, b, d, opts)
+        ctx.sync()
+        _, _, peak = ctx.mem_info()
+        del out
+    return peak - live
+
+
+def test_peak_counts_sides_that_run_side_by_side():
+    """The sides of a product run on two streams of a context's own, one after
+    the other on a caller's.  Both sides' temporaries are then in use at once:
+    at least the B side's digits (eight blocks of beta (nq + alpha) limbs and
+    a base of 2 nq) come on top of what one stream needs."""
+    from paper_2305_17341_amd import he
+    ch, d = I.MID, 64
+    opts = {"flags": LAZY | FUSED}
+    hip = he.load()     # the HIP runtime that the library links
+    stream = C.c_void_p()
+    assert hip.hipStreamCreate(C.byref(stream)) == 0
+    peaks = []
+    try:
+        for hooks in (None, he.DeviceHooks(stream=stream.value)):
+            ctx = he.Context(ch.log_n, ch.q_bits, ch.p_bits, seed=81, hooks=hooks)
+            ctx.keygen(ctx.matmul_rot_steps(d))
+            A = I.uniform_matrix(1, d)
+            peaks.append(_peak(ctx, ctx.encrypt_matrix(A, nonce=1), ctx.encrypt_matrix(A, nonce=2), d, opts))
+            ctx.close()
+    finally:
+        hip.hipStreamDestroy(stream)
+    alpha, nq = len(ch.p_bits), ch.top_level
+    beta = -(-nq // alpha)
+    digits = 8 * (beta * (nq + alpha) + 2 * nq) * ch.N * 8
+    print("peak side by side", peaks[0], "in order", peaks[1], "digits of one side", digits, flush=True)
+    assert peaks[0] >= peaks[1] + digits
+
+
+def _taken(ctx, call):
+    """bytes that a call takes from the device beyond what its context held"""
+    call()              # plaintext diagonals cached
+    ctx.sync()
+    ctx.trim()
+    live, cached, _ = ctx.mem_info()
+    assert cached == 0
+    out = call()
+    ctx.sync()
+    held = sum(ctx.mem_info()[:2]) - live
+    del out
+    return held
+
+
+@pytest.mark.parametrize("chain,ds", [(I.SMALL, (16, 64)), (I.MID, (16, 32, 64)), (I.SERVE15, (16, 32, 128)),
+                                      (I.LARGE, (16, 64))], ids=lambda v: getattr(v, "name", None))
+def test_products_take_no_more_than_their_footprint(chain, ds):
+    """What admission counts on: blocks in use and blocks kept, on every
+    stream, stay within the footprints of the products of a call, alone,
+    stacked and merged, in either order of relinearisation."""
+    from paper_2305_17341_amd import he, serve as S
+    ctx = he.chain_context(chain, seed=82)
+    ctx.keygen(sorted({s for d in ds for s in ctx.matmul_rot_steps(d)}))
+    x = {d: ctx.encrypt_matrix(I.uniform_matrix(d, d), nonce=d) for d in ds}
+    model = {d: S.product_footprint(chain.log_n, chain.top_level, len(chain.p_bits), d) for d in ds}
+    over = []
+
+    def check(what, held, bound):
+        print(f"{chain.name} {what}: {held / 2**20:.1f} MiB taken, footprint {bound / 2**20:.1f} MiB", flush=True)
+        if held > bound:
+            over.append(what)
+
+    for d in ds:
+        for flags in (0, LAZY, LAZY | FUSED):
+            check(f"d={d} flags={flags}", _taken(ctx, lambda: ctx.matmul(x[d], x[d], d, {"flags": flags})), model[d])
+        check(f"d={d} three stacked", _taken(ctx, lambda: ctx.matmul_batch([x[d]] * 3, [x[d]] * 3, [d] * 3,
+                                                                           {"flags": BATCHED | LAZY | FUSED})),
+              3 * model[d])
+    if chain is not I.LARGE:
+        mix = [d for d in ds for _ in range(2)] + [ds[0]]
+        ops = [x[d] for d in mix]
+        check("merged", _taken(ctx, lambda: ctx.matmul_batch(ops, ops, mix, {"flags": BATCHED | MERGED | LAZY | FUSED})),
+              sum(model[d] for d in mix))
+    assert not over
+
+
+@pytest.mark.parametrize("k,row_blocks", [(1, 1), (2, 1), (2, 3), (2, 6), (3, 2)])
+def test_covariances_take_no_more_than_their_footprint(k, row_blocks):
+    from paper_2305_17341_amd import he, serve as S
+    ch, n = I.MID, 32
+    ctx = he.chain_context(ch, seed=83)
+    ctx.keygen(sorted(set(ctx.matmul_rot_steps(n)) | set(ctx.transpose_rot_steps(n))))
+    x = [ctx.encrypt_matrix(I.uniform_matrix(i, n), nonce=i) for i in range(k * row_blocks)]
+    bound = S.covariance_footprint(ch.log_n, ch.top_level, len(ch.p_bits), n, k, row_blocks)
+    for flags in (0, LAZY | FUSED):
+        held = _taken(ctx, lambda: ctx.covariance(x, row_blocks, k, n, row_blocks * n, {"flags": flags}))
+        print(f"k={k} rows={row_blocks} flags={flags}: {held / 2**20:.1f} MiB taken, footprint {bound / 2**20:.1f} MiB",
+              flush=True)
+        assert held <= bound
+        assert bound < 4 * held
