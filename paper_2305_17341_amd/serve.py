@@ -18,7 +18,9 @@ Scheduling
     them as one merged batch: products of equal d are stacked, and the
     stacks of different d run side by side on streams of the context
     (HE_MM_MERGED).  Requests that arrived while earlier
-    work was on the device join the next batch.  Workers of different N run
+    work was on the device join the next batch.  A product that is alone lets
+    others join it for up to `join_s` where the last ones of its N met others;
+    products asked for one at a time start at once.  Workers of different N run
     concurrently, each on its context's stream, so their kernels overlap on
     the GPU.  Memory freed by a finished batch admits waiting requests.
   * A covariance job runs in chunks of row blocks (he_covariance_begin /
@@ -276,6 +278,9 @@ class Server:
         self._batches = []
         self._cov_chunks = 0
         self._since_chunk = {n: 0 for n in backend.log_ns()}   # product batches since the last chunk
+        self._running = {n: 0 for n in backend.log_ns()}       # products on the device
+        # of each ring's last products: was another one unfinished when it came?
+        self._met = {n: collections.deque(maxlen=16) for n in backend.log_ns()}
         self._workers = [threading.Thread(target=self._work, args=(n,), daemon=True) for n in backend.log_ns()]
         for w in self._workers:
             w.start()
@@ -297,6 +302,9 @@ class Server:
                 return r.future
             if self._stop:
                 raise RuntimeError("server is stopping")
+            if kind == "matmul":
+                self._met[log_n].append(self._running[log_n] > 0 or self._products(log_n) > 0 or
+                                        any(p.log_n == log_n and p.kind == "matmul" for p in self._pending))
             self._pending.append(r)
             self._admit()
             self._cv.notify_all()
@@ -355,6 +363,19 @@ class Server:
             r.t_admit = time.perf_counter()
             self._ready[r.log_n].append(r)
 
+    def _products(self, log_n):
+        return sum(r.kind == "matmul" for r in self._ready[log_n])
+
+    def _join_left(self, log_n):
+        """seconds that a lone product still lets others join: up to join_s
+        from its submission, and only where products have lately met others
+        (0.5 ms is half of a small product's own time, which a client that
+        asks for one after another would pay on each)"""
+        lone = self._ready[log_n][0]
+        if lone.kind != "matmul" or self.max_batch < 2 or self._products(log_n) > 1 or not any(self._met[log_n]):
+            return 0.0
+        return self.join_s - (time.perf_counter() - lone.t_submit)
+
     def _take(self, log_n):
         ready = self._ready[log_n]
         mats = [r for r in ready if r.kind == "matmul"]
@@ -377,14 +398,12 @@ class Server:
                     if self._stop and not any(p.log_n == log_n for p in self._pending):
                         return
                     self._cv.wait()
-                # a lone product lets others join for join_s from its
-                # submission: a small one takes about as long itself, and two
-                # stacked little longer than one
-                lone = self._ready[log_n][0]
-                left = self.join_s - (time.perf_counter() - lone.t_submit)
-                if left > 0 and lone.kind == "matmul":
-                    self._cv.wait_for(lambda: self._stop or len(self._ready[log_n]) > 1, left)
+                left = self._join_left(log_n)
+                if left > 0:
+                    self._cv.wait_for(lambda: self._stop or self._products(log_n) > 1, left)
                 group = self._take(log_n)
+                if group[0].kind == "matmul":
+                    self._running[log_n] = len(group)
             t0 = time.perf_counter()
             err, out = None, None
             try:
@@ -407,6 +426,8 @@ class Server:
                     self._cv.notify_all()
                 continue
             with self._cv:
+                if group[0].kind == "matmul":
+                    self._running[log_n] = 0
                 for r in group:
                     self._in_use -= r.footprint
                     r.t_start, r.t_done, r.batch = r.t_start or t0, t1, len(group)

@@ -207,3 +207,48 @@ def test_products_run_between_covariance_chunks():
     st = srv.stats()
     assert st["covariance_chunks"] == 4 and st["jobs"] == 4
     assert srv.stats()["peak_admitted_bytes"] >= 128 * 10
+
+
+def test_products_one_at_a_time_start_at_once():
+    """a client that waits for each result before it asks again has nobody to
+    wait for"""
+    be = FakeBackend(log_ns=(13,), cost=0.0)
+    srv = S.Server(be, hbm_budget=10**9, join_s=0.5)
+    t0 = time.perf_counter()
+    for _ in range(4):
+        srv.submit("matmul", 13, 16, ()).result(timeout=10)
+    took = time.perf_counter() - t0
+    srv.close()
+    assert took < 0.5
+    assert [len(reqs) for _, reqs, _, _ in be.calls] == [1] * 4
+
+
+def test_max_batch_of_one_does_not_wait():
+    be = FakeBackend(log_ns=(13,), cost=0.05)
+    srv = S.Server(be, hbm_budget=10**9, max_batch=1, join_s=2.0)
+    futs = [srv.submit("matmul", 13, 16, ()) for _ in range(3)]
+    t0 = time.perf_counter()
+    for f in futs:
+        f.result(timeout=10)
+    srv.close()
+    assert time.perf_counter() - t0 < 2.0
+
+
+def test_lone_product_waits_for_products_where_they_have_met():
+    """after two products that met: the next one lets a product join, and a
+    covariance arriving meanwhile does not end its wait"""
+    be = FakeBackend(log_ns=(13,), cost=0.05)
+    srv = S.Server(be, hbm_budget=10**9, join_s=1.0)
+    first = [srv.submit("matmul", 13, 16, ()) for _ in range(2)]
+    for f in first:
+        f.result(timeout=10)
+    n = len(be.calls)
+    lone = srv.submit("matmul", 13, 16, ())
+    time.sleep(0.1)
+    cov = srv.submit("covariance", 13, 16, ())
+    time.sleep(0.1)
+    joined = srv.submit("matmul", 13, 32, ())
+    for f in (lone, cov, joined):
+        f.result(timeout=10)
+    srv.close()
+    assert [[k for k, _, _ in reqs] for _, reqs, _, _ in be.calls[n:]] == [["matmul", "matmul"], ["covariance"]]
