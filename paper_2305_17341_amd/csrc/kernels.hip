@@ -13,6 +13,18 @@
 #define TPB 256
 #define NTT_LDS 4096  // u64 words of LDS per NTT work-group (32 KiB)
 
+// The work-group barrier of every kernel, with the wait for the wave's own LDS
+// writes spelled out.  __syncthreads() leaves it to the compiler, and where a
+// stage loop had its barrier at the head, ROCm 7.2 left it out: one tile of the
+// embedding's FFT in some 250 000 then read a value too early.  Where the
+// compiler waits by itself the two are one instruction.
+__device__ __forceinline__ void block_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters at their ends
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 static inline int cdiv(u64 a, u64 b) { return (int)((a + b - 1) / b); }
 
 // Launch-shape knobs (process-wide).  They change how work is grouped into
@@ -378,7 +390,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols(u64* data, LimbMap map, int lo
     int r = e / C, c = e - r * C;
     sh[e] = a[(size_t)r * T1 + c0 + c];
   }
-  __syncthreads();
+  block_sync();
   const ModConst mk = mc[m];
   const u64 q = mk.q;
   const u64* w = tw + (size_t)m * N;
@@ -397,7 +409,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols(u64* data, LimbMap map, int lo
         sh[r * C + c] = add_mod(U, V, q);
         sh[(r + half) * C + c] = sub_mod(U, V, q);
       }
-      __syncthreads();
+      block_sync();
     }
     for (int e = threadIdx.x; e < tot; e += TPB) {
       int r = e / C, c = e - r * C;
@@ -416,7 +428,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_cols(u64* data, LimbMap map, int lo
         sh[r * C + c] = add_mod(U, V, q);
         sh[(r + half) * C + c] = shoup_mul(sub_mod(U, V, q), W, Wp, q);
       }
-      __syncthreads();
+      block_sync();
     }
     for (int e = threadIdx.x; e < tot; e += TPB) {
       int r = e / C, c = e - r * C;
@@ -439,7 +451,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows(u64* data, LimbMap map, int lo
   u64* a = data + limb_slot(map, limb) * N + (size_t)blk0 * T1;
   const int tot = K * T1;
   for (int e = threadIdx.x; e < tot; e += TPB) sh[e] = a[e];
-  __syncthreads();
+  block_sync();
   const u64 q = mc[m].q;
   const u64* w = tw + (size_t)m * N;
   const u64* wsh = twsh + (size_t)m * N;
@@ -460,7 +472,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows(u64* data, LimbMap map, int lo
         sh[x] = add_mod(U, V, q);
         sh[x + t] = sub_mod(U, V, q);
       }
-      __syncthreads();
+      block_sync();
     }
   } else {
     for (int t = 1; t < T1; t <<= 1) {
@@ -478,7 +490,7 @@ __global__ void __launch_bounds__(TPB) k_ntt_rows(u64* data, LimbMap map, int lo
         sh[x] = add_mod(U, V, q);
         sh[x + t] = shoup_mul(sub_mod(U, V, q), W, Wp, q);
       }
-      __syncthreads();
+      block_sync();
     }
   }
   for (int e = threadIdx.x; e < tot; e += TPB) a[e] = sh[e];
@@ -738,7 +750,7 @@ __device__ __forceinline__ void ntt_cols2_fwd(u64* a, int c0, typename A::V* sh,
 #pragma unroll
     for (int mm = 0; mm < (1 << GA); mm++) sh[lds_rc(rl + (mm << GB), c, C)] = v[mm];
   }
-  __syncthreads();
+  block_sync();
   // group B: r bits [0, GB) -> stages GA..S1-1
   constexpr int ITB = 16 >> GB;
 #pragma unroll
@@ -775,7 +787,7 @@ __device__ __forceinline__ void ntt_cols2_body(u64* a, int c0, typename A::V* sh
 #pragma unroll
       for (int mm = 0; mm < (1 << GB); mm++) sh[lds_rc((rh << GB) + mm, c, C)] = v[mm];
     }
-    __syncthreads();
+    block_sync();
     // inverse bits [S2+GB, LOGN) = r bits [GB, S1), then N^{-1}
     constexpr int ITA = 16 >> GA;
 #pragma unroll
@@ -930,7 +942,7 @@ __device__ __forceinline__ void ntt_rows2_body(u64* a, int blk0, typename A::V* 
 #pragma unroll
       for (int mm = 0; mm < (1 << GC); mm++) sh[lds_be(b, el + (mm << GD), T1)] = v[mm];
     }
-    __syncthreads();
+    block_sync();
     // group D: e bits [0, GD) -> stages S1+GC..LOGN-1
     constexpr int ITD = 16 >> GD;
     constexpr int HIGHD = 1 << (S2 - GD);
@@ -943,7 +955,7 @@ __device__ __forceinline__ void ntt_rows2_body(u64* a, int blk0, typename A::V* 
 #pragma unroll
       for (int mm = 0; mm < (1 << GD); mm++) sh[lds_be(b, (eh << GD) + mm, T1)] = v[mm];
     }
-    __syncthreads();
+    block_sync();
 #pragma unroll
     for (int k = 0; k < TILE / TPB; k++) {
       const int e = tid + k * TPB;
@@ -962,7 +974,7 @@ __device__ __forceinline__ void ntt_rows2_body(u64* a, int blk0, typename A::V* 
       const int e = tid + k * TPB;
       sh[lds_be(e / T1, e % T1, T1)] = v[k];
     }
-    __syncthreads();
+    block_sync();
 #pragma unroll
     for (int k = 0; k < ITD; k++) {
       const int it = tid + TPB * k, eh = it % HIGHD, b = it / HIGHD;
@@ -972,7 +984,7 @@ __device__ __forceinline__ void ntt_rows2_body(u64* a, int blk0, typename A::V* 
 #pragma unroll
       for (int mm = 0; mm < (1 << GD); mm++) sh[lds_be(b, (eh << GD) + mm, T1)] = v[mm];
     }
-    __syncthreads();
+    block_sync();
     // inverse bits [GD, S2) of e
     constexpr int ITC = 16 >> GC;
 #pragma unroll
@@ -1105,7 +1117,7 @@ __device__ __forceinline__ void ntt_cols4_body(u64* a, int c0, typename A::V* sh
   each_group<NG>([&](auto gc) {
     constexpr int g = decltype(gc)::value, G = Groups4<S1>::size(g), LO = INV ? 2 * g : S1 - 2 * g - G, IT = 4 >> G,
                   P = 1 << G;
-    if (g > 0) __syncthreads();
+    if (g > 0) block_sync();
 #pragma unroll
     for (int k = 0; k < IT; k++) {
       const int it = tid + TPB * k, c = it % C;
@@ -1170,7 +1182,7 @@ __device__ __forceinline__ void ntt_rows4_body(u64* a, int blk0, typename A::V* 
   each_group<NG>([&](auto gc) {
     constexpr int g = decltype(gc)::value, G = Groups4<S2>::size(g), LO = INV ? 2 * g : S2 - 2 * g - G, IT = 4 >> G,
                   P = 1 << G;
-    if (INV || g > 0) __syncthreads();
+    if (INV || g > 0) block_sync();
 #pragma unroll
     for (int k = 0; k < IT; k++) {
       const Item4<G, LO> x((u32)(tid + TPB * k));
@@ -1196,7 +1208,7 @@ __device__ __forceinline__ void ntt_rows4_body(u64* a, int blk0, typename A::V* 
     }
   });
   if (!INV) {
-    __syncthreads();
+    block_sync();
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const int e = tid + k * TPB;
@@ -2526,7 +2538,7 @@ __global__ void k_modup(u64* digits, const u64* coef, const u64* ntt_in, ModupAr
     hat_l[e] = A.hat_t[j][e];
     hat_sh_l[e] = A.hat_t_sh[j][e];
   }
-  __syncthreads();
+  block_sync();
   if (i >= N) return;
   u64 y[4];
   u32 src_bits = 0;
@@ -3018,10 +3030,10 @@ __global__ void __launch_bounds__(NS * TPB)
   const ShoupArith as{tw + (size_t)m * N, twsh + (size_t)m * N, mk.q, scales[2 * m], scales[2 * m + 1]};
   if (f64) intt_cols_first<LOGN, GA, GB>(a, c0, reinterpret_cast<double*>(sh[src]), af, tid);
   else intt_cols_first<LOGN, GA, GB>(a, c0, sh[src], as, tid);
-  __syncthreads();
+  block_sync();
   if (f64) intt_cols_last_lds<LOGN, GA, GB>(reinterpret_cast<double*>(sh[src]), af, tid);
   else intt_cols_last_lds<LOGN, GA, GB>(sh[src], as, tid);
-  __syncthreads();
+  block_sync();
   u64* o = rec + (size_t)poly * KU * N;
   for (int e = threadIdx.x; e < TILE; e += NS * TPB) {
     const int row = e / C, col = e % C;
@@ -3223,7 +3235,7 @@ __global__ void __launch_bounds__(2 * TPB) __attribute__((amdgpu_waves_per_eu(4)
       for (int mm = 0; mm < NA; mm++) tile[lds_rc(rl + (mm << GB), c, C)] = v[mm];
     }
   }
-  __syncthreads();
+  block_sync();
   // second group: r bits [0, GB) -> stages GA..S1-1; y stored packed (the
   // block pass reads it with LoadPacked)
   const bool store = !hl || has1;
@@ -4436,7 +4448,7 @@ __global__ void __launch_bounds__(TPB) k_multsum_giant(u64* out, GiantKeys K, in
         sh[(((part - 1) * MB + b) * 2 + 0) * CO + lane] = r0[b];
         sh[(((part - 1) * MB + b) * 2 + 1) * CO + lane] = r1[b];
       }
-    __syncthreads();
+    block_sync();
     if (part > 0) return;
 #pragma unroll
     for (int x = 0; x < SPLIT - 1; x++)
@@ -4890,9 +4902,6 @@ __device__ __forceinline__ cdd cdd_sub(cdd a, cdd b) { return {dd_add(a.re, dd_n
 // apart).  The first pass forms its input as it loads it, the second ends in
 // what is wanted of the result.  A launch per radix-2 stage spent 3 us on
 // each of 13 to 16 stages, nearly all of it latency.
-// The stage loops end in their barrier: with it at the loop's head the compiler
-// (ROCm 7.2) leaves out the wait for the LDS writes of the stage before, and
-// one tile in some 250 000 then read a value too early.
 #define FFT_TILE (2 * TPB)
 #define FFT_LOW 9
 static_assert(FFT_TILE == 1 << FFT_LOW, "the low pass takes a whole tile");
@@ -4910,11 +4919,11 @@ __global__ void __launch_bounds__(TPB) k_fft_low(cdd* x, IN in, int logN, int si
   const u32 p0 = blockIdx.x * FFT_TILE;
   const int b = blockIdx.y;
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) sh[e] = in(b, brv(p0 + e, logN), N);
-  __syncthreads();
+  block_sync();
   for (int st = 0; st < FFT_LOW; st++) {
     const u32 half = 1u << st, k = threadIdx.x & (half - 1), i0 = ((threadIdx.x >> st) << (st + 1)) + k;
     fft_bf(sh[i0], sh[i0 + half], (u64)k << (logN - st - 1), sign, tw);
-    __syncthreads();
+    block_sync();
   }
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB) x[(size_t)b * N + p0 + e] = sh[e];
 }
@@ -4929,12 +4938,12 @@ __global__ void __launch_bounds__(TPB) k_fft_high(const cdd* __restrict__ x, OUT
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
     sh[e] = x[(size_t)b * N + ((size_t)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1))];
   const u32 c = threadIdx.x & (C - 1), rr = threadIdx.x >> lc;
-  __syncthreads();
+  block_sync();
   for (int st = 0; st < lr; st++) {
     const u32 half = 1u << st, k = rr & (half - 1), r0 = ((rr >> st) << (st + 1)) + k;
     const u64 kk = ((u64)k << FFT_LOW) + c0 + c;
     fft_bf(sh[(r0 << lc) + c], sh[((r0 + half) << lc) + c], kk << (lr - st - 1), sign, tw);
-    __syncthreads();
+    block_sync();
   }
   for (u32 e = threadIdx.x; e < FFT_TILE; e += TPB)
     out(b, ((u64)(e >> lc) << FFT_LOW) + c0 + (e & (C - 1)), sh[e], N);
