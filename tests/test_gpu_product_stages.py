@@ -186,3 +186,26 @@ def test_key_words_of_all_sizes_match_oracle(oracle_mod, bits):
         for member in many:
             assert np.array_equal(member[r].export(), o.rotate(y, s).data())
     assert np.array_equal(ctx.lintrans(x, "sigma", n, 4).export(), o.lt_sigma(y, n, 4).data())
+
+
+def test_more_giant_steps_than_a_launch_takes(oracle_mod):
+    """127 giant steps of sigma (one baby step, d = 64): 126 key inner products
+    in two launches, the second onto the first; alone against the oracle, and
+    in batches of three against each product alone"""
+    from paper_2305_17341_amd import he
+    n, ch, opts = 64, I.SMALL, {"n1_z": 1, "n1_t": 1}
+    ctx = he.chain_context(ch, seed=80)
+    ctx.keygen(ctx.matmul_rot_steps(n, opts))
+    steps = he.lintrans_rot_steps("Z", n, 1)
+    assert len(steps) == 126
+    o = oracle_mod.Oracle(ch.log_n, ch.q_bits, ch.p_bits, seed=80)
+    o.keygen(rot_steps=steps)
+    A = I.uniform_matrix(5, n)
+    g = ctx.lintrans(ctx.encrypt_matrix(A, nonce=2), "sigma", n, 1)
+    w = o.lt_sigma(o.encrypt(A.ravel(), nonce=2), n, 1)
+    assert g.level == w.level and g.scale == w.scale
+    assert np.array_equal(g.export(), w.data())
+    x = [ctx.encrypt_matrix(I.uniform_matrix(20 + i, n), nonce=20 + i) for i in range(6)]
+    got = ctx.matmul_batch(x[:3], x[3:], [n] * 3, dict(opts, flags=BATCHED))
+    for i in range(3):
+        assert np.array_equal(got[i].export(), ctx.matmul(x[i], x[3 + i], n, opts).export()), i
