@@ -202,7 +202,7 @@ struct DevPool {
   std::map<void*, size_t> cut_;     // block cut out -> bytes
   void* cut(size_t bytes);          // out of a gap; null if none is large enough
   bool rejoin(void* p);             // false: not a block cut out here
-  void reserve(size_t bytes);       // a gap of so many bytes, where the device has them
+  void reserve(std::vector<size_t> parts);  // gaps of so many bytes, where the device has them
   void drop_segments(bool all);     // those that nothing is cut out of (or all)
   void* obtain(size_t bytes);       // from the device or the caller's allocator
   void* get(size_t bytes);
@@ -220,7 +220,7 @@ struct DevPool {
 struct ScratchScope {
   DevPool& pool;
   explicit ScratchScope(DevPool& p, size_t bytes = 0) : pool(p) {
-    if (bytes) pool.reserve(bytes);
+    if (bytes) pool.reserve({bytes});
     pool.scratch++;
   }
   ~ScratchScope() { pool.scratch--; }

@@ -1,6 +1,5 @@
 // Host runtime declarations (internal).
 #pragma once
-#include <algorithm>
 #include <functional>
 #include <list>
 #include <memory>
@@ -186,7 +185,6 @@ struct HeCtxImpl {
   // summed, and its temporaries
   struct SideBytes {
     size_t keep = 0, scratch = 0;
-    SideBytes operator+(const SideBytes& o) const { return {keep + o.keep, std::max(scratch, o.scratch)}; }
   };
   SideBytes side_bytes(bool a_side, int level, int out_level, int B, int n, int n1, int nprime, bool fused_rs = false,
                        bool folded = false) const;
@@ -282,6 +280,7 @@ struct HeCtxImpl {
   };
   void run_lanes(const std::vector<Job>& jobs);
   void run_in_order(const std::vector<Job>& jobs);
+  void reserve_sides(DevPool& to, const std::vector<SideBytes>& sides);
   void run_sides(const std::vector<Job>& jobs, int B);
   // device memory to a caller's host buffer, waited for
   void download(void* host, const void* dev, size_t bytes);

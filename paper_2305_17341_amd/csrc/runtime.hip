@@ -151,25 +151,42 @@ void DevPool::drop_segments(bool all) {
     }
   }
 }
-void DevPool::reserve(size_t bytes) {
-  if (redirect) return redirect->reserve(bytes);
+// What does not fit the gaps is obtained as segments of its own, so that needs
+// that grow from call to call cost what they grow by: freeing waits for the
+// whole device (all contexts' work, up to 0.6 s beside a batch at N = 2^16) and
+// holds up every other allocation meanwhile.  Only where the segments would then
+// pass twice the need, those that nothing uses are given back.
+void DevPool::reserve(std::vector<size_t> parts) {
+  if (redirect) return redirect->reserve(std::move(parts));
   if (user_alloc || bump_base || exact) return;
-  bytes = (bytes + 4095) & ~(size_t)4095;
-  auto fits = [&](const DevPool& d) {
-    for (auto& kv : d.gaps_)
-      if (kv.second >= bytes) return true;
-    return false;
-  };
-  if (fits(*this)) return;
-  if (!parent && !lanes_on)
-    for (DevPool* s : subs)
-      if (fits(*s)) return;
-  // a larger segment in place of those that nothing uses
-  if (!segs_.empty()) {
+  for (size_t& p : parts) p = (p + 4095) & ~(size_t)4095;
+  std::sort(parts.rbegin(), parts.rend());
+  std::vector<size_t> missing;
+  for (int attempt = 0; attempt < 2; attempt++) {
+    std::vector<size_t> gaps;
+    size_t need = 0, held = 0;
+    for (auto& kv : gaps_) gaps.push_back(kv.second);
+    if (!parent && !lanes_on)
+      for (DevPool* s : subs)
+        for (auto& kv : s->gaps_) gaps.push_back(kv.second);
+    for (auto& kv : segs_) held += kv.second;
+    missing.clear();
+    for (size_t p : parts) {
+      auto best = gaps.end();
+      for (auto it = gaps.begin(); it != gaps.end(); ++it)
+        if (*it >= p && (best == gaps.end() || *it < *best)) best = it;
+      need += p;
+      if (best != gaps.end()) *best -= p;
+      else if (p) missing.push_back(p), held += p;
+    }
+    if (missing.empty()) return;
+    if (attempt || segs_.empty() || held <= 2 * need) break;
     wait();
     drop_segments(false);
   }
-  if (void* p = obtain(bytes)) {  // else the blocks are obtained one by one
+  for (size_t bytes : missing) {
+    void* p = obtain(bytes);
+    if (!p) return;  // the blocks are obtained one by one then
     segs_[(char*)p] = bytes;
     gaps_[(char*)p] = bytes;
     bytes_cached += bytes;
@@ -2478,10 +2495,10 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
     load[lane[t]] += jobs[t].weight;
   }
   for (size_t i = 0; i < nl; i++) {
-    SideBytes all;
+    std::vector<SideBytes> of;
     for (size_t t = 0; t < jobs.size(); t++)
-      if (lane[t] == i) all = all + jobs[t].bytes;
-    (i ? lanes[i - 1]->pool : pool).reserve(all.keep + all.scratch);
+      if (lane[t] == i) of.push_back(jobs[t].bytes);
+    reserve_sides(i ? lanes[i - 1]->pool : pool, of);
   }
   for (size_t t : order) {
     const size_t i = lane[t];
@@ -2491,10 +2508,19 @@ void HeCtxImpl::run_lanes(const std::vector<Job>& jobs) {
   }
 }
 void HeCtxImpl::run_in_order(const std::vector<Job>& jobs) {
-  SideBytes all;
-  for (const Job& j : jobs) all = all + j.bytes;
-  pool.reserve(all.keep + all.scratch);
+  std::vector<SideBytes> of;
+  for (const Job& j : jobs) of.push_back(j.bytes);
+  reserve_sides(pool, of);
   for (const Job& j : jobs) j.run();
+}
+// every side's results, and the temporaries of one at a time
+void HeCtxImpl::reserve_sides(DevPool& to, const std::vector<SideBytes>& sides) {
+  std::vector<size_t> parts{0};
+  for (const SideBytes& s : sides) {
+    parts[0] = std::max(parts[0], s.scratch);
+    if (s.keep) parts.push_back(s.keep);
+  }
+  to.reserve(std::move(parts));
 }
 
 // The sides of a product do not depend on each other.  Side by side they fill
@@ -2564,13 +2590,15 @@ void HeCtxImpl::cov_add(CovState& st, const std::vector<const HeCt*>& x, int rb)
       return gb == 1 ? ct_copy(*xs[0]) : stack(xs);
     };
     std::vector<std::vector<HeCt>> A(k), B(k);
-    const SideBytes turned{0, lintrans_scratch(level, gb, st.n1g, 2 * ceil_div_i(n, st.n1g))};
+    const size_t turned = lintrans_scratch(level, gb, st.n1g, 2 * ceil_div_i(n, st.n1g));
+    SideBytes a_bytes = side_bytes(true, level - 1, common, gb, n, st.n1z, st.npz, st.fused);
+    a_bytes.scratch = std::max(a_bytes.scratch, turned);
     std::vector<Job> sides;
     for (int a = 0; a < k; a++)
       sides.push_back({3.0, [&, a] {
         HeCt xt = lintrans(rows_of(a), LT_TRANSPOSE, n, st.n1g, 1.0 / (double)st.n_samples);
         A[a] = matmul_side_a(xt, n, st.n1z, st.npz, common, st.fused, st.lazy);
-      }, turned + side_bytes(true, level - 1, common, gb, n, st.n1z, st.npz, st.fused)});
+      }, a_bytes});
     for (int b = 0; b < k; b++)
       sides.push_back({1.0, [&, b] {
         HeCt xb = drop(rows_of(b), level - 1);

@@ -110,3 +110,27 @@ def test_covariances_take_no_more_than_their_footprint(k, row_blocks):
               flush=True)
         assert held <= bound
         assert bound < 4 * held
+
+
+def test_scratch_that_grows_stays_within_twice_the_largest_need():
+    """products of other sizes one after the other, each finding the scratch
+    of those before it: segments are added where a need does not fit, and given
+    back before they pass twice of it (beside them the blocks of every size
+    that products hold outside scratch, less than a footprint each)"""
+    from paper_2305_17341_amd import he, serve as S
+    ch, ds = I.MID, (16, 32, 64, 16, 64, 32)
+    ctx = he.chain_context(ch, seed=84)
+    ctx.keygen(sorted({s for d in ds for s in ctx.matmul_rot_steps(d)}))
+    x = {d: ctx.encrypt_matrix(I.uniform_matrix(d, d), nonce=d) for d in ds}
+    alone = {d: ctx.matmul(x[d], x[d], d).export() for d in sorted(set(ds))}
+    ctx.sync()
+    ctx.trim()
+    live, _, _ = ctx.mem_info()
+    held = []
+    for d in ds:
+        assert (ctx.matmul(x[d], x[d], d).export() == alone[d]).all()
+        held.append(sum(ctx.mem_info()[:2]) - live)
+    bound = 2 * S.product_footprint(ch.log_n, ch.top_level, len(ch.p_bits), max(ds))
+    print([f"{h / 2**20:.0f}" for h in held], f"bound {bound / 2**20:.0f} MiB", flush=True)
+    assert max(held) <= bound
+    assert held[4:] == [held[4]] * 2     # what has been needed before is there
