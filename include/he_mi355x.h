@@ -119,7 +119,10 @@ typedef struct {
  * are kept per context).  A replay reads the operands' buffers as they are at
  * that time; results are copied out of the graph's own buffers into new
  * ciphertexts, residue for residue those of the unrecorded call.  The first call runs the product three
- * times (warm-up, arena sizing, recording).  Not while the kernel profile is
+ * times (warm-up, arena sizing, recording).  A recording holds one stream's
+ * launches: it saves the host time of a batch that fills the chip, but while
+ * (pairs) * N is at most 2^16 the unrecorded call runs the two sides side by
+ * side and is the faster one (d = 64 at N = 2^14: 2.2 ms against 2.9).  Not while the kernel profile is
  * enabled (HE_EINVAL).  he_trim and he_keygen drop the recordings. */
 #define HE_MM_GRAPH 8u
 /* he_covariance only: the dataset is not centred (see he_covariance) */
