@@ -196,7 +196,9 @@ struct DevPool {
   // GiB from the device, and takes 11.4 for the 11.0 of its two sides; one of
   // d = 16 there 8.4 and 4.4; the times are the same).  Not over a caller's
   // allocator (it may do the same itself), nor in a recording's arena.
+  static constexpr size_t SEGMENT_BYTES = 2ull << 30;
   int scratch = 0;                  // ScratchScopes standing (of the context's pool)
+  size_t most = 0;                  // the largest need since unused segments were given back
   std::map<char*, size_t> segs_;    // segment -> bytes
   std::map<char*, size_t> gaps_;    // free part of a segment -> bytes
   std::map<void*, size_t> cut_;     // block cut out -> bytes

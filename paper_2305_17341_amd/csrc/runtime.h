@@ -181,10 +181,13 @@ struct HeCtxImpl {
   size_t giant_count(int level, int B, size_t giant) const;
   size_t lintrans_scratch(int level, int B, size_t babies, size_t giant) const;
   size_t shift_scratch(int level, int sides, int B, int blocks, int n1, bool rescale_apart) const;
+  // ... and the results of a side's shifts, in blocks (bytes) in the order they are filled
+  std::vector<size_t> shift_results(int level, int out_level, int sides, int B, int blocks, int n1, int group) const;
   // device bytes of a product's side: its results, kept until the tensors are
   // summed, and its temporaries
   struct SideBytes {
-    size_t keep = 0, scratch = 0;
+    std::vector<size_t> keep;
+    size_t scratch = 0;
   };
   SideBytes side_bytes(bool a_side, int level, int out_level, int B, int n, int n1, int nprime, bool fused_rs = false,
                        bool folded = false) const;
@@ -305,9 +308,10 @@ struct HeCtxImpl {
   size_t shift_rotations(int level, int B, int nb, int n1) const;
   size_t shift_downs(int level, int B, int nb, size_t cnt) const;
   ShiftBases shift_bases(ShiftBases&& prev, HeCt& first, long second_step, long step, int sides, int blocks);
+  using Blocks = std::vector<std::shared_ptr<DevBuf>>;  // as shift_results says
   void shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
                            const std::vector<const u64*>* masks, int out_level, bool rescale_after, bool fused_rs,
-                           bool pack, double scale, const std::shared_ptr<DevBuf>& side, std::vector<HeCt>& out);
+                           bool pack, double scale, const Blocks& side, size_t& at, std::vector<HeCt>& out);
   // pack: the A_k (with one rounding) and the ModDown'ed B_k may come out
   // packed, for the tensor sums alone
   std::vector<HeCt> matmul_side_a(const HeCt& ca, int n, int n1z, int npz, int out_level = -1,

@@ -151,11 +151,14 @@ void DevPool::drop_segments(bool all) {
     }
   }
 }
-// What does not fit the gaps is obtained as segments of its own, so that needs
-// that grow from call to call cost what they grow by: freeing waits for the
-// whole device (all contexts' work, up to 0.6 s beside a batch at N = 2^16) and
-// holds up every other allocation meanwhile.  Only where the segments would then
-// pass twice the need, those that nothing uses are given back.
+// What does not fit the gaps is obtained as segments of its own, of small parts
+// together (up to SEGMENT_BYTES, which parts of other sizes fill as well later),
+// so that needs that grow from call to call cost what they grow by: freeing waits
+// for the whole device (all contexts' work, up to 0.6 s beside a batch at N =
+// 2^16), and memory given back is cleared before it can be had again (1 to 2.5 s
+// for tens of GiB), which holds up every other allocation meanwhile.  Only where
+// the segments would then pass twice the largest need, those that nothing uses
+// are given back.
 void DevPool::reserve(std::vector<size_t> parts) {
   if (redirect) return redirect->reserve(std::move(parts));
   if (user_alloc || bump_base || exact) return;
@@ -179,12 +182,16 @@ void DevPool::reserve(std::vector<size_t> parts) {
       if (best != gaps.end()) *best -= p;
       else if (p) missing.push_back(p), held += p;
     }
+    most = std::max(most, need);
     if (missing.empty()) return;
-    if (attempt || segs_.empty() || held <= 2 * need) break;
+    if (attempt || segs_.empty() || held <= 2 * most) break;
     wait();
     drop_segments(false);
+    most = need;
   }
-  for (size_t bytes : missing) {
+  for (size_t i = 0; i < missing.size();) {
+    size_t bytes = missing[i++];
+    while (i < missing.size() && bytes + missing[i] <= SEGMENT_BYTES) bytes += missing[i++];
     void* p = obtain(bytes);
     if (!p) return;  // the blocks are obtained one by one then
     segs_[(char*)p] = bytes;
@@ -271,6 +278,7 @@ void DevPool::trim() {
     bytes_cached -= kv.first;
   }
   free_.clear();
+  most = 0;
 }
 DevPool::~DevPool() {
   if (free_.empty() && live_.empty() && segs_.empty()) return;
@@ -843,12 +851,28 @@ size_t HeCtxImpl::shift_scratch(int level, int sides, int B, int blocks, int n1,
   const size_t limbs = base + std::max(step, outs);
   return (limbs + limbs / 16 + 2) * N * 8;
 }
+// a block a ModDown (the B side's unrotated bases: one a group)
+std::vector<size_t> HeCtxImpl::shift_results(int level, int out_level, int sides, int B, int blocks, int n1,
+                                             int group) const {
+  const size_t one = (size_t)2 * B * nq_of(out_level) * N * 8;
+  std::vector<size_t> out;
+  for (int b = 0; b < blocks; b += group) {
+    const int nb = std::min(group, blocks - b), per = (int)shift_rotations(level, B, nb, n1);
+    if (sides == 1) out.push_back(nb * one);
+    for (int r0 = sides == 1 ? 1 : 0; r0 < n1; r0 += per) {
+      const int cnt = std::min(per, n1 - r0), rd = (int)shift_downs(level, B, nb, cnt);
+      for (int r = 0; r < cnt; r += rd) out.push_back((size_t)std::min(rd, cnt - r) * nb * one);
+    }
+  }
+  return out;
+}
 HeCtxImpl::SideBytes HeCtxImpl::side_bytes(bool a_side, int level, int out_level, int B, int n, int n1, int nprime,
                                            bool fused_rs, bool folded) const {
   const int low = level - (nprime >= n - 1 ? 1 : ceil_div_i(n - 1, nprime));  // after Z (T)
   const size_t turns = lintrans_scratch(level, B, n1, (a_side ? 2 : 1) * ceil_div_i(n, n1));
-  if (folded || low < 0) return {0, turns};
-  return {(size_t)n * 2 * B * nq_of(out_level) * N * 8,
+  if (folded || low < 0) return {{}, turns};
+  const int sides = a_side ? 2 : 1;
+  return {shift_results(low, out_level, sides, B, n / n1, n1, shift_group(low, sides, B, n / n1)),
           std::max(turns, shift_scratch(low, a_side ? 2 : 1, B, n / n1, n1, a_side && !fused_rs))};
 }
 HeCt HeCtxImpl::ct_new(int level, bool qp, double scale, int B) {
@@ -2013,11 +2037,14 @@ std::vector<HeCt> HeCtxImpl::matmul_side_a(const HeCt& ca, int n, int n1z, int n
   for (size_t e = 0; e < masks.size(); e++)
     if (masks[e] != masks[0] + e * (size_t)nqp_of(lvl) * N) group = 1;  // not one bank
   ScratchScope scratch(pool);
-  auto side = std::make_shared<DevBuf>(&pool, (size_t)n * 2 * A0.B * nq_of(ol) * N);
+  Blocks side;
+  for (size_t bytes : shift_results(lvl, ol, 2, A0.B, nblk, n1z, group))
+    side.push_back(std::make_shared<DevBuf>(&pool, bytes / 8));
+  size_t at = 0;
   ShiftBases sb;
   for (int b = 0; b < nblk; b += group) {
     sb = shift_bases(std::move(sb), A0, -(long)n, n1z, 2, std::min(group, nblk - b));
-    shift_block_outputs(sb, b, n1z, gs, &masks, ol, true, fused_rs, pack, scale, side, Ak);
+    shift_block_outputs(sb, b, n1z, gs, &masks, ol, true, fused_rs, pack, scale, side, at, Ak);
   }
   return Ak;
 }
@@ -2034,11 +2061,14 @@ std::vector<HeCt> HeCtxImpl::matmul_side_b(const HeCt& cb, int n, int n1t, int n
   std::vector<HeCt> Bk(n);
   const int nblk = n / n1t, group = shift_group(lvl, 1, C0.B, nblk);
   ScratchScope scratch(pool);
-  auto side = std::make_shared<DevBuf>(&pool, (size_t)n * 2 * C0.B * nq_of(ol) * N);
+  Blocks side;
+  for (size_t bytes : shift_results(lvl, ol, 1, C0.B, nblk, n1t, group))
+    side.push_back(std::make_shared<DevBuf>(&pool, bytes / 8));
+  size_t at = 0;
   ShiftBases sb;
   for (int b = 0; b < nblk; b += group) {
     sb = shift_bases(std::move(sb), C0, 0, (long)n * n1t, 1, std::min(group, nblk - b));
-    shift_block_outputs(sb, b, n1t, gs, nullptr, ol, false, false, pack, scale, side, Bk);
+    shift_block_outputs(sb, b, n1t, gs, nullptr, ol, false, false, pack, scale, side, at, Bk);
   }
   return Bk;
 }
@@ -2125,7 +2155,7 @@ HeCtxImpl::ShiftBases HeCtxImpl::shift_bases(ShiftBases&& prev, HeCt& first, lon
 // mask times rotation, rescaled afterwards (with one rounding if fused_rs).
 void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n1, const std::vector<u64>& gs,
                                     const std::vector<const u64*>* masks, int out_level, bool rescale_after,
-                                    bool fused_rs, bool pack, double scale, const std::shared_ptr<DevBuf>& side,
+                                    bool fused_rs, bool pack, double scale, const Blocks& side, size_t& at,
                                     std::vector<HeCt>& out) {
   const int level = sb.x.level, nq = nq_of(level), nqp = nqp_of(level), nb = sb.blocks, B = sb.B, S = sb.sides;
   const size_t dstride = (size_t)beta_at(level) * nqp * N;
@@ -2152,19 +2182,26 @@ void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n
   const u64* c1 = sb.x.poly(0);
   const u64* c2 = sb.x.poly(0) + (size_t)B * nq * N;
   auto mask_of = [&](int r, int second) { return (*masks)[2 * (first_block * n1 + r) + second]; };
-  // results, [2][B][out_level + 1][N] each, go to `side` in the order they come
+  // results, [2][B][out_level + 1][N] each, go to the blocks of `side` from
+  // `at` on, in the order they come
   const size_t one = (size_t)2 * B * nq_of(out_level) * N;
-  size_t at = (size_t)first_block * n1;
-  if (!masks)
+  auto next = [&](size_t results) {
+    const std::shared_ptr<DevBuf> to = side.at(at++);
+    if (to->words != results * one) fail(HE_EINVAL, "a side's blocks do not match its shifts");
+    return to;
+  };
+  if (!masks) {
+    const std::shared_ptr<DevBuf> to = next(nb);
     for (int j = 0; j < nb; j++) {  // r = 0: the bases themselves
-      HeCt c = ct_at(side->p + at++ * one, out_level, scale, B);
+      HeCt c = ct_at(to->p + j * one, out_level, scale, B);
       for (int p = 0; p < 2; p++)
         hip_check(copy2d_async("copy_gather", c.poly(p), (size_t)(out_level + 1) * N * 8, sb.x.member(p, j * B),
                                (size_t)nq * N * 8, (size_t)(out_level + 1) * N * 8, B, stream),
                   "gather");
-      c.whole = side;
+      c.whole = to;
       out[(size_t)(first_block + j) * n1] = std::move(c);
     }
+  }
   const int r_lo = masks ? 0 : 1;
   const int per = (int)shift_rotations(level, B, nb, n1);
   for (int r0 = r_lo; r0 < n1; r0 += per) {
@@ -2215,21 +2252,21 @@ void HeCtxImpl::shift_block_outputs(const ShiftBases& sb, int first_block, int n
       HeCt x = ct_part(part[c], like, 0, (size_t)nrd * nb, B);
       const u64* rr = rec.p ? rec.p + (size_t)r * nb * rs : nullptr;
       HeCt y;
-      u64* to = side->p + at * one;
+      const std::shared_ptr<DevBuf> to = next((size_t)nrd * nb);
       if (rescale_after && fused_rs) {
-        y = moddown_rescale(x, out_level, true, fused_conv, rr, pack, to);
+        y = moddown_rescale(x, out_level, true, fused_conv, rr, pack, to->p);
       } else if (rescale_after) {
         HeCt md = moddown(x, -1, true, fused_conv, rr);
-        y = rescale(md, out_level, to);
+        y = rescale(md, out_level, to->p);
       } else {
-        y = moddown(x, out_level, true, fused_conv, rr, pack, to);
+        y = moddown(x, out_level, true, fused_conv, rr, pack, to->p);
       }
       x = HeCt();
       part[c].reset();
       y.scale = scale;
       for (int q = 0; q < nrd; q++)
         for (int j = 0; j < nb; j++)
-          out[(size_t)(first_block + j) * n1 + r0 + r + q] = ct_part(side, y, at++, 1, B);
+          out[(size_t)(first_block + j) * n1 + r0 + r + q] = ct_part(to, y, (size_t)q * nb + j, 1, B);
     }
   }
 }
@@ -2518,7 +2555,7 @@ void HeCtxImpl::reserve_sides(DevPool& to, const std::vector<SideBytes>& sides) 
   std::vector<size_t> parts{0};
   for (const SideBytes& s : sides) {
     parts[0] = std::max(parts[0], s.scratch);
-    if (s.keep) parts.push_back(s.keep);
+    parts.insert(parts.end(), s.keep.begin(), s.keep.end());
   }
   to.reserve(std::move(parts));
 }

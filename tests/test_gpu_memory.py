@@ -134,3 +134,28 @@ def test_scratch_that_grows_stays_within_twice_the_largest_need():
     print([f"{h / 2**20:.0f}" for h in held], f"bound {bound / 2**20:.0f} MiB", flush=True)
     assert max(held) <= bound
     assert held[4:] == [held[4]] * 2     # what has been needed before is there
+
+
+def test_batches_that_grow_find_the_memory_of_those_before():
+    """one product, then batches of two, three and four: each holds what it
+    needs alone and up to a quarter more, as blocks of other sizes may be"""
+    from paper_2305_17341_amd import he
+    ch, d = I.LARGE, 64
+    ctx = he.chain_context(ch, seed=85)
+    ctx.keygen(ctx.matmul_rot_steps(d))
+    x = ctx.encrypt_matrix(I.uniform_matrix(1, d), nonce=1)
+
+    def batch(m):
+        return ctx.matmul_batch([x] * m, [x] * m, [d] * m, {"flags": BATCHED | LAZY | FUSED})
+
+    alone = {m: _taken(ctx, lambda: batch(m)) for m in (1, 2, 3, 4)}
+    ctx.trim()
+    live, cached, _ = ctx.mem_info()
+    assert cached == 0
+    held = {}
+    for m in alone:
+        out = batch(m)
+        held[m] = sum(ctx.mem_info()[:2]) - live
+        print(f"{m} stacked: {held[m] / 2**30:.2f} GiB held, {alone[m] / 2**30:.2f} GiB alone", flush=True)
+        del out
+    assert all(held[m] <= 1.25 * alone[m] for m in alone)
